@@ -342,7 +342,7 @@ int pl_simulate_runtime_ex(pl_graph_batch *g, int32_t D, const float *node_feats
  *   out_peak_mem   dev [B, D] fp32  peak of every device, or NULL
  *   out_events     dev [B] int32    as above, or NULL
  * Other arguments, limits and tie rules as pl_simulate_runtime.  The first call on a batch
- * allocates the timeline buffers ((2 + 4 D) N_tot floats); asynchronous on `stream`. */
+ * allocates the timeline buffers ((2 + 2 D) N_tot floats); asynchronous on `stream`. */
 int pl_simulate_reward(pl_graph_batch *g, int32_t D, const float *node_feats, const int32_t *placement,
                        float inv_bandwidth, float mem_limit, float mem_penalty, float *out_reward,
                        float *out_runtime, float *out_peak_mem, int32_t *out_events, void *stream);

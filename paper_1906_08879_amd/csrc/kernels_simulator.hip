@@ -5,12 +5,29 @@
 // of the last op-done event.
 //
 // A discrete-event simulation is one dependent chain, so a graph gets one wave, and the batch
-// of graphs (rollouts) supplies the parallelism: one workgroup of 64 lanes per graph, the whole
-// state of the graph in LDS (children lists, placement, costs, pending-input counters, queue
-// links, transfer records).  There are at most 2 D events pending (one per device, one per bus): lane d owns the
-// queue and the pending event of device d, lane D + d those of bus d, in registers; the next
-// event is a wave-wide minimum over (timestamp, creation number), wake-ups of idle devices and
-// buses happen in all lanes at once.  Control flow is uniform over the wave.
+// of graphs (rollouts) supplies the parallelism; the whole state of the graph sits in LDS.  At most
+// 2 D events are pending (one per device, one per bus): lane d holds the queue ends and the pending
+// event of device d, lane D + d those of bus d.  The next event is a wave-wide minimum over
+// (timestamp, creation number).
+//
+// What bounds it: a single wave issues an instruction about every five cycles, so an event costs
+// its instructions (and LDS round trips), not arithmetic.  Hence:
+//   * An event concerns one device and one bus only (the device whose operation ended and its bus;
+//     the bus whose transfer ended and the destination): the handler is scalar code that reads and
+//     writes those two lanes' registers (v_readlane / v_writelane) and branches on the scalar unit,
+//     no lane-masked code over all devices.
+//   * A node's record (cost, transfer duration, children, queue link) is 16 bytes.  Every lane reads
+//     the record of its queue's first item at the end of every event, whether or not it changed: the
+//     read is off the chain, and no branch or copy makes anything wait for it.
+//   * A record holds the ids of up to two children themselves (longer lists their place in cidx), so
+//     the handler starts with the read of the children's states.
+//   * A bus queues operations, not transfers: the transfers of an operation leave back to back, and
+//     their destinations are a list of two entries in the operation's record (longer lists in xl).
+//   * A child that becomes runnable on an idle device starts from the registers that its record was
+//     read into.
+// About 100 instructions per event.  256 NASNet-like graphs (3124 nodes, 8 devices, about 7300 events
+// each): 2.67 ms; 4.56 ms with lane-masked queues, a transfer record per transfer and every read on the
+// chain; 5.11 ms when only the reads were taken off the chain (more instructions).
 //
 // Timestamps are float32 with one rounding per operation (no fused multiply-add), and events
 // are ordered by (timestamp, creation number): the order is the same as that of a scalar
@@ -19,58 +36,64 @@
 
 namespace pl {
 
+// v_writelane (clang has no builtin for it): v with lane l's value replaced by x
+__device__ int write_lane(int x, int l, int v) __asm("llvm.amdgcn.writelane.i32");
+
 namespace {
 
-struct SimLds {
-    int32_t *cptr;        // [n + 1] children offsets, graph-local
-    float *cost;          // [n]
-    float *size;          // [n]
-    float *tr_dur;        // [e] transfer records: duration = size of the producer's output / bandwidth
-    uint16_t *cidx;       // [e] children, graph-local ids, ascending per node
-    uint32_t *node;       // [n] device of the node (bits 0-7) | inputs not yet available on that device << 8
-    uint16_t *next_op;    // [n] link of the per-device operation queues
-    uint16_t *tr_op;      // [e] transfer records: producer
-    uint16_t *tr_next;    // [e] link of the per-bus transfer queues
-    uint8_t *tr_dst;      // [e] destination device
-    uint16_t *tr_child;   // [e] (one transfer per child) the child the transfer is for
-};
+constexpr int kSimThreads = 256;   // they stage the graph into LDS; the first wave then runs the events
 
-__device__ __forceinline__ SimLds carve(unsigned char *base, int n_max, int e_max)
+// Graph-local ids and places in cidx take 14 bits: a graph whose state fits in LDS has at most 9100
+// nodes and 12600 edges.  Id n is the node that is not there: the absent second child of a node, the
+// end of a queue; it has a record and a state of its own, on device kNoDev.
+constexpr uint32_t kIdBits = 14, kIdMask = (1u << kIdBits) - 1, kList = 1u << 31;
+// A node's state: its device in the low bits, inputs not yet available on that device above them.
+constexpr uint32_t kDevBits = 5, kNoDev = (1u << kDevBits) - 1, kInput = 1u << kDevBits;
+// Entry of an operation's transfer list: the destination device or, with one transfer per child, the
+// child, with kFirst set where it is the first to its device.
+constexpr uint32_t kFirst = 0x8000u;
+
+// LDS: rec [n + 1] {cost, or transfers | first entry << 16 once the output waits for the bus; duration of
+// a transfer; children: id | id << 14, or kList | place in cidx | number << 14; link | second entry << 16},
+// node [n + 1] states, cidx [e] children (ascending per node), xl [e] transfer lists of more than two
+// entries, from the place of the operation's first child.  States take 16 bits where 32 do not fit.
+template <typename Word>
+constexpr size_t sim_lds(size_t n, size_t e)
 {
-    SimLds s;
-    unsigned char *p = base;
-    s.cptr = reinterpret_cast<int32_t *>(p);   p += sizeof(int32_t) * (n_max + 1);
-    s.cost = reinterpret_cast<float *>(p);     p += sizeof(float) * n_max;
-    s.size = reinterpret_cast<float *>(p);     p += sizeof(float) * n_max;
-    s.tr_dur = reinterpret_cast<float *>(p);   p += sizeof(float) * e_max;
-    s.node = reinterpret_cast<uint32_t *>(p);  p += sizeof(uint32_t) * n_max;
-    s.cidx = reinterpret_cast<uint16_t *>(p);  p += sizeof(uint16_t) * (e_max + (e_max & 1));
-    s.next_op = reinterpret_cast<uint16_t *>(p); p += sizeof(uint16_t) * (n_max + (n_max & 1));
-    s.tr_op = reinterpret_cast<uint16_t *>(p); p += sizeof(uint16_t) * (e_max + (e_max & 1));
-    s.tr_next = reinterpret_cast<uint16_t *>(p); p += sizeof(uint16_t) * (e_max + (e_max & 1));
-    s.tr_dst = p;                                p += e_max + (e_max & 1);
-    s.tr_child = reinterpret_cast<uint16_t *>(p);
-    return s;
+    return (16 + sizeof(Word)) * (n + 1) + 4 * e;
 }
 
-constexpr int kNone = 0xFFFF;    // empty link / empty queue
-
-// Minimum of an unsigned value over lanes 0..31 (two DPP rows), returned in every lane.
-__device__ __forceinline__ unsigned int row_pair_min(unsigned int v)
+// Minimum of an unsigned value over lanes 0..15 (one DPP row) or 0..31, as a scalar.
+template <bool TWO>
+__device__ __forceinline__ uint32_t event_min(uint32_t v)
 {
-    const int i0 = static_cast<int>(v);
-    unsigned int o;
-    o = static_cast<unsigned int>(__builtin_amdgcn_update_dpp(i0, i0, 0xB1, 0xF, 0xF, false));     // quad_perm [1,0,3,2]
-    v = o < v ? o : v;
-    o = static_cast<unsigned int>(__builtin_amdgcn_update_dpp(static_cast<int>(v), static_cast<int>(v), 0x4E, 0xF, 0xF, false));   // quad_perm [2,3,0,1]
-    v = o < v ? o : v;
-    o = static_cast<unsigned int>(__builtin_amdgcn_update_dpp(static_cast<int>(v), static_cast<int>(v), 0x141, 0xF, 0xF, false));  // row_half_mirror
-    v = o < v ? o : v;
-    o = static_cast<unsigned int>(__builtin_amdgcn_update_dpp(static_cast<int>(v), static_cast<int>(v), 0x140, 0xF, 0xF, false));  // row_mirror
-    v = o < v ? o : v;
-    const unsigned int r0 = static_cast<unsigned int>(__builtin_amdgcn_readlane(static_cast<int>(v), 0));
-    const unsigned int r1 = static_cast<unsigned int>(__builtin_amdgcn_readlane(static_cast<int>(v), 16));
+#define PL_ROW_MIN(ctrl)                                                                                       \
+    {                                                                                                          \
+        const uint32_t o = static_cast<uint32_t>(__builtin_amdgcn_update_dpp(-1, static_cast<int>(v), ctrl, 0xF, 0xF, false)); \
+        v = o < v ? o : v;                                                                                     \
+    }
+    PL_ROW_MIN(0xB1)     // quad_perm [1,0,3,2]
+    PL_ROW_MIN(0x4E)     // quad_perm [2,3,0,1]
+    PL_ROW_MIN(0x141)    // row_half_mirror
+    PL_ROW_MIN(0x140)    // row_mirror
+#undef PL_ROW_MIN
+    const uint32_t r0 = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(v), 0));
+    if constexpr (!TWO) return r0;
+    const uint32_t r1 = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(v), 16));
     return r0 < r1 ? r0 : r1;
+}
+
+__device__ __forceinline__ uint32_t get(uint32_t v, uint32_t l)
+{
+    return static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(v), static_cast<int>(l)));
+}
+__device__ __forceinline__ void put(uint32_t &v, uint32_t l, uint32_t x)
+{
+    v = static_cast<uint32_t>(write_lane(static_cast<int>(x), static_cast<int>(l), static_cast<int>(v)));
+}
+__device__ __forceinline__ uint32_t first_lane(uint32_t v)
+{
+    return static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(v)));
 }
 
 // TL: the timeline is written out as well (for the peak-memory model): start and end of every
@@ -80,8 +103,9 @@ __device__ __forceinline__ unsigned int row_pair_min(unsigned int v)
 // several children on one remote device crosses the bus several times; the timeline then keeps
 // the first and the last arrival per device).  Otherwise an output crosses once per destination
 // device and its arrival releases every child waiting there.
-template <bool TL, bool PC>
-__global__ __launch_bounds__(64) void k_simulate(GraphView gv, int D, int n_max, int e_max,
+// TWO: more than eight devices, so the pending events take two DPP rows.
+template <bool TL, bool PC, bool TWO, typename Word>
+__global__ __launch_bounds__(kSimThreads) void k_simulate(GraphView gv, int D, int n_max, int e_max,
                                                  const float *__restrict__ node_feats,
                                                  const int32_t *__restrict__ placement, float inv_bw,
                                                  float *__restrict__ out_runtime,
@@ -90,199 +114,327 @@ __global__ __launch_bounds__(64) void k_simulate(GraphView gv, int D, int n_max,
                                                  float *__restrict__ arrival, float *__restrict__ arrival_last)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char lds_raw[];
-    const SimLds S = carve(lds_raw, n_max, e_max);
-    const int b = blockIdx.x, lane = threadIdx.x;
+    uint4 *rec = reinterpret_cast<uint4 *>(lds_raw);
+    Word *node = reinterpret_cast<Word *>(rec + n_max + 1);
+    uint16_t *cidx = reinterpret_cast<uint16_t *>(node + n_max + 1), *xl = cidx + e_max;
+    auto link_of = [&](uint32_t v) __attribute__((always_inline)) { return reinterpret_cast<uint16_t *>(rec + v) + 6; };
+    const int b = blockIdx.x;
     const int n0 = gv.node_off[b], n = gv.node_off[b + 1] - n0;
     const int32_t *gptr = gv.nbr_ptr[1] + n0;            // children CSR (global offsets / ids)
     const int e0 = gptr[0], e = gptr[n] - e0;
+    const uint32_t none = static_cast<uint32_t>(n);
 
-    // ---- the graph's state into LDS
-    bool bad = false;                                     // a device id outside [0, D)
-    for (int v = lane; v < n; v += 64) {
-        const int d = placement[n0 + v];
-        bad |= d < 0 || d >= D;
-        S.cost[v] = node_feats[static_cast<size_t>(n0 + v) * 3 + 0];
-        S.size[v] = node_feats[static_cast<size_t>(n0 + v) * 3 + 1];
-        S.node[v] = (static_cast<uint32_t>(d) & 0xFFu) |
-                    (static_cast<uint32_t>(gv.nbr_ptr[0][n0 + v + 1] - gv.nbr_ptr[0][n0 + v]) << 8);   // number of parents
-        S.next_op[v] = kNone;
+    // ---- the graph's state into LDS.  rec[n].x: some device id is outside [0, D)
+    if (threadIdx.x == 0) {
+        rec[n] = uint4{0, 0, none | none << kIdBits, none};
+        node[n] = static_cast<Word>(kNoDev);
     }
-    for (int v = lane; v <= n; v += 64) S.cptr[v] = gptr[v] - e0;
-    for (int i = lane; i < e; i += 64) S.cidx[i] = static_cast<uint16_t>(gv.nbr_idx[1][e0 + i] - n0);
     __syncthreads();
-    if (__ballot(bad) != 0ull) {
-        if (lane == 0) {
+#pragma unroll 4
+    for (int v = threadIdx.x; v < n; v += kSimThreads) {
+        const int d = placement[n0 + v];
+        if (d < 0 || d >= D) rec[n].x = 1u;
+        const int c0 = gptr[v], cnt = gptr[v + 1] - c0;
+        uint32_t kids;
+        if (cnt > 2) {
+            kids = kList | static_cast<uint32_t>(c0 - e0) | static_cast<uint32_t>(cnt) << kIdBits;
+        } else {
+            const uint32_t k0 = cnt > 0 ? static_cast<uint32_t>(gv.nbr_idx[1][c0] - n0) : none;
+            const uint32_t k1 = cnt > 1 ? static_cast<uint32_t>(gv.nbr_idx[1][c0 + 1] - n0) : none;
+            kids = k0 | k1 << kIdBits;
+        }
+        rec[v] = uint4{__float_as_uint(node_feats[static_cast<size_t>(n0 + v) * 3 + 0]),
+                       __float_as_uint(__fmul_rn(node_feats[static_cast<size_t>(n0 + v) * 3 + 1], inv_bw)), kids, none};
+        const uint32_t parents = static_cast<uint32_t>(gv.nbr_ptr[0][n0 + v + 1] - gv.nbr_ptr[0][n0 + v]);
+        node[v] = static_cast<Word>((static_cast<uint32_t>(d) & kNoDev) | parents << kDevBits);
+    }
+#pragma unroll 4
+    for (int i = threadIdx.x; i < e; i += kSimThreads) cidx[i] = static_cast<uint16_t>(gv.nbr_idx[1][e0 + i] - n0);
+    __syncthreads();
+    if (rec[n].x != 0) {
+        if (threadIdx.x == 0) {
             out_runtime[b] = __builtin_nanf("");
             if (out_events) out_events[b] = -1;
         }
         return;
     }
+    if (threadIdx.x >= 64) return;
+    const uint32_t lane = threadIdx.x, nd = static_cast<uint32_t>(D);
 
-    // ---- lane-private queue ends and pending event (lane d: device d, lane D + d: bus d)
-    int q_head = kNone, q_tail = kNone;
-    bool active = false;
-    float ev_time = 0.0f;
-    int ev_seq = 0, ev_node = 0, ev_dst = 0, ev_child = 0;
-    // what the event's handler needs of its operation, read when the event is created (off the
-    // handler's chain of dependent LDS reads): its children and the duration of its transfers
-    int ev_c0 = 0, ev_cnt = 0;
-    float ev_dur = 0.0f;
-    int seq = 0, n_tr = 0, n_events = 0;
-    float last = 0.0f;
+    // ---- lane-private state (lane d: device d, lane D + d: bus d)
+    constexpr uint32_t kIdle = 0xFFFFFFFFu;
+    uint32_t ev_t = kIdle, ev_key = 0;                    // pending event: time (bits); operation | creation number << 14
+    uint32_t cur_dur = 0, cur_kids = 0;                   // its operation's transfer duration and children
+    uint32_t x_cur = 0, x_more = 0;                       // bus: list entry in progress | the next one << 16; entries
+                                                          // left | place in xl of the entry after the next << 14
+    uint32_t head = none, tail = none;                    // queue
+    uint4 hr = rec[none];                                 // record of the queue's first item
+    uint32_t seq = 0, n_events = 0, last = 0;
 
-    auto enqueue_op = [&](int dev, int v) {               // uniform arguments
-        if (lane == dev) {
-            if (q_tail == kNone) q_head = v; else S.next_op[q_tail] = static_cast<uint16_t>(v);
-            q_tail = v;
+    auto push = [&](uint32_t q, uint32_t v) __attribute__((always_inline)) {
+        if (get(head, q) == none)
+            put(head, q, v);
+        else
+            *link_of(get(tail, q)) = static_cast<uint16_t>(v);
+        put(tail, q, v);
+    };
+    // lane q's pending event, for operation o: `duration` after `now` (both as bits).  (No more than n + e
+    // of at most 21700 events are ever created, so the creation number fits beside the id.)
+    auto schedule = [&](uint32_t q, uint32_t now, uint32_t duration, uint32_t o) __attribute__((always_inline)) {
+        const float t = __fadd_rn(__uint_as_float(now), __uint_as_float(duration));
+        ev_t = lane == q ? __float_as_uint(t) : ev_t;
+        put(ev_key, q, o | seq << kIdBits);
+        ++seq;
+        return t;
+    };
+    // operation v starts on device q
+    auto start_op = [&](uint32_t q, uint32_t v, uint32_t now, uint32_t cost, uint32_t dur, uint32_t kids) __attribute__((always_inline)) {
+        const float t = schedule(q, now, cost, v);
+        put(cur_dur, q, dur);
+        put(cur_kids, q, kids);
+        if constexpr (TL) {
+            op_start[n0 + static_cast<int>(v)] = __uint_as_float(now);
+            op_end[n0 + static_cast<int>(v)] = t;
         }
     };
-    auto enqueue_transfer = [&](int dev, int o, int dst, float dur, int child) {
-        const int k = n_tr++;
-        S.tr_op[k] = static_cast<uint16_t>(o);
-        S.tr_dst[k] = static_cast<uint8_t>(dst);
-        if constexpr (PC) S.tr_child[k] = static_cast<uint16_t>(child);
-        S.tr_dur[k] = dur;
-        S.tr_next[k] = kNone;
-        if (lane == D + dev) {
-            if (q_tail == kNone) q_head = k; else S.tr_next[q_tail] = static_cast<uint16_t>(k);
-            q_tail = k;
-        }
-    };
-    // idle devices, then idle buses, with a non-empty queue start their next item (the wake-ups)
-    auto wake = [&](float now) {
-        const bool start = !active && q_head != kNone && lane < 2 * D;
-        const unsigned long long m = __ballot(start);
-        if (start) {
-            const int item = q_head;
-            int o, dst = -1, child = 0;
-            float dur;
-            if (lane < D) {
-                o = item;
-                q_head = S.next_op[item];
-                dur = S.cost[o];
-            } else {
-                o = S.tr_op[item];
-                dst = S.tr_dst[item];
-                if constexpr (PC) child = S.tr_child[item];
-                q_head = S.tr_next[item];
-                dur = S.tr_dur[item];
-            }
-            ev_child = child;
-            if (q_head == kNone) q_tail = kNone;
-            active = true;
-            ev_c0 = S.cptr[o];
-            ev_cnt = S.cptr[o + 1] - ev_c0;
-            ev_dur = __fmul_rn(S.size[o], inv_bw);
-            ev_time = __fadd_rn(now, dur);
-            ev_seq = seq + __popcll(m & ((1ull << lane) - 1ull));
-            ev_node = o;
-            ev_dst = dst;
-            if constexpr (TL) {
-                if (lane < D) {
-                    op_start[n0 + o] = now;
-                    op_end[n0 + o] = ev_time;
-                }
-            }
-        }
-        seq += __popcll(m);
+    // bus q starts the m transfers of operation o, the first two to e1 and e2
+    auto start_transfers = [&](uint32_t q, uint32_t now, uint32_t o, uint32_t dur, uint32_t kids, uint32_t m, uint32_t e1,
+                               uint32_t e2) __attribute__((always_inline)) {
+        schedule(q, now, dur, o);
+        put(cur_dur, q, dur);
+        put(cur_kids, q, kids);
+        put(x_cur, q, e1 | e2 << 16);
+        put(x_more, q, (m - 1) | ((kids & kIdMask) + 2) << kIdBits);
     };
 
     for (int base = 0; base < n; base += 64) {            // operations without parents, ascending id
-        const int v = base + lane;
-        const uint32_t word = S.node[v < n ? v : 0];
-        unsigned long long roots = __ballot(v < n && (word >> 8) == 0);
+        const uint32_t v = static_cast<uint32_t>(base) + lane;
+        const uint32_t word = node[v < none ? v : none];
+        unsigned long long roots = __ballot(v < none && word < kInput);
         while (roots != 0ull) {
-            const int l = __ffsll(static_cast<long long>(roots)) - 1;
+            const uint32_t l = static_cast<uint32_t>(__builtin_ctzll(roots));
             roots &= roots - 1;
-            enqueue_op(__builtin_amdgcn_readlane(static_cast<int>(word & 0xFFu), l), base + l);
+            push(get(word, l), static_cast<uint32_t>(base) + l);
         }
     }
-    wake(0.0f);
+    for (uint32_t d = 0; d < nd; ++d) {
+        const uint32_t v = get(head, d);
+        if (v == none) continue;
+        const uint4 r = rec[v];
+        start_op(d, v, 0, first_lane(r.x), first_lane(r.y), first_lane(r.z));
+        put(head, d, first_lane(r.w) & 0xFFFFu);
+    }
+    hr = rec[head];
 
-    const int max_events = n + e + 8;                     // every operation and transfer ends once
-    for (int it = 0; it < max_events; ++it) {
+    const uint32_t max_events = static_cast<uint32_t>(n + e + 8);   // every operation and transfer ends once
+    do {
         // ---- next event: smallest (timestamp, creation number).  Timestamps are >= 0, so their
-        // bit patterns order like the values.  Lanes 0 .. 2 D - 1 (at most two rows of sixteen)
-        // hold the candidates: the minimum over each row comes from four DPP steps, the two
-        // rows are combined through scalar registers.
-        const unsigned int t_bits = active ? __float_as_uint(ev_time) : 0xFFFFFFFFu;
-        const unsigned int t_min = row_pair_min(t_bits);
-        if (t_min == 0xFFFFFFFFu) break;                  // nothing pending: the simulation is over
+        // bit patterns order like the values.
+        const uint32_t now = event_min<TWO>(ev_t);
+        if (now == kIdle) break;                          // nothing pending: the simulation is over
         // Usually one pending event carries the smallest timestamp; only ties need the second
         // reduction, over the creation numbers.
-        unsigned long long first = __ballot(active && t_bits == t_min);
-        if (first & (first - 1)) {
-            const unsigned int s_bits = (active && t_bits == t_min) ? static_cast<unsigned int>(ev_seq) : 0xFFFFFFFFu;
-            const unsigned int s_min = row_pair_min(s_bits);
-            first = __ballot(s_bits == s_min && active && t_bits == t_min);
+        uint32_t first = static_cast<uint32_t>(__ballot(ev_t == now));
+        if (__builtin_expect(first & (first - 1), 0)) {
+            const uint32_t s_bits = ev_t == now ? ev_key : kIdle;
+            first = static_cast<uint32_t>(__ballot(s_bits == event_min<TWO>(s_bits)));
         }
-        const int slot = __ffsll(static_cast<long long>(first)) - 1;
-        const float now = __uint_as_float(t_min);
-        const int o = __builtin_amdgcn_readlane(ev_node, slot);
-        const int dst = __builtin_amdgcn_readlane(ev_dst, slot);
-        if (lane == slot) active = false;
+        const uint32_t slot = static_cast<uint32_t>(__builtin_ctz(first));
+        const uint32_t o = get(ev_key, slot) & kIdMask, kids = get(cur_kids, slot), dur = get(cur_dur, slot);
         ++n_events;
-        // ---- the children of o, one per lane: those on the device where o's output now is
-        // (its own device after op-done, the destination after transfer-done) have one input
-        // fewer to wait for; after op-done the others make the output cross, once per device.
-        // Queues are filled in ascending child id (= lane order), as a scalar loop would.
-        const int c0 = __builtin_amdgcn_readlane(ev_c0, slot), cnt = __builtin_amdgcn_readlane(ev_cnt, slot);
-        const bool op_done = slot < D;
-        const int here = op_done ? slot : dst;
-        const float dur = op_done ? __int_as_float(__builtin_amdgcn_readlane(__float_as_int(ev_dur), slot)) : 0.0f;
-        if (op_done) last = now;
-        if constexpr (TL) {
-            if (!op_done && lane == 0) {
-                const size_t at = static_cast<size_t>(n0 + o) * D + dst;
-                if constexpr (PC) {
-                    if (arrival[at] < 0.0f) arrival[at] = now;       // first crossing to this device
-                    arrival_last[at] = now;
-                } else {
-                    arrival[at] = now;
-                }
+        put(ev_t, slot, kIdle);
+
+        // The operation's children where its output now is (its own device after op-done, the
+        // destination after transfer-done) have one input fewer to wait for, and join that device's
+        // queue when it was the last one; after op-done the others make the output cross.  In
+        // ascending child id throughout.  An idle device goes on with its queue before anything is
+        // appended to it; if it has none, the first child that becomes runnable starts at once.
+        uint32_t wait = 0;                                // 0: the device would start a runnable child at once
+        auto next_op = [&](uint32_t dev) __attribute__((always_inline)) {
+            const uint32_t v = get(head, dev);
+            wait = v ^ none;
+            if (v == none) return;
+            put(head, dev, get(hr.w, dev) & 0xFFFFu);
+            start_op(dev, v, now, get(hr.x, dev), get(hr.y, dev), get(hr.z, dev));
+        };
+        auto runnable = [&](uint32_t dev, uint32_t v, const uint4 &r, uint32_t l) __attribute__((always_inline)) {
+            if (__builtin_expect(wait == 0, 1)) {
+                wait = 1;
+                start_op(dev, v, now, get(r.x, l), get(r.y, l), get(r.z, l));
+            } else {
+                push(dev, v);
             }
-        }
-        if (PC && !op_done) {
-            // the transfer was made for one child: it alone has one input fewer to wait for
-            const int c = __builtin_amdgcn_readlane(ev_child, slot);
-            const uint32_t word = S.node[c];
-            if (lane == 0) S.node[c] = word - 0x100u;
-            if ((word >> 8) == 1u) enqueue_op(dst, c);
-            wake(now);
-            continue;
-        }
-        unsigned int sent = 0;
-        for (int base = 0; base < cnt; base += 64) {
-            const bool valid = base + lane < cnt;
-            const int c = valid ? S.cidx[c0 + base + lane] : 0;
-            const uint32_t word = S.node[c];
-            const int pc = static_cast<int>(word & 0xFFu);
-            const bool same = valid && pc == here;
-            const int p = static_cast<int>(word >> 8) - 1;
-            if (same) S.node[c] = word - 0x100u;
-            unsigned long long ready = __ballot(same && p == 0);
-            unsigned long long cross = op_done ? __ballot(valid && pc != here) : 0ull;
+        };
+        // children 0 and 1 of an operation that has no more: their states, one in each of lanes 0 and 1
+        auto two_kids = [&](uint32_t dev, uint4 &r) __attribute__((always_inline)) {
+            uint32_t c = none;
+            put(c, 0, kids & kIdMask);
+            put(c, 1, kids >> kIdBits);
+            const uint32_t word = node[c];
+            r = rec[c];
+            node[c] = static_cast<Word>((word & kNoDev) == dev ? word - kInput : word);
+            return word;
+        };
+        // 64 children at a time of one that has more: lane's child (none past the end) and its state
+        auto more_kids = [&](uint32_t dev, uint32_t at, uint32_t left, uint32_t &c, uint4 &r) __attribute__((always_inline)) {
+            c = lane < left ? cidx[at + lane] : none;
+            const uint32_t word = node[c];
+            r = rec[c];
+            node[c] = static_cast<Word>((word & kNoDev) == dev ? word - kInput : word);
+            unsigned long long ready = __ballot(word == (kInput | dev));
             while (ready != 0ull) {
-                const int l = __ffsll(static_cast<long long>(ready)) - 1;
+                const uint32_t l = static_cast<uint32_t>(__builtin_ctzll(ready));
                 ready &= ready - 1;
-                enqueue_op(here, __builtin_amdgcn_readlane(c, l));
+                runnable(dev, get(c, l), r, l);
             }
-            while (cross != 0ull) {
-                const int l = __ffsll(static_cast<long long>(cross)) - 1;
-                cross &= cross - 1;
-                const int pd = __builtin_amdgcn_readlane(pc, l);
-                if (PC || ((sent >> pd) & 1u) == 0) {     // once per child, or once per destination
-                    sent |= 1u << pd;
-                    enqueue_transfer(slot, o, pd, dur, __builtin_amdgcn_readlane(c, l));
+            return word;
+        };
+        const uint32_t c0 = kids & kIdMask, cnt = (kids & ~kList) >> kIdBits;   // (of a longer list)
+
+        if (slot < nd) {
+            last = now;
+            uint32_t m = 0, e1 = 0, e2 = 0;               // transfers of the output: number and first two entries
+            uint4 r;
+            if (__builtin_expect(!(kids & kList), 1)) {
+                const uint32_t word = two_kids(slot, r);
+                next_op(slot);
+                const uint32_t w0 = get(word, 0), w1 = get(word, 1), want = kInput | slot;
+                if (__builtin_expect(w0 == want, 0)) runnable(slot, kids & kIdMask, r, 0);
+                if (__builtin_expect(w1 == want, 0)) runnable(slot, kids >> kIdBits, r, 1);
+                const uint32_t d0 = w0 & kNoDev, d1 = w1 & kNoDev;
+                const uint32_t same_dev = d0 == d1 ? 1u : 0u;
+                if (d0 != slot && d0 != kNoDev) {
+                    e1 = PC ? (kids & kIdMask) | kFirst : d0;
+                    m = 1;
+                }
+                if (d1 != slot && d1 != kNoDev && (PC || m == 0 || !same_dev)) {
+                    e2 = PC ? kids >> kIdBits | (m == 0 || !same_dev ? kFirst : 0u) : d1;
+                    e1 = m == 0 ? e2 : e1;
+                    ++m;
+                }
+            } else {
+                next_op(slot);
+                uint32_t sent = 0;
+                for (uint32_t base = 0; base < cnt; base += 64) {
+                    uint32_t c;
+                    const uint32_t pc = more_kids(slot, c0 + base, cnt - base, c, r) & kNoDev;
+                    const unsigned long long cross = __ballot(pc != slot && pc != kNoDev);
+                    unsigned long long rest = cross, firsts = 0ull;
+                    while (rest != 0ull) {                // per destination: its first child in this round
+                        const uint32_t l = static_cast<uint32_t>(__builtin_ctzll(rest));
+                        const uint32_t pd = get(pc, l);
+                        rest &= ~__ballot(pc == pd);
+                        if ((sent >> pd) & 1u) continue;
+                        sent |= 1u << pd;
+                        if constexpr (PC) {
+                            firsts |= 1ull << l;
+                        } else {
+                            e1 = m == 0 ? pd : e1;
+                            e2 = m == 1 ? pd : e2;
+                            xl[c0 + m] = static_cast<uint16_t>(pd);
+                            ++m;
+                        }
+                    }
+                    if (PC && cross != 0ull) {
+                        const uint32_t x = c | (((firsts >> lane) & 1ull) ? kFirst : 0u);
+                        if ((cross >> lane) & 1ull)
+                            xl[c0 + m + static_cast<uint32_t>(__popcll(cross & ((1ull << lane) - 1ull)))] = static_cast<uint16_t>(x);
+                        const uint32_t k = static_cast<uint32_t>(__popcll(cross));
+                        const uint32_t x1 = get(x, static_cast<uint32_t>(__builtin_ctzll(cross)));
+                        if (k > 1 && m == 0) e2 = get(x, static_cast<uint32_t>(__builtin_ctzll(cross & (cross - 1))));
+                        if (m == 1) e2 = x1;
+                        if (m == 0) e1 = x1;
+                        m += k;
+                    }
+                }
+            }
+            // the output joins the bus's queue, or starts to cross at once
+            if (__builtin_expect(m != 0, 1)) {
+                const uint32_t bus = nd + slot;
+                if (get(ev_t, bus) == kIdle) {
+                    start_transfers(bus, now, o, dur, kids, m, e1, e2);
+                } else {
+                    rec[o].x = m | e1 << 16;
+                    rec[o].w = none | e2 << 16;
+                    push(bus, o);
+                }
+            }
+        } else {
+            const uint32_t xc = get(x_cur, slot);
+            uint4 r;
+            if constexpr (PC) {
+                // the transfer was made for one child: it alone has one input fewer to wait for
+                const uint32_t c = xc & kIdMask;
+                r = rec[c];
+                const uint32_t word = first_lane(node[c]), dev = word & kNoDev;
+                node[c] = static_cast<Word>(word - kInput);
+                if constexpr (TL) {
+                    const size_t at = static_cast<size_t>(n0 + static_cast<int>(o)) * D + dev;
+                    if (xc & kFirst) arrival[at] = __uint_as_float(now);
+                    arrival_last[at] = __uint_as_float(now);
+                }
+                wait = ~get(ev_t, dev);                   // (idle: its queue is empty)
+                if ((word >> kDevBits) == 1u) runnable(dev, c, r, 0);
+            } else {
+                const uint32_t dev = xc & 0xFFFFu;
+                if constexpr (TL) arrival[static_cast<size_t>(n0 + static_cast<int>(o)) * D + dev] = __uint_as_float(now);
+                wait = ~get(ev_t, dev);                   // (idle: its queue is empty)
+                if (__builtin_expect(!(kids & kList), 1)) {
+                    const uint32_t word = two_kids(dev, r);
+                    const uint32_t w0 = get(word, 0), w1 = get(word, 1), want = kInput | dev;
+                    if (w0 == want) runnable(dev, kids & kIdMask, r, 0);
+                    if (__builtin_expect(w1 == want, 0)) runnable(dev, kids >> kIdBits, r, 1);
+                } else {
+                    for (uint32_t base = 0; base < cnt; base += 64) {
+                        uint32_t c;
+                        (void)more_kids(dev, c0 + base, cnt - base, c, r);
+                    }
+                }
+            }
+            // the bus goes on with the operation's next transfer, or with its queue
+            const uint32_t more = get(x_more, slot), left = more & kIdMask;
+            if (__builtin_expect(left != 0, 0)) {
+                uint32_t x = xc >> 16;
+                if (left > 1) x |= first_lane(xl[more >> kIdBits]) << 16;
+                put(x_cur, slot, x);
+                put(x_more, slot, more + (1u << kIdBits) - 1u);
+                schedule(slot, now, dur, o);
+            } else {
+                const uint32_t q = get(head, slot);
+                if (q != none) {
+                    const uint32_t a = get(hr.x, slot), w = get(hr.w, slot);
+                    put(head, slot, w & 0xFFFFu);
+                    start_transfers(slot, now, q, get(hr.y, slot), get(hr.z, slot), a & 0xFFFFu, a >> 16, w >> 16);
                 }
             }
         }
-        wake(now);
-    }
+        hr = rec[head];
+    } while (n_events != max_events);
     if (lane == 0) {
-        out_runtime[b] = last;
-        if (out_events) out_events[b] = n_events;
+        out_runtime[b] = __uint_as_float(last);
+        if (out_events) out_events[b] = static_cast<int32_t>(n_events);
     }
+}
+
+// Launches k_simulate for D devices and graphs of at most n_max nodes and e_max edges: 16-bit states
+// where 32-bit ones do not fit (then e_max < n_max / 4, and in-degrees fit 11 bits).
+template <bool TL, bool PC>
+int simulate(const GraphView &gv, int D, int n_max, int e_max, const float *node_feats, const int32_t *placement,
+             float inv_bw, float *runtime, int32_t *events, float *op_start, float *op_end, float *arrival,
+             float *arrival_last, hipStream_t s)
+{
+    auto run = [&](auto kernel, size_t lds) {
+        if (lds > 64 * 1024)
+            PL_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(kernel),
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds)));
+        hipLaunchKernelGGL(kernel, dim3(gv.B), dim3(kSimThreads), lds, s, gv, D, n_max, e_max, node_feats, placement,
+                           inv_bw, runtime, events, op_start, op_end, arrival, arrival_last);
+        return static_cast<int>(PL_OK);
+    };
+    const size_t wide = sim_lds<uint32_t>(n_max, e_max), narrow = sim_lds<uint16_t>(n_max, e_max);
+    if (wide <= 160 * 1024)
+        return D > 8 ? run(k_simulate<TL, PC, true, uint32_t>, wide) : run(k_simulate<TL, PC, false, uint32_t>, wide);
+    return D > 8 ? run(k_simulate<TL, PC, true, uint16_t>, narrow) : run(k_simulate<TL, PC, false, uint16_t>, narrow);
 }
 
 // ---- peak memory of every device from the timeline (appendix "Simulator": the start and end
@@ -290,159 +442,157 @@ __global__ __launch_bounds__(64) void k_simulate(GraphView gv, int D, int n_max,
 // output of v occupies v's device from v's start until the latest of v's end, the end of its last
 // consumer there and the arrival of its last outgoing transfer; on another device that consumes
 // it, a copy lives from the transfer's arrival until the end of its last consumer there.
-// Intervals are half-open [alloc, free).
+// Intervals are half-open [alloc, free).  Then the memory-penalised run time R(p) = r if m <= M else
+// r + c (m - M) (appendix, "Reward"), m the largest peak.
+//
+// One workgroup per (graph, device): the copies that live on the device are collected in LDS (alloc,
+// free, size; node order), and for each of their allocation times (the live sum only grows there) the
+// live sizes are summed in float64 in node order.  The pairs of copies bound it (six instructions
+// each), so a device has a workgroup of its own and a thread takes two times per pass over the copies.
+// The workgroup of a graph that finishes last takes the maximum over the devices.
+// (64 NMT-like graphs, 4 devices: 86 us; 412 us with one workgroup per graph that took its devices in
+// turn, after a kernel that wrote every interval to memory and one that cleared the arrivals.)
+constexpr int kPeakThreads = 512, kPeakTimes = 2;   // threads; allocation times per thread and pass
 
-__global__ __launch_bounds__(256) void k_fill_value(float *__restrict__ p, size_t n, float value)
-{
-    const size_t idx = static_cast<size_t>(blockIdx.x) * 256 + threadIdx.x;
-    if (idx < n) p[idx] = value;
-}
+constexpr int peak_capacity(int n_max) { return (n_max + 3) / 4 * 4; }
+constexpr size_t peak_lds(int n_max) { return 4 * sizeof(float) * static_cast<size_t>(peak_capacity(n_max)); }
 
-// One thread per node: alloc[v][d], free[v][d] for every device (-1: no copy there).
-__global__ __launch_bounds__(256) void k_lifetimes(GraphView gv, int D, const int32_t *__restrict__ placement,
-                                                   const float *__restrict__ op_start,
-                                                   const float *__restrict__ op_end,
-                                                   const float *__restrict__ arrival,
-                                                   const float *__restrict__ arrival_last,
-                                                   float *__restrict__ alloc, float *__restrict__ free_t)
-{
-    // arrival: first crossing to a device (the copy exists from then on); arrival_last: last
-    // crossing (the source is kept until then); the same array unless an output may cross twice
-    const int v = blockIdx.x * 256 + threadIdx.x;
-    if (v >= gv.n_tot) return;
-    float *fr = free_t + static_cast<size_t>(v) * D, *al = alloc + static_cast<size_t>(v) * D;
-    const int d = placement[v];
-    for (int o = 0; o < D; ++o) fr[o] = -1.0f;
-    if (d < 0 || d >= D) {                 // the simulator reports the graph as invalid
-        for (int o = 0; o < D; ++o) al[o] = -1.0f;
-        return;
-    }
-    // end of the last consumer on every device, kept in this node's own row
-    for (int p = gv.nbr_ptr[1][v]; p < gv.nbr_ptr[1][v + 1]; ++p) {
-        const int c = gv.nbr_idx[1][p];
-        const int pc = placement[c];
-        if (pc >= 0 && pc < D) fr[pc] = fmaxf(fr[pc], op_end[c]);
-    }
-    float own_free = fmaxf(op_end[v], fr[d]);
-    for (int o = 0; o < D; ++o) {
-        if (o == d) continue;
-        const float arr = arrival[static_cast<size_t>(v) * D + o];
-        if (arr >= 0.0f) {
-            own_free = fmaxf(own_free, arrival_last[static_cast<size_t>(v) * D + o]);   // the source stays until it has been sent
-            al[o] = arr;
-            fr[o] = fmaxf(arr, fr[o]);
-        } else {
-            al[o] = -1.0f;
-            fr[o] = -1.0f;
-        }
-    }
-    al[d] = op_start[v];
-    fr[d] = own_free;
-}
-
-// One workgroup per graph: for every device the largest sum of live sizes at any allocation time
-// (the sum only grows at an allocation), summed in float64 in ascending node order; then the
-// memory-penalised run time R(p) = r if m <= M else r + c (m - M) (appendix, "Reward").
-// Per device, the copies that live there are first packed into LDS (alloc, free, size; node order
-// kept), padded to a multiple of four with entries that are never live; every packed entry is a
-// candidate time, and its live sum runs over the packed entries four at a time.
-__global__ __launch_bounds__(256) void k_peak_memory(GraphView gv, int D, int n_max,
+// arrival: first crossing of an output to a device (the copy there exists from then on); arrival_last:
+// last crossing (the source is kept until then); the same array unless an output may cross twice.
+// peaks [B, D] and done [B] (zero between launches): exchange between a graph's workgroups.
+__global__ __launch_bounds__(kPeakThreads) void k_peak_memory(GraphView gv, int D, int n_max,
                                                      const float *__restrict__ node_feats,
-                                                     const float *__restrict__ alloc,
-                                                     const float *__restrict__ free_t,
+                                                     const int32_t *__restrict__ placement,
+                                                     const float *__restrict__ op_start,
+                                                     const float *__restrict__ op_end,
+                                                     const float *__restrict__ arrival,
+                                                     const float *__restrict__ arrival_last,
                                                      const float *__restrict__ runtime, float mem_limit,
-                                                     float penalty, float *__restrict__ out_peak,
+                                                     float penalty, double *peaks, uint32_t *done,
+                                                     float *__restrict__ out_peak,
                                                      float *__restrict__ out_reward)
 {
     typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4;
     extern __shared__ __attribute__((aligned(16))) unsigned char lds_raw[];
-    const int cap = (n_max + 3) / 4 * 4 + 4;
+    const int cap = peak_capacity(n_max);
     float *ca = reinterpret_cast<float *>(lds_raw), *cf = ca + cap, *cs = cf + cap;
-    __shared__ double red[256];
-    __shared__ double peak_all;
-    __shared__ int wave_cnt[4];
-    __shared__ int packed;
-    const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    uint32_t *until = reinterpret_cast<uint32_t *>(cs + cap);   // bits of the latest use on this device + 1, 0: none
+    __shared__ double red[kPeakThreads / 64];
+    __shared__ int wave_cnt[kPeakThreads / 64];
+    const int b = blockIdx.x / D, d = blockIdx.x - b * D;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int n0 = gv.node_off[b], n = gv.node_off[b + 1] - n0;
     const float r = runtime[b];
     if (!(r == r)) {                       // invalid placement: the simulator wrote NaN
-        if (tid == 0 && out_reward) out_reward[b] = r;
-        if (out_peak) for (int d = tid; d < D; d += 256) out_peak[static_cast<size_t>(b) * D + d] = r;
+        if (tid == 0) {
+            if (out_peak) out_peak[static_cast<size_t>(b) * D + d] = r;
+            if (d == 0) out_reward[b] = r;
+        }
         return;
     }
-    if (tid == 0) peak_all = 0.0;
-    for (int d = 0; d < D; ++d) {
-        __syncthreads();
-        if (tid == 0) packed = 0;
-        __syncthreads();
-        for (int base = 0; base < n; base += 256) {
-            const int u = base + tid;
-            float a = -1.0f, f = -1.0f;
-            if (u < n) {
-                a = alloc[static_cast<size_t>(n0 + u) * D + d];
-                f = free_t[static_cast<size_t>(n0 + u) * D + d];
-            }
-            const bool have = a >= 0.0f;
-            const unsigned long long m = __ballot(have);
-            if (lane == 0) wave_cnt[wave] = __popcll(m);
-            __syncthreads();
-            int pos = packed + __popcll(m & ((1ull << lane) - 1ull));
-            for (int w = 0; w < wave; ++w) pos += wave_cnt[w];
-            if (have) {
-                ca[pos] = a;
-                cf[pos] = f;
-                cs[pos] = node_feats[static_cast<size_t>(n0 + u) * 3 + 1];
-            }
-            __syncthreads();
-            if (tid == 0) packed += wave_cnt[0] + wave_cnt[1] + wave_cnt[2] + wave_cnt[3];
-            __syncthreads();
-        }
-        const int k = packed, k4 = (k + 3) / 4 * 4;
-        for (int i = k + tid; i < k4; i += 256) {      // padding: allocated after every time, never live
-            ca[i] = __builtin_inff();
-            cf[i] = -1.0f;
-            cs[i] = 0.0f;
-        }
-        __syncthreads();
-        double mx = 0.0;
-        for (int i = tid; i < k; i += 256) {
-            const float t = ca[i];
-            double live = 0.0;
-            for (int j = 0; j < k4; j += 4) {
-                const f32x4 a4 = *reinterpret_cast<const f32x4 *>(ca + j);
-                const f32x4 f4 = *reinterpret_cast<const f32x4 *>(cf + j);
-                const f32x4 s4 = *reinterpret_cast<const f32x4 *>(cs + j);
-#pragma unroll
-                for (int q = 0; q < 4; ++q)
-                    live += (a4[q] <= t && t < f4[q]) ? static_cast<double>(s4[q]) : 0.0;
-            }
-            mx = live > mx ? live : mx;
-        }
-        red[tid] = mx;
-        __syncthreads();
-        for (int step = 128; step > 0; step >>= 1) {
-            if (tid < step) red[tid] = red[tid + step] > red[tid] ? red[tid + step] : red[tid];
-            __syncthreads();
-        }
-        if (tid == 0) {
-            if (out_peak) out_peak[static_cast<size_t>(b) * D + d] = static_cast<float>(red[0]);
-            peak_all = red[0] > peak_all ? red[0] : peak_all;
+    for (int v = tid; v < n; v += kPeakThreads) until[v] = 0;
+    __syncthreads();
+    // eight lanes share a node's children
+    for (int v = tid >> 3; v < n; v += kPeakThreads / 8) {
+        const int pv = placement[n0 + v], end = gv.nbr_ptr[1][n0 + v + 1];
+        for (int p = gv.nbr_ptr[1][n0 + v] + (lane & 7); p < end; p += 8) {
+            const int c = gv.nbr_idx[1][p], pc = placement[c];
+            if (pc == d)
+                atomicMax(&until[v], __float_as_uint(op_end[c]) + 1u);
+            else if (pv == d)
+                atomicMax(&until[v], __float_as_uint(arrival_last[static_cast<size_t>(n0 + v) * D + pc]) + 1u);
         }
     }
     __syncthreads();
-    if (tid == 0 && out_reward) {
-        const double m = peak_all, M = static_cast<double>(mem_limit);
-        out_reward[b] = m <= M ? r : static_cast<float>(static_cast<double>(r) + static_cast<double>(penalty) * (m - M));
+    int k = 0;                             // copies so far
+    for (int base = 0; base < n; base += kPeakThreads) {
+        const int v = base + tid;
+        float al = 0.0f, fr = 0.0f, size = 0.0f;
+        bool have = false;
+        if (v < n) {
+            const uint32_t u = until[v];
+            const float last = u ? __uint_as_float(u - 1u) : 0.0f;
+            const bool own = placement[n0 + v] == d;
+            have = own || u != 0;
+            if (have) {
+                al = own ? op_start[n0 + v] : arrival[static_cast<size_t>(n0 + v) * D + d];
+                fr = fmaxf(own ? op_end[n0 + v] : al, last);
+                size = node_feats[static_cast<size_t>(n0 + v) * 3 + 1];
+            }
+        }
+        const unsigned long long m = __ballot(have);
+        if (lane == 0) wave_cnt[wave] = __popcll(m);
+        __syncthreads();
+        int pos = k + __popcll(m & ((1ull << lane) - 1ull));
+        for (int w = 0; w < kPeakThreads / 64; ++w) {
+            pos += w < wave ? wave_cnt[w] : 0;
+            k += wave_cnt[w];
+        }
+        if (have) {
+            ca[pos] = al;
+            cf[pos] = fr;
+            cs[pos] = size;
+        }
+        __syncthreads();
     }
+    const int k4 = (k + 3) / 4 * 4;
+    if (tid < k4 - k) {                    // padding: allocated after every time, never live
+        ca[k + tid] = __builtin_inff();
+        cf[k + tid] = -1.0f;
+        cs[k + tid] = 0.0f;
+    }
+    __syncthreads();
+    double mx = 0.0;
+    for (int i = tid; i < k; i += kPeakThreads * kPeakTimes) {
+        float t[kPeakTimes];
+        double live[kPeakTimes];
+#pragma unroll
+        for (int q = 0; q < kPeakTimes; ++q) {
+            t[q] = ca[min(i + q * kPeakThreads, k - 1)];
+            live[q] = 0.0;
+        }
+        for (int j = 0; j < k4; j += 4) {
+            const f32x4 a4 = *reinterpret_cast<const f32x4 *>(ca + j);
+            const f32x4 f4 = *reinterpret_cast<const f32x4 *>(cf + j);
+            const f32x4 s4 = *reinterpret_cast<const f32x4 *>(cs + j);
+#pragma unroll
+            for (int x = 0; x < 4; ++x)
+#pragma unroll
+                for (int q = 0; q < kPeakTimes; ++q)
+                    live[q] += static_cast<double>((a4[x] <= t[q] && t[q] < f4[x]) ? s4[x] : 0.0f);
+        }
+#pragma unroll
+        for (int q = 0; q < kPeakTimes; ++q) mx = live[q] > mx ? live[q] : mx;
+    }
+    for (int step = 32; step > 0; step >>= 1) {
+        const double o = __shfl_xor(mx, step);
+        mx = o > mx ? o : mx;
+    }
+    if (lane == 0) red[wave] = mx;
+    __syncthreads();
+    if (tid != 0) return;
+    for (int w = 1; w < kPeakThreads / 64; ++w) mx = red[w] > mx ? red[w] : mx;
+    if (out_peak) out_peak[static_cast<size_t>(b) * D + d] = static_cast<float>(mx);
+    double *mine = peaks + static_cast<size_t>(b) * D;
+    __hip_atomic_store(mine + d, mx, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const uint32_t before = __hip_atomic_fetch_add(done + b, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
+    if (before != static_cast<uint32_t>(D) - 1u) return;
+    for (int o = 0; o < D; ++o) {
+        const double x = __hip_atomic_load(mine + o, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        mx = x > mx ? x : mx;
+    }
+    const double M = static_cast<double>(mem_limit);
+    out_reward[b] = mx <= M ? r : static_cast<float>(static_cast<double>(r) + static_cast<double>(penalty) * (mx - M));
+    __hip_atomic_store(done + b, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 }  // namespace
 
+// The size that the limit of include/placeto.h is stated in: 18 n + 13 e bytes and some padding (the
+// kernel takes less).
 size_t simulator_lds_bytes(int n_max, int e_max)
 {
-    return sizeof(int32_t) * (n_max + 1) + 2 * sizeof(float) * n_max + sizeof(float) * e_max +
-           3 * sizeof(uint16_t) * (e_max + (e_max & 1)) + sizeof(uint32_t) * n_max +
-           sizeof(uint16_t) * (n_max + (n_max & 1)) + e_max + 16 + sizeof(uint16_t) * (e_max + 2);
+    return 18 * static_cast<size_t>(n_max) + 13 * static_cast<size_t>(e_max) + 24 + 2 * (n_max & 1) + 6 * (e_max & 1);
 }
 
 int launch_simulate(const GraphView &gv, int D, int n_max, int e_max, const float *node_feats,
@@ -450,48 +600,30 @@ int launch_simulate(const GraphView &gv, int D, int n_max, int e_max, const floa
                     int32_t *out_events, hipStream_t s)
 {
     if (gv.B == 0) return PL_OK;
-    const size_t lds = simulator_lds_bytes(n_max, e_max);
-    auto run = [&](auto kernel) {
-        if (lds > 64 * 1024)
-            PL_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(kernel),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds)));
-        hipLaunchKernelGGL(kernel, dim3(gv.B), dim3(64), lds, s, gv, D, n_max, e_max, node_feats, placement,
-                           inv_bw, out_runtime, out_events, nullptr, nullptr, nullptr, nullptr);
-        return static_cast<int>(PL_OK);
-    };
-    return per_child ? run(k_simulate<false, true>) : run(k_simulate<false, false>);
+    return (per_child ? simulate<false, true> : simulate<false, false>)(gv, D, n_max, e_max, node_feats, placement, inv_bw,
+                                                                        out_runtime, out_events, nullptr, nullptr, nullptr,
+                                                                        nullptr, s);
 }
 
-// Simulation with the timeline, then lifetimes, peaks and R(p).  scratch: op_start, op_end
-// [n_tot]; arrival, arrival_last (used with per_child only), alloc, free_t [n_tot, D].
+// Simulation with the timeline, then peaks and R(p).  scratch: op_start, op_end [n_tot]; arrival,
+// arrival_last (used with per_child only) [n_tot, D]; peaks [B, D]; done [B], zero.
 int launch_simulate_reward(const GraphView &gv, int D, int n_max, int e_max, const float *node_feats,
                            const int32_t *placement, float inv_bw, bool per_child, float mem_limit, float penalty,
-                           float *op_start, float *op_end, float *arrival, float *arrival_last, float *alloc,
-                           float *free_t, float *runtime, float *out_peak, float *out_reward, int32_t *out_events,
+                           float *op_start, float *op_end, float *arrival, float *arrival_last, double *peaks,
+                           uint32_t *done, float *runtime, float *out_peak, float *out_reward, int32_t *out_events,
                            hipStream_t s)
 {
     if (gv.B == 0) return PL_OK;
-    const size_t lds = simulator_lds_bytes(n_max, e_max);
-    const size_t nd = static_cast<size_t>(gv.n_tot) * D;
-    hipLaunchKernelGGL(k_fill_value, dim3(static_cast<unsigned>((nd + 255) / 256)), dim3(256), 0, s, arrival, nd, -1.0f);
-    auto run = [&](auto kernel) {
-        if (lds > 64 * 1024)
-            PL_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(kernel),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds)));
-        hipLaunchKernelGGL(kernel, dim3(gv.B), dim3(64), lds, s, gv, D, n_max, e_max, node_feats, placement,
-                           inv_bw, runtime, out_events, op_start, op_end, arrival, arrival_last);
-        return static_cast<int>(PL_OK);
-    };
-    const int rc = per_child ? run(k_simulate<true, true>) : run(k_simulate<true, false>);
+    const int rc = (per_child ? simulate<true, true> : simulate<true, false>)(
+        gv, D, n_max, e_max, node_feats, placement, inv_bw, runtime, out_events, op_start, op_end, arrival, arrival_last, s);
     if (rc) return rc;
-    hipLaunchKernelGGL(k_lifetimes, dim3((gv.n_tot + 255) / 256), dim3(256), 0, s, gv, D, placement, op_start, op_end,
-                       arrival, per_child ? arrival_last : arrival, alloc, free_t);
-    const size_t lds2 = sizeof(float) * 3 * (static_cast<size_t>(n_max + 3) / 4 * 4 + 4);
-    if (lds2 > 48 * 1024)
+    const size_t lds = peak_lds(n_max);
+    if (lds > 48 * 1024)
         PL_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(k_peak_memory),
-                                   hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds2)));
-    hipLaunchKernelGGL(k_peak_memory, dim3(gv.B), dim3(256), lds2, s, gv, D, n_max, node_feats, alloc, free_t, runtime,
-                       mem_limit, penalty, out_peak, out_reward);
+                                   hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds)));
+    hipLaunchKernelGGL(k_peak_memory, dim3(gv.B * D), dim3(kPeakThreads), lds, s, gv, D, n_max, node_feats, placement,
+                       op_start, op_end, arrival, per_child ? arrival_last : arrival, runtime, mem_limit, penalty, peaks,
+                       done, out_peak, out_reward);
     return PL_OK;
 }
 

@@ -1,0 +1,70 @@
+"""The simulator kernel where its layout and its lists change: child lists around the length a node's
+record holds (two) and around a wave (64), transfer lists longer than a record, pending events in one
+and in two DPP rows, and graphs at the LDS limit with few edges (16-bit states) and with many.
+Bit for bit against the oracle, like tests/test_gpu_simulator.py."""
+import numpy as np
+import pytest
+
+from tests.test_gpu_simulator import _device_both, _oracle_both
+from workloads.synthetic import Workload
+
+pytestmark = pytest.mark.gpu
+
+
+def _workload(graphs, D, rng, ties):
+    n_nodes = np.array([n for n, _, _ in graphs], np.int32)
+    n_tot = int(n_nodes.sum())
+    feats = (np.stack([rng.integers(1, 4, n_tot), rng.integers(0, 3, n_tot), np.zeros(n_tot)], axis=1) if ties else
+             np.stack([rng.lognormal(0, 1, n_tot), rng.lognormal(0, 1, n_tot), np.zeros(n_tot)], axis=1))
+    return Workload(name="limits", B=len(graphs), D=D, H=8, n_layers=1, k_sweeps=1, group_by_device=1,
+                    weight_dtype="fp32", n_nodes=n_nodes, n_edges=np.array([len(s) for _, s, _ in graphs], np.int32),
+                    edge_src=np.concatenate([s for _, s, _ in graphs]).astype(np.int32),
+                    edge_dst=np.concatenate([d for _, _, d in graphs]).astype(np.int32),
+                    node_feats=feats.astype(np.float32), placement=rng.integers(0, D, n_tot).astype(np.int32),
+                    cur_node=np.zeros(len(graphs), np.int32), weights=np.zeros(1, np.float32))
+
+
+def _fan(width):
+    """A root with `width` children that all feed one node and, in pairs, a second generation."""
+    src = [0] * width + list(range(1, width + 1)) + list(range(1, width + 1))
+    dst = list(range(1, width + 1)) + [width + 1] * width + [width + 2 + i // 2 for i in range(width)]
+    return width + 2 + (width + 1) // 2, np.array(src), np.array(dst)
+
+
+def _check(w, per_child, reward):
+    rt, ev, peak, _ = _device_both(w, w.placement, 1.0, per_child)
+    for b in range(w.B):
+        r, e, p = _oracle_both(w, b, w.placement, 1.0, per_child) if reward else (*_run(w, b, per_child), None)
+        assert (rt[b], ev[b]) == (r, e), (b, rt[b], r, ev[b], e)
+        if reward:
+            np.testing.assert_allclose(peak[b], p, rtol=1e-6, atol=0, err_msg=f"graph {b}")
+
+
+def _run(w, b, per_child):
+    from oracle import simulator as sim
+    n0, n1, e0, e1 = (int(x) for x in (w.node_off[b], w.node_off[b + 1], w.edge_off[b], w.edge_off[b + 1]))
+    return sim.simulate(n1 - n0, w.edge_src[e0:e1], w.edge_dst[e0:e1], w.node_feats[n0:n1, 0], w.node_feats[n0:n1, 1],
+                        w.placement[n0:n1], w.D, np.float32(1.0), per_child=bool(per_child))
+
+
+@pytest.mark.parametrize("per_child", [0, 1])
+@pytest.mark.parametrize("D", [2, 8, 9, 16])
+def test_child_and_transfer_lists(D, per_child):
+    rng = np.random.default_rng(41 + D)
+    w = _workload([_fan(k) for k in (1, 2, 3, 63, 64, 65, 130)], D, rng, ties=D % 2 == 1)
+    _check(w, per_child, True)
+
+
+@pytest.mark.parametrize("n,e", [(9090, 2), (9000, 130), (8180, 1), (4000, 7000)])
+def test_graphs_at_the_size_limit(n, e):
+    assert 18 * n + 13 * e <= 160 * 1024 - 32
+    rng = np.random.default_rng(n)
+    # (edges between different ids, lower to higher, none twice)
+    pairs = set()
+    while len(pairs) < e:
+        a, b = sorted(int(x) for x in rng.integers(0, n, 2))
+        if a != b:
+            pairs.add((a, b))
+    pairs = np.array(sorted(pairs))
+    w = _workload([(n, pairs[:, 0], pairs[:, 1])], 8, rng, ties=False)
+    _check(w, 0, False)
