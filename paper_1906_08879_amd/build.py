@@ -18,10 +18,12 @@ HIPCC_FLAGS = [
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
 ]
 
-# Flags of single sources.  The simulator's event loop is scalar code that branches on the scalar unit:
-# structured control flow (which the back end otherwise gives uniform branches too) makes it copy its
-# whole register state at every join (3.38 -> 2.70 ms for 256 NASNet-like graphs).
-SOURCE_FLAGS = {"kernels_simulator.hip": ["-mllvm", "-structurizecfg-skip-uniform-regions"]}
+# Flags of single sources.  Both kernels branch on the scalar unit inside a long dependent chain, and
+# structured control flow (which the back end otherwise gives uniform branches too) costs them copies
+# of their register state at every join.  Simulator: 3.38 -> 2.70 ms for 256 NASNet-like graphs; sweep:
+# forward pass 0.715 -> 0.690 ms (64 NMT-like graphs), 2.16 -> 2.12 ms (256 NASNet-like ones).
+_NO_STRUCTURE = ["-mllvm", "-structurizecfg-skip-uniform-regions"]
+SOURCE_FLAGS = {"kernels_simulator.hip": _NO_STRUCTURE, "kernels_mfma.hip": _NO_STRUCTURE}
 
 
 def hipcc() -> str:
