@@ -293,7 +293,8 @@ size_t carve_workspace(unsigned char *base, size_t n, size_t B, const ModelView 
     ws->featb = reinterpret_cast<float4 *>(take(sizeof(float4) * (n + 1)));
     ws->partial = reinterpret_cast<float *>(take(sizeof(float) * (B * ws->n_chunks * 3 * mv.G * H + 4)));
     ws->zbuf = reinterpret_cast<float *>(take(sizeof(float) * (B * mv.Z + 4)));
-    ws->hidp = reinterpret_cast<double *>(take(sizeof(double) * (static_cast<size_t>((mv.Z + 255) / 256) * B * H + 4)));
+    ws->hid = reinterpret_cast<double *>(take(sizeof(double) * (B * H + 4)));
+    ws->logit = reinterpret_cast<float *>(take(sizeof(float) * (B * mv.D + 4)));
     ws->klist = reinterpret_cast<int32_t *>(take(sizeof(int32_t) * (n + 16)));
     ws->koff = reinterpret_cast<int32_t *>(take(sizeof(int32_t) * (B * (3 * kMaxD + 1) + 4)));
     if (with_reach) ws->reach = take(2 * n + 32);
@@ -305,7 +306,7 @@ size_t carve_workspace(unsigned char *base, size_t n, size_t B, const ModelView 
 void free_grad_workspace(GradWorkspace &gw)
 {
     float *all[] = {gw.fact, gw.gact, gw.agg, gw.dagg, gw.dfg, gw.keep, gw.snap_emb, gw.snap_msg, gw.lact, gw.dl, gw.demb, gw.dx, gw.phi,
-                    gw.pooled, gw.dP, gw.hin, gw.hact, gw.dh, gw.dz, gw.hid, gw.dpre, gw.dlogit, gw.partial};
+                    gw.dP, gw.hin, gw.hact, gw.dh, gw.dz, gw.hid, gw.dpre, gw.dlogit, gw.partial};
     for (float *p : all) (void)hipFree(p);
     (void)hipFree(gw.cls);
     (void)hipFree(gw.mask4);
@@ -375,7 +376,6 @@ int ensure_grad_workspace(pl_graph_batch *g, const ModelView &mv)
     PL_HIP(hipMalloc(reinterpret_cast<void **>(&gw.counts), 64));
     PL_HIP(hipMalloc(reinterpret_cast<void **>(&gw.blk_cnt), sizeof(int32_t) * (3 * ((n + 255) / 256) + 4)));
     PL_HIP(hipMalloc(reinterpret_cast<void **>(&gw.lists), sizeof(int32_t) * (3 * n + 4)));
-    PL_HIP(take(&gw.pooled, 3 * BG * H));
     PL_HIP(take(&gw.dP, 3 * BG * H));
     PL_HIP(take(&gw.hin, 3 * BG * H));
     PL_HIP(take(&gw.hact, 3 * L * BG * H));
@@ -512,7 +512,8 @@ int forward_impl(pl_graph_batch *g, const float *node_feats, const int32_t *plac
                  float *out_node_emb, float *out_pooled, uint8_t *out_class, void *stream, bool validate,
                  float *keep = nullptr, size_t keep_stride = 0, float *keep_pool = nullptr,
                  bool *pool_kept = nullptr, float *snap_emb = nullptr, float *snap_msg = nullptr,
-                 const Workspace *static_ws = nullptr, uint8_t *gates = nullptr)
+                 const Workspace *static_ws = nullptr, uint8_t *gates = nullptr, float *keep_hin = nullptr,
+                 float *keep_hact = nullptr)
 {
     if (!g || !w) return fail(PL_ERR_NULL, "graph batch or weights handle is NULL");
     if (g->host.B == 0) return PL_OK;
@@ -531,7 +532,7 @@ int forward_impl(pl_graph_batch *g, const float *node_feats, const int32_t *plac
     const Workspace &ws = static_ws ? *static_ws : g->ws;
     StageTimer off;
     StageTimer &timer = static_ws ? off : g->timer;
-    ForwardArgs fa{node_feats, placement, cur_node, out_logits, out_probs, out_pooled};
+    ForwardArgs fa{node_feats, placement, cur_node, out_logits, out_probs, out_pooled, keep_hin, keep_hact};
     const GraphView &gv = g->view;
     // the matrix-core sweep addresses its buffers with 32-bit offsets
     const bool fits32 = (static_cast<double>(g->host.n_tot) + 2) * 2 * mv.H * sizeof(float) < 4.0e9;
@@ -580,7 +581,7 @@ int forward_impl(pl_graph_batch *g, const float *node_feats, const int32_t *plac
     }
     {
         StageScope scope(timer, PL_STAGE_HEAD, s);
-        launch_head_generic(gv, mv, ws, fa, pool_slices, s);
+        launch_head(gv, mv, ws, fa, pool_slices, s);
     }
     if (out_node_emb)
         PL_HIP(hipMemcpyAsync(out_node_emb, ws.emb,
@@ -1102,12 +1103,13 @@ static int policy_gradient_impl(pl_graph_batch *g, const float *node_feats, cons
     }
     // likewise the matrix-core pooling kernel keeps the outputs of l's layers
     bool pool_kept = false;
-    rc = forward_impl(g, node_feats, placement, cur_node, w, out_logits, nullptr, nullptr, g->gw.pooled, nullptr,
+    rc = forward_impl(g, node_feats, placement, cur_node, w, out_logits, nullptr, nullptr, nullptr, nullptr,
                       stream, false, keep, g->gw.dfg_stride, w->path == 0 ? g->gw.lact : nullptr, &pool_kept,
-                      w->cfg.k_sweeps > 1 ? g->gw.snap_emb : nullptr, g->gw.snap_msg, nullptr, g->gw.mask4);
+                      w->cfg.k_sweeps > 1 ? g->gw.snap_emb : nullptr, g->gw.snap_msg, nullptr, g->gw.mask4,
+                      g->gw.hin, g->gw.hact);
     if (rc) return rc;
     if (!accumulate) launch_fill_zero(grad, plan_weights(w->cfg, nullptr), s);
-    ForwardArgs fa{node_feats, placement, cur_node, out_logits, nullptr, g->gw.pooled};
+    ForwardArgs fa{node_feats, placement, cur_node, out_logits, nullptr, nullptr};
     const StageMarks marks{&g->timer, stage_mark};
     const BackwardArgs ba{actions, coeff, entropy_coeff, grad, out_logp, out_entropy, g->gw.snap_emb, g->gw.snap_msg,
                           w->path == 0 ? reinterpret_cast<const uint4 *>(w->d_pool_bwfrag) : nullptr};

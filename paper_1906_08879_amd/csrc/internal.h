@@ -99,24 +99,6 @@ struct ModelView {
     LayerRef pol1, pol2;
 };
 
-// ---- the policy network's hidden unit j and logit d of graph b (Appendix A.7), in float64 from
-// the partial products of its first layer; one definition for the forward and the reverse pass.
-__device__ __forceinline__ double policy_hidden(const ModelView &mv, const double *__restrict__ hidp,
-                                                int n_slices, int B, int b, int j)
-{
-    double s = static_cast<double>(mv.blob[mv.pol1.b + j]);
-    for (int sl = 0; sl < n_slices; ++sl) s += hidp[(static_cast<size_t>(sl) * B + b) * mv.H + j];
-    return s > 0.0 ? s : 0.0;
-}
-
-__device__ __forceinline__ float policy_logit(const ModelView &mv, const double *hid, int d)
-{
-    const float *W = mv.blob + mv.pol2.w;
-    double s = static_cast<double>(mv.blob[mv.pol2.b + d]);
-    for (int k = 0; k < mv.H; ++k) s = fma(hid[k], static_cast<double>(W[k * mv.D + d]), s);
-    return static_cast<float>(s);
-}
-
 // ---- scratch owned by a batch for one (D, H)
 struct Workspace {
     unsigned char *base = nullptr;  // the one allocation that holds every buffer but reach (null: not owned)
@@ -127,7 +109,8 @@ struct Workspace {
     uint8_t *reach = nullptr;   // [2, n_tot]   0: descendant-of-v* bit, 1: ancestor-of-v* bit
     float *partial = nullptr;   // [B, n_chunks_max, 3G, H] pooling partial sums
     float *zbuf = nullptr;      // [B, Z] policy inputs
-    double *hidp = nullptr;     // [ceil(Z / 256), B, H] partial products of policy layer 1 (float64 sums)
+    double *hid = nullptr;      // [B, H] hidden layer of the policy network
+    float *logit = nullptr;     // [B, D] logits, also of graphs that have no valid current node
     int32_t *klist = nullptr;   // [n_tot] node ids grouped by (set, device group), per graph (matrix-core pooling)
     int32_t *koff = nullptr;    // [B][3 kMaxD + 1] first position of every key within its graph
     int32_t n_chunks = 0;
@@ -142,6 +125,9 @@ struct ForwardArgs {
     float *out_logits;
     float *out_probs;
     float *out_pooled;
+    // inputs [3, B G, H] and layer outputs [3, L, B G, H] of h, kept for the reverse pass, or null
+    float *keep_hin = nullptr;
+    float *keep_hact = nullptr;
 };
 
 constexpr int kPoolChunk = 128;   // nodes per pooling workgroup
@@ -156,8 +142,24 @@ void launch_classes(const GraphView &gv, const int32_t *cur_node, const uint8_t 
                     uint8_t *out_class, hipStream_t s);
 void launch_pool_generic(const GraphView &gv, const ModelView &mv, const Workspace &ws,
                          const ForwardArgs &fa, hipStream_t s);
-void launch_head_generic(const GraphView &gv, const ModelView &mv, const Workspace &ws,
-                         const ForwardArgs &fa, int max_chunks, hipStream_t s);
+
+// ---- policy head (kernels_head.hip)
+void launch_head(const GraphView &gv, const ModelView &mv, const Workspace &ws, const ForwardArgs &fa, int max_chunks,
+                 hipStream_t s);
+struct HeadBwArgs {
+    const double *hid64;          // [B, H], logit [B, D]: left by the forward pass
+    const float *logit;
+    const int32_t *actions;
+    const float *coeff, *entropy_coeff;
+    const float *hact;            // [3, L, B G, H] layer outputs of h
+    float *hid, *dpre, *dlogit;   // [B, H], [B, H], [B, D]
+    float *dz;                    // [B, Z]
+    float *dh;                    // [3, L, B G, H] deltas of h's layers
+    float *dP;                    // [B, 3, G, H]
+    float *out_logp, *out_entropy;
+};
+void launch_head_bw(const GraphView &gv, const ModelView &mv, const float *blob_t, const int32_t *cur_node,
+                    const HeadBwArgs &a, hipStream_t s);
 
 // ---- MDP transition (kernels_episode.hip)
 void launch_episode_step(const GraphView &gv, int D, const float *logits, const float *uniforms,
@@ -222,7 +224,7 @@ struct GradWorkspace {
     int32_t *counts = nullptr;                // [4] sizes of the three node sets
     int32_t *blk_cnt = nullptr;               // [ceil(n_tot / 256), 3] per-block counts, then offsets
     int32_t *lists = nullptr;                 // [3, n_tot] nodes of each set
-    float *pooled = nullptr, *dP = nullptr;   // [B, 3, G, H]
+    float *dP = nullptr;                      // [B, 3, G, H]
     float *hin = nullptr;                     // [3, B G, H] inputs of h per set
     float *hact = nullptr, *dh = nullptr;     // [3, L, B G, H]
     float *dz = nullptr;                      // [B, Z]

@@ -84,180 +84,6 @@ __device__ __forceinline__ size_t slab(int dir, int l, int L, int n_tot, int H)
     return (static_cast<size_t>(dir) * L + l) * static_cast<size_t>(n_tot) * H;
 }
 
-// ------------------------------------------------------------------ 1. policy head
-// One workgroup per graph: logits again from the stored partial products of policy layer 1,
-// d logits = c (one-hot(a) - softmax), back to the hidden layer and to the policy input z.
-// A graph whose current node or action is out of range gets a zero gradient and logp = NaN.
-__global__ __launch_bounds__(kThreads) void k_bw_head(GraphView gv, ModelView mv,
-                                                      const float *__restrict__ blob_t,
-                                                      const double *__restrict__ hidp, int n_slices,
-                                                      const int32_t *__restrict__ cur_node,
-                                                      const int32_t *__restrict__ actions,
-                                                      const float *__restrict__ coeff,
-                                                      const float *__restrict__ ent_coeff,
-                                                      float *__restrict__ out_entropy,
-                                                      float *__restrict__ hid_out,
-                                                      float *__restrict__ dpre_out,
-                                                      float *__restrict__ dlogit_out,
-                                                      float *__restrict__ dz,
-                                                      float *__restrict__ out_logp)
-{
-    __shared__ double hid64[kMaxH];
-    __shared__ float hid[kMaxH];
-    __shared__ float dpre[kMaxH];
-    __shared__ float logit[kMaxD];
-    __shared__ float dlog[kMaxD];
-    const int H = mv.H, D = mv.D, b = blockIdx.x, tid = threadIdx.x;
-    const int n_b = gv.node_off[b + 1] - gv.node_off[b];
-    const int cl = cur_node[b];
-    const bool cur_ok = cl >= 0 && cl < n_b;
-    for (int j = tid; j < H; j += kThreads) {
-        hid64[j] = policy_hidden(mv, hidp, n_slices, gv.B, b, j);
-        hid[j] = static_cast<float>(hid64[j]);
-    }
-    __syncthreads();
-    if (tid < D) logit[tid] = policy_logit(mv, hid64, tid);
-    __syncthreads();
-    if (tid == 0) {
-        float mx = logit[0];
-        for (int d = 1; d < D; ++d) mx = fmaxf(mx, logit[d]);
-        float tot = 0.0f;
-        for (int d = 0; d < D; ++d) tot += expf(logit[d] - mx);
-        const int a = actions[b];
-        const bool ok = cur_ok && a >= 0 && a < D;
-        const float c = ok ? coeff[b] : 0.0f;
-        // entropy term (Appendix A.7): H = - sum p log p, dH / d logit_d = - p_d (log p_d + H), with
-        // log p_d = logit_d - max - log(sum), which stays finite where p_d underflows to 0
-        const float beta = (ok && ent_coeff) ? ent_coeff[b] : 0.0f;
-        const float lse = logf(tot);
-        float ent = 0.0f;
-        for (int d = 0; d < D; ++d) {
-            const float p = expf(logit[d] - mx) / tot;
-            ent -= p * ((logit[d] - mx) - lse);
-        }
-        for (int d = 0; d < D; ++d) {
-            const float p = expf(logit[d] - mx) / tot;
-            dlog[d] = c * ((d == a ? 1.0f : 0.0f) - p) - beta * p * (((logit[d] - mx) - lse) + ent);
-        }
-        if (out_logp) out_logp[b] = ok ? (logit[a] - mx) - lse : __builtin_nanf("");
-        if (out_entropy) out_entropy[b] = cur_ok ? ent : __builtin_nanf("");
-    }
-    __syncthreads();
-    for (int j = tid; j < H; j += kThreads) {
-        const float *W = mv.blob + mv.pol2.w + static_cast<size_t>(j) * D;
-        float s = 0.0f;
-        for (int d = 0; d < D; ++d) s = fmaf(W[d], dlog[d], s);
-        const float dp = hid[j] > 0.0f ? s : 0.0f;
-        dpre[j] = dp;
-        hid_out[static_cast<size_t>(b) * H + j] = hid[j];
-        dpre_out[static_cast<size_t>(b) * H + j] = dp;
-    }
-    if (tid < D) dlogit_out[static_cast<size_t>(b) * D + tid] = dlog[tid];
-}
-
-// dz[b][k] = sum_j W1[k][j] dpre[b][j] for kDzGraphs graphs per workgroup and one 256-wide slice of
-// the policy input: a weight is loaded once for all the workgroup's graphs (one workgroup per graph
-// read the whole first policy layer, 1.7 MB at the NASNet-like shape, from L2 every time).
-constexpr int kDzGraphs = 8;
-__global__ __launch_bounds__(kThreads) void k_bw_dz(ModelView mv, int B, const float *__restrict__ blob_t,
-                                                    const float *__restrict__ dpre, float *__restrict__ dz)
-{
-    __shared__ float dp[kDzGraphs][kMaxH];
-    const int H = mv.H, Z = mv.Z, tid = threadIdx.x;
-    const int k = blockIdx.x * kThreads + tid, b0 = blockIdx.y * kDzGraphs;
-    const int nb = min(kDzGraphs, B - b0);
-    for (int i = tid; i < kDzGraphs * H; i += kThreads) {
-        const int g = i / H, j = i - g * H;
-        dp[g][j] = g < nb ? dpre[static_cast<size_t>(b0 + g) * H + j] : 0.0f;
-    }
-    __syncthreads();
-    if (k >= Z) return;
-    const float *W1t = blob_t + mv.pol1.w;   // [H][Z]
-    float acc[kDzGraphs];
-#pragma unroll
-    for (int g = 0; g < kDzGraphs; ++g) acc[g] = 0.0f;
-    constexpr int KB = 16;                   // weights per batch of loads
-    int j = 0;
-    for (; j + KB <= H; j += KB) {
-        float w[KB];
-#pragma unroll
-        for (int u = 0; u < KB; ++u) w[u] = W1t[static_cast<size_t>(j + u) * Z + k];
-#pragma unroll
-        for (int u = 0; u < KB; ++u)
-#pragma unroll
-            for (int g = 0; g < kDzGraphs; ++g) acc[g] = fmaf(w[u], dp[g][j + u], acc[g]);
-    }
-    for (; j < H; ++j) {
-        const float w = W1t[static_cast<size_t>(j) * Z + k];
-#pragma unroll
-        for (int g = 0; g < kDzGraphs; ++g) acc[g] = fmaf(w, dp[g][j], acc[g]);
-    }
-#pragma unroll
-    for (int g = 0; g < kDzGraphs; ++g)
-        if (g < nb) dz[static_cast<size_t>(b0 + g) * Z + k] = acc[g];
-}
-
-// Workgroup (set, graph): q[set][d] = h_set(P[set][d]) again for the G device groups, keeping
-// every layer's output, then back from dz to dP[set][d].
-template <int RPT>
-__global__ __launch_bounds__(kThreads) void k_bw_head_sets(GraphView gv, ModelView mv,
-                                                           const float *__restrict__ blob_t,
-                                                           const float *__restrict__ pooled,
-                                                           const float *__restrict__ dz,
-                                                           float *__restrict__ hin,
-                                                           float *__restrict__ hact,
-                                                           float *__restrict__ dh,
-                                                           float *__restrict__ dP)
-{
-    extern __shared__ float lds[];
-    const int H = mv.H, G = mv.G, L = mv.L, Z = mv.Z;
-    const int set = blockIdx.x, b = blockIdx.y, tid = threadIdx.x;
-    const size_t BG = static_cast<size_t>(gv.B) * G;
-    float *buf_p = lds, *buf_a = lds + kTile * H, *buf_b = buf_a + kTile * H;
-    const float *src = pooled + (static_cast<size_t>(b) * 3 + set) * G * H;
-    for (int i = tid; i < G * H; i += kThreads) {
-        const float v = src[i];
-        buf_p[i] = v;
-        hin[(static_cast<size_t>(set) * BG + static_cast<size_t>(b) * G) * H + i] = v;
-    }
-    __syncthreads();
-    const MlpRef &hn = mv.h[set];
-    const float *in = buf_p;
-    for (int l = 0; l < L; ++l) {
-        float *out = (l & 1) ? buf_b : buf_a;
-        dense_rows<RPT>(mv.blob + hn.layer[l].w, H, mv.blob + hn.layer[l].b, H, H, in, H, out, H, G, true);
-        __syncthreads();
-        float *dst = hact + ((static_cast<size_t>(set) * L + l) * BG + static_cast<size_t>(b) * G) * H;
-        for (int i = tid; i < G * H; i += kThreads) dst[i] = out[i];
-        in = out;
-    }
-    __threadfence_block();
-    __syncthreads();
-    // delta of the last layer: dz of this set's slots, masked by the layer's output
-    float *dcur = buf_a, *dnext = buf_b;
-    {
-        const float *act = hact + ((static_cast<size_t>(set) * L + (L - 1)) * BG + static_cast<size_t>(b) * G) * H;
-        const float *g = dz + static_cast<size_t>(b) * Z + static_cast<size_t>(2 + set * G) * H;
-        for (int i = tid; i < G * H; i += kThreads) dcur[i] = act[i] > 0.0f ? g[i] : 0.0f;
-    }
-    __syncthreads();
-    for (int l = L - 1; l >= 0; --l) {
-        float *dst = dh + ((static_cast<size_t>(set) * L + l) * BG + static_cast<size_t>(b) * G) * H;
-        for (int i = tid; i < G * H; i += kThreads) dst[i] = dcur[i];
-        dense_rows<RPT>(blob_t + hn.layer[l].w, H, nullptr, H, H, dcur, H, dnext, H, G, false);
-        __syncthreads();
-        if (l > 0) {
-            const float *act = hact + ((static_cast<size_t>(set) * L + (l - 1)) * BG + static_cast<size_t>(b) * G) * H;
-            for (int i = tid; i < G * H; i += kThreads) dnext[i] = act[i] > 0.0f ? dnext[i] : 0.0f;
-        } else {
-            float *out = dP + (static_cast<size_t>(b) * 3 + set) * G * H;
-            for (int i = tid; i < G * H; i += kThreads) out[i] = dnext[i];
-        }
-        __syncthreads();
-        float *t = dcur; dcur = dnext; dnext = t;
-    }
-}
-
 // Section 2.2 step 3: 0 = v*, 1 = can reach v*, 2 = reachable from v*, 3 = neither.
 __device__ __forceinline__ int node_class_bw(int v, int cur, const uint8_t *reach, int n_tot, int single)
 {
@@ -1670,7 +1496,6 @@ void launch_backward(const GraphView &gv, const ModelView &mv, const float *blob
     float *grad = ba.grad;
     const int H = mv.H, L = mv.L, G = mv.G, B = gv.B, n = gv.n_tot;
     const int rpt = pick_rpt_bw(H);
-    const int n_slices = (mv.Z + 255) / 256;
     const size_t NH = static_cast<size_t>(n) * H;
     const size_t BG = static_cast<size_t>(B) * G;
 
@@ -1679,26 +1504,10 @@ void launch_backward(const GraphView &gv, const ModelView &mv, const float *blob
     };
     // 1. head
     mark(PL_STAGE_BW_HEAD, true);
-    hipLaunchKernelGGL(k_bw_head, dim3(B), dim3(kThreads), 0, s, gv, mv, blob_t, ws.hidp, n_slices, fa.cur_node,
-                       ba.actions, ba.coeff, ba.entropy_coeff, ba.out_entropy, gw.hid, gw.dpre, gw.dlogit, gw.dz,
-                       ba.out_logp);
-    hipLaunchKernelGGL(k_bw_dz, dim3((mv.Z + kThreads - 1) / kThreads, (B + kDzGraphs - 1) / kDzGraphs), dim3(kThreads),
-                       0, s, mv, B, blob_t, gw.dpre, gw.dz);
-    {
-        const size_t lds = sizeof(float) * 3 * kTile * H;
-#define CALL(R)                                                                                          \
-    allow_lds_bw(k_bw_head_sets<R>, lds);                                                                \
-    hipLaunchKernelGGL(k_bw_head_sets<R>, dim3(3, B), dim3(kThreads), lds, s, gv, mv, blob_t, gw.pooled, \
-                       gw.dz, gw.hin, gw.hact, gw.dh, gw.dP)
-        // h_i works on the G rows of a set: as many rows per thread as that needs
-        int groups = kThreads / H;
-        if (groups > kTile) groups = kTile;
-        if (groups < 1) groups = 1;
-        int rpt_sets = 1;
-        while (groups * rpt_sets < G) rpt_sets *= 2;
-        PL_DISPATCH_RPT(rpt_sets, CALL)
-#undef CALL
-    }
+    launch_head_bw(gv, mv, blob_t, fa.cur_node,
+                   {ws.hid, ws.logit, ba.actions, ba.coeff, ba.entropy_coeff, gw.hact, gw.hid, gw.dpre, gw.dlogit, gw.dz,
+                    gw.dh, gw.dP, ba.out_logp, ba.out_entropy},
+                   s);
     mark(PL_STAGE_BW_HEAD, false);
     mark(PL_STAGE_BW_POOL, true);
     // matrix-core dense layers: every output width of the embedding networks is H

@@ -5,8 +5,6 @@
 // Section 2.2 of the paper: (1) raw features, (2) two-way message passing
 // x_v <- g(sum_{u in xi(v)} f(x_u)), (3) pooling h_i(sum_{u in S_i(v)} l_i(x_u)) over the
 // parent / child / parallel sets of the current node, then the policy head (Appendix A.7).
-#include <type_traits>
-
 #include "internal.h"
 
 namespace pl {
@@ -20,7 +18,7 @@ constexpr int kTile = 16;   // rows (nodes) pushed through a network together
 // x and y live in LDS.  Thread (grp, j): column j = tid % n_out, row group grp = tid / n_out;
 // it owns rows grp, grp + groups, ... (at most RPT of them), so one weight load feeds up to
 // RPT FMAs.  Requires n_out <= kThreads and min(kThreads / n_out, kTile) * RPT >= rows.
-template <int RPT, bool WIDE = false, int KL = 16>
+template <int RPT>
 __device__ __forceinline__ void dense_layer(const float *__restrict__ W,
                                             const float *__restrict__ bias, int n_in, int n_out,
                                             const float *x, int ldx, float *y, int ldy, int rows,
@@ -31,84 +29,35 @@ __device__ __forceinline__ void dense_layer(const float *__restrict__ W,
     if (groups > kTile) groups = kTile;
     const int grp = tid / n_out, j = tid - grp * n_out;
     if (grp >= groups || grp >= rows) return;
-    // WIDE: blocks of sixteen fp32 terms are added up in float64 (the policy head's networks,
-    // whose inputs are sums over thousands of nodes)
-    typedef typename std::conditional<WIDE, double, float>::type acc_t;
-    acc_t acc[RPT];
+    float acc[RPT];
     const float bj = bias[j];
 #pragma unroll
     for (int i = 0; i < RPT; ++i) acc[i] = bj;
     int xoff[RPT];   // rows past the tile's end re-read its last row (never stored)
 #pragma unroll
     for (int i = 0; i < RPT; ++i) xoff[i] = min(grp + i * groups, rows - 1) * ldx;
-    // weights KL at a time, all loads issued before the first use: the loop is bound by the
-    // latency of one batch instead of one load per step.  (WIDE: the float64 blocks stay sixteen
-    // terms long whatever KL is.)
+    // weights sixteen at a time, all loads issued before the first use: the loop is bound by the
+    // latency of one batch instead of one load per step.
     constexpr int KB = 16;
-    static_assert(KL % KB == 0, "a batch of loads is a whole number of blocks");
     int k = 0;
-    for (; k + KL <= n_in; k += KL) {
-        float w[KL];
+    for (; k + KB <= n_in; k += KB) {
+        float w[KB];
 #pragma unroll
-        for (int u = 0; u < KL; ++u) w[u] = W[static_cast<size_t>(k + u) * n_out + j];
-        if constexpr (WIDE) {
+        for (int u = 0; u < KB; ++u) w[u] = W[static_cast<size_t>(k + u) * n_out + j];
 #pragma unroll
-            for (int u0 = 0; u0 < KL; u0 += KB) {
-                float part[RPT];
-#pragma unroll
-                for (int i = 0; i < RPT; ++i) part[i] = 0.0f;
-#pragma unroll
-                for (int u = u0; u < u0 + KB; ++u)
-#pragma unroll
-                    for (int i = 0; i < RPT; ++i) part[i] = fmaf(x[xoff[i] + k + u], w[u], part[i]);
-#pragma unroll
-                for (int i = 0; i < RPT; ++i) acc[i] += static_cast<double>(part[i]);
-            }
-            continue;
-        }
-#pragma unroll
-        for (int u = 0; u < KL; ++u)
+        for (int u = 0; u < KB; ++u)
 #pragma unroll
             for (int i = 0; i < RPT; ++i) acc[i] = fmaf(x[xoff[i] + k + u], w[u], acc[i]);
-    }
-    if constexpr (KL > KB) {          // whole blocks left over
-        for (; k + KB <= n_in; k += KB) {
-            float w[KB];
-#pragma unroll
-            for (int u = 0; u < KB; ++u) w[u] = W[static_cast<size_t>(k + u) * n_out + j];
-            if constexpr (WIDE) {
-                float part[RPT];
-#pragma unroll
-                for (int i = 0; i < RPT; ++i) part[i] = 0.0f;
-#pragma unroll
-                for (int u = 0; u < KB; ++u)
-#pragma unroll
-                    for (int i = 0; i < RPT; ++i) part[i] = fmaf(x[xoff[i] + k + u], w[u], part[i]);
-#pragma unroll
-                for (int i = 0; i < RPT; ++i) acc[i] += static_cast<double>(part[i]);
-            } else {
-#pragma unroll
-                for (int u = 0; u < KB; ++u)
-#pragma unroll
-                    for (int i = 0; i < RPT; ++i) acc[i] = fmaf(x[xoff[i] + k + u], w[u], acc[i]);
-            }
-        }
     }
     for (; k < n_in; ++k) {
         const float w = W[static_cast<size_t>(k) * n_out + j];
 #pragma unroll
-        for (int i = 0; i < RPT; ++i) {
-            if constexpr (WIDE)
-                acc[i] += static_cast<double>(x[xoff[i] + k]) * static_cast<double>(w);
-            else
-                acc[i] = fmaf(x[xoff[i] + k], w, acc[i]);
-        }
+        for (int i = 0; i < RPT; ++i) acc[i] = fmaf(x[xoff[i] + k], w, acc[i]);
     }
 #pragma unroll
     for (int i = 0; i < RPT; ++i) {
         const int r = grp + i * groups;
-        const float out = static_cast<float>(acc[i]);
-        if (r < rows) y[r * ldy + j] = relu ? fmaxf(out, 0.0f) : out;
+        if (r < rows) y[r * ldy + j] = relu ? fmaxf(acc[i], 0.0f) : acc[i];
     }
 }
 
@@ -464,166 +413,6 @@ __global__ __launch_bounds__(kThreads) void k_pool_generic(GraphView gv, ModelVi
     for (int i = tid; i < 3 * G * H; i += kThreads) dst[i] = acc[i];
 }
 
-// ------------------------------------------------------------------ policy head
-// Three small kernels, parallel over (graph, set), over (16 graphs, slice of Z) and over
-// graphs: q[i][d] = h_i(P[i][d]) (also for empty groups); z = [e_{v*} ; q]; two-layer policy
-// network with a softmax over devices (Appendix A.7).
-constexpr int kZSlice = 256;   // inputs of policy layer 1 handled by one workgroup
-
-// (1) workgroup (set, graph): P[set] = sum of the pooling partials in slice order, then h_set;
-// set 0 also copies the current node's own embedding into z.
-template <int RPT>
-__global__ __launch_bounds__(kThreads) void k_head_sets(GraphView gv, ModelView mv,
-                                                        const float *__restrict__ emb,
-                                                        const float *__restrict__ partial,
-                                                        const int32_t *__restrict__ cur_node,
-                                                        int max_chunks, float *__restrict__ zbuf,
-                                                        float *__restrict__ out_pooled)
-{
-    extern __shared__ float lds[];
-    const int H = mv.H, G = mv.G, L = mv.L, Z = mv.Z;
-    const int set = blockIdx.x, b = blockIdx.y, tid = threadIdx.x;
-    const int n0 = gv.node_off[b], n_b = gv.node_off[b + 1] - n0;
-    int chunks = (n_b + kPoolChunk - 1) / kPoolChunk;
-    if (chunks > max_chunks) chunks = max_chunks;
-    float *P = lds;                     // [G][H]
-    float *buf_a = P + kTile * H;       // [kTile][H]
-    float *buf_b = buf_a + kTile * H;
-    float *z = zbuf + static_cast<size_t>(b) * Z;
-    const float *src = partial + (static_cast<size_t>(b) * max_chunks * 3 + set) * G * H;
-    for (int i = tid; i < G * H; i += kThreads) {
-        float s = 0.0f;
-        for (int c = 0; c < chunks; ++c) s += src[static_cast<size_t>(c) * 3 * G * H + i];
-        P[i] = s;
-        if (out_pooled) out_pooled[(static_cast<size_t>(b) * 3 + set) * G * H + i] = s;
-    }
-    if (set == 0) {
-        const int cl = cur_node[b];
-        const bool ok = cl >= 0 && cl < n_b;
-        for (int i = tid; i < 2 * H; i += kThreads)
-            z[i] = ok ? emb[static_cast<size_t>(n0 + cl) * 2 * H + i] : 0.0f;
-    }
-    __syncthreads();
-    const MlpRef &hn = mv.h[set];
-    const float *in = P;
-    for (int l = 0; l < L; ++l) {
-        float *out = (l & 1) ? buf_b : buf_a;
-        dense_layer<RPT, true>(mv.blob + hn.layer[l].w, mv.blob + hn.layer[l].b, H, H, in, H, out, H, G, true);
-        __syncthreads();
-        in = out;
-    }
-    for (int i = tid; i < G * H; i += kThreads) z[(2 + set * G) * H + i] = in[i];
-}
-
-// (2) workgroup (row tile, slice): partial products of policy layer 1 for 16 graphs and one
-// slice of z: hidp[slice][b][j] = sum over k in the slice of z[b][k] W1[k][j].
-// The two policy layers accumulate in float64 (the first one in blocks of sixteen fp32 terms):
-// z holds sums over thousands of nodes, so a logit is a difference of terms far larger than
-// itself, and a running fp32 sum over the (2 + 3G) H inputs alone would cost about 1e-6 of the
-// largest logit of the graph, several times what the rest of the pass contributes.
-template <int RPT>
-__global__ __launch_bounds__(kThreads) void k_head_policy1(ModelView mv, int B,
-                                                           const float *__restrict__ zbuf,
-                                                           double *__restrict__ hidp)
-{
-    __shared__ float x[kTile][kZSlice];
-    const int H = mv.H, Z = mv.Z, tid = threadIdx.x;
-    const int b0 = blockIdx.x * kTile, slice = blockIdx.y;
-    const int k0 = slice * kZSlice, kn = min(kZSlice, Z - k0);
-    const int rows = min(kTile, B - b0);
-    for (int i = tid; i < rows * kZSlice; i += kThreads) {
-        const int r = i / kZSlice, k = i - r * kZSlice;
-        x[r][k] = k < kn ? zbuf[static_cast<size_t>(b0 + r) * Z + k0 + k] : 0.0f;
-    }
-    __syncthreads();
-    // same thread mapping as dense_layer, without bias and activation
-    int groups = kThreads / H;
-    if (groups > kTile) groups = kTile;
-    const int grp = tid / H, j = tid - grp * H;
-    if (grp >= groups || grp >= rows) return;
-    double acc[RPT];
-    int xoff[RPT];
-#pragma unroll
-    for (int i = 0; i < RPT; ++i) {
-        acc[i] = 0.0;
-        xoff[i] = min(grp + i * groups, rows - 1) * kZSlice;
-    }
-    const float *W = mv.blob + mv.pol1.w + static_cast<size_t>(k0) * H;
-    const float *xf = &x[0][0];
-    // terms per float64 block; weights per batch of loads, in flight together (the deeper batch pays
-    // where a thread takes eight rows: 41 -> 35 us at H = 128; with four rows it cost 14 -> 24 us)
-    constexpr int KB = 16, KL = RPT >= 8 ? 64 : 16;
-    int k = 0;
-    // sixteen terms in fp32, the blocks in float64: rounding errors stay relative to a
-    // block's own size instead of the running sum's
-    auto block = [&](const float *w, int kk) __attribute__((always_inline)) {
-        float part[RPT];
-#pragma unroll
-        for (int i = 0; i < RPT; ++i) part[i] = 0.0f;
-#pragma unroll
-        for (int u = 0; u < KB; ++u)
-#pragma unroll
-            for (int i = 0; i < RPT; ++i) part[i] = fmaf(xf[xoff[i] + kk + u], w[u], part[i]);
-#pragma unroll
-        for (int i = 0; i < RPT; ++i) acc[i] += static_cast<double>(part[i]);
-    };
-    for (; k + KL <= kn; k += KL) {
-        float w[KL];
-#pragma unroll
-        for (int u = 0; u < KL; ++u) w[u] = W[static_cast<size_t>(k + u) * H + j];
-#pragma unroll
-        for (int u0 = 0; u0 < KL; u0 += KB) block(w + u0, k + u0);
-    }
-    for (; k + KB <= kn; k += KB) {
-        float w[KB];
-#pragma unroll
-        for (int u = 0; u < KB; ++u) w[u] = W[static_cast<size_t>(k + u) * H + j];
-        block(w, k);
-    }
-    for (; k < kn; ++k) {
-        const double w = static_cast<double>(W[static_cast<size_t>(k) * H + j]);
-#pragma unroll
-        for (int i = 0; i < RPT; ++i) acc[i] = fma(static_cast<double>(xf[xoff[i] + k]), w, acc[i]);
-    }
-#pragma unroll
-    for (int i = 0; i < RPT; ++i) {
-        const int r = grp + i * groups;
-        if (r < rows) hidp[(static_cast<size_t>(slice) * B + b0 + r) * H + j] = acc[i];
-    }
-}
-
-// (3) one workgroup per graph: hidden = relu(sum of the slices + bias), output layer, softmax.
-// policy_hidden / policy_logit (internal.h) are shared with the reverse pass, which forms the same
-// logits again and must get the same bits.
-__global__ __launch_bounds__(64) void k_head_out(GraphView gv, ModelView mv,
-                                                 const double *__restrict__ hidp, int n_slices,
-                                                 const int32_t *__restrict__ cur_node,
-                                                 float *__restrict__ out_logits,
-                                                 float *__restrict__ out_probs)
-{
-    __shared__ double hid[kMaxH];
-    __shared__ float logit[kMaxD];
-    const int H = mv.H, D = mv.D, b = blockIdx.x, tid = threadIdx.x;
-    const int n_b = gv.node_off[b + 1] - gv.node_off[b];
-    const int cl = cur_node[b];
-    const bool cur_ok = cl >= 0 && cl < n_b;
-    for (int j = tid; j < H; j += 64) hid[j] = policy_hidden(mv, hidp, n_slices, gv.B, b, j);
-    __syncthreads();
-    if (tid < D) logit[tid] = policy_logit(mv, hid, tid);
-    __syncthreads();
-    if (tid == 0) {
-        float mx = logit[0];
-        for (int d = 1; d < D; ++d) mx = fmaxf(mx, logit[d]);
-        float tot = 0.0f;
-        for (int d = 0; d < D; ++d) tot += expf(logit[d] - mx);
-        const float bad = __builtin_nanf("");   // no valid current node: nothing to decide
-        for (int d = 0; d < D; ++d) {
-            out_logits[static_cast<size_t>(b) * D + d] = cur_ok ? logit[d] : bad;
-            if (out_probs) out_probs[static_cast<size_t>(b) * D + d] = cur_ok ? expf(logit[d] - mx) / tot : bad;
-        }
-    }
-}
-
 int pick_rpt(int H)
 {
     int groups = kThreads / H;
@@ -715,34 +504,6 @@ void launch_pool_generic(const GraphView &gv, const ModelView &mv, const Workspa
                        ws.emb, ws.reach, fa.placement, fa.cur_node, ws.partial, ws.n_chunks)
     PL_DISPATCH_RPT(pick_rpt(mv.H), CALL)
 #undef CALL
-}
-
-void launch_head_generic(const GraphView &gv, const ModelView &mv, const Workspace &ws,
-                         const ForwardArgs &fa, int max_chunks, hipStream_t s)
-{
-    if (gv.B == 0) return;
-    const size_t lds = sizeof(float) * 3 * kTile * mv.H;
-    const int n_slices = (mv.Z + kZSlice - 1) / kZSlice;
-    const int row_tiles = (gv.B + kTile - 1) / kTile;
-    // h_i works on the G rows of a set, the first policy layer on tiles of kTile graphs: each
-    // thread takes as many rows as that needs
-    int groups = kThreads / mv.H;
-    if (groups > kTile) groups = kTile;
-    if (groups < 1) groups = 1;
-    int rpt_sets = 1;
-    while (groups * rpt_sets < mv.G) rpt_sets *= 2;
-#define CALL(R)                                                                                  \
-    hipLaunchKernelGGL(k_head_sets<R>, dim3(3, gv.B), dim3(kThreads), lds, s, gv, mv, ws.emb,    \
-                       ws.partial, fa.cur_node, max_chunks, ws.zbuf, fa.out_pooled)
-    PL_DISPATCH_RPT(rpt_sets, CALL)
-#undef CALL
-#define CALL(R)                                                                                  \
-    hipLaunchKernelGGL(k_head_policy1<R>, dim3(row_tiles, n_slices), dim3(kThreads), 0, s, mv,   \
-                       gv.B, ws.zbuf, ws.hidp)
-    PL_DISPATCH_RPT(pick_rpt(mv.H), CALL)
-#undef CALL
-    hipLaunchKernelGGL(k_head_out, dim3(gv.B), dim3(64), 0, s, gv, mv, ws.hidp, n_slices, fa.cur_node,
-                       fa.out_logits, fa.out_probs);
 }
 
 }  // namespace pl
