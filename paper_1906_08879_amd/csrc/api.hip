@@ -295,6 +295,8 @@ size_t carve_workspace(unsigned char *base, size_t n, size_t B, const ModelView 
     ws->zbuf = reinterpret_cast<float *>(take(sizeof(float) * (B * mv.Z + 4)));
     ws->hid = reinterpret_cast<double *>(take(sizeof(double) * (B * H + 4)));
     ws->logit = reinterpret_cast<float *>(take(sizeof(float) * (B * mv.D + 4)));
+    ws->hidp = reinterpret_cast<double *>(take(sizeof(double) * (B * 3 * H + 4)));
+    ws->head_done = reinterpret_cast<uint32_t *>(take(sizeof(uint32_t) * (B + 4)));
     ws->klist = reinterpret_cast<int32_t *>(take(sizeof(int32_t) * (n + 16)));
     ws->koff = reinterpret_cast<int32_t *>(take(sizeof(int32_t) * (B * (3 * kMaxD + 1) + 4)));
     if (with_reach) ws->reach = take(2 * n + 32);
@@ -343,6 +345,7 @@ int ensure_workspace(pl_graph_batch *g, const ModelView &mv)
     ws.base = base;
     carve_workspace(base, n, B, mv, false, &ws);
     PL_HIP(hipMemset(ws.msg, 0, sizeof(float) * ((2 * n + 2) * mv.H + 4)));
+    PL_HIP(hipMemset(ws.head_done, 0, sizeof(uint32_t) * B));
     return PL_OK;
 }
 
@@ -956,6 +959,7 @@ int pl_embed_forward_static(pl_graph_batch *g, const float *node_feats, const in
     // without ever writing them are cleared by a fill kernel (a memset node must not be captured)
     launch_fill_zero(ws.msg + 2 * n * w->view.H, 2 * static_cast<size_t>(w->view.H), s);
     launch_fill_zero(reinterpret_cast<float *>(ws.reach + (2 * n) / 4 * 4), 5, s);
+    launch_fill_zero(reinterpret_cast<float *>(ws.head_done), B, s);
     return forward_impl(g, node_feats, placement, cur_node, w, out_logits, out_probs, nullptr, nullptr, nullptr,
                         stream, false, nullptr, 0, nullptr, nullptr, nullptr, nullptr, &ws);
 }

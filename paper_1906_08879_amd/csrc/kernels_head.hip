@@ -14,7 +14,8 @@
 // Sums are taken in float64 by blocks (sixteen fp32 terms, the blocks in float64, the output layer
 // entirely in float64): z holds sums over thousands of nodes, so a logit is a difference of terms far
 // larger than itself, and plain fp32 sums would be the largest single source of its error.
-// HEAD_FIG
+// Forward head of 256 NASNet-like graphs (H = 128, 8 devices): 81 us as three launches, 37 us now; of one: 52,
+// now 18; of 64 graphs at H = 32: 19, now 8.  Reverse head of those 256 graphs: 63, now 41.
 #include <type_traits>
 
 #include "internal.h"
@@ -23,81 +24,122 @@ namespace pl {
 
 namespace {
 
-constexpr int kHeadThreads = 1024;
-constexpr int kBlock = 16;       // fp32 terms per float64 block
+constexpr int kBlock = 16;            // fp32 terms per float64 block
+constexpr int kComputeUnits = 256;
 
 typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4;
 
-// columns per thread, rows per pass, and whether the three networks are taken together, for width H
-// (HT = H where it is known when the kernel is compiled, else 0)
-constexpr int head_cols(int HT) { return HT >= 32 ? 4 : 1; }
-constexpr bool head_sets_together(int H) { return H <= 128; }
+// Instantiations: HT = H where it is known when the kernel is compiled (32, 64, 128), else 0; RT: rows of a
+// set per pass; SPLIT: a workgroup per (graph, set) instead of per graph.
+constexpr int head_threads(int HT, bool split) { return HT == 0 || (HT == 128 && !split) ? 1024 : 512; }
+constexpr int head_cols(int HT) { return HT >= 32 ? 4 : 1; }             // columns per thread
+constexpr int head_sets(int H, bool split) { return !split && H <= 128 ? 3 : 1; }   // networks taken together
 constexpr int head_rows_max(int H) { return H <= 128 ? 8 : 4; }
 
-constexpr size_t head_lds(int H, int G, int RT, int HT)
+constexpr size_t head_lds(int H, int G, int RT, int HT, bool split)
 {
-    const size_t units = static_cast<size_t>(head_sets_together(H) ? 3 : 1) * ((H + kBlock - 1) / kBlock);
+    const size_t units = static_cast<size_t>(head_sets(H, split)) * ((H + kBlock - 1) / kBlock);
     const size_t part = units * RT * H * sizeof(float);
-    const size_t red = static_cast<size_t>(kHeadThreads / (H / head_cols(HT))) * H * sizeof(double);
-    return (part > red ? part : red) + sizeof(float) * (static_cast<size_t>(2 + 3 * G) * H + 4);
+    const size_t red = static_cast<size_t>(head_threads(HT, split) / (H / head_cols(HT))) * H * sizeof(double);
+    return (part > red ? part : red) + sizeof(float) * (static_cast<size_t>(2 + (split ? 1 : 3) * G) * H + 4);
 }
 
-// One layer of the three h networks on the rows x [3][G][H] (LDS), in place: finish(set, row, column,
-// sum) gives the new value, `sum` in float64 over the inputs in blocks.  w0: place in `blob` of the
-// layer's [H, H] matrix of the first set, ws: distance to the next set's.  part: LDS scratch.
-template <int HT, int RT, typename F>
-__device__ __forceinline__ void head_layer(const float *__restrict__ blob, int w0, int ws, float *x, float *part,
-                                           int H_, int G, F finish)
-{
-    constexpr int CPT = head_cols(HT);
-    const int H = HT ? HT : H_;
-    const int slices = (H + kBlock - 1) / kBlock, cols = H / CPT;
-    const int sets = head_sets_together(H) ? 3 : 1;
-    const int tid = threadIdx.x, groups = kHeadThreads / cols, grp = tid / cols, j = (tid - grp * cols) * CPT;
-    for (int set0 = 0; set0 < 3; set0 += sets)
-        for (int r0 = 0; r0 < G; r0 += RT) {
-            const int rows = min(RT, G - r0);
-            for (int u = grp; u < sets * slices && grp < groups; u += groups) {
-                const int set = set0 + u / slices, k0 = (u - (u / slices) * slices) * kBlock;
-                const float *W = blob + w0 + static_cast<ptrdiff_t>(set) * ws + static_cast<size_t>(k0) * H + j;
-                const int kn = min(kBlock, H - k0);
-                float w[kBlock][CPT];
+// Sixteen rows of four columns (one column where H is not known), the weights of one unit.
+template <int HT>
+struct WeightBlock {
+    static constexpr int CPT = head_cols(HT);
+    float w[kBlock][CPT];
+    // rows k0 .. k0 + kn - 1 of a matrix with H columns, from column j on (kn = kBlock where H is known)
+    __device__ __forceinline__ void load(const float *__restrict__ W, int H, int kn)
+    {
 #pragma unroll
-                for (int k = 0; k < kBlock; ++k) {
-                    if constexpr (CPT == 4) {
-                        const f32x4 v = *reinterpret_cast<const f32x4 *>(W + static_cast<size_t>(k) * H);
+        for (int k = 0; k < kBlock; ++k) {
+            if constexpr (CPT == 4) {
+                const f32x4 v = *reinterpret_cast<const f32x4 *>(W + static_cast<size_t>(k) * H);
 #pragma unroll
-                        for (int c = 0; c < CPT; ++c) w[k][c] = v[c];
-                    } else {
-                        w[k][0] = k < kn ? W[static_cast<size_t>(k) * H] : 0.0f;
-                    }
-                }
-#pragma unroll
-                for (int r = 0; r < RT; ++r) {
-                    const float *xr = x + (set * G + r0 + min(r, rows - 1)) * H + k0;
-                    float s[CPT];
-#pragma unroll
-                    for (int c = 0; c < CPT; ++c) s[c] = 0.0f;
-#pragma unroll
-                    for (int k = 0; k < kBlock; ++k) {
-                        const float xv = (CPT == 4 || k < kn) ? xr[k] : 0.0f;
-#pragma unroll
-                        for (int c = 0; c < CPT; ++c) s[c] = fmaf(xv, w[k][c], s[c]);
-                    }
-#pragma unroll
-                    for (int c = 0; c < CPT; ++c) part[(u * RT + r) * H + j + c] = s[c];
-                }
+                for (int c = 0; c < CPT; ++c) w[k][c] = v[c];
+            } else {
+                w[k][0] = k < kn ? W[static_cast<size_t>(k) * H] : 0.0f;
             }
-            __syncthreads();
-            for (int i = tid; i < sets * rows * H; i += kHeadThreads) {
-                const int sr = i / H, c = i - sr * H, q = sr / rows, r = sr - q * rows;
-                double s = 0.0;
-                for (int sl = 0; sl < slices; ++sl) s += static_cast<double>(part[((q * slices + sl) * RT + r) * H + c]);
-                x[((set0 + q) * G + r0 + r) * H + c] = finish(set0 + q, r0 + r, c, s);
-            }
-            __syncthreads();
         }
-}
+    }
+    __device__ __forceinline__ void apply(const float *x, int kn, float (&s)[CPT]) const
+    {
+#pragma unroll
+        for (int c = 0; c < CPT; ++c) s[c] = 0.0f;
+#pragma unroll
+        for (int k = 0; k < kBlock; ++k) {
+            const float xv = (CPT == 4 || k < kn) ? x[k] : 0.0f;
+#pragma unroll
+            for (int c = 0; c < CPT; ++c) s[c] = fmaf(xv, w[k][c], s[c]);
+        }
+    }
+};
+
+// The layers of the h networks (set0 .. set0 + sets - 1 of the three) on the rows x [sets][G][H] (LDS), in
+// place.  A unit is (set, slice of sixteen inputs), H / CPT threads; where H is known a thread has at most
+// one.  AHEAD: its weights of the next layer are requested before the current layer's slices are added up.
+template <int HT, int RT, bool SPLIT, bool AHEAD>
+struct HeadLayers {
+    static constexpr int CPT = head_cols(HT), T = head_threads(HT, SPLIT);
+    WeightBlock<HT> wb;
+    int H, G, slices, cols, sets, groups, grp, j;
+
+    __device__ __forceinline__ HeadLayers(int H_, int G_)
+    {
+        H = HT ? HT : H_;
+        G = G_;
+        slices = (H + kBlock - 1) / kBlock;
+        cols = H / CPT;
+        sets = head_sets(H, SPLIT);
+        groups = T / cols;
+        grp = static_cast<int>(threadIdx.x) / cols;
+        j = (static_cast<int>(threadIdx.x) - grp * cols) * CPT;
+    }
+    // w0: place in `blob` of the layer's matrix of the first set, ws: distance to the next set's
+    __device__ __forceinline__ void request(const float *__restrict__ blob, int w0, int ws, int set0)
+    {
+        if constexpr (AHEAD) {
+            if (grp < sets * slices) {
+                const int set = set0 + grp / slices, k0 = (grp % slices) * kBlock;
+                wb.load(blob + w0 + static_cast<ptrdiff_t>(set) * ws + static_cast<size_t>(k0) * H + j, H, kBlock);
+            }
+        }
+    }
+    // next(): what to request while the sums settle; finish(set, row, column, sum): the new value, `sum` in
+    // float64 over the inputs in blocks
+    template <typename N, typename F>
+    __device__ __forceinline__ void layer(const float *__restrict__ blob, int w0, int ws, int set_first, float *x,
+                                          float *part, N next, F finish)
+    {
+        const int tid = threadIdx.x;
+        for (int set0 = 0; set0 < (SPLIT ? 1 : 3); set0 += sets)
+            for (int r0 = 0; r0 < G; r0 += RT) {
+                const int rows = min(RT, G - r0);
+                for (int u = grp; u < sets * slices && grp < groups; u += groups) {
+                    const int q = u / slices, k0 = (u - q * slices) * kBlock, kn = min(kBlock, H - k0);
+                    if constexpr (!AHEAD)
+                        wb.load(blob + w0 + static_cast<ptrdiff_t>(set_first + set0 + q) * ws + static_cast<size_t>(k0) * H + j, H, kn);
+#pragma unroll
+                    for (int r = 0; r < RT; ++r) {
+                        float s[CPT];
+                        wb.apply(x + ((set0 + q) * G + r0 + min(r, rows - 1)) * H + k0, kn, s);
+#pragma unroll
+                        for (int c = 0; c < CPT; ++c) part[(u * RT + r) * H + j + c] = s[c];
+                    }
+                }
+                if (AHEAD && r0 + RT >= G) next();
+                __syncthreads();
+                for (int i = tid; i < sets * rows * H; i += T) {
+                    const int sr = i / H, c = i - sr * H, q = sr / rows, r = sr - q * rows;
+                    double s = 0.0;
+                    for (int sl = 0; sl < slices; ++sl) s += static_cast<double>(part[((q * slices + sl) * RT + r) * H + c]);
+                    x[((set0 + q) * G + r0 + r) * H + c] = finish(set_first + set0 + q, r0 + r, c, s);
+                }
+                __syncthreads();
+            }
+    }
+};
 
 struct HeadOut {
     float *zbuf;          // [B, Z] policy inputs
@@ -105,21 +147,40 @@ struct HeadOut {
     float *logit;         // [B, D] logits, also where out_logits gets NaN
     float *out_logits, *out_probs, *out_pooled;
     float *hin, *hact;    // kept for the reverse pass (or null): inputs [3, B G, H] and layer outputs [3, L, B G, H] of h
+    double *hidp;         // (SPLIT) [B, 3, H] the sets' parts of the first policy layer
+    uint32_t *done;       // (SPLIT) [B] workgroups of a graph that have written theirs; zero between calls
 };
 
-template <int HT, int RT>
-__global__ __launch_bounds__(kHeadThreads) void k_head(GraphView gv, ModelView mv, const float *__restrict__ emb,
-                                                       const float *__restrict__ partial,
-                                                       const int32_t *__restrict__ cur_node, int max_chunks, HeadOut o)
+template <int HT, int RT, bool SPLIT>
+__global__ __launch_bounds__(head_threads(HT, SPLIT)) void k_head(GraphView gv, ModelView mv, const float *__restrict__ emb,
+                                                              const float *__restrict__ partial,
+                                                              const int32_t *__restrict__ cur_node, int max_chunks,
+                                                              HeadOut o)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
     __shared__ double hid[kMaxH];
-    __shared__ float logit[kMaxD];
-    constexpr int CPT = head_cols(HT);
+    __shared__ float logit[kMaxD], bias[(3 * kMaxLayers + 1) * (HT ? HT : kMaxH)], w2[HT ? HT * kMaxD : 1];
+    __shared__ uint32_t order;
+    constexpr int CPT = head_cols(HT), T = head_threads(HT, SPLIT);
     const int H = HT ? HT : mv.H, G = mv.G, L = mv.L, D = mv.D, Z = mv.Z;
-    const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    float *z = reinterpret_cast<float *>(lds);              // [Z]: e_{v*}, then the rows of the three sets
-    float *part = z + ((Z + 3) & ~3), *x = z + 2 * H;
+    const int b = SPLIT ? blockIdx.x / 3 : blockIdx.x, set_first = SPLIT ? blockIdx.x - 3 * b : 0;
+    constexpr int n_sets = SPLIT ? 1 : 3;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    // (a workgroup of 1024 threads has no registers to hold weights ahead and add up float64 sums)
+    constexpr bool AHEAD = HT != 0 && T == 512;
+    HeadLayers<HT, RT, SPLIT, AHEAD> hl(mv.H, G);
+    // h's weights and everything small that later phases need: requested before the graph's own data
+    hl.request(mv.blob, mv.h[0].layer[0].w, mv.h[1].layer[0].w - mv.h[0].layer[0].w, set_first);
+    for (int i = tid; i < n_sets * L * H; i += T) {
+        const int set = i / (L * H), r = i - set * L * H, l = r / H;
+        bias[i] = mv.blob[mv.h[set_first + set].layer[l].b + r - l * H];
+    }
+    float *bias1 = bias + n_sets * L * H;
+    for (int i = tid; i < H; i += T) bias1[i] = mv.blob[mv.pol1.b + i];
+    if constexpr (HT != 0)
+        for (int i = tid; i < H * D; i += T) w2[i] = mv.blob[mv.pol2.w + i];
+    float *z = reinterpret_cast<float *>(lds);              // e_{v*}, then the rows of the sets
+    float *x = z + 2 * H, *part = z + (((2 + n_sets * G) * H + 3) & ~3);
     const int n0 = gv.node_off[b], n_b = gv.node_off[b + 1] - n0;
     const int cl = cur_node[b];
     const bool cur_ok = cl >= 0 && cl < n_b;
@@ -131,86 +192,105 @@ __global__ __launch_bounds__(kHeadThreads) void k_head(GraphView gv, ModelView m
     };
 
     // ---- P[set][group] = sum of the pooling partials in slice order
-    const float *src = partial + static_cast<size_t>(b) * max_chunks * 3 * G * H;
-    for (int i = tid; i < 3 * G * H; i += kHeadThreads) {
+    const int first = set_first * G * H;
+    const float *src = partial + static_cast<size_t>(b) * max_chunks * 3 * G * H + first;
+    for (int i = tid; i < n_sets * G * H; i += T) {
         float s = 0.0f;
-#pragma unroll 4
+#pragma unroll 8
         for (int c = 0; c < chunks; ++c) s += src[static_cast<size_t>(c) * 3 * G * H + i];
         x[i] = s;
-        if (o.out_pooled) o.out_pooled[static_cast<size_t>(b) * 3 * G * H + i] = s;
+        if (o.out_pooled) o.out_pooled[static_cast<size_t>(b) * 3 * G * H + first + i] = s;
         if (o.hin) {
             const int set = i / (G * H);
-            o.hin[kept(set, 0, 1, i - set * G * H)] = s;
+            o.hin[kept(set_first + set, 0, 1, i - set * G * H)] = s;
         }
     }
-    for (int i = tid; i < 2 * H; i += kHeadThreads) z[i] = cur_ok ? emb[static_cast<size_t>(n0 + cl) * 2 * H + i] : 0.0f;
+    for (int i = tid; i < 2 * H && set_first == 0; i += T)
+        z[i] = cur_ok ? emb[static_cast<size_t>(n0 + cl) * 2 * H + i] : 0.0f;
     __syncthreads();
 
-    // ---- h of the three sets
+    // ---- first policy layer: group g takes the blocks g, g + groups, ... of this workgroup's part of z (the
+    // first set's comes with e_{v*}); place of its first weight
+    const int p_cols = H / CPT, p_groups = T / p_cols, p_grp = tid / p_cols, p_j = (tid - p_grp * p_cols) * CPT;
+    const float *zp = set_first == 0 ? z : x;
+    const int z_at = set_first == 0 ? 0 : (2 + set_first * G) * H;
+    const int z_n = SPLIT ? (G + (set_first == 0 ? 2 : 0)) * H : Z;
+    const int blocks = (z_n + kBlock - 1) / kBlock, used = min(p_groups, blocks);
+    const float *W1 = mv.blob + mv.pol1.w + static_cast<size_t>(z_at) * H + p_j;
+
+    // ---- h of the sets
     for (int l = 0; l < L; ++l) {
         const LayerRef &l0 = mv.h[0].layer[l];
-        const int ws = mv.h[1].layer[l].w - l0.w;
-        head_layer<HT, RT>(mv.blob, l0.w, ws, x, part, H, G, [&](int set, int r, int c, double s) {
-            const float y = fmaxf(static_cast<float>(s + static_cast<double>(mv.blob[l0.b + set * ws + c])), 0.0f);
-            if (o.hact) o.hact[kept(set, l, L, r * H + c)] = y;
-            return y;
-        });
+        hl.layer(
+            mv.blob, l0.w, mv.h[1].layer[l].w - l0.w, set_first, x, part,
+            [&]() {
+                if (l + 1 < L)
+                    hl.request(mv.blob, mv.h[0].layer[l + 1].w, mv.h[1].layer[l + 1].w - mv.h[0].layer[l + 1].w, set_first);
+                else if (p_grp < used)
+                    hl.wb.load(W1 + static_cast<size_t>(p_grp) * kBlock * H, H, kBlock);
+            },
+            [&](int set, int r, int c, double s) {
+                const float y = fmaxf(static_cast<float>(s + static_cast<double>(bias[((set - set_first) * L + l) * H + c])), 0.0f);
+                if (o.hact) o.hact[kept(set, l, L, r * H + c)] = y;
+                return y;
+            });
     }
     if (o.zbuf)
-        for (int i = tid; i < Z; i += kHeadThreads) o.zbuf[static_cast<size_t>(b) * Z + i] = z[i];
+        for (int i = tid; i < z_n; i += T) o.zbuf[static_cast<size_t>(b) * Z + z_at + i] = zp[i];
 
-    // ---- first policy layer: group g takes the blocks g, g + groups, ... of z
-    {
-        const int cols = H / CPT, groups = kHeadThreads / cols, grp = tid / cols, j = (tid - grp * cols) * CPT;
-        const int blocks = (Z + kBlock - 1) / kBlock, used = min(groups, blocks);
-        double *red = reinterpret_cast<double *>(part);     // [used][H]
-        if (grp < used) {
-            double acc[CPT];
+    double *red = reinterpret_cast<double *>(part);         // [used][H]
+    if (p_grp < used) {
+        double acc[CPT];
 #pragma unroll
-            for (int c = 0; c < CPT; ++c) acc[c] = 0.0;
-            const float *W1 = mv.blob + mv.pol1.w + j;
-#pragma unroll 2
-            for (int q = grp; q < blocks; q += groups) {
-                const int k0 = q * kBlock;
-                float w[kBlock][CPT], s[CPT];
+        for (int c = 0; c < CPT; ++c) acc[c] = 0.0;
+        for (int q = p_grp; q < blocks; q += p_groups) {
+            const int kn = min(kBlock, z_n - q * kBlock);
+            if (!AHEAD || q != p_grp) hl.wb.load(W1 + static_cast<size_t>(q) * kBlock * H, H, kn);
+            float s[CPT];
+            hl.wb.apply(zp + q * kBlock, kn, s);
 #pragma unroll
-                for (int k = 0; k < kBlock; ++k) {
-                    if constexpr (CPT == 4) {
-                        const f32x4 v = *reinterpret_cast<const f32x4 *>(W1 + static_cast<size_t>(k0 + k) * H);
-#pragma unroll
-                        for (int c = 0; c < CPT; ++c) w[k][c] = v[c];
-                    } else {
-                        w[k][0] = k0 + k < Z ? W1[static_cast<size_t>(k0 + k) * H] : 0.0f;
-                    }
-                }
-#pragma unroll
-                for (int c = 0; c < CPT; ++c) s[c] = 0.0f;
-#pragma unroll
-                for (int k = 0; k < kBlock; ++k) {
-                    const float xv = (CPT == 4 || k0 + k < Z) ? z[k0 + k] : 0.0f;
-#pragma unroll
-                    for (int c = 0; c < CPT; ++c) s[c] = fmaf(xv, w[k][c], s[c]);
-                }
-#pragma unroll
-                for (int c = 0; c < CPT; ++c) acc[c] += static_cast<double>(s[c]);
-            }
-#pragma unroll
-            for (int c = 0; c < CPT; ++c) red[grp * H + j + c] = acc[c];
+            for (int c = 0; c < CPT; ++c) acc[c] += static_cast<double>(s[c]);
         }
+#pragma unroll
+        for (int c = 0; c < CPT; ++c) red[p_grp * H + p_j + c] = acc[c];
+    }
+    __syncthreads();
+    for (int c = tid; c < H; c += T) {
+        double s = 0.0;
+        for (int g = 0; g < used; ++g) s += red[g * H + c];
+        hid[c] = s;
+        // (stored past the caches that workgroups on other dies do not share)
+        if constexpr (SPLIT)
+            __hip_atomic_store(o.hidp + (static_cast<size_t>(b) * 3 + set_first) * H + c, s, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    if constexpr (SPLIT) {
+        // the workgroup that finishes a graph last adds the sets' parts up and goes on: every thread's
+        // stores have arrived before the one atomic that announces them
+        __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0)
         __syncthreads();
-        for (int c = tid; c < H; c += kHeadThreads) {
-            double s = static_cast<double>(mv.blob[mv.pol1.b + c]);
-            for (int g = 0; g < used; ++g) s += red[g * H + c];
-            hid[c] = s > 0.0 ? s : 0.0;
-            o.hid[static_cast<size_t>(b) * H + c] = hid[c];
+        if (tid == 0) order = __hip_atomic_fetch_add(o.done + b, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __syncthreads();
+        if (order != 2u) return;
+        if (tid == 0) __hip_atomic_store(o.done + b, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        for (int c = tid; c < H; c += T) {
+            double s = 0.0;
+            for (int set = 0; set < 3; ++set)
+                s += __hip_atomic_load(o.hidp + (static_cast<size_t>(b) * 3 + set) * H + c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            hid[c] = s;
         }
+    }
+    for (int c = tid; c < H; c += T) {                      // (a column's sum is its own thread's)
+        const double s = hid[c] + static_cast<double>(bias1[c]);
+        hid[c] = s > 0.0 ? s : 0.0;
+        o.hid[static_cast<size_t>(b) * H + c] = hid[c];
     }
     __syncthreads();
 
     // ---- output layer (a wave per device), softmax
-    for (int d = wave; d < D; d += kHeadThreads / 64) {
+    for (int d = wave; d < D; d += T / 64) {
         double s = 0.0;
-        for (int k = lane; k < H; k += 64) s = fma(hid[k], static_cast<double>(mv.blob[mv.pol2.w + k * D + d]), s);
+        for (int k = lane; k < H; k += 64)
+            s = fma(hid[k], static_cast<double>(HT != 0 ? w2[k * D + d] : mv.blob[mv.pol2.w + k * D + d]), s);
 #pragma unroll
         for (int step = 32; step > 0; step >>= 1) s += __shfl_xor(s, step);
         if (lane == 0) logit[d] = static_cast<float>(s + static_cast<double>(mv.blob[mv.pol2.b + d]));
@@ -235,14 +315,18 @@ __global__ __launch_bounds__(kHeadThreads) void k_head(GraphView gv, ModelView m
 // (dz; its first 2H entries are the gradient of e_{v*}) and through the h networks to dP[set][group].
 // A graph whose current node or action is out of range gets a zero gradient and logp = NaN.
 template <int HT, int RT>
-__global__ __launch_bounds__(kHeadThreads) void k_head_bw(GraphView gv, ModelView mv, const float *__restrict__ blob_t,
+__global__ __launch_bounds__(head_threads(HT, false)) void k_head_bw(GraphView gv, ModelView mv, const float *__restrict__ blob_t,
                                                           const int32_t *__restrict__ cur_node, HeadBwArgs a)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
     __shared__ float dpre[kMaxH];
     __shared__ float dlog[kMaxD];
+    constexpr int T = head_threads(HT, false);
     const int H = HT ? HT : mv.H, G = mv.G, L = mv.L, D = mv.D, Z = mv.Z;
     const int b = blockIdx.x, tid = threadIdx.x;
+    HeadLayers<HT, RT, false, HT != 0> hl(mv.H, G);
+    auto request = [&](int l) { hl.request(blob_t, mv.h[0].layer[l].w, mv.h[1].layer[l].w - mv.h[0].layer[l].w, 0); };
+    request(L - 1);
     float *z = reinterpret_cast<float *>(lds);              // [Z]: dz
     float *part = z + ((Z + 3) & ~3), *x = z + 2 * H;
     const int n_b = gv.node_off[b + 1] - gv.node_off[b];
@@ -275,7 +359,7 @@ __global__ __launch_bounds__(kHeadThreads) void k_head_bw(GraphView gv, ModelVie
         }
     }
     __syncthreads();
-    for (int j = tid; j < H; j += kHeadThreads) {
+    for (int j = tid; j < H; j += T) {
         const float *W = mv.blob + mv.pol2.w + static_cast<size_t>(j) * D;
         const float h = static_cast<float>(a.hid64[static_cast<size_t>(b) * H + j]);
         float s = 0.0f;
@@ -289,7 +373,7 @@ __global__ __launch_bounds__(kHeadThreads) void k_head_bw(GraphView gv, ModelVie
     // dz[k] = sum_j W1[k][j] dpre[j], from the transposed layer [H, Z]; the rows of h's outputs gated
     {
         const float *W1t = blob_t + mv.pol1.w;
-        for (int k = tid; k < Z; k += kHeadThreads) {
+        for (int k = tid; k < Z; k += T) {
             float s = 0.0f;
             int j = 0;
             for (; j + kBlock <= H; j += kBlock) {
@@ -313,7 +397,8 @@ __global__ __launch_bounds__(kHeadThreads) void k_head_bw(GraphView gv, ModelVie
     __syncthreads();
     for (int l = L - 1; l >= 0; --l) {
         const LayerRef &l0 = mv.h[0].layer[l];
-        head_layer<HT, RT>(blob_t, l0.w, mv.h[1].layer[l].w - l0.w, x, part, H, G, [&](int set, int r, int c, double s) {
+        hl.layer(blob_t, l0.w, mv.h[1].layer[l].w - l0.w, 0, x, part, [&]() { if (l > 0) request(l - 1); },
+                 [&](int set, int r, int c, double s) {
             float y = static_cast<float>(s);
             if (l > 0) {
                 const size_t at = kept(set, l - 1, r * H + c);
@@ -327,17 +412,14 @@ __global__ __launch_bounds__(kHeadThreads) void k_head_bw(GraphView gv, ModelVie
     }
 }
 
-// Calls run(kernel, dynamic LDS bytes) with the instantiation for width H and G rows per set.
-template <typename Pick, typename Run>
-void head_dispatch(int H, int G, Pick pick, Run run)
+// Calls go(HT, RT) with the instantiation for width H and G rows per set.
+template <typename F>
+void head_dispatch(int H, int G, F go)
 {
-    const int most = head_rows_max(H);
     auto rows = [&](auto ht) {
-        constexpr int HT = decltype(ht)::value;
-        auto go = [&](auto rt) { run(pick(ht, rt), head_lds(H, G, decltype(rt)::value, HT)); };
-        if (G == 1) go(std::integral_constant<int, 1>{});
-        else if (G <= 4 || most == 4) go(std::integral_constant<int, 4>{});
-        else go(std::integral_constant<int, 8>{});
+        if (G == 1) go(ht, std::integral_constant<int, 1>{});
+        else if (G <= 4 || head_rows_max(H) == 4) go(ht, std::integral_constant<int, 4>{});
+        else go(ht, std::integral_constant<int, 8>{});
     };
     if (H == 128) rows(std::integral_constant<int, 128>{});
     else if (H == 64) rows(std::integral_constant<int, 64>{});
@@ -359,26 +441,40 @@ void launch_head(const GraphView &gv, const ModelView &mv, const Workspace &ws, 
                  hipStream_t s)
 {
     if (gv.B == 0) return;
-    const HeadOut o{ws.zbuf, ws.hid, ws.logit, fa.out_logits, fa.out_probs, fa.out_pooled, fa.keep_hin, fa.keep_hact};
-    head_dispatch(
-        mv.H, mv.G, [](auto ht, auto rt) { return k_head<decltype(ht)::value, decltype(rt)::value>; },
-        [&](auto kernel, size_t lds) {
-            allow_lds(kernel, lds);
-            hipLaunchKernelGGL(kernel, dim3(gv.B), dim3(kHeadThreads), lds, s, gv, mv, ws.emb, ws.partial, fa.cur_node,
-                               max_chunks, o);
-        });
+    const HeadOut o{ws.zbuf,      ws.hid,       ws.logit, fa.out_logits, fa.out_probs, fa.out_pooled,
+                    fa.keep_hin,  fa.keep_hact, ws.hidp,  ws.head_done};
+    head_dispatch(mv.H, mv.G, [&](auto ht, auto rt) {
+        constexpr int HT = decltype(ht)::value, RT = decltype(rt)::value;
+        auto run = [&](auto split) {
+            constexpr bool SPLIT = decltype(split)::value;
+            const size_t lds = head_lds(mv.H, mv.G, RT, HT, SPLIT);
+            allow_lds(k_head<HT, RT, SPLIT>, lds);
+            hipLaunchKernelGGL((k_head<HT, RT, SPLIT>), dim3(SPLIT ? 3 * gv.B : gv.B), dim3(head_threads(HT, SPLIT)), lds, s,
+                               gv, mv, ws.emb, ws.partial, fa.cur_node, max_chunks, o);
+        };
+        // At H = 128 a graph's 2 MB of weights take one CU 18 us longer than three (34 against 18 us for one
+        // graph, 8 device groups); with more workgroups than CUs the hand-over between them costs more
+        // than it gives (256 graphs: 43 us together, 55 us split).
+        if constexpr (HT == 128) {
+            if (3 * gv.B <= kComputeUnits) {
+                run(std::true_type{});
+                return;
+            }
+        }
+        run(std::false_type{});
+    });
 }
 
 void launch_head_bw(const GraphView &gv, const ModelView &mv, const float *blob_t, const int32_t *cur_node,
                     const HeadBwArgs &a, hipStream_t s)
 {
     if (gv.B == 0) return;
-    head_dispatch(
-        mv.H, mv.G, [](auto ht, auto rt) { return k_head_bw<decltype(ht)::value, decltype(rt)::value>; },
-        [&](auto kernel, size_t lds) {
-            allow_lds(kernel, lds);
-            hipLaunchKernelGGL(kernel, dim3(gv.B), dim3(kHeadThreads), lds, s, gv, mv, blob_t, cur_node, a);
-        });
+    head_dispatch(mv.H, mv.G, [&](auto ht, auto rt) {
+        constexpr int HT = decltype(ht)::value, RT = decltype(rt)::value;
+        const size_t lds = head_lds(mv.H, mv.G, RT, HT, false);
+        allow_lds(k_head_bw<HT, RT>, lds);
+        hipLaunchKernelGGL((k_head_bw<HT, RT>), dim3(gv.B), dim3(head_threads(HT, false)), lds, s, gv, mv, blob_t, cur_node, a);
+    });
 }
 
 }  // namespace pl
