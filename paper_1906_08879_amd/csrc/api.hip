@@ -387,13 +387,8 @@ int ensure_grad_workspace(pl_graph_batch *g, const ModelView &mv)
     PL_HIP(take(&gw.hid, B * H));
     PL_HIP(take(&gw.dpre, B * H));
     PL_HIP(take(&gw.dlogit, B * mv.D));
-    // (three times: the gradients of l's layers are taken for the three node sets in one launch)
-    size_t part = 3 * wgrad_partial_floats(static_cast<int64_t>(n), 2 * mv.H, mv.H);
-    part = std::max(part, wgrad_partial_floats(static_cast<int64_t>(n), 32, mv.H));
-    part = std::max(part, wgrad_partial_floats(static_cast<int64_t>(BG), mv.H, mv.H));
-    part = std::max(part, wgrad_partial_floats(static_cast<int64_t>(B), mv.Z, mv.H));
-    part = std::max(part, wgrad_partial_floats(static_cast<int64_t>(B), mv.H, mv.D));
-    PL_HIP(take(&gw.partial, part));
+    gw.partial_floats = wgrad_workspace_floats(static_cast<int64_t>(n), static_cast<int64_t>(B), mv);
+    PL_HIP(take(&gw.partial, gw.partial_floats));
     gw.H = mv.H;
     gw.G = mv.G;
     gw.L = mv.L;

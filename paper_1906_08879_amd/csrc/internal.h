@@ -232,7 +232,8 @@ struct GradWorkspace {
     float *dz = nullptr;                      // [B, Z]
     float *hid = nullptr, *dpre = nullptr;    // [B, H] policy hidden layer and its delta
     float *dlogit = nullptr;                  // [B, D]
-    float *partial = nullptr;                 // slab sums of the weight-gradient contraction
+    float *partial = nullptr;                 // slab sums of the weight-gradient contractions
+    size_t partial_floats = 0;
     int32_t H = 0, G = 0, L = 0, D = 0;
 };
 
@@ -242,7 +243,7 @@ struct StageMarks {
     void (*mark)(void *ctx, int stage, bool begin, hipStream_t s);
 };
 
-size_t wgrad_partial_floats(int64_t R, int I, int J);
+size_t wgrad_workspace_floats(int64_t n, int64_t B, const ModelView &mv);
 void launch_fill_zero(float *p, size_t n, hipStream_t s);
 // what a reverse pass is asked for (device arrays; the last three may be null)
 struct BackwardArgs {

@@ -1,0 +1,33 @@
+"""The weight gradients of a pass as tables of contractions: more layers than a table holds (four layers a
+network, 43 contractions), slab sums that need several launches (35 thousand nodes at H = 128), two sweeps
+(whose contractions must run before the earlier sweep overwrites what they read) and shapes that take the
+plain kernel for every layer.  Against the generic fp32 kernels, per layer block in the 2-norm: 5e-4 (four
+times what a single ReLU input within rounding of zero moves a gradient; a missing slab moves its block by
+about 1 / sqrt(slabs), 4e-2 or more); equal calls give equal bits."""
+import numpy as np
+import pytest
+
+from oracle import gradient as og
+from tests.gpu_common import custom_workload, run_gradient
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("sizes,D,H,L,k,wd", [
+    ([32] * 1100, 4, 128, 2, 1, "bf16"), ([70, 1, 33], 3, 32, 4, 1, "fp32"), ([64, 65, 9] * 20, 8, 64, 4, 2, "bf16"),
+    ([2, 40, 17], 2, 32, 1, 2, "fp32"), ([31, 12], 5, 24, 4, 1, "fp32"),
+])
+def test_tables_of_contractions(sizes, D, H, L, k, wd):
+    rng = np.random.default_rng(H + L)
+    w = custom_workload(rng, sizes, D, H, L, k, 1, wd, p_edge=0.1)
+    actions = rng.integers(0, D, w.B).astype(np.int32)
+    coeff = rng.normal(0, 1, w.B).astype(np.float32)
+    got = run_gradient(w, actions, coeff)["grad"]
+    assert np.array_equal(got, run_gradient(w, actions, coeff)["grad"])
+    ref = run_gradient(w, actions, coeff, path=1)["grad"].astype(np.float64)
+    gmax = np.abs(ref).max()
+    slices, _ = og.layer_slices(D, H, L, 1)
+    for name, parts in slices.items():
+        for sl in parts:
+            err = np.linalg.norm(got[sl] - ref[sl])
+            assert err <= 5e-4 * np.linalg.norm(ref[sl]) + 1e-7 * gmax * np.sqrt(ref[sl].size), (name, err, np.linalg.norm(ref[sl]))
