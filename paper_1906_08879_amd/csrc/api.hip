@@ -293,10 +293,18 @@ size_t carve_workspace(unsigned char *base, size_t n, size_t B, const ModelView 
     ws->featb = reinterpret_cast<float4 *>(take(sizeof(float4) * (n + 1)));
     ws->partial = reinterpret_cast<float *>(take(sizeof(float) * (B * ws->n_chunks * 3 * mv.G * H + 4)));
     ws->zbuf = reinterpret_cast<float *>(take(sizeof(float) * (B * mv.Z + 4)));
-    ws->hid = reinterpret_cast<double *>(take(sizeof(double) * (B * H + 4)));
-    ws->logit = reinterpret_cast<float *>(take(sizeof(float) * (B * mv.D + 4)));
-    ws->hidp = reinterpret_cast<double *>(take(sizeof(double) * (B * 3 * H + 4)));
-    ws->head_done = reinterpret_cast<uint32_t *>(take(sizeof(uint32_t) * (B + 4)));
+    // (a split head has H = 128 and Z >= 640: three parts of a graph's first policy layer fit)
+    ws->hidp = reinterpret_cast<double *>(take(sizeof(double) * (static_cast<size_t>((mv.Z + 255) / 256) * B * H + 4)));
+    if (with_reach) {
+        // a block of fixed size, whose callers have no reverse pass: what only that reads is not kept,
+        // so that the block takes every batch that it took before those arrays were there
+        ws->head_done = reinterpret_cast<uint32_t *>(ws->zbuf);
+        ws->zbuf = nullptr;
+    } else {
+        ws->hid = reinterpret_cast<double *>(take(sizeof(double) * (B * H + 4)));
+        ws->logit = reinterpret_cast<float *>(take(sizeof(float) * (B * mv.D + 4)));
+        ws->head_done = reinterpret_cast<uint32_t *>(take(sizeof(uint32_t) * (B + 4)));
+    }
     ws->klist = reinterpret_cast<int32_t *>(take(sizeof(int32_t) * (n + 16)));
     ws->koff = reinterpret_cast<int32_t *>(take(sizeof(int32_t) * (B * (3 * kMaxD + 1) + 4)));
     if (with_reach) ws->reach = take(2 * n + 32);
@@ -346,6 +354,8 @@ int ensure_workspace(pl_graph_batch *g, const ModelView &mv)
     carve_workspace(base, n, B, mv, false, &ws);
     PL_HIP(hipMemset(ws.msg, 0, sizeof(float) * ((2 * n + 2) * mv.H + 4)));
     PL_HIP(hipMemset(ws.head_done, 0, sizeof(uint32_t) * B));
+    // (the caller's stream may be one that does not wait for the null stream's work)
+    PL_HIP(hipStreamSynchronize(nullptr));
     return PL_OK;
 }
 

@@ -142,9 +142,11 @@ struct HeadLayers {
 };
 
 struct HeadOut {
+    // kept for the reverse pass, or null
     float *zbuf;          // [B, Z] policy inputs
     double *hid;          // [B, H] hidden layer of the policy network
     float *logit;         // [B, D] logits, also where out_logits gets NaN
+
     float *out_logits, *out_probs, *out_pooled;
     float *hin, *hact;    // kept for the reverse pass (or null): inputs [3, B G, H] and layer outputs [3, L, B G, H] of h
     double *hidp;         // (SPLIT) [B, 3, H] the sets' parts of the first policy layer
@@ -282,7 +284,7 @@ __global__ __launch_bounds__(head_threads(HT, SPLIT)) void k_head(GraphView gv, 
     for (int c = tid; c < H; c += T) {                      // (a column's sum is its own thread's)
         const double s = hid[c] + static_cast<double>(bias1[c]);
         hid[c] = s > 0.0 ? s : 0.0;
-        o.hid[static_cast<size_t>(b) * H + c] = hid[c];
+        if (o.hid) o.hid[static_cast<size_t>(b) * H + c] = hid[c];
     }
     __syncthreads();
 
@@ -299,7 +301,7 @@ __global__ __launch_bounds__(head_threads(HT, SPLIT)) void k_head(GraphView gv, 
     if (tid < D) {
         const float bad = __builtin_nanf("");               // no valid current node: nothing to decide
         const size_t at = static_cast<size_t>(b) * D + tid;
-        o.logit[at] = logit[tid];
+        if (o.logit) o.logit[at] = logit[tid];
         o.out_logits[at] = cur_ok ? logit[tid] : bad;
         if (o.out_probs) {
             float mx = logit[0], tot = 0.0f;

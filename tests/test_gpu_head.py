@@ -34,3 +34,48 @@ def test_head_launch_shapes(B, D, H, by_device):
     ref = oracle.forward_workload(w, n_threads=4, want_emb=False)["logits"]
     # (logits near zero in a row of larger ones miss a bound relative to themselves: see test_gpu_parity.py)
     assert_logits_close(got[0].cpu().numpy().astype(np.float64), ref, f"B {B} D {D} H {H}", max_fail_frac=0.01)
+
+
+def _block_bytes(n, B, D, H, by_device):
+    """Buffers of the call that allocates nothing, each from a 256-byte boundary: embeddings, messages,
+    projections, feature records, pooling partials, policy inputs, parts of the policy network's first layer,
+    node order, its offsets (for 16 devices), reachability."""
+    G = D if by_device else 1
+    Z = (2 + 3 * G) * H
+    parts = [4 * ((n + 1) * 2 * H + 4), 4 * ((2 * n + 2) * H + 4), 4 * ((2 * n + 1) * H + 4), 16 * (n + 1),
+             4 * (B * 8 * 3 * G * H + 4), 4 * (B * Z + 4), 8 * (-(-Z // 256) * B * H + 4), 4 * (n + 16),
+             4 * (B * 49 + 4), 2 * n + 32]
+    return sum((p + 255) // 256 * 256 for p in parts)
+
+
+@pytest.mark.parametrize("D,H,by_device,wd", [(2, 8, 1, "fp32"), (5, 32, 0, "fp32"), (4, 64, 1, "bf16"), (3, 128, 0, "bf16"),
+                                              (8, 128, 1, "bf16")])
+def test_fixed_block_takes_the_same_batches(D, H, by_device, wd):
+    """The largest batch of one-node graphs that the fixed block takes: accepted, with the logits of the call
+    that allocates; one graph more: refused.  And, for the split head, 85 graphs."""
+    import torch
+    import paper_1906_08879_amd as pl
+    dev = torch.device("cuda:0")
+    limit = pl.embed_forward_static_limit()
+    most = max(B for B in range(1, 40000) if _block_bytes(B, B, D, H, by_device) <= limit)
+    rng = np.random.default_rng(D * H)
+    n_par = pl.weights_count(D, H, 2, 1, by_device, wd)
+    wt = pl.Weights(rng.normal(0.0, 0.1, n_par).astype(np.float32), D, H, 2, 1, by_device, wd)
+    empty = np.zeros(0, np.int32)
+    for B in (min(85, most), most, most + 1):
+        g = pl.GraphBatch(np.ones(B, np.int32), np.zeros(B, np.int32), empty, empty)
+        pl.graph_batch_upload(g)
+        assert pl.embed_forward_static_bytes(g, wt) == _block_bytes(B, B, D, H, by_device)
+        feats = torch.from_numpy(rng.random((B, 3), np.float32)).to(dev)
+        place = torch.from_numpy(rng.integers(0, D, B).astype(np.int32)).to(dev)
+        cur = torch.zeros(B, dtype=torch.int32, device=dev)
+        a, b = (torch.empty((B, D), device=dev) for _ in range(2))
+        if B > most:
+            with pytest.raises(Exception, match="fixed block"):
+                pl.embed_forward_static(g, feats, place, cur, wt, a)
+            continue
+        for _ in range(2):
+            pl.embed_forward_static(g, feats, place, cur, wt, a)
+        pl.embed_forward(g, feats, place, cur, wt, b)
+        torch.cuda.synchronize()
+        assert torch.equal(a, b)
