@@ -367,11 +367,16 @@ __global__ __launch_bounds__(kThreads) void k_pool_generic(GraphView gv, ModelVi
         const int cnt = min(kSub, hi - s0);
         if (tid < cnt) s_cls[tid] = static_cast<int8_t>(node_class(s0 + tid, cur, reach, gv.n_tot, mv.single_set));
         __syncthreads();
-        if (tid < 3) {
+        // a wave per set, 64 nodes at a time (a thread per set took a dependent read per node)
+        if (const int set = tid >> 6, lane = tid & 63; set < 3) {
             int m = 0;
-            for (int i = 0; i < cnt; ++i)
-                if (s_cls[i] == tid + 1) s_list[tid][m++] = static_cast<int16_t>(i);
-            s_count[tid] = m;
+            for (int base = 0; base < cnt; base += 64) {
+                const bool in = base + lane < cnt && s_cls[base + lane] == set + 1;
+                const unsigned long long all = __ballot(in);
+                if (in) s_list[set][m + __popcll(all & ((1ull << lane) - 1ull))] = static_cast<int16_t>(base + lane);
+                m += __popcll(all);
+            }
+            if (lane == 0) s_count[set] = m;
         }
         __syncthreads();
         for (int set = 0; set < 3; ++set) {

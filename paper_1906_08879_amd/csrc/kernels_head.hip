@@ -161,7 +161,7 @@ __global__ __launch_bounds__(head_threads(HT, SPLIT)) void k_head(GraphView gv, 
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
     __shared__ double hid[kMaxH];
-    __shared__ float logit[kMaxD], bias[(3 * kMaxLayers + 1) * (HT ? HT : kMaxH)], w2[HT ? HT * kMaxD : 1];
+    __shared__ float logit[kMaxD], bias2[kMaxD], bias[(3 * kMaxLayers + 1) * (HT ? HT : kMaxH)], w2[HT ? HT * kMaxD : 1];
     __shared__ uint32_t order;
     constexpr int CPT = head_cols(HT), T = head_threads(HT, SPLIT);
     const int H = HT ? HT : mv.H, G = mv.G, L = mv.L, D = mv.D, Z = mv.Z;
@@ -173,10 +173,15 @@ __global__ __launch_bounds__(head_threads(HT, SPLIT)) void k_head(GraphView gv, 
     HeadLayers<HT, RT, SPLIT, AHEAD> hl(mv.H, G);
     // h's weights and everything small that later phases need: requested before the graph's own data
     hl.request(mv.blob, mv.h[0].layer[0].w, mv.h[1].layer[0].w - mv.h[0].layer[0].w, set_first);
+    // (places by distance between sets and layers: an index of a thread's own into the kernel's arguments
+    // would be a load of its own ahead of each)
+    const int b_set = mv.h[1].layer[0].b - mv.h[0].layer[0].b, b_layer = L > 1 ? mv.h[0].layer[1].b - mv.h[0].layer[0].b : 0;
+    const float *b_first = mv.blob + mv.h[0].layer[0].b;
     for (int i = tid; i < n_sets * L * H; i += T) {
         const int set = i / (L * H), r = i - set * L * H, l = r / H;
-        bias[i] = mv.blob[mv.h[set_first + set].layer[l].b + r - l * H];
+        bias[i] = b_first[(set_first + set) * b_set + l * b_layer + r - l * H];
     }
+    if (tid < D) bias2[tid] = mv.blob[mv.pol2.b + tid];
     float *bias1 = bias + n_sets * L * H;
     for (int i = tid; i < H; i += T) bias1[i] = mv.blob[mv.pol1.b + i];
     if constexpr (HT != 0)
@@ -295,7 +300,7 @@ __global__ __launch_bounds__(head_threads(HT, SPLIT)) void k_head(GraphView gv, 
             s = fma(hid[k], static_cast<double>(HT != 0 ? w2[k * D + d] : mv.blob[mv.pol2.w + k * D + d]), s);
 #pragma unroll
         for (int step = 32; step > 0; step >>= 1) s += __shfl_xor(s, step);
-        if (lane == 0) logit[d] = static_cast<float>(s + static_cast<double>(mv.blob[mv.pol2.b + d]));
+        if (lane == 0) logit[d] = static_cast<float>(s + static_cast<double>(bias2[d]));
     }
     __syncthreads();
     if (tid < D) {
