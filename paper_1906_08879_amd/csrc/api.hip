@@ -270,49 +270,6 @@ void free_workspace(Workspace &ws)
     ws = Workspace();
 }
 
-// Lays the intermediate buffers of one forward pass out in one block starting at `base` (which
-// may be null: then only the size is computed) and returns the block's size in bytes.  Every
-// buffer starts on a 256-byte boundary.  With `with_reach` the reachability bytes are part of
-// the block, otherwise ws->reach is left alone.
-// Rows past the data (matrix-core sweep): emb row n, msg row 2n + 1, xb row 2n and reach byte
-// 2n + 1 take the stores of a chunk's unused rows; msg row 2n and reach byte 2n are never
-// written, must read as zero, and are the target of dummy loads.
-size_t carve_workspace(unsigned char *base, size_t n, size_t B, const ModelView &mv, bool with_reach, Workspace *ws)
-{
-    size_t at = 0;
-    auto take = [&](size_t bytes) {
-        unsigned char *p = base ? base + at : nullptr;
-        at += (bytes + 255) / 256 * 256;
-        return p;
-    };
-    const size_t H = mv.H;
-    ws->n_chunks = 8;
-    ws->emb = reinterpret_cast<float *>(take(sizeof(float) * ((n + 1) * 2 * H + 4)));
-    ws->msg = reinterpret_cast<float *>(take(sizeof(float) * ((2 * n + 2) * H + 4)));
-    ws->xb = reinterpret_cast<float *>(take(sizeof(float) * ((2 * n + 1) * H + 4)));
-    ws->featb = reinterpret_cast<float4 *>(take(sizeof(float4) * (n + 1)));
-    ws->partial = reinterpret_cast<float *>(take(sizeof(float) * (B * ws->n_chunks * 3 * mv.G * H + 4)));
-    ws->zbuf = reinterpret_cast<float *>(take(sizeof(float) * (B * mv.Z + 4)));
-    // (a split head has H = 128 and Z >= 640: three parts of a graph's first policy layer fit)
-    ws->hidp = reinterpret_cast<double *>(take(sizeof(double) * (static_cast<size_t>((mv.Z + 255) / 256) * B * H + 4)));
-    if (with_reach) {
-        // a block of fixed size, whose callers have no reverse pass: what only that reads is not kept,
-        // so that the block takes every batch that it took before those arrays were there
-        ws->head_done = reinterpret_cast<uint32_t *>(ws->zbuf);
-        ws->zbuf = nullptr;
-    } else {
-        ws->hid = reinterpret_cast<double *>(take(sizeof(double) * (B * H + 4)));
-        ws->logit = reinterpret_cast<float *>(take(sizeof(float) * (B * mv.D + 4)));
-        ws->head_done = reinterpret_cast<uint32_t *>(take(sizeof(uint32_t) * (B + 4)));
-    }
-    ws->klist = reinterpret_cast<int32_t *>(take(sizeof(int32_t) * (n + 16)));
-    ws->koff = reinterpret_cast<int32_t *>(take(sizeof(int32_t) * (B * (3 * kMaxD + 1) + 4)));
-    if (with_reach) ws->reach = take(2 * n + 32);
-    ws->H = mv.H;
-    ws->G = mv.G;
-    return at;
-}
-
 void free_grad_workspace(GradWorkspace &gw)
 {
     float *all[] = {gw.fact, gw.gact, gw.agg, gw.dagg, gw.dfg, gw.keep, gw.snap_emb, gw.snap_msg, gw.lact, gw.dl, gw.demb, gw.dx, gw.phi,
@@ -338,7 +295,7 @@ int ensure_reach(pl_graph_batch *g)
 int ensure_workspace(pl_graph_batch *g, const ModelView &mv)
 {
     Workspace &ws = g->ws;
-    if (ws.emb && ws.H == mv.H && ws.G == mv.G) return PL_OK;
+    if (ws.emb && workspace_fits(ws, mv)) return PL_OK;
     uint8_t *keep = ws.reach;
     ws.reach = nullptr;
     free_workspace(ws);

@@ -99,7 +99,7 @@ struct ModelView {
     LayerRef pol1, pol2;
 };
 
-// ---- scratch owned by a batch for one (D, H)
+// ---- scratch owned by a batch for one (H, G)
 struct Workspace {
     unsigned char *base = nullptr;  // the one allocation that holds every buffer but reach (null: not owned)
     float *emb = nullptr;       // [n_tot, 2H]  [td ; bu]
@@ -111,7 +111,7 @@ struct Workspace {
     // for the reverse pass (null: not kept)
     float *zbuf = nullptr;      // [B, Z] policy inputs
     double *hid = nullptr;      // [B, H] hidden layer of the policy network
-    float *logit = nullptr;     // [B, D] logits, also of graphs that have no valid current node
+    float *logit = nullptr;     // [B, D] (room for kMaxD) logits, also of graphs that have no valid current node
     double *hidp = nullptr;     // [B, 3, H] the node sets' parts of the first policy layer (H = 128)
     uint32_t *head_done = nullptr;   // [B] workgroups of a graph that have written theirs; zero between calls
     int32_t *klist = nullptr;   // [n_tot] node ids grouped by (set, device group), per graph (matrix-core pooling)
@@ -119,6 +119,10 @@ struct Workspace {
     int32_t n_chunks = 0;
     int32_t H = 0, G = 0;
 };
+
+// (workspace.cpp)
+bool workspace_fits(const Workspace &ws, const ModelView &mv);
+size_t carve_workspace(unsigned char *base, size_t n, size_t B, const ModelView &mv, bool with_reach, Workspace *ws);
 
 // ---- kernel launchers (kernels_generic.hip)
 struct ForwardArgs {
