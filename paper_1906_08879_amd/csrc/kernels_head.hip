@@ -11,9 +11,10 @@
 //     16-byte load, and an input read from LDS feeds four columns.  The slices' sums meet in LDS.
 //   * The first policy layer spreads its blocks of sixteen inputs over groups of H / 4 threads, 64
 //     weights per thread in flight; the output layer has a wave per device.
-// Sums are taken in float64 by blocks (sixteen fp32 terms, the blocks in float64, the output layer
-// entirely in float64): z holds sums over thousands of nodes, so a logit is a difference of terms far
-// larger than itself, and plain fp32 sums would be the largest single source of its error.
+// Sums are taken in float64 by blocks (sixteen fp32 terms, the blocks and the terms past the last whole one
+// in float64, the output layer entirely in float64): z holds sums over thousands of nodes, so a logit is a
+// difference of terms far larger than itself, and plain fp32 sums would be the largest single source of its
+// error.
 // Forward head of 256 NASNet-like graphs (H = 128, 8 devices): 81 us as three launches, 37 us now; of one: 52,
 // now 18; of 64 graphs at H = 32: 19, now 8.  Reverse head of those 256 graphs: 63, now 41.
 #include <type_traits>
@@ -32,53 +33,86 @@ typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4;
 // Instantiations: HT = H where it is known when the kernel is compiled (32, 64, 128), else 0; RT: rows of a
 // set per pass; SPLIT: a workgroup per (graph, set) instead of per graph.
 constexpr int head_threads(int HT, bool split) { return HT == 0 || (HT == 128 && !split) ? 1024 : 512; }
-constexpr int head_cols(int HT) { return HT >= 32 ? 4 : 1; }             // columns per thread
+constexpr int head_cols(int HT) { return HT != 0 ? 4 : 1; }             // columns per thread
 constexpr int head_sets(int H, bool split) { return !split && H <= 128 ? 3 : 1; }   // networks taken together
-constexpr int head_rows_max(int H) { return H <= 128 ? 8 : 4; }
 
 constexpr size_t head_lds(int H, int G, int RT, int HT, bool split)
 {
-    const size_t units = static_cast<size_t>(head_sets(H, split)) * ((H + kBlock - 1) / kBlock);
-    const size_t part = units * RT * H * sizeof(float);
-    const size_t red = static_cast<size_t>(head_threads(HT, split) / (H / head_cols(HT))) * H * sizeof(double);
+    const size_t groups = static_cast<size_t>(head_threads(HT, split) / (H / head_cols(HT)));
+    const size_t part = HT == 0 ? groups * RT * H * sizeof(double)
+                                : static_cast<size_t>(head_sets(H, split)) * (H / kBlock) * RT * H * sizeof(float);
+    const size_t red = groups * H * sizeof(double);
     return (part > red ? part : red) + sizeof(float) * (static_cast<size_t>(2 + (split ? 1 : 3) * G) * H + 4);
 }
 
-// Sixteen rows of four columns (one column where H is not known), the weights of one unit.
+// Sixteen rows of four columns, the weights of one unit.
 template <int HT>
 struct WeightBlock {
     static constexpr int CPT = head_cols(HT);
     float w[kBlock][CPT];
-    // rows k0 .. k0 + kn - 1 of a matrix with H columns, from column j on (kn = kBlock where H is known)
-    __device__ __forceinline__ void load(const float *__restrict__ W, int H, int kn)
+    // rows k0 .. k0 + 15 of a matrix with H columns, from column j on
+    __device__ __forceinline__ void load(const float *__restrict__ W, int H)
     {
 #pragma unroll
         for (int k = 0; k < kBlock; ++k) {
-            if constexpr (CPT == 4) {
-                const f32x4 v = *reinterpret_cast<const f32x4 *>(W + static_cast<size_t>(k) * H);
+            const f32x4 v = *reinterpret_cast<const f32x4 *>(W + static_cast<size_t>(k) * H);
 #pragma unroll
-                for (int c = 0; c < CPT; ++c) w[k][c] = v[c];
-            } else {
-                w[k][0] = k < kn ? W[static_cast<size_t>(k) * H] : 0.0f;
-            }
+            for (int c = 0; c < CPT; ++c) w[k][c] = v[c];
         }
     }
-    __device__ __forceinline__ void apply(const float *x, int kn, float (&s)[CPT]) const
+    __device__ __forceinline__ void apply(const float *x, float (&s)[CPT]) const
     {
 #pragma unroll
         for (int c = 0; c < CPT; ++c) s[c] = 0.0f;
 #pragma unroll
         for (int k = 0; k < kBlock; ++k) {
-            const float xv = (CPT == 4 || k < kn) ? x[k] : 0.0f;
+            const float xv = x[k];
 #pragma unroll
             for (int c = 0; c < CPT; ++c) s[c] = fmaf(xv, w[k][c], s[c]);
         }
     }
 };
 
+// Any width: acc[r] += one column's product with row r of x over the blocks first, first + step, ... of the
+// n_in inputs.  The inputs past the last whole block are summed in float64 one by one (by the group whose
+// turn that block is): at H < 16 those are all of a layer's terms.
+template <int RT>
+__device__ __forceinline__ void dot_rows(const float *__restrict__ W, int H, int n_in, int first, int step, const float *x,
+                                         int ldx, int rows, double (&acc)[RT])
+{
+    const int whole = n_in / kBlock;
+    int u = first;
+    for (; u < whole; u += step) {
+        float w[kBlock];
+#pragma unroll
+        for (int k = 0; k < kBlock; ++k) w[k] = W[static_cast<size_t>(u * kBlock + k) * H];
+#pragma unroll
+        for (int r = 0; r < RT; ++r) {
+            const float *xr = x + min(r, rows - 1) * ldx + u * kBlock;
+            float s = 0.0f;
+#pragma unroll
+            for (int k = 0; k < kBlock; ++k) s = fmaf(xr[k], w[k], s);
+            acc[r] += static_cast<double>(s);
+        }
+    }
+    if (u != whole) return;
+    const int kn = n_in - whole * kBlock;
+    float w[kBlock];
+#pragma unroll
+    for (int k = 0; k < kBlock; ++k) w[k] = k < kn ? W[static_cast<size_t>(whole * kBlock + k) * H] : 0.0f;
+#pragma unroll
+    for (int k = 0; k < kBlock; ++k) {
+        if (k >= kn) break;
+#pragma unroll
+        for (int r = 0; r < RT; ++r)
+            acc[r] = fma(static_cast<double>(x[min(r, rows - 1) * ldx + whole * kBlock + k]), static_cast<double>(w[k]), acc[r]);
+    }
+}
+
 // The layers of the h networks (set0 .. set0 + sets - 1 of the three) on the rows x [sets][G][H] (LDS), in
-// place.  A unit is (set, slice of sixteen inputs), H / CPT threads; where H is known a thread has at most
-// one.  AHEAD: its weights of the next layer are requested before the current layer's slices are added up.
+// place.  Where H is known, a unit is (set, slice of sixteen inputs), H / 4 threads, and a thread has at most
+// one; AHEAD: its weights of the next layer are requested before the current layer's slices are added up.
+// Otherwise the groups of H threads are shared out among the sets, and a group takes every so manieth slice.
 template <int HT, int RT, bool SPLIT, bool AHEAD>
 struct HeadLayers {
     static constexpr int CPT = head_cols(HT), T = head_threads(HT, SPLIT);
@@ -89,7 +123,7 @@ struct HeadLayers {
     {
         H = HT ? HT : H_;
         G = G_;
-        slices = (H + kBlock - 1) / kBlock;
+        slices = H / kBlock;
         cols = H / CPT;
         sets = head_sets(H, SPLIT);
         groups = T / cols;
@@ -102,7 +136,7 @@ struct HeadLayers {
         if constexpr (AHEAD) {
             if (grp < sets * slices) {
                 const int set = set0 + grp / slices, k0 = (grp % slices) * kBlock;
-                wb.load(blob + w0 + static_cast<ptrdiff_t>(set) * ws + static_cast<size_t>(k0) * H + j, H, kBlock);
+                wb.load(blob + w0 + static_cast<ptrdiff_t>(set) * ws + static_cast<size_t>(k0) * H + j, H);
             }
         }
     }
@@ -113,27 +147,42 @@ struct HeadLayers {
                                           float *part, N next, F finish)
     {
         const int tid = threadIdx.x;
+        // sums to add up for an entry, and their distance
+        const int n_part = HT ? slices : min(groups / sets, (H + kBlock - 1) / kBlock), part_step = RT * H;
+        double *part64 = reinterpret_cast<double *>(part);
         for (int set0 = 0; set0 < (SPLIT ? 1 : 3); set0 += sets)
             for (int r0 = 0; r0 < G; r0 += RT) {
                 const int rows = min(RT, G - r0);
-                for (int u = grp; u < sets * slices && grp < groups; u += groups) {
-                    const int q = u / slices, k0 = (u - q * slices) * kBlock, kn = min(kBlock, H - k0);
-                    if constexpr (!AHEAD)
-                        wb.load(blob + w0 + static_cast<ptrdiff_t>(set_first + set0 + q) * ws + static_cast<size_t>(k0) * H + j, H, kn);
+                if constexpr (HT != 0) {
+                    if (grp < sets * slices) {
+                        const int q = grp / slices, k0 = (grp - q * slices) * kBlock;
+                        if constexpr (!AHEAD)
+                            wb.load(blob + w0 + static_cast<ptrdiff_t>(set_first + set0 + q) * ws + static_cast<size_t>(k0) * H + j, H);
 #pragma unroll
-                    for (int r = 0; r < RT; ++r) {
-                        float s[CPT];
-                        wb.apply(x + ((set0 + q) * G + r0 + min(r, rows - 1)) * H + k0, kn, s);
+                        for (int r = 0; r < RT; ++r) {
+                            float s[CPT];
+                            wb.apply(x + ((set0 + q) * G + r0 + min(r, rows - 1)) * H + k0, s);
 #pragma unroll
-                        for (int c = 0; c < CPT; ++c) part[(u * RT + r) * H + j + c] = s[c];
+                            for (int c = 0; c < CPT; ++c) part[(grp * RT + r) * H + j + c] = s[c];
+                        }
                     }
+                } else if (grp < sets * n_part) {
+                    const int q = grp / n_part;
+                    double acc[RT];
+#pragma unroll
+                    for (int r = 0; r < RT; ++r) acc[r] = 0.0;
+                    dot_rows<RT>(blob + w0 + static_cast<ptrdiff_t>(set_first + set0 + q) * ws + j, H, H, grp - q * n_part,
+                                 n_part, x + ((set0 + q) * G + r0) * H, H, rows, acc);
+#pragma unroll
+                    for (int r = 0; r < RT; ++r) part64[(grp * RT + r) * H + j] = acc[r];
                 }
                 if (AHEAD && r0 + RT >= G) next();
                 __syncthreads();
                 for (int i = tid; i < sets * rows * H; i += T) {
                     const int sr = i / H, c = i - sr * H, q = sr / rows, r = sr - q * rows;
+                    const int at = q * n_part * part_step + r * H + c;
                     double s = 0.0;
-                    for (int sl = 0; sl < slices; ++sl) s += static_cast<double>(part[((q * slices + sl) * RT + r) * H + c]);
+                    for (int k = 0; k < n_part; ++k) s += HT ? static_cast<double>(part[at + k * part_step]) : part64[at + k * part_step];
                     x[((set0 + q) * G + r0 + r) * H + c] = finish(set_first + set0 + q, r0 + r, c, s);
                 }
                 __syncthreads();
@@ -234,7 +283,7 @@ __global__ __launch_bounds__(head_threads(HT, SPLIT)) void k_head(GraphView gv, 
                 if (l + 1 < L)
                     hl.request(mv.blob, mv.h[0].layer[l + 1].w, mv.h[1].layer[l + 1].w - mv.h[0].layer[l + 1].w, set_first);
                 else if (p_grp < used)
-                    hl.wb.load(W1 + static_cast<size_t>(p_grp) * kBlock * H, H, kBlock);
+                    hl.wb.load(W1 + static_cast<size_t>(p_grp) * kBlock * H, H);
             },
             [&](int set, int r, int c, double s) {
                 const float y = fmaxf(static_cast<float>(s + static_cast<double>(bias[((set - set_first) * L + l) * H + c])), 0.0f);
@@ -250,13 +299,16 @@ __global__ __launch_bounds__(head_threads(HT, SPLIT)) void k_head(GraphView gv, 
         double acc[CPT];
 #pragma unroll
         for (int c = 0; c < CPT; ++c) acc[c] = 0.0;
-        for (int q = p_grp; q < blocks; q += p_groups) {
-            const int kn = min(kBlock, z_n - q * kBlock);
-            if (!AHEAD || q != p_grp) hl.wb.load(W1 + static_cast<size_t>(q) * kBlock * H, H, kn);
-            float s[CPT];
-            hl.wb.apply(zp + q * kBlock, kn, s);
+        if constexpr (HT == 0) {
+            dot_rows<1>(W1, H, z_n, p_grp, p_groups, zp, 0, 1, acc);
+        } else {
+            for (int q = p_grp; q < blocks; q += p_groups) {
+                if (!AHEAD || q != p_grp) hl.wb.load(W1 + static_cast<size_t>(q) * kBlock * H, H);
+                float s[CPT];
+                hl.wb.apply(zp + q * kBlock, s);
 #pragma unroll
-            for (int c = 0; c < CPT; ++c) acc[c] += static_cast<double>(s[c]);
+                for (int c = 0; c < CPT; ++c) acc[c] += static_cast<double>(s[c]);
+            }
         }
 #pragma unroll
         for (int c = 0; c < CPT; ++c) red[p_grp * H + p_j + c] = acc[c];
@@ -425,7 +477,7 @@ void head_dispatch(int H, int G, F go)
 {
     auto rows = [&](auto ht) {
         if (G == 1) go(ht, std::integral_constant<int, 1>{});
-        else if (G <= 4 || head_rows_max(H) == 4) go(ht, std::integral_constant<int, 4>{});
+        else if (G <= 4) go(ht, std::integral_constant<int, 4>{});
         else go(ht, std::integral_constant<int, 8>{});
     };
     if (H == 128) rows(std::integral_constant<int, 128>{});
