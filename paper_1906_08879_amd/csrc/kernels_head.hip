@@ -1,10 +1,10 @@
 // Policy head (Section 2.2 step 3, Appendix A.7), forward and reverse: q[i][d] = h_i(P[i][d]) (also for
 // empty groups); z = [e_{v*} ; q]; two-layer policy network with a softmax over devices.
 //
-// One workgroup of 1024 threads per graph does all of it.  The head is small (2 MB of weights at the
-// NASNet-like shape, 0.3 MB at H = 64) and a chain of dense layers, so its time is its launches, the
-// latency of its weight loads and, with many graphs, the rate at which a CU reads weights from L2; three
-// launches with a workgroup per (graph, set), per (16 graphs, slice of z) and per graph spent most of
+// One workgroup per graph does all of it (at H >= 128 and few graphs three, one per node set: see HeadShape).  The
+// head is small (2 MB of weights at the NASNet-like shape, 0.3 MB at H = 64) and a chain of dense layers, so its
+// time is its launches, the latency of its weight loads and, with many graphs, the rate at which a CU reads weights
+// from L2; three launches with a workgroup per (graph, set), per (16 graphs, slice of z) and per graph spent most of
 // theirs starting and on sequential loops (the output layer took one thread per device).
 //   * A layer of the three h networks is one phase: a unit (set, slice of sixteen inputs) is H / 4
 //     threads with four columns and up to eight rows each, so a weight is loaded once, as part of a
@@ -30,19 +30,39 @@ constexpr int kComputeUnits = 256;
 
 typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4;
 
-// Instantiations: HT = H where it is known when the kernel is compiled (32, 64, 128), else 0; RT: rows of a
-// set per pass; SPLIT: a workgroup per (graph, set) instead of per graph.
-constexpr int head_threads(int HT, bool split) { return HT == 0 || (HT == 128 && !split) ? 1024 : 512; }
-constexpr int head_cols(int HT) { return HT != 0 ? 4 : 1; }             // columns per thread
-constexpr int head_sets(int H, bool split) { return !split && H <= 128 ? 3 : 1; }   // networks taken together
+// Launch shapes.  kPerGraph: a workgroup per graph with as many threads as a layer of the h networks can use.
+// kPerSet (H >= 128): a workgroup per (graph, set).  kPacked (H <= 64): a workgroup of few threads per graph.
+enum HeadShape { kPerGraph, kPerSet, kPacked };
 
-constexpr size_t head_lds(int H, int G, int RT, int HT, bool split)
+// Instantiations: HT = H where it is known when the kernel is compiled (32, 64, 128), else 0; RT: rows of a
+// set per pass; SHAPE.
+constexpr int head_threads(int HT, HeadShape shape)
 {
-    const size_t groups = static_cast<size_t>(head_threads(HT, split) / (H / head_cols(HT)));
+    return shape == kPacked ? (HT == 64 ? 256 : 128) : HT == 0 || (HT == 128 && shape == kPerGraph) ? 1024 : 512;
+}
+// Threads of a launch over B graphs.  Where H is not known the kernel takes any whole number of waves: 1024 while a
+// graph has a CU to itself, else five groups of H threads, so that several graphs share a CU.  Forward head at H =
+// 48, 4 devices: 256 graphs 17 us with 1024 threads, 21 with 384; 2048 graphs 101 us with 1024, 77 with 384, 54
+// with 256; at H = 8, 2 devices, 4096 graphs: 130 us with 1024, 19 with 64.
+constexpr int head_launch_threads(int H, int B, int HT, HeadShape shape)
+{
+    if (HT != 0 || B <= kComputeUnits || 5 * H >= 1024) return head_threads(HT, shape);
+    return (5 * H + 63) / 64 * 64;
+}
+constexpr int head_cols(int HT) { return HT != 0 ? 4 : 1; }             // columns per thread
+constexpr int head_sets(int H, HeadShape shape) { return shape != kPerSet && H <= 128 ? 3 : 1; }   // networks taken together
+
+// What a kernel of a width that is not known keeps in dynamic LDS beside the rows: the biases of `layers` layers
+// and the output layer's weights.
+constexpr size_t head_small(int H, int D, int layers, int HT) { return HT != 0 ? 0 : static_cast<size_t>(layers + D) * H; }
+
+constexpr size_t head_lds(int H, int G, int RT, int HT, HeadShape shape, int threads, size_t small = 0)
+{
+    const size_t groups = static_cast<size_t>(threads / (H / head_cols(HT)));
     const size_t part = HT == 0 ? groups * RT * H * sizeof(double)
-                                : static_cast<size_t>(head_sets(H, split)) * (H / kBlock) * RT * H * sizeof(float);
+                                : static_cast<size_t>(head_sets(H, shape)) * (H / kBlock) * RT * H * sizeof(float);
     const size_t red = groups * H * sizeof(double);
-    return (part > red ? part : red) + sizeof(float) * (static_cast<size_t>(2 + (split ? 1 : 3) * G) * H + 4);
+    return (part > red ? part : red) + sizeof(float) * (static_cast<size_t>(2 + (shape == kPerSet ? 1 : 3) * G) * H + small + 4);
 }
 
 // Sixteen rows of four columns, the weights of one unit.
@@ -75,8 +95,9 @@ struct WeightBlock {
 
 // Any width: acc[r] += one column's product with row r of x over the blocks first, first + step, ... of the
 // n_in inputs.  The inputs past the last whole block are summed in float64 one by one (by the group whose
-// turn that block is): at H < 16 those are all of a layer's terms.
-template <int RT>
+// turn that block is): at H < 16 those are all of a layer's terms.  VEC: rows of x start on 16-byte boundaries, and
+// are read four entries at a time (LDS reads are what these loops wait for: 1024 graphs at H = 100: 110 -> 97 us).
+template <int RT, bool VEC>
 __device__ __forceinline__ void dot_rows(const float *__restrict__ W, int H, int n_in, int first, int step, const float *x,
                                          int ldx, int rows, double (&acc)[RT])
 {
@@ -89,9 +110,17 @@ __device__ __forceinline__ void dot_rows(const float *__restrict__ W, int H, int
 #pragma unroll
         for (int r = 0; r < RT; ++r) {
             const float *xr = x + min(r, rows - 1) * ldx + u * kBlock;
+            float xv[kBlock];
+#pragma unroll
+            for (int k = 0; k < kBlock; k += VEC ? 4 : 1) {
+                if constexpr (VEC)
+                    *reinterpret_cast<f32x4 *>(xv + k) = *reinterpret_cast<const f32x4 *>(xr + k);
+                else
+                    xv[k] = xr[k];
+            }
             float s = 0.0f;
 #pragma unroll
-            for (int k = 0; k < kBlock; ++k) s = fmaf(xr[k], w[k], s);
+            for (int k = 0; k < kBlock; ++k) s = fmaf(xv[k], w[k], s);
             acc[r] += static_cast<double>(s);
         }
     }
@@ -113,19 +142,20 @@ __device__ __forceinline__ void dot_rows(const float *__restrict__ W, int H, int
 // place.  Where H is known, a unit is (set, slice of sixteen inputs), H / 4 threads, and a thread has at most
 // one; AHEAD: its weights of the next layer are requested before the current layer's slices are added up.
 // Otherwise the groups of H threads are shared out among the sets, and a group takes every so manieth slice.
-template <int HT, int RT, bool SPLIT, bool AHEAD>
+template <int HT, int RT, HeadShape SHAPE, bool AHEAD>
 struct HeadLayers {
-    static constexpr int CPT = head_cols(HT), T = head_threads(HT, SPLIT);
+    static constexpr int CPT = head_cols(HT);
     WeightBlock<HT> wb;
-    int H, G, slices, cols, sets, groups, grp, j;
+    int H, G, T, slices, cols, sets, groups, grp, j;
 
     __device__ __forceinline__ HeadLayers(int H_, int G_)
     {
         H = HT ? HT : H_;
         G = G_;
+        T = HT ? head_threads(HT, SHAPE) : blockDim.x;
         slices = H / kBlock;
         cols = H / CPT;
-        sets = head_sets(H, SPLIT);
+        sets = head_sets(H, SHAPE);
         groups = T / cols;
         grp = static_cast<int>(threadIdx.x) / cols;
         j = (static_cast<int>(threadIdx.x) - grp * cols) * CPT;
@@ -150,7 +180,7 @@ struct HeadLayers {
         // sums to add up for an entry, and their distance
         const int n_part = HT ? slices : min(groups / sets, (H + kBlock - 1) / kBlock), part_step = RT * H;
         double *part64 = reinterpret_cast<double *>(part);
-        for (int set0 = 0; set0 < (SPLIT ? 1 : 3); set0 += sets)
+        for (int set0 = 0; set0 < (SHAPE == kPerSet ? 1 : 3); set0 += sets)
             for (int r0 = 0; r0 < G; r0 += RT) {
                 const int rows = min(RT, G - r0);
                 if constexpr (HT != 0) {
@@ -171,8 +201,11 @@ struct HeadLayers {
                     double acc[RT];
 #pragma unroll
                     for (int r = 0; r < RT; ++r) acc[r] = 0.0;
-                    dot_rows<RT>(blob + w0 + static_cast<ptrdiff_t>(set_first + set0 + q) * ws + j, H, H, grp - q * n_part,
-                                 n_part, x + ((set0 + q) * G + r0) * H, H, rows, acc);
+                    const float *W = blob + w0 + static_cast<ptrdiff_t>(set_first + set0 + q) * ws + j, *xq = x + ((set0 + q) * G + r0) * H;
+                    if (H % 4 == 0)
+                        dot_rows<RT, true>(W, H, H, grp - q * n_part, n_part, xq, H, rows, acc);
+                    else
+                        dot_rows<RT, false>(W, H, H, grp - q * n_part, n_part, xq, H, rows, acc);
 #pragma unroll
                     for (int r = 0; r < RT; ++r) part64[(grp * RT + r) * H + j] = acc[r];
                 }
@@ -202,28 +235,33 @@ struct HeadOut {
     uint32_t *done;       // (SPLIT) [B] workgroups of a graph that have written theirs; zero between calls
 };
 
-template <int HT, int RT, bool SPLIT>
-__global__ __launch_bounds__(head_threads(HT, SPLIT)) void k_head(GraphView gv, ModelView mv, const float *__restrict__ emb,
+template <int HT, int RT, HeadShape SHAPE>
+__global__ __launch_bounds__(head_threads(HT, SHAPE)) void k_head(GraphView gv, ModelView mv, const float *__restrict__ emb,
                                                               const float *__restrict__ partial,
                                                               const int32_t *__restrict__ cur_node, int max_chunks,
                                                               HeadOut o)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
     __shared__ double hid[kMaxH];
-    __shared__ float logit[kMaxD], bias2[kMaxD], bias[(3 * kMaxLayers + 1) * (HT ? HT : kMaxH)], w2[HT ? HT * kMaxD : 1];
+    __shared__ float logit[kMaxD], bias2[kMaxD], bias_s[HT ? (3 * kMaxLayers + 1) * HT : 1], w2_s[HT ? HT * kMaxD : 1];
     __shared__ uint32_t order;
-    constexpr int CPT = head_cols(HT), T = head_threads(HT, SPLIT);
-    const int H = HT ? HT : mv.H, G = mv.G, L = mv.L, D = mv.D, Z = mv.Z;
+    constexpr int CPT = head_cols(HT);
+    constexpr bool SPLIT = SHAPE == kPerSet;
+    const int H = HT ? HT : mv.H, G = mv.G, L = mv.L, D = mv.D, Z = mv.Z, T = HT ? head_threads(HT, SHAPE) : blockDim.x;
     const int b = SPLIT ? blockIdx.x / 3 : blockIdx.x, set_first = SPLIT ? blockIdx.x - 3 * b : 0;
     constexpr int n_sets = SPLIT ? 1 : 3;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    // (a workgroup of 1024 threads has no registers to hold weights ahead and add up float64 sums)
-    constexpr bool AHEAD = HT != 0 && T == 512;
-    HeadLayers<HT, RT, SPLIT, AHEAD> hl(mv.H, G);
+    // (weights ahead take registers that 1024 threads do not have beside the float64 sums, and that many small
+    // workgroups on a CU need for themselves)
+    constexpr bool AHEAD = HT != 0 && head_threads(HT, SHAPE) == 512;
+    HeadLayers<HT, RT, SHAPE, AHEAD> hl(mv.H, G);
     // h's weights and everything small that later phases need: requested before the graph's own data
     hl.request(mv.blob, mv.h[0].layer[0].w, mv.h[1].layer[0].w - mv.h[0].layer[0].w, set_first);
     // (places by distance between sets and layers: an index of a thread's own into the kernel's arguments
     // would be a load of its own ahead of each)
+    float *z = reinterpret_cast<float *>(lds);              // e_{v*}, then the rows of the sets
+    float *small = z + (2 + n_sets * G) * H;
+    float *bias = HT ? bias_s : small, *w2 = HT ? w2_s : small + (n_sets * L + 1) * H;
     const int b_set = mv.h[1].layer[0].b - mv.h[0].layer[0].b, b_layer = L > 1 ? mv.h[0].layer[1].b - mv.h[0].layer[0].b : 0;
     const float *b_first = mv.blob + mv.h[0].layer[0].b;
     for (int i = tid; i < n_sets * L * H; i += T) {
@@ -233,10 +271,8 @@ __global__ __launch_bounds__(head_threads(HT, SPLIT)) void k_head(GraphView gv, 
     if (tid < D) bias2[tid] = mv.blob[mv.pol2.b + tid];
     float *bias1 = bias + n_sets * L * H;
     for (int i = tid; i < H; i += T) bias1[i] = mv.blob[mv.pol1.b + i];
-    if constexpr (HT != 0)
-        for (int i = tid; i < H * D; i += T) w2[i] = mv.blob[mv.pol2.w + i];
-    float *z = reinterpret_cast<float *>(lds);              // e_{v*}, then the rows of the sets
-    float *x = z + 2 * H, *part = z + (((2 + n_sets * G) * H + 3) & ~3);
+    for (int i = tid; i < H * D; i += T) w2[i] = mv.blob[mv.pol2.w + i];
+    float *x = z + 2 * H, *part = z + (((2 + n_sets * G) * H + static_cast<int>(head_small(H, D, n_sets * L + 1, HT)) + 3) & ~3);
     const int n0 = gv.node_off[b], n_b = gv.node_off[b + 1] - n0;
     const int cl = cur_node[b];
     const bool cur_ok = cl >= 0 && cl < n_b;
@@ -300,7 +336,10 @@ __global__ __launch_bounds__(head_threads(HT, SPLIT)) void k_head(GraphView gv, 
 #pragma unroll
         for (int c = 0; c < CPT; ++c) acc[c] = 0.0;
         if constexpr (HT == 0) {
-            dot_rows<1>(W1, H, z_n, p_grp, p_groups, zp, 0, 1, acc);
+            if (!SPLIT || H % 4 == 0)
+                dot_rows<1, true>(W1, H, z_n, p_grp, p_groups, zp, 0, 1, acc);
+            else
+                dot_rows<1, false>(W1, H, z_n, p_grp, p_groups, zp, 0, 1, acc);
         } else {
             for (int q = p_grp; q < blocks; q += p_groups) {
                 if (!AHEAD || q != p_grp) hl.wb.load(W1 + static_cast<size_t>(q) * kBlock * H, H);
@@ -349,7 +388,7 @@ __global__ __launch_bounds__(head_threads(HT, SPLIT)) void k_head(GraphView gv, 
     for (int d = wave; d < D; d += T / 64) {
         double s = 0.0;
         for (int k = lane; k < H; k += 64)
-            s = fma(hid[k], static_cast<double>(HT != 0 ? w2[k * D + d] : mv.blob[mv.pol2.w + k * D + d]), s);
+            s = fma(hid[k], static_cast<double>(w2[k * D + d]), s);
 #pragma unroll
         for (int step = 32; step > 0; step >>= 1) s += __shfl_xor(s, step);
         if (lane == 0) logit[d] = static_cast<float>(s + static_cast<double>(bias2[d]));
@@ -373,17 +412,16 @@ __global__ __launch_bounds__(head_threads(HT, SPLIT)) void k_head(GraphView gv, 
 // d logits = c (one-hot(a) - softmax) + entropy term, back to the hidden layer, to the policy input z
 // (dz; its first 2H entries are the gradient of e_{v*}) and through the h networks to dP[set][group].
 // A graph whose current node or action is out of range gets a zero gradient and logp = NaN.
-template <int HT, int RT>
-__global__ __launch_bounds__(head_threads(HT, false)) void k_head_bw(GraphView gv, ModelView mv, const float *__restrict__ blob_t,
+template <int HT, int RT, HeadShape SHAPE>
+__global__ __launch_bounds__(head_threads(HT, SHAPE)) void k_head_bw(GraphView gv, ModelView mv, const float *__restrict__ blob_t,
                                                           const int32_t *__restrict__ cur_node, HeadBwArgs a)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
     __shared__ float dpre[kMaxH];
     __shared__ float dlog[kMaxD];
-    constexpr int T = head_threads(HT, false);
-    const int H = HT ? HT : mv.H, G = mv.G, L = mv.L, D = mv.D, Z = mv.Z;
+    const int H = HT ? HT : mv.H, G = mv.G, L = mv.L, D = mv.D, Z = mv.Z, T = HT ? head_threads(HT, SHAPE) : blockDim.x;
     const int b = blockIdx.x, tid = threadIdx.x;
-    HeadLayers<HT, RT, false, HT != 0> hl(mv.H, G);
+    HeadLayers<HT, RT, SHAPE, HT != 0 && SHAPE != kPacked> hl(mv.H, G);
     auto request = [&](int l) { hl.request(blob_t, mv.h[0].layer[l].w, mv.h[1].layer[l].w - mv.h[0].layer[l].w, 0); };
     request(L - 1);
     float *z = reinterpret_cast<float *>(lds);              // [Z]: dz
@@ -471,19 +509,39 @@ __global__ __launch_bounds__(head_threads(HT, false)) void k_head_bw(GraphView g
     }
 }
 
-// Calls go(HT, RT) with the instantiation for width H and G rows per set.
+// Calls go(HT, RT, SHAPE) with the instantiation for width H, G rows per set and B graphs.
+//   * H >= 128, forward: a graph's 2 MB of weights take one CU 18 us longer than three (H = 128, 8 device groups: 34
+//     against 18 us for one graph); with more workgroups than CUs the hand-over between them costs more than it
+//     gives (256 graphs: 43 us together, 55 us split).
+//   * H = 32 and 64: 512 threads with weights ahead have a CU to themselves, so a second graph per CU waits for the
+//     first.  Above one graph per CU: small workgroups without (forward head at H = 64, 8 devices: 256 graphs 19 us,
+//     small 22, 1024 graphs 60 and 40; at H = 32, 4 devices: 12 and 14, 30 and 16).  The reverse head at H = 64
+//     takes fewer registers and changes over later (512 graphs of 8 devices: 27 us, small 30; 1024: 50 and 46).
 template <typename F>
-void head_dispatch(int H, int G, F go)
+void head_dispatch(int H, int G, int B, bool forward, F go)
 {
-    auto rows = [&](auto ht) {
-        if (G == 1) go(ht, std::integral_constant<int, 1>{});
-        else if (G <= 4) go(ht, std::integral_constant<int, 4>{});
-        else go(ht, std::integral_constant<int, 8>{});
+    auto rows = [&](auto ht, auto shape) {
+        if (G == 1) go(ht, std::integral_constant<int, 1>{}, shape);
+        else if (G == 2) go(ht, std::integral_constant<int, 2>{}, shape);
+        else if (G <= 4) go(ht, std::integral_constant<int, 4>{}, shape);
+        else go(ht, std::integral_constant<int, 8>{}, shape);
     };
-    if (H == 128) rows(std::integral_constant<int, 128>{});
-    else if (H == 64) rows(std::integral_constant<int, 64>{});
-    else if (H == 32) rows(std::integral_constant<int, 32>{});
-    else rows(std::integral_constant<int, 0>{});
+    const std::integral_constant<HeadShape, kPerGraph> per_graph;
+    const std::integral_constant<HeadShape, kPerSet> per_set;
+    const std::integral_constant<HeadShape, kPacked> packed;
+    const std::integral_constant<int, 128> h128;
+    const std::integral_constant<int, 64> h64;
+    const std::integral_constant<int, 32> h32;
+    const std::integral_constant<int, 0> any;
+    const bool split = forward && H >= 128 && 3 * B <= kComputeUnits;
+    if (H == 128 && split) rows(h128, per_set);
+    else if (H == 128) rows(h128, per_graph);
+    else if (H == 64 && B <= (forward ? 1 : 2) * kComputeUnits) rows(h64, per_graph);
+    else if (H == 64) rows(h64, packed);
+    else if (H == 32 && B <= kComputeUnits) rows(h32, per_graph);
+    else if (H == 32) rows(h32, packed);
+    else if (split) rows(any, per_set);
+    else rows(any, per_graph);
 }
 
 template <typename K>
@@ -502,25 +560,14 @@ void launch_head(const GraphView &gv, const ModelView &mv, const Workspace &ws, 
     if (gv.B == 0) return;
     const HeadOut o{ws.zbuf,      ws.hid,       ws.logit, fa.out_logits, fa.out_probs, fa.out_pooled,
                     fa.keep_hin,  fa.keep_hact, ws.hidp,  ws.head_done};
-    head_dispatch(mv.H, mv.G, [&](auto ht, auto rt) {
+    head_dispatch(mv.H, mv.G, gv.B, true, [&](auto ht, auto rt, auto shape) {
         constexpr int HT = decltype(ht)::value, RT = decltype(rt)::value;
-        auto run = [&](auto split) {
-            constexpr bool SPLIT = decltype(split)::value;
-            const size_t lds = head_lds(mv.H, mv.G, RT, HT, SPLIT);
-            allow_lds(k_head<HT, RT, SPLIT>, lds);
-            hipLaunchKernelGGL((k_head<HT, RT, SPLIT>), dim3(SPLIT ? 3 * gv.B : gv.B), dim3(head_threads(HT, SPLIT)), lds, s,
-                               gv, mv, ws.emb, ws.partial, fa.cur_node, max_chunks, o);
-        };
-        // At H = 128 a graph's 2 MB of weights take one CU 18 us longer than three (34 against 18 us for one
-        // graph, 8 device groups); with more workgroups than CUs the hand-over between them costs more
-        // than it gives (256 graphs: 43 us together, 55 us split).
-        if constexpr (HT == 128) {
-            if (3 * gv.B <= kComputeUnits) {
-                run(std::true_type{});
-                return;
-            }
-        }
-        run(std::false_type{});
+        constexpr HeadShape SHAPE = decltype(shape)::value;
+        const int threads = head_launch_threads(mv.H, gv.B, HT, SHAPE), sets = SHAPE == kPerSet ? 1 : 3;
+        const size_t lds = head_lds(mv.H, mv.G, RT, HT, SHAPE, threads, head_small(mv.H, mv.D, sets * mv.L + 1, HT));
+        allow_lds(k_head<HT, RT, SHAPE>, lds);
+        hipLaunchKernelGGL((k_head<HT, RT, SHAPE>), dim3(SHAPE == kPerSet ? 3 * gv.B : gv.B), dim3(threads), lds, s, gv, mv,
+                           ws.emb, ws.partial, fa.cur_node, max_chunks, o);
     });
 }
 
@@ -528,11 +575,15 @@ void launch_head_bw(const GraphView &gv, const ModelView &mv, const float *blob_
                     const HeadBwArgs &a, hipStream_t s)
 {
     if (gv.B == 0) return;
-    head_dispatch(mv.H, mv.G, [&](auto ht, auto rt) {
+    head_dispatch(mv.H, mv.G, gv.B, false, [&](auto ht, auto rt, auto shape) {
         constexpr int HT = decltype(ht)::value, RT = decltype(rt)::value;
-        const size_t lds = head_lds(mv.H, mv.G, RT, HT, false);
-        allow_lds(k_head_bw<HT, RT>, lds);
-        hipLaunchKernelGGL((k_head_bw<HT, RT>), dim3(gv.B), dim3(head_threads(HT, false)), lds, s, gv, mv, blob_t, cur_node, a);
+        constexpr HeadShape SHAPE = decltype(shape)::value;
+        const int threads = head_launch_threads(mv.H, gv.B, HT, SHAPE);
+        const size_t lds = head_lds(mv.H, mv.G, RT, HT, SHAPE, threads);
+        if constexpr (SHAPE != kPerSet) {
+            allow_lds(k_head_bw<HT, RT, SHAPE>, lds);
+            hipLaunchKernelGGL((k_head_bw<HT, RT, SHAPE>), dim3(gv.B), dim3(threads), lds, s, gv, mv, blob_t, cur_node, a);
+        }
     });
 }
 

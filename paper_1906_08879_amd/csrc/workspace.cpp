@@ -33,7 +33,7 @@ size_t carve_workspace(unsigned char *base, size_t n, size_t B, const ModelView 
     ws->featb = reinterpret_cast<float4 *>(take(sizeof(float4) * (n + 1)));
     ws->partial = reinterpret_cast<float *>(take(sizeof(float) * (B * ws->n_chunks * 3 * mv.G * H + 4)));
     ws->zbuf = reinterpret_cast<float *>(take(sizeof(float) * (B * mv.Z + 4)));
-    // (a split head has H = 128 and Z >= 640: three parts of a graph's first policy layer fit)
+    // (a split head has H >= 128 and Z >= 640: three parts of a graph's first policy layer fit)
     ws->hidp = reinterpret_cast<double *>(take(sizeof(double) * (static_cast<size_t>((mv.Z + 255) / 256) * B * H + 4)));
     if (with_reach) {
         // a block of fixed size, whose callers have no reverse pass: what only that reads is not kept,

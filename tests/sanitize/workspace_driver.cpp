@@ -29,7 +29,7 @@ std::vector<Extent> extents(const pl::Workspace &ws, size_t n, size_t B, const p
                           {"head_done", ws.head_done, 4 * B},
                           {"klist", ws.klist, 4 * n},
                           {"koff", ws.koff, 4 * B * (3 * pl::kMaxD + 1)}};
-    if (H == 128) e.push_back({"hidp", ws.hidp, 8 * B * 3 * H});
+    if (H >= 128) e.push_back({"hidp", ws.hidp, 8 * B * 3 * H});
     if (fixed) {
         e.push_back({"reach", ws.reach, 2 * n + 2});
     } else {

@@ -10,7 +10,7 @@ from oracle import gradient as og
 from tests.gpu_common import custom_workload, run_library
 
 SHAPES = [(2, 8, 1, 2, "fp32"), (16, 3, 1, 2, "fp32"), (5, 17, 1, 3, "fp32"), (4, 100, 1, 2, "fp32"), (3, 255, 0, 1, "fp32"),
-          (9, 24, 1, 4, "fp32"), (8, 48, 1, 2, "fp32"), (2, 256, 1, 2, "fp32"), (4, 64, 1, 2, "fp32"), (8, 128, 1, 2, "bf16")]
+          (9, 24, 1, 4, "fp32"), (8, 48, 1, 2, "fp32"), (2, 256, 1, 2, "fp32"), (2, 201, 1, 2, "fp32"), (4, 64, 1, 2, "fp32"), (8, 128, 1, 2, "bf16")]
 
 
 def _dense(x, W, b, relu, short_fp32):
@@ -44,7 +44,12 @@ def _head(w, emb, pooled, short_fp32=False):
         for l in range(w.n_layers):
             x = _dense(x, *layer(f"h_{name}.{l}"), True, short_fp32).astype(np.float32)
         z.append(x.reshape(w.B, -1))
-    hid = _dense(np.concatenate(z, axis=1), *layer("pol.0"), True, short_fp32)
+    W1, b1 = layer("pol.0")
+    # (a wide head over few graphs sums the three sets' inputs of this layer apart)
+    parts = [np.concatenate(z[:2], axis=1), z[2], z[3]] if w.H >= 128 and 3 * w.B <= 256 else [np.concatenate(z, axis=1)]
+    rows = np.cumsum([0] + [p.shape[1] for p in parts])
+    hid = b1.astype(np.float64) + sum(_dense(p, W1[rows[i]:rows[i + 1]], np.zeros_like(b1), False, short_fp32) for i, p in enumerate(parts))
+    hid = np.maximum(hid, 0.0)
     W2, b2 = (a.astype(np.float64) for a in layer("pol.1"))
     return hid @ W2 + b2, np.abs(hid) @ np.abs(W2) + np.abs(b2)
 
@@ -54,16 +59,19 @@ def _outside(got, ref, size):
     return float(np.mean(np.abs(got.astype(np.float64) - ref) > 2.0 ** -24 * 1.01 * np.abs(ref) + 1e-13 * size))
 
 
-def _workload(D, H, group, L, wd):
+def _workload(D, H, group, L, wd, B=24):
     rng = np.random.default_rng(1000 * H + D)
     # (output sizes of about e^2 summed over the nodes: logits are differences of larger terms)
-    return custom_workload(rng, [24, 9, 31, 17] * 6, D, H, L, 1, group, wd, w_scale=0.8 / np.sqrt(H))
+    return custom_workload(rng, ([24, 9, 31, 17] * (B // 4 + 1))[:B], D, H, L, 1, group, wd, w_scale=0.8 / np.sqrt(H))
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("D,H,group,L,wd", SHAPES)
-def test_sums_of_the_head(D, H, group, L, wd):
-    w = _workload(D, H, group, L, wd)
+@pytest.mark.parametrize("D,H,group,L,wd,B", [s + (24,) for s in SHAPES] +
+                         # either side of one graph per compute unit, where the launch shape changes, and of a third
+                         [(3, 32, 1, 2, "fp32", 256), (3, 32, 1, 2, "fp32", 257), (9, 64, 1, 2, "fp32", 257), (2, 17, 1, 2, "fp32", 300),
+                          (2, 201, 1, 2, "fp32", 85), (2, 201, 1, 2, "fp32", 86), (16, 48, 1, 2, "fp32", 257)])
+def test_sums_of_the_head(D, H, group, L, wd, B):
+    w = _workload(D, H, group, L, wd, B)
     got = run_library(w)
     ref, size = _head(w, got["emb"], got["pooled"])
     assert np.isfinite(ref).all() and _outside(got["logits"], ref, size) == 0.0, (D, H, np.abs(got["logits"] - ref).max())
