@@ -269,6 +269,17 @@ void free_workspace(Workspace &ws)
     ws = Workspace();
 }
 
+// The rows and bytes past the data that the kernels read as zero without ever writing them (carve_workspace).
+void clear_spare_messages(const Workspace &ws, size_t n, hipStream_t s)
+{
+    launch_fill_zero(ws.msg + 2 * n * ws.H, 2 * static_cast<size_t>(ws.H), s);
+}
+
+void clear_reach(const Workspace &ws, size_t n, hipStream_t s)
+{
+    launch_fill_zero(reinterpret_cast<float *>(ws.reach + (2 * n) / 4 * 4), 5, s);
+}
+
 void free_grad_workspace(GradWorkspace &gw)
 {
     float *all[] = {gw.fact, gw.gact, gw.agg, gw.dagg, gw.dfg, gw.keep, gw.snap_emb, gw.snap_msg, gw.lact, gw.dl, gw.demb, gw.dx, gw.phi,
@@ -282,16 +293,19 @@ void free_grad_workspace(GradWorkspace &gw)
     gw = GradWorkspace();
 }
 
-int ensure_reach(pl_graph_batch *g)
+// Buffers that a first call allocates.  What has to be zero in them is cleared on the caller's stream: work on the
+// null stream is not ordered with a stream that does not block, and waiting for it costs a small batch's first call
+// 10 us.
+int ensure_reach(pl_graph_batch *g, hipStream_t s)
 {
     if (g->ws.reach) return PL_OK;
     const size_t n = static_cast<size_t>(g->host.n_tot);
-    PL_HIP(hipMalloc(reinterpret_cast<void **>(&g->ws.reach), 2 * n + 16));
-    PL_HIP(hipMemset(g->ws.reach, 0, 2 * n + 16));
+    PL_HIP(hipMalloc(reinterpret_cast<void **>(&g->ws.reach), 2 * n + 32));
+    clear_reach(g->ws, n, s);
     return PL_OK;
 }
 
-int ensure_workspace(pl_graph_batch *g, const ModelView &mv)
+int ensure_workspace(pl_graph_batch *g, const ModelView &mv, hipStream_t s)
 {
     Workspace &ws = g->ws;
     if (ws.emb && workspace_fits(ws, mv)) return PL_OK;
@@ -300,7 +314,7 @@ int ensure_workspace(pl_graph_batch *g, const ModelView &mv)
     free_workspace(ws);
     ws.reach = keep;
     const size_t n = static_cast<size_t>(g->host.n_tot), B = static_cast<size_t>(g->host.B);
-    int rc = ensure_reach(g);
+    int rc = ensure_reach(g, s);
     if (rc) return rc;
     Workspace sized;
     const size_t bytes = carve_workspace(nullptr, n, B, mv, false, &sized);
@@ -308,14 +322,11 @@ int ensure_workspace(pl_graph_batch *g, const ModelView &mv)
     PL_HIP(hipMalloc(reinterpret_cast<void **>(&base), bytes));
     ws.base = base;
     carve_workspace(base, n, B, mv, false, &ws);
-    PL_HIP(hipMemset(ws.msg, 0, sizeof(float) * ((2 * n + 2) * mv.H + 4)));
-    PL_HIP(hipMemset(ws.head_done, 0, sizeof(uint32_t) * B));
-    // (the caller's stream may be one that does not wait for the null stream's work)
-    PL_HIP(hipStreamSynchronize(nullptr));
+    clear_spare_messages(ws, n, s);
     return PL_OK;
 }
 
-int ensure_grad_workspace(pl_graph_batch *g, const ModelView &mv)
+int ensure_grad_workspace(pl_graph_batch *g, const ModelView &mv, hipStream_t s)
 {
     GradWorkspace &gw = g->gw;
     if (gw.demb && gw.H == mv.H && gw.G == mv.G && gw.L == mv.L && gw.D == mv.D) return PL_OK;
@@ -331,7 +342,7 @@ int ensure_grad_workspace(pl_graph_batch *g, const ModelView &mv)
     // the matrix-core chain kernel reads row 2 n of dagg as an all-zero row and stores the rows
     // of unused chunk slots to row 2 n + 1, to row n of demb and to the spare floats of dfg
     PL_HIP(take(&gw.dagg, 2 * NH + 2 * H));
-    PL_HIP(hipMemset(gw.dagg, 0, sizeof(float) * (2 * NH + 2 * H)));
+    launch_fill_zero(gw.dagg + 2 * NH, 2 * H, s);
     gw.dfg_stride = 2 * L * NH + H;
     PL_HIP(take(&gw.dfg, 2 * gw.dfg_stride));
     PL_HIP(take(&gw.keep, 2 * gw.dfg_stride));
@@ -491,7 +502,7 @@ int forward_impl(pl_graph_batch *g, const float *node_feats, const int32_t *plac
     const ModelView &mv = w->view;
     if (!static_ws) {
         if ((rc = ensure_on_device(g))) return rc;
-        if ((rc = ensure_workspace(g, mv))) return rc;
+        if ((rc = ensure_workspace(g, mv, s))) return rc;
     }
     const Workspace &ws = static_ws ? *static_ws : g->ws;
     StageTimer off;
@@ -703,7 +714,7 @@ int pl_node_classes(pl_graph_batch *g, const int32_t *cur_node, uint8_t *out_cla
     if (!cur_node || !out_class) return fail(PL_ERR_NULL, "cur_node / out_class are NULL");
     int rc = ensure_on_device(g);
     if (rc) return rc;
-    if ((rc = ensure_reach(g))) return rc;
+    if ((rc = ensure_reach(g, static_cast<hipStream_t>(stream)))) return rc;
     hipStream_t s = static_cast<hipStream_t>(stream);
     const GraphExtent x = graph_extent(g->host);
     launch_reach_only(g->view, cur_node, g->ws.reach, x.n_max, x.e_max, g->host.max_depth, s);
@@ -918,9 +929,8 @@ int pl_embed_forward_static(pl_graph_batch *g, const float *node_feats, const in
     hipStream_t s = static_cast<hipStream_t>(stream);
     // the block keeps the last call's contents: the rows and bytes that the kernels read as zero
     // without ever writing them are cleared by a fill kernel (a memset node must not be captured)
-    launch_fill_zero(ws.msg + 2 * n * w->view.H, 2 * static_cast<size_t>(w->view.H), s);
-    launch_fill_zero(reinterpret_cast<float *>(ws.reach + (2 * n) / 4 * 4), 5, s);
-    launch_fill_zero(reinterpret_cast<float *>(ws.head_done), B, s);
+    clear_spare_messages(ws, n, s);
+    clear_reach(ws, n, s);
     return forward_impl(g, node_feats, placement, cur_node, w, out_logits, out_probs, nullptr, nullptr, nullptr,
                         stream, false, nullptr, 0, nullptr, nullptr, nullptr, nullptr, &ws);
 }
@@ -1047,8 +1057,8 @@ static int policy_gradient_impl(pl_graph_batch *g, const float *node_feats, cons
         return rc;
     if ((rc = ensure_on_device(g))) return rc;
     const ModelView &mv = w->view;
-    if ((rc = ensure_grad_workspace(g, mv))) return rc;
     hipStream_t s = static_cast<hipStream_t>(stream);
+    if ((rc = ensure_grad_workspace(g, mv, s))) return rc;
     // the chain kernel addresses the delta arrays with 32-bit element offsets
     const bool fits = (2.0 * mv.L * static_cast<double>(g->host.n_tot) + 1) * mv.H < 2.0e9 &&
                       (static_cast<double>(g->host.n_tot) + 2) * 2 * mv.H * sizeof(float) < 4.0e9;

@@ -113,7 +113,7 @@ struct Workspace {
     double *hid = nullptr;      // [B, H] hidden layer of the policy network
     float *logit = nullptr;     // [B, D] (room for kMaxD) logits, also of graphs that have no valid current node
     double *hidp = nullptr;     // [B, 3, H] the node sets' parts of the first policy layer (H >= 128)
-    uint32_t *head_done = nullptr;   // [B] workgroups of a graph that have written theirs; zero between calls
+    uint32_t *head_done = nullptr;   // [B] workgroups of a graph that have written theirs; cleared by the pooling kernels
     int32_t *klist = nullptr;   // [n_tot] node ids grouped by (set, device group), per graph (matrix-core pooling)
     int32_t *koff = nullptr;    // [B][3 kMaxD + 1] first position of every key within its graph
     int32_t n_chunks = 0;

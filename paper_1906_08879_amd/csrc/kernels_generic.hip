@@ -339,7 +339,7 @@ __global__ __launch_bounds__(kThreads) void k_pool_generic(GraphView gv, ModelVi
                                                            const int32_t *__restrict__ placement,
                                                            const int32_t *__restrict__ cur_node,
                                                            float *__restrict__ partial,
-                                                           int max_chunks)
+                                                           int max_chunks, uint32_t *__restrict__ head_done)
 {
     extern __shared__ float lds[];
     __shared__ int16_t s_list[3][kSub];
@@ -348,6 +348,7 @@ __global__ __launch_bounds__(kThreads) void k_pool_generic(GraphView gv, ModelVi
     __shared__ int s_dev[kTile];
     const int H = mv.H, G = mv.G, D = mv.D, L = mv.L;
     const int b = blockIdx.y, c = blockIdx.x, tid = threadIdx.x;
+    if (c == 0 && tid == 0) head_done[b] = 0;        // for this pass's head
     const int n0 = gv.node_off[b], n_b = gv.node_off[b + 1] - n0;
     int chunks = (n_b + kPoolChunk - 1) / kPoolChunk;
     if (chunks > max_chunks) chunks = max_chunks;
@@ -506,7 +507,7 @@ void launch_pool_generic(const GraphView &gv, const ModelView &mv, const Workspa
 #define CALL(R)                                                                              \
     allow_lds(k_pool_generic<R>, lds);                                                       \
     hipLaunchKernelGGL(k_pool_generic<R>, dim3(ws.n_chunks, gv.B), dim3(kThreads), lds, s, gv, mv, \
-                       ws.emb, ws.reach, fa.placement, fa.cur_node, ws.partial, ws.n_chunks)
+                       ws.emb, ws.reach, fa.placement, fa.cur_node, ws.partial, ws.n_chunks, ws.head_done)
     PL_DISPATCH_RPT(pick_rpt(mv.H), CALL)
 #undef CALL
 }

@@ -232,7 +232,7 @@ struct HeadOut {
     float *out_logits, *out_probs, *out_pooled;
     float *hin, *hact;    // kept for the reverse pass (or null): inputs [3, B G, H] and layer outputs [3, L, B G, H] of h
     double *hidp;         // (SPLIT) [B, 3, H] the sets' parts of the first policy layer
-    uint32_t *done;       // (SPLIT) [B] workgroups of a graph that have written theirs; zero between calls
+    uint32_t *done;       // (SPLIT) [B] workgroups of a graph that have written theirs; cleared by the pooling kernels
 };
 
 template <int HT, int RT, HeadShape SHAPE>
@@ -369,7 +369,6 @@ __global__ __launch_bounds__(head_threads(HT, SHAPE)) void k_head(GraphView gv, 
         if (tid == 0) order = __hip_atomic_fetch_add(o.done + b, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         __syncthreads();
         if (order != 2u) return;
-        if (tid == 0) __hip_atomic_store(o.done + b, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         for (int c = tid; c < H; c += T) {
             double s = 0.0;
             for (int set = 0; set < 3; ++set)

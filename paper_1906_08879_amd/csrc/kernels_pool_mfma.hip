@@ -64,11 +64,12 @@ __global__ __launch_bounds__(kThreads) void k_pool_sort(GraphView gv, const uint
                                                         const int32_t *__restrict__ placement,
                                                         const int32_t *__restrict__ cur_node, int D, int G,
                                                         int single, int32_t *__restrict__ klist,
-                                                        int32_t *__restrict__ koff)
+                                                        int32_t *__restrict__ koff, uint32_t *__restrict__ head_done)
 {
     __shared__ uint16_t hist[kMaxKeys][kThreads];    // nodes of key k in thread t's block, then their first position
     __shared__ int total[kMaxKeys + 1];
     const int b = blockIdx.x, tid = threadIdx.x;
+    if (tid == 0) head_done[b] = 0;                  // for this pass's head
     const int n0 = gv.node_off[b], n_b = gv.node_off[b + 1] - n0;
     const int cl = cur_node[b];
     const int cur = (cl >= 0 && cl < n_b) ? n0 + cl : -1;
@@ -1214,7 +1215,7 @@ int launch_pool_mfma(const GraphView &gv, const ModelView &mv, const Workspace &
 {
     if (gv.B == 0) return kPoolSlices;
     hipLaunchKernelGGL(k_pool_sort, dim3(gv.B), dim3(kThreads), 0, s, gv, ws.reach, fa.placement, fa.cur_node, mv.D,
-                       mv.G, mv.single_set, ws.klist, ws.koff);
+                       mv.G, mv.single_set, ws.klist, ws.koff, ws.head_done);
     // the shapes that the streaming kernel covers take it (eight slices per set, one per wave)
     if (afrag && WS == 1 && pool_stream_supported(mv.H, mv.L, PL_WEIGHTS_BF16)) {
         PoolParams Q{gv, afrag, bias, ws.emb, ws.klist, ws.koff, ws.partial, kStreamWaves, mv.G, keep};
