@@ -83,6 +83,8 @@ def _compare(w, what, seed=0, path=0):
     (8, 128, 2, 1, 1, "bf16"), (2, 256, 2, 1, 1, "fp32"), (4, 64, 4, 1, 1, "bf16"), (12, 6, 2, 1, 1, "fp32"),
     (4, 64, 1, 1, 1, "bf16"), (4, 32, 2, 1, 1, "bf16"), (4, 64, 2, 1, 1, "fp32"), (3, 128, 1, 1, 0, "bf16"),
     (5, 128, 2, 1, 1, "fp32"), (4, 32, 1, 1, 1, "fp32"),
+    # more device groups than rows in a pass of the head, and widths that take its networks one after the other
+    (16, 64, 2, 1, 1, "fp32"), (12, 128, 2, 1, 1, "bf16"), (9, 32, 2, 1, 1, "fp32"), (9, 256, 2, 1, 1, "fp32"),
 ])
 def test_shapes_and_variants(D, H, L, k, group, wd):
     """Ragged batches (single nodes, edgeless graphs, wide levels) over the supported range of D,
@@ -90,6 +92,15 @@ def test_shapes_and_variants(D, H, L, k, group, wd):
     rng = np.random.default_rng(100 * D + H)
     w = custom_workload(rng, [1, 2, 40, 1, 17, 70, 3], D, H, L, k, group, wd)
     _compare(w, f"D={D} H={H} L={L} k={k} g={group} {wd}")
+
+
+@pytest.mark.parametrize("B,D,H,group,wd", [(260, 9, 32, 1, "fp32"), (515, 3, 64, 1, "bf16"), (260, 2, 8, 1, "fp32"),
+                                            (300, 5, 17, 1, "fp32"), (260, 4, 128, 0, "bf16"), (258, 1, 256, 1, "fp32")])
+def test_more_graphs_than_compute_units(B, D, H, group, wd):
+    """The head's launch shape changes with the number of graphs; every parameter compared."""
+    rng = np.random.default_rng(B + H)
+    w = custom_workload(rng, [1 + i % 4 for i in range(B)], D, H, 2, 1, group, wd)
+    _compare(w, f"B={B} D={D} H={H} g={group} {wd}")
 
 
 @pytest.mark.parametrize("name,B", [("random32", 4), ("layered200", 4), ("inception", 2), ("nmt", 2), ("nasnet", 1)])

@@ -31,20 +31,12 @@ def _fan(width):
     return width + 2 + (width + 1) // 2, np.array(src), np.array(dst)
 
 
-def _check(w, per_child, reward):
+def _check(w, per_child):
     rt, ev, peak, _ = _device_both(w, w.placement, 1.0, per_child)
     for b in range(w.B):
-        r, e, p = _oracle_both(w, b, w.placement, 1.0, per_child) if reward else (*_run(w, b, per_child), None)
+        r, e, p = _oracle_both(w, b, w.placement, 1.0, per_child)
         assert (rt[b], ev[b]) == (r, e), (b, rt[b], r, ev[b], e)
-        if reward:
-            np.testing.assert_allclose(peak[b], p, rtol=1e-6, atol=0, err_msg=f"graph {b}")
-
-
-def _run(w, b, per_child):
-    from oracle import simulator as sim
-    n0, n1, e0, e1 = (int(x) for x in (w.node_off[b], w.node_off[b + 1], w.edge_off[b], w.edge_off[b + 1]))
-    return sim.simulate(n1 - n0, w.edge_src[e0:e1], w.edge_dst[e0:e1], w.node_feats[n0:n1, 0], w.node_feats[n0:n1, 1],
-                        w.placement[n0:n1], w.D, np.float32(1.0), per_child=bool(per_child))
+        np.testing.assert_allclose(peak[b], p, rtol=1e-6, atol=0, err_msg=f"graph {b}")
 
 
 @pytest.mark.parametrize("per_child", [0, 1])
@@ -52,11 +44,12 @@ def _run(w, b, per_child):
 def test_child_and_transfer_lists(D, per_child):
     rng = np.random.default_rng(41 + D)
     w = _workload([_fan(k) for k in (1, 2, 3, 63, 64, 65, 130)], D, rng, ties=D % 2 == 1)
-    _check(w, per_child, True)
+    _check(w, per_child)
 
 
+@pytest.mark.parametrize("per_child", [0, 1])
 @pytest.mark.parametrize("n,e", [(9090, 2), (9000, 130), (8180, 1), (4000, 7000)])
-def test_graphs_at_the_size_limit(n, e):
+def test_graphs_at_the_size_limit(n, e, per_child):
     assert 18 * n + 13 * e <= 160 * 1024 - 32
     rng = np.random.default_rng(n)
     # (edges between different ids, lower to higher, none twice)
@@ -67,4 +60,4 @@ def test_graphs_at_the_size_limit(n, e):
             pairs.add((a, b))
     pairs = np.array(sorted(pairs))
     w = _workload([(n, pairs[:, 0], pairs[:, 1])], 8, rng, ties=False)
-    _check(w, 0, False)
+    _check(w, per_child)

@@ -1,9 +1,10 @@
 """The weight gradients of a pass as tables of contractions: more layers than a table holds (four layers a
-network, 43 contractions), slab sums that need several launches (35 thousand nodes at H = 128), two sweeps
+network, 43 contractions), slab sums that need several launches (8 and 35 thousand nodes at H = 128), two sweeps
 (whose contractions must run before the earlier sweep overwrites what they read) and shapes that take the
-plain kernel for every layer.  Against the generic fp32 kernels, per layer block in the 2-norm: 5e-4 (four
-times what a single ReLU input within rounding of zero moves a gradient; a missing slab moves its block by
-about 1 / sqrt(slabs), 4e-2 or more); equal calls give equal bits."""
+plain kernel for every layer.  Per layer block in the 2-norm, 5e-4 (four times what a single ReLU input within
+rounding of zero moves a gradient; a missing slab moves its block by about 1 / sqrt(slabs), 4e-2 or more): against
+the float64 autograd oracle, which shares nothing with the tables, and against the generic fp32 kernels, which take
+every contraction with another kernel but share the tables and the slab sums; equal calls give equal bits."""
 import numpy as np
 import pytest
 
@@ -11,6 +12,15 @@ from oracle import gradient as og
 from tests.gpu_common import custom_workload, run_gradient
 
 pytestmark = pytest.mark.gpu
+
+
+def _assert_blocks_close(got, ref, D, H, L):
+    gmax = np.abs(ref).max()
+    slices, _ = og.layer_slices(D, H, L, 1)
+    for name, parts in slices.items():
+        for sl in parts:
+            err = np.linalg.norm(got[sl] - ref[sl])
+            assert err <= 5e-4 * np.linalg.norm(ref[sl]) + 1e-7 * gmax * np.sqrt(ref[sl].size), (name, err, np.linalg.norm(ref[sl]))
 
 
 @pytest.mark.parametrize("sizes,D,H,L,k,wd", [
@@ -25,9 +35,18 @@ def test_tables_of_contractions(sizes, D, H, L, k, wd):
     got = run_gradient(w, actions, coeff)["grad"]
     assert np.array_equal(got, run_gradient(w, actions, coeff)["grad"])
     ref = run_gradient(w, actions, coeff, path=1)["grad"].astype(np.float64)
-    gmax = np.abs(ref).max()
-    slices, _ = og.layer_slices(D, H, L, 1)
-    for name, parts in slices.items():
-        for sl in parts:
-            err = np.linalg.norm(got[sl] - ref[sl])
-            assert err <= 5e-4 * np.linalg.norm(ref[sl]) + 1e-7 * gmax * np.sqrt(ref[sl].size), (name, err, np.linalg.norm(ref[sl]))
+    _assert_blocks_close(got, ref, D, H, L)
+
+
+# (every fourth graph of the large batch has a weight: one in each slab of 64 rows)
+@pytest.mark.parametrize("sizes,D,H,L,k,wd,every", [
+    ([16] * 500, 4, 128, 2, 1, "bf16", 4), ([70, 1, 33], 3, 32, 4, 1, "fp32", 1), ([64, 65, 9] * 8, 8, 64, 4, 2, "bf16", 1),
+    ([2, 40, 17], 2, 32, 1, 2, "fp32", 1), ([31, 12], 5, 24, 4, 1, "fp32", 1),
+])
+def test_tables_against_the_oracle(sizes, D, H, L, k, wd, every):
+    rng = np.random.default_rng(H + L)
+    w = custom_workload(rng, sizes, D, H, L, k, 1, wd, p_edge=0.1)
+    actions = rng.integers(0, D, w.B).astype(np.int32)
+    coeff = np.where(np.arange(w.B) % every == 0, rng.normal(0, 1, w.B), 0.0).astype(np.float32)
+    ref, _ = og.gradient_workload(w, actions, coeff.astype(np.float64), only=[int(b) for b in range(0, w.B, every)])
+    _assert_blocks_close(run_gradient(w, actions, coeff)["grad"], ref, D, H, L)
