@@ -45,12 +45,13 @@ POOL_SOURCES = ("kernels_pool_mfma.hip",)
 
 def csrc_digest(sources=SWEEP_SOURCES) -> str:
     """sha256 over the sources of a kernel (by default the dominant one: the sweep kernel, its
-    gather plan and the shared declarations): ties a stored counter measurement to the kernel it
-    was taken on."""
+    gather plan and the shared declarations) and what they are compiled with: ties a stored counter
+    measurement to the kernel it was taken on."""
     import hashlib
-    h = hashlib.sha256()
+    from paper_1906_08879_amd.build import HIPCC_FLAGS, SOURCE_FLAGS
+    h = hashlib.sha256(" ".join(HIPCC_FLAGS).encode())
     for name in sources:
-        h.update(name.encode())
+        h.update(" ".join([name, *SOURCE_FLAGS.get(name, [])]).encode())
         h.update(open(os.path.join(ROOT, "paper_1906_08879_amd", "csrc", name), "rb").read())
     return h.hexdigest()
 

@@ -20,7 +20,8 @@ HIPCC_FLAGS = [
 
 # Flags of single sources.  Both kernels branch on the scalar unit inside a long dependent chain, and
 # structured control flow (which the back end otherwise gives uniform branches too) costs them copies
-# of their register state at every join.  Simulator: 3.38 -> 2.70 ms for 256 NASNet-like graphs; sweep:
+# of their register state at every join.  (An option of the back end, not of the driver: checked with ROCm 7.2.0,
+# clang 22, whose code with and without it gives the same bits on the timed cases.)  Simulator: 3.38 -> 2.70 ms for 256 NASNet-like graphs; sweep:
 # forward pass 0.715 -> 0.690 ms (64 NMT-like graphs), 2.16 -> 2.12 ms (256 NASNet-like ones).
 _NO_STRUCTURE = ["-mllvm", "-structurizecfg-skip-uniform-regions"]
 SOURCE_FLAGS = {"kernels_simulator.hip": _NO_STRUCTURE, "kernels_mfma.hip": _NO_STRUCTURE}

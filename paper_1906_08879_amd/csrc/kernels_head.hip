@@ -362,8 +362,11 @@ __global__ __launch_bounds__(head_threads(HT, SHAPE)) void k_head(GraphView gv, 
             __hip_atomic_store(o.hidp + (static_cast<size_t>(b) * 3 + set_first) * H + c, s, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
     if constexpr (SPLIT) {
-        // the workgroup that finishes a graph last adds the sets' parts up and goes on: every thread's
-        // stores have arrived before the one atomic that announces them
+        // The workgroup that finishes a graph last adds the sets' parts up and goes on.  Every thread's stores have
+        // arrived where all dies see them before the one atomic that announces them: they are agent-scope stores, each
+        // thread waits for its own, and the barrier is behind all of them; the loads are agent-scope loads and come
+        // after the barrier that hands the atomic's result round.  An acquire-release atomic would order them too, but
+        // writes the die's whole L2 back first (85 graphs: 22 -> 25.7 us).
         __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0)
         __syncthreads();
         if (tid == 0) order = __hip_atomic_fetch_add(o.done + b, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -420,6 +423,7 @@ __global__ __launch_bounds__(head_threads(HT, SHAPE)) void k_head_bw(GraphView g
     __shared__ float dlog[kMaxD];
     const int H = HT ? HT : mv.H, G = mv.G, L = mv.L, D = mv.D, Z = mv.Z, T = HT ? head_threads(HT, SHAPE) : blockDim.x;
     const int b = blockIdx.x, tid = threadIdx.x;
+    // (weights ahead also with 1024 threads: no float64 sums are held here, 110 registers)
     HeadLayers<HT, RT, SHAPE, HT != 0 && SHAPE != kPacked> hl(mv.H, G);
     auto request = [&](int l) { hl.request(blob_t, mv.h[0].layer[l].w, mv.h[1].layer[l].w - mv.h[0].layer[l].w, 0); };
     request(L - 1);
@@ -509,9 +513,10 @@ __global__ __launch_bounds__(head_threads(HT, SHAPE)) void k_head_bw(GraphView g
 }
 
 // Calls go(HT, RT, SHAPE) with the instantiation for width H, G rows per set and B graphs.
-//   * H >= 128, forward: a graph's 2 MB of weights take one CU 18 us longer than three (H = 128, 8 device groups: 34
-//     against 18 us for one graph); with more workgroups than CUs the hand-over between them costs more than it
-//     gives (256 graphs: 43 us together, 55 us split).
+//   * H >= 128, forward: one CU reads a graph's weights longer than three; with more workgroups than CUs the hand-over
+//     between them costs more than it gives.  Together / split at H = 128, 8 device groups: 1 graph 35 / 22 us, 85
+//     graphs 32 / 22, 100 graphs 32 / 34, 256 graphs 35 / 53; one group: 15 / 13 at 85, 15 / 19 at 100; at H = 256, 4
+//     groups: 78 / 41 at 85, 79 / 68 at 100 (the pass 1.807 / 1.792 ms), 98 / 115 at 256.
 //   * H = 32 and 64: 512 threads with weights ahead have a CU to themselves, so a second graph per CU waits for the
 //     first.  Above one graph per CU: small workgroups without (forward head at H = 64, 8 devices: 256 graphs 19 us,
 //     small 22, 1024 graphs 60 and 40; at H = 32, 4 devices: 12 and 14, 30 and 16).  The reverse head at H = 64

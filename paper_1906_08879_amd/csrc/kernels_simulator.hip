@@ -179,7 +179,8 @@ __global__ __launch_bounds__(kSimThreads) void k_simulate(GraphView gv, int D, i
         put(tail, q, v);
     };
     // lane q's pending event, for operation o: `duration` after `now` (both as bits).  (No more than n + e
-    // of at most 21700 events are ever created, so the creation number fits beside the id.)
+    // events are ever created, and 18 n + 13 e bytes of at most 160 KB leave n + e below 12700: the creation number
+    // fits beside the id.)
     auto schedule = [&](uint32_t q, uint32_t now, uint32_t duration, uint32_t o) __attribute__((always_inline)) {
         const float t = __fadd_rn(__uint_as_float(now), __uint_as_float(duration));
         ev_t = lane == q ? __float_as_uint(t) : ev_t;
