@@ -87,9 +87,10 @@ struct pl_graph_batch {
     pl::Workspace ws;
     pl::GradWorkspace gw;
     // pl_simulate_reward: one block with peaks [B, sim_D], op_start, op_end [n_tot], arrival, arrival_last
-    // [n_tot, sim_D] and run times [B]
+    // [n_tot, sim_D], run times [B] and workgroup counters [B] (zero between calls)
     float *sim_start = nullptr, *sim_end = nullptr, *sim_arrival = nullptr, *sim_arrival_last = nullptr, *sim_rt = nullptr;
     double *sim_peaks = nullptr;
+    uint32_t *sim_done = nullptr;
     int sim_D = 0;
     pl::StageTimer timer;
 };
@@ -1173,18 +1174,21 @@ int pl_simulate_reward_ex(pl_graph_batch *g, int32_t D, const float *node_feats,
         (void)hipFree(g->sim_peaks);
         g->sim_peaks = nullptr;
         const size_t B = static_cast<size_t>(g->host.B), BD = B * D, nD = n * D;
-        PL_HIP(hipMalloc(reinterpret_cast<void **>(&g->sim_peaks), sizeof(double) * BD + sizeof(float) * (2 * n + 2 * nD + B)));
+        PL_HIP(hipMalloc(reinterpret_cast<void **>(&g->sim_peaks), sizeof(double) * BD + sizeof(float) * (2 * n + 2 * nD + 2 * B)));
         g->sim_start = reinterpret_cast<float *>(g->sim_peaks + BD);
         g->sim_end = g->sim_start + n;
         g->sim_arrival = g->sim_end + n;
         g->sim_arrival_last = g->sim_arrival + nD;
         g->sim_rt = g->sim_arrival_last + nD;
+        g->sim_done = reinterpret_cast<uint32_t *>(g->sim_rt + B);
         g->sim_D = D;
+        launch_fill_zero(reinterpret_cast<float *>(g->sim_done), B, static_cast<hipStream_t>(stream));
     }
     rc = launch_simulate_reward(g->view, D, static_cast<int>(n_max), static_cast<int>(e_max), node_feats, placement,
                                 inv_bandwidth, per_child_transfers != 0, mem_limit, mem_penalty, g->sim_start,
-                                g->sim_end, g->sim_arrival, g->sim_arrival_last, g->sim_peaks,
-                                out_runtime ? out_runtime : g->sim_rt, out_peak_mem, out_reward, out_events, static_cast<hipStream_t>(stream));
+                                g->sim_end, g->sim_arrival, g->sim_arrival_last, g->sim_peaks, g->sim_done,
+                                out_runtime ? out_runtime : g->sim_rt, out_peak_mem, out_reward, out_events,
+                                static_cast<hipStream_t>(stream));
     if (rc) return rc;
     PL_HIP(hipGetLastError());
     return PL_OK;

@@ -187,7 +187,8 @@ int launch_simulate(const GraphView &gv, int D, int n_max, int e_max, const floa
 int launch_simulate_reward(const GraphView &gv, int D, int n_max, int e_max, const float *node_feats,
                            const int32_t *placement, float inv_bw, bool per_child, float mem_limit, float penalty,
                            float *op_start, float *op_end, float *arrival, float *arrival_last, double *peaks,
-                           float *runtime, float *out_peak, float *out_reward, int32_t *out_events, hipStream_t s);
+                           uint32_t *done, float *runtime, float *out_peak, float *out_reward, int32_t *out_events,
+                           hipStream_t s);
 
 // ---- matrix-core pooling (kernels_pool_mfma.hip); writes ws.partial as [B, kPoolSlices, 3G, H]
 constexpr int kPoolSlices = 4;

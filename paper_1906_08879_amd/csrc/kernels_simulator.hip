@@ -450,7 +450,7 @@ int simulate(const GraphView &gv, int D, int n_max, int e_max, const float *node
 // each of their allocation times (the live sum only grows there) the live sizes are summed in float64 in node
 // order.  The pairs of copies bound it (six instructions each), so a thread takes two times per pass over the
 // copies.  TOGETHER: a workgroup has all D devices of a graph, a wave each, and takes the maximum over them itself;
-// otherwise it has one device, and k_reward takes the maximum.
+// otherwise it has one device, and the workgroup of a graph that finishes last takes the maximum.
 // (64 NMT-like graphs, 4 devices: 86 us; 412 us with one workgroup per graph that took its devices in
 // turn, after a kernel that wrote every interval to memory and one that cleared the arrivals.)
 constexpr int kPeakTimes = 2;          // allocation times per thread and pass
@@ -458,14 +458,9 @@ constexpr int kPeakTimes = 2;          // allocation times per thread and pass
 constexpr int peak_capacity(int n_max) { return (n_max + 3) / 4 * 4; }
 constexpr size_t peak_lds(int n_max) { return 4 * sizeof(float) * static_cast<size_t>(peak_capacity(n_max)); }   // per device
 
-__device__ __forceinline__ float penalised(float r, double m, float mem_limit, float penalty)
-{
-    const double M = static_cast<double>(mem_limit);
-    return m <= M ? r : static_cast<float>(static_cast<double>(r) + static_cast<double>(penalty) * (m - M));
-}
-
 // arrival: first crossing of an output to a device (the copy there exists from then on); arrival_last:
 // last crossing (the source is kept until then); the same array unless an output may cross twice.
+// peaks [B, D] and done [B] (zero between launches): exchange between a graph's workgroups.
 template <int T, bool TOGETHER>
 __global__ __launch_bounds__(TOGETHER ? T * kMaxD : T) void k_peak_memory(GraphView gv, int D, int n_max,
                                                      const float *__restrict__ node_feats,
@@ -475,7 +470,7 @@ __global__ __launch_bounds__(TOGETHER ? T * kMaxD : T) void k_peak_memory(GraphV
                                                      const float *__restrict__ arrival,
                                                      const float *__restrict__ arrival_last,
                                                      const float *__restrict__ runtime, float mem_limit,
-                                                     float penalty, double *__restrict__ peaks,
+                                                     float penalty, double *peaks, uint32_t *done,
                                                      float *__restrict__ out_peak,
                                                      float *__restrict__ out_reward)
 {
@@ -489,7 +484,7 @@ __global__ __launch_bounds__(TOGETHER ? T * kMaxD : T) void k_peak_memory(GraphV
     // (scalars: a device's threads are whole waves)
     const int seat = TOGETHER ? __builtin_amdgcn_readfirstlane(threadIdx.x / T) : 0, seats = TOGETHER ? D : 1;
     const int b = TOGETHER ? blockIdx.x : blockIdx.x / D, d = TOGETHER ? seat : blockIdx.x - b * D;
-    const int tid = threadIdx.x - seat * T, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x - seat * T, lane = tid & 63, wave = tid >> 6, threads = TOGETHER ? blockDim.x : T;
     float *ca = reinterpret_cast<float *>(lds_raw) + seat * 3 * cap, *cf = ca + cap, *cs = cf + cap;
     // by seat: bits of the latest use on that device + 1, 0: none
     uint32_t *until = reinterpret_cast<uint32_t *>(lds_raw) + seats * 3 * cap;
@@ -498,21 +493,27 @@ __global__ __launch_bounds__(TOGETHER ? T * kMaxD : T) void k_peak_memory(GraphV
     if (!(r == r)) {                       // invalid placement: the simulator wrote NaN
         if (tid == 0) {
             if (out_peak) out_peak[static_cast<size_t>(b) * D + d] = r;
-            if (TOGETHER && d == 0) out_reward[b] = r;
+            if (d == 0) out_reward[b] = r;
         }
         return;
     }
-    for (int v = threadIdx.x; v < seats * cap; v += blockDim.x) until[v] = 0;
+    for (int v = threadIdx.x; v < (TOGETHER ? seats * cap : n); v += threads) until[v] = 0;
     __syncthreads();
     // eight lanes share a node's children
-    for (int v = threadIdx.x >> 3; v < n; v += blockDim.x / 8) {
+    for (int v = threadIdx.x >> 3; v < n; v += threads / 8) {
         const int pv = placement[n0 + v], end = gv.nbr_ptr[1][n0 + v + 1];
         for (int p = gv.nbr_ptr[1][n0 + v] + (lane & 7); p < end; p += 8) {
             const int c = gv.nbr_idx[1][p], pc = placement[c];
-            if (TOGETHER || pc == d) atomicMax(&until[(TOGETHER ? pc * cap : 0) + v], __float_as_uint(op_end[c]) + 1u);
-            if (pc != pv && (TOGETHER || pv == d))
-                atomicMax(&until[(TOGETHER ? pv * cap : 0) + v],
-                          __float_as_uint(arrival_last[static_cast<size_t>(n0 + v) * D + pc]) + 1u);
+            auto use = [&](int dev, float t) { atomicMax(&until[(TOGETHER ? dev * cap : 0) + v], __float_as_uint(t) + 1u); };
+            auto sent = [&]() { return arrival_last[static_cast<size_t>(n0 + v) * D + pc]; };
+            if constexpr (TOGETHER) {
+                use(pc, op_end[c]);
+                if (pc != pv) use(pv, sent());
+            } else if (pc == d) {
+                use(d, op_end[c]);
+            } else if (pv == d) {
+                use(d, sent());
+            }
         }
     }
     __syncthreads();
@@ -593,24 +594,26 @@ __global__ __launch_bounds__(TOGETHER ? T * kMaxD : T) void k_peak_memory(GraphV
     if constexpr (TOGETHER) {
         if (seat != 0) return;
         for (int o = 1; o < D; ++o) mx = red[o] > mx ? red[o] : mx;
-        out_reward[b] = penalised(r, mx, mem_limit, penalty);
     } else {
-        peaks[static_cast<size_t>(b) * D + d] = mx;
+        // The peak has arrived where all dies see it (an agent-scope store, waited for) before the atomic that
+        // announces it, and the loads come after the atomic's result.  An acquire-release atomic would order them
+        // too, but writes the die's whole L2 back first, 20 ns per workgroup and one after the other; a kernel of
+        // its own for the maximum takes up to 5 us.
+        double *mine = peaks + static_cast<size_t>(b) * D;
+        __hip_atomic_store(mine + d, mx, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+        __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0)
+        const uint32_t before = __hip_atomic_fetch_add(done + b, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+        if (before != static_cast<uint32_t>(D) - 1u) return;
+        for (int o = 0; o < D; ++o) {
+            const double x = __hip_atomic_load(mine + o, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            mx = x > mx ? x : mx;
+        }
+        __hip_atomic_store(done + b, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
-}
-
-// R(p) from the peaks of all devices.  A launch of its own: the workgroups of k_peak_memory could hand their peaks
-// over to the one that finishes last, but each then has to write its die's L2 back first (20 ns each, one after the
-// other: 1.25 ms for 4096 graphs of 16 devices).
-__global__ __launch_bounds__(256) void k_reward(int B, int D, const double *__restrict__ peaks, const float *__restrict__ runtime,
-                                                float mem_limit, float penalty, float *__restrict__ out_reward)
-{
-    const int b = blockIdx.x * 256 + threadIdx.x;
-    if (b >= B) return;
-    const float r = runtime[b];
-    double mx = 0.0;
-    for (int o = 0; o < D && r == r; ++o) mx = fmax(mx, peaks[static_cast<size_t>(b) * D + o]);
-    out_reward[b] = r == r ? penalised(r, mx, mem_limit, penalty) : r;
+    const double M = static_cast<double>(mem_limit);
+    out_reward[b] = mx <= M ? r : static_cast<float>(static_cast<double>(r) + static_cast<double>(penalty) * (mx - M));
 }
 
 }  // namespace
@@ -633,11 +636,12 @@ int launch_simulate(const GraphView &gv, int D, int n_max, int e_max, const floa
 }
 
 // Simulation with the timeline, then peaks and R(p).  scratch: op_start, op_end [n_tot]; arrival,
-// arrival_last (used with per_child only) [n_tot, D]; peaks [B, D].
+// arrival_last (used with per_child only) [n_tot, D]; peaks [B, D]; done [B].
 int launch_simulate_reward(const GraphView &gv, int D, int n_max, int e_max, const float *node_feats,
                            const int32_t *placement, float inv_bw, bool per_child, float mem_limit, float penalty,
                            float *op_start, float *op_end, float *arrival, float *arrival_last, double *peaks,
-                           float *runtime, float *out_peak, float *out_reward, int32_t *out_events, hipStream_t s)
+                           uint32_t *done, float *runtime, float *out_peak, float *out_reward, int32_t *out_events,
+                           hipStream_t s)
 {
     if (gv.B == 0) return PL_OK;
     const int rc = (per_child ? simulate<true, true> : simulate<true, false>)(
@@ -648,18 +652,17 @@ int launch_simulate_reward(const GraphView &gv, int D, int n_max, int e_max, con
             PL_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
                                        static_cast<int>(lds)));
         hipLaunchKernelGGL(kernel, dim3(blocks), dim3(threads), lds, s, gv, D, n_max, node_feats, placement, op_start, op_end,
-                           arrival, per_child ? arrival_last : arrival, runtime, mem_limit, penalty, peaks, out_peak, out_reward);
+                           arrival, per_child ? arrival_last : arrival, runtime, mem_limit, penalty, peaks, done, out_peak,
+                           out_reward);
         return static_cast<int>(PL_OK);
     };
-    // A wave per device in one workgroup: no launch for the maximum and the children read once per graph.  On large
+    // A wave per device in one workgroup: no hand-over and the children read once per graph.  On large
     // graphs 512 threads share a device's pairs; in between that pays while the chip is not full of workgroups.
     // (peaks and R(p), together / apart: 4096 graphs of 32 nodes, 16 devices: 48 and 269 us; 1024 of 400, 8 devices: 115
     // and 184; 64 of 250, 4 devices: 33 and 27; 512 of 1000, 2 devices: 307 and 186.)
     if (n_max <= 128 || (n_max <= 512 && gv.B * D >= 1024))
         return run(k_peak_memory<64, true>, gv.B, 64 * D, D * peak_lds(n_max));
-    if (const int failed = run(k_peak_memory<512, false>, gv.B * D, 512, peak_lds(n_max))) return failed;
-    hipLaunchKernelGGL(k_reward, dim3((gv.B + 255) / 256), dim3(256), 0, s, gv.B, D, peaks, runtime, mem_limit, penalty, out_reward);
-    return PL_OK;
+    return run(k_peak_memory<512, false>, gv.B * D, 512, peak_lds(n_max));
 }
 
 }  // namespace pl

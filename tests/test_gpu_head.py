@@ -49,7 +49,7 @@ def _block_bytes(n, B, D, H, by_device):
 
 
 @pytest.mark.parametrize("D,H,by_device,wd", [(2, 8, 1, "fp32"), (5, 32, 0, "fp32"), (4, 64, 1, "bf16"), (3, 128, 0, "bf16"),
-                                              (8, 128, 1, "bf16")])
+                                              (8, 128, 1, "bf16"), (3, 201, 1, "fp32")])
 def test_fixed_block_takes_the_same_batches(D, H, by_device, wd):
     """The largest batch of one-node graphs that the fixed block takes: accepted, with the logits of the call
     that allocates; one graph more: refused.  And, for the split head, 85 graphs."""
