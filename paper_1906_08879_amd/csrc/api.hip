@@ -512,11 +512,12 @@ int forward_impl(pl_graph_batch *g, const float *node_feats, const int32_t *plac
     const GraphView &gv = g->view;
     // the matrix-core sweep addresses its buffers with 32-bit offsets
     const bool fits32 = (static_cast<double>(g->host.n_tot) + 2) * 2 * mv.H * sizeof(float) < 4.0e9;
-    const bool mfma = w->d_wfrag && w->path == 0 && w->cfg.k_sweeps > 0 && fits32;
+    const bool fast = w->path == 0 && w->cfg.k_sweeps > 0 && fits32;
+    const bool lanes = fast && sweep_lanes_preferred(mv.H, mv.L, gv.B, w->cfg.weight_dtype), mfma = fast && !lanes && w->d_wfrag;
     {
-        // the matrix-core sweep computes x_v itself from the raw features (first sweep)
+        // these sweeps compute x_v themselves from the raw features (first sweep)
         StageScope scope(timer, PL_STAGE_PROJECT, s);
-        if (!mfma) launch_project(gv, mv, ws, fa, true, false, s);
+        if (!lanes && !mfma) launch_project(gv, mv, ws, fa, true, false, s);
     }
     {
         StageScope scope(timer, PL_STAGE_SWEEP, s);
@@ -527,7 +528,9 @@ int forward_impl(pl_graph_batch *g, const float *node_feats, const int32_t *plac
             launch_reach_only(gv, cur_node, ws.reach, x.n_max, x.e_max, g->host.max_depth, s);
         }
         for (int k = 0; k < w->cfg.k_sweeps; ++k) {
-            if (mfma)
+            if (lanes)
+                launch_sweep_lanes(gv, mv, ws, fa, k == 0, k + 1 < w->cfg.k_sweeps, keep, keep_stride, gates, s);
+            else if (mfma)
                 launch_sweep_mfma(gv, mv, ws, fa, reinterpret_cast<const uint4 *>(w->d_wfrag),
                                   w->d_sweep_bias, w->sweep_ws, k == 0, k + 1 < w->cfg.k_sweeps, keep, keep_stride,
                                   gates, s);
@@ -1063,9 +1066,10 @@ static int policy_gradient_impl(pl_graph_batch *g, const float *node_feats, cons
     // the chain kernel addresses the delta arrays with 32-bit element offsets
     const bool fits = (2.0 * mv.L * static_cast<double>(g->host.n_tot) + 1) * mv.H < 2.0e9 &&
                       (static_cast<double>(g->host.n_tot) + 2) * 2 * mv.H * sizeof(float) < 4.0e9;
-    const bool chain_cores = w->d_wfrag_bw && w->path == 0 && w->cfg.k_sweeps >= 1 && fits;
+    const bool fast = w->path == 0 && w->cfg.k_sweeps >= 1 && fits;
+    const bool lanes = fast && sweep_lanes_preferred(mv.H, mv.L, g->view.B, w->cfg.weight_dtype), chain_cores = fast && !lanes && w->d_wfrag_bw;
     // on that path a single forward sweep keeps a_v and the layer outputs, so nothing is computed twice
-    float *keep = (chain_cores && w->cfg.k_sweeps == 1) ? g->gw.keep : nullptr;
+    float *keep = ((lanes || chain_cores) && w->cfg.k_sweeps == 1) ? g->gw.keep : nullptr;
     // several sweeps: the states and messages after every sweep but the last are copied aside
     if (w->cfg.k_sweeps > 1 && g->gw.snap_sweeps < w->cfg.k_sweeps - 1) {
         (void)hipFree(g->gw.snap_emb);
@@ -1090,7 +1094,7 @@ static int policy_gradient_impl(pl_graph_batch *g, const float *node_feats, cons
     const BackwardArgs ba{actions, coeff, entropy_coeff, grad, out_logp, out_entropy, g->gw.snap_emb, g->gw.snap_msg,
                           w->path == 0 ? reinterpret_cast<const uint4 *>(w->d_pool_bwfrag) : nullptr};
     launch_backward(g->view, mv, w->d_blob_t, g->ws, g->gw, fa, ba, w->cfg.k_sweeps, g->ws.n_chunks, w->path,
-                    chain_cores ? reinterpret_cast<const uint4 *>(w->d_wfrag_bw) : nullptr, w->d_sweep_bias,
+                    lanes, chain_cores ? reinterpret_cast<const uint4 *>(w->d_wfrag_bw) : nullptr, w->d_sweep_bias,
                     w->sweep_ws, keep, pool_kept, &marks, s);
     PL_HIP(hipGetLastError());
     return PL_OK;

@@ -267,8 +267,16 @@ struct BackwardArgs {
 
 void launch_backward(const GraphView &gv, const ModelView &mv, const float *blob_t, const Workspace &ws,
                      const GradWorkspace &gw, const ForwardArgs &fa, const BackwardArgs &ba, int k_sweeps,
-                     int pool_chunks, int generic, const uint4 *wfrag_bw, const float *sweep_bias, int sweep_ws,
+                     int pool_chunks, int generic, bool lanes, const uint4 *wfrag_bw, const float *sweep_bias, int sweep_ws,
                      const float *keep, bool pool_kept, const StageMarks *marks, hipStream_t s);
+
+// ---- sweep of narrow networks (kernels_lanes.hip)
+bool sweep_lanes_preferred(int H, int L, int B, int weight_dtype);
+void launch_sweep_lanes(const GraphView &gv, const ModelView &mv, const Workspace &ws, const ForwardArgs &fa,
+                        bool first_sweep, bool more_sweeps, float *keep, size_t keep_stride, uint8_t *gates,
+                        hipStream_t s);
+void launch_sweep_lanes_bw(const GraphView &gv, const ModelView &mv, const float *blob_t, const int32_t *cur_node,
+                           float *demb, float *dagg, uint8_t *mask4, float *delta, size_t delta_stride, hipStream_t s);
 
 // ---- matrix-core sweep (kernels_mfma.hip)
 bool sweep_mfma_supported(int H, int L, int weight_dtype);

@@ -1570,7 +1570,7 @@ void launch_dense(const DenseCall &c, int H, hipStream_t s)
 
 void launch_backward(const GraphView &gv, const ModelView &mv, const float *blob_t, const Workspace &ws,
                      const GradWorkspace &gw, const ForwardArgs &fa, const BackwardArgs &ba, int k_sweeps,
-                     int pool_chunks, int generic, const uint4 *wfrag_bw, const float *sweep_bias, int sweep_ws,
+                     int pool_chunks, int generic, bool lanes, const uint4 *wfrag_bw, const float *sweep_bias, int sweep_ws,
                      const float *keep, bool pool_kept, const StageMarks *marks, hipStream_t s)
 {
     if (gv.B == 0) return;
@@ -1594,6 +1594,8 @@ void launch_backward(const GraphView &gv, const ModelView &mv, const float *blob
     mark(PL_STAGE_BW_POOL, true);
     // matrix-core dense layers: every output width of the embedding networks is H
     const bool dense = generic == 0 && (H == 32 || H == 64 || H == 128);
+    // a chain that reads gate bytes and, with one sweep, activations that the forward pass kept
+    const bool chain = lanes || wfrag_bw;
     // 2. pooling
     if (dense) {
         const int n_blocks = (n + kThreads - 1) / kThreads;
@@ -1680,7 +1682,7 @@ void launch_backward(const GraphView &gv, const ModelView &mv, const float *blob
         // the last layer of f is the message itself, which the forward pass left in msg_j (the
         // generic chain kernel reads it from fact, so there it is computed again)
         for (int dir = 0; dir < 2; ++dir)
-            for (int l = 0; l + 1 < L || (l < L && !wfrag_bw); ++l) {
+            for (int l = 0; l + 1 < L || (l < L && !chain); ++l) {
                 const LayerRef &ly = mv.f[dir].layer[l];
                 launch_dense({l == 0 ? emb_j + dir * H : gw.fact + (static_cast<size_t>(dir) * L + l - 1) * NH,
                               l == 0 ? 2 * H : H, nullptr, nullptr, n, H, blob_t + ly.w, H, mv.blob + ly.b, 1,
@@ -1700,7 +1702,7 @@ void launch_backward(const GraphView &gv, const ModelView &mv, const float *blob
     {
         const size_t lds = sizeof(float) * 2 * kTile * H;
         const unsigned tiles = static_cast<unsigned>((n + kTile - 1) / kTile);
-        if (!dense) {
+        if (!dense && !keep) {
 #define CALL(R)                                                                                              \
     allow_lds_bw(k_bw_f_acts<R>, lds);                                                                       \
     allow_lds_bw(k_bw_g_acts<R>, lds);                                                                       \
@@ -1709,7 +1711,7 @@ void launch_backward(const GraphView &gv, const ModelView &mv, const float *blob
             PL_DISPATCH_RPT(rpt, CALL)
 #undef CALL
         }
-        if (wfrag_bw && !keep) {
+        if (chain && !keep) {
             // the forward sweep that keeps activations also writes the gate bytes; otherwise they
             // are taken from the recomputed layer outputs here
             GateSrc src[2];
@@ -1724,7 +1726,9 @@ void launch_backward(const GraphView &gv, const ModelView &mv, const float *blob
         }
         mark(PL_STAGE_BW_ACTS, false);
         mark(PL_STAGE_BW_CHAIN, true);
-        if (wfrag_bw) {
+        if (lanes) {
+            launch_sweep_lanes_bw(gv, mv, blob_t, fa.cur_node, gw.demb, gw.dagg, gw.mask4, gw.dfg, gw.dfg_stride, s);
+        } else if (wfrag_bw) {
             launch_sweep_mfma_bw(gv, mv, wfrag_bw, sweep_bias, sweep_ws, fa.cur_node, gw.demb, gw.dagg, gw.mask4,
                                  gw.dfg, gw.dfg_stride, s);
         } else {
