@@ -316,42 +316,66 @@ __global__ __launch_bounds__(64 * lane_waves(H), 2) void k_sweep_lanes(LaneParam
         for (int k = 0; k < K; ++k) add(s, signs, x[k]);
     };
     // A row with more sources than its record holds: a list of table slots and node ids.  The lanes of the row load an
-    // entry each and hand them round; the other source of an entry is a row of zeros.  Of the first H entries the
-    // lanes hold the ids a chunk before the sum, and the messages of the first kPre are on their way.
+    // entry each (an entry past the end names the rows of zeros) and form its rows' byte offsets, once for H entries;
+    // then an entry takes a shuffle, a load and an addition, and only lists that have near sources read the table.  Of
+    // the first H entries the lanes hold the ids a chunk before the sum, and the messages of the first kPre are on
+    // their way.
     auto entry = [&](const u32x4 &rec, int i) __attribute__((always_inline)) {
         const bool in = (rec[0] & kRecListed) && i < static_cast<int>(rec[0] & 0xFFFFFFu);
         return in ? elem(plan.ovf, 4u * (rec[1] + static_cast<uint32_t>(i))) : -1 - kZeroSlot;
     };
-    auto from_lane = [&](int x, int k) __attribute__((always_inline)) {   // lane k of this row's
-        if constexpr (H == 64) return __builtin_amdgcn_readlane(x, k);
-        return __shfl(x, (lane & ~(H - 1)) + k);
+    auto from_lane = [&](uint32_t x, int k) __attribute__((always_inline)) {   // lane k of this row's
+        if constexpr (H == 64) return static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(x), k));
+        return static_cast<uint32_t>(__shfl(static_cast<int>(x), (lane & ~(H - 1)) + k));
     };
-    auto near_of = [&](int u) __attribute__((always_inline)) { return msgtab[(u < 0 ? -1 - u : kZeroSlot) * H + col]; };
-    auto far_of = [&](int u) __attribute__((always_inline)) { return elem(msg, at4(u >= 0 ? static_cast<uint32_t>(u) : spare_row)); };
+    auto far_row = [&](int u) __attribute__((always_inline)) { return 4u * H * (u >= 0 ? static_cast<uint32_t>(u) : spare_row); };
+    auto request = [&](uint32_t rows, int first_lane, auto &y) __attribute__((always_inline)) {
+        constexpr int K = sizeof(y) / sizeof(y[0]);
+#pragma unroll
+        for (int k = 0; k < K; ++k) y[k] = elem(msg, from_lane(rows, first_lane + k) + 4u * static_cast<uint32_t>(col));
+    };
     auto sum_list = [&](const u32x4 &rec, int ids, const float (&pre)[kPre], float &s, uint32_t &signs) __attribute__((always_inline)) {
+        constexpr int PB = H < 16 ? H : 16;
         const int cnt = static_cast<int>(rec[0] & 0xFFFFFFu);
-        float x[kPre], y[kPre];
+        auto take = [&](const auto &y) __attribute__((always_inline)) {
+            constexpr int K = sizeof(y) / sizeof(y[0]);
 #pragma unroll
-        for (int k = 0; k < kPre; ++k) x[k] = near_of(from_lane(ids, k));
+            for (int k = 0; k < K; ++k) add(s, signs, y[k]);
+        };
+        auto take_near = [&]() __attribute__((always_inline)) {       // among the H entries: the few places that are near in some row
+            unsigned long long near = __ballot(ids < 0 && ids != -1 - kZeroSlot);
+            const uint32_t rows = H * static_cast<uint32_t>(ids < 0 ? -1 - ids : kZeroSlot);
 #pragma unroll
-        for (int k = 0; k < kPre; ++k) {
-            add(s, signs, x[k]);
-            add(s, signs, pre[k]);
+            for (int w = 32; w >= H; w /= 2) near |= near >> w;
+            if constexpr (H < 64) near &= (1ull << H) - 1ull;
+#pragma unroll 1
+            for (; near != 0ull; near &= near - 1ull) {
+                const float x[1] = {msgtab[from_lane(rows, __builtin_ctzll(near)) + col]};
+                take(x);
+            }
+        };
+        static_assert(kPre == 8, "the first pass asks for the second half of its entries only");
+        uint32_t rows = far_row(ids);
+        if (PB > kPre && cnt > kPre) {
+            float y[kPre];
+            request(rows, PB > kPre ? kPre : 0, y);
+            take(pre);
+            take_near();
+            take(y);
+        } else {
+            take(pre);
+            take_near();
         }
 #pragma unroll 1
-        for (int p = kPre; p < cnt; p += kPre) {
-            if (p % H == 0) ids = entry(rec, p + col);
-#pragma unroll
-            for (int k = 0; k < kPre; ++k) {
-                const int u = from_lane(ids, p % H + k);
-                x[k] = near_of(u);
-                y[k] = far_of(u);
+        for (int p = PB; p < cnt; p += PB) {
+            if (p % H == 0) {
+                ids = entry(rec, p + col);
+                rows = far_row(ids);
             }
-#pragma unroll
-            for (int k = 0; k < kPre; ++k) {
-                add(s, signs, x[k]);
-                add(s, signs, y[k]);
-            }
+            float y[PB];
+            request(rows, p % H, y);
+            if (p % H == 0) take_near();
+            take(y);
         }
         // (nothing of this path is in flight where it joins the others: they would wait for it)
         __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0)
@@ -421,10 +445,7 @@ __global__ __launch_bounds__(64 * lane_waves(H), 2) void k_sweep_lanes(LaneParam
         auto delta_at = [&](int slot) __attribute__((always_inline)) {   // (unused rows: the spare row)
             return live ? static_cast<uint32_t>(slot * gv.n_tot * H) + at(static_cast<uint32_t>(n0) + v) : static_cast<uint32_t>(2 * L * gv.n_tot * H + col);
         };
-        if ((info1 >> kRecGeneralBit) & 1u) {
-#pragma unroll
-            for (int k = 0; k < kPre; ++k) pre[k] = far_of(from_lane(idsA, k));
-        }
+        if ((info1 >> kRecGeneralBit) & 1u) request(far_row(idsA), 0, pre);
         farB = load_far(rB);
         rT = load_rec(c + 4);
         if ((first(rB[3]) >> kRecGeneralBit) & 1u) idsB = entry(rB, col);
