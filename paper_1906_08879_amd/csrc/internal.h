@@ -278,6 +278,15 @@ void launch_sweep_lanes(const GraphView &gv, const ModelView &mv, const Workspac
 void launch_sweep_lanes_bw(const GraphView &gv, const ModelView &mv, const float *blob_t, const int32_t *cur_node,
                            float *demb, float *dagg, uint8_t *mask4, float *delta, size_t delta_stride, hipStream_t s);
 
+// ---- matrix-core sweep of 32 or 64 columns (kernels_tiles.hip); called by the launchers of kernels_mfma.hip
+void launch_sweep_tiles(const GraphView &gv, const ModelView &mv, const Workspace &ws,
+                       const ForwardArgs &fa, const uint4 *wfrag, const float *bias, int WS,
+                       bool first_sweep, bool more_sweeps, float *keep, size_t keep_stride, uint8_t *gates,
+                       hipStream_t s);
+void launch_sweep_tiles_bw(const GraphView &gv, const ModelView &mv, const uint4 *wfrag, const float *bias,
+                          int WS, const int32_t *cur_node, float *demb, float *dagg, uint8_t *mask4,
+                          float *delta, size_t delta_stride, hipStream_t s);
+
 // ---- matrix-core sweep (kernels_mfma.hip)
 bool sweep_mfma_supported(int H, int L, int weight_dtype);
 void pack_sweep_weights(const ModelView &mv, const float *blob, int WS, std::vector<uint16_t> *frag,

@@ -1,8 +1,8 @@
 // Matrix-core sweep kernel for gfx950: the message passing of Section 2.2 step 2,
 //   a_v = sum_{u in xi(v)} m_u,   s_v <- s_v + g(a_v),   m_v = f(s_v),
-// for H in {32, 64, 128} and one or two layers per network.
+// for H = 128 and one or two layers per network (H = 32 and 64: kernels_tiles.hip and kernels_lanes.hip).
 //
-// One workgroup (one wave per 16 or 32 output columns, at most four waves) per (graph, direction)
+// One workgroup (four waves, one per 32 output columns) per (graph, direction)
 // walks the graph's levels in chunks of at most 8 nodes.  Design points, all specific to
 // CDNA4:
 //   * v_mfma_f32_16x16x32_bf16 with the node activations as the A operand and the WEIGHTS as
@@ -137,8 +137,7 @@ __global__ __launch_bounds__(64 * sweep_waves(H), 2) void k_sweep_mfma(SweepPara
                                                // four consecutive rows fall on disjoint banks)
     constexpr int kZeroSlot = kMsgSlots;
     static_assert(NTL % NW == 0, "column tiles must divide over the waves");
-    static_assert(TPW == 1 || TPW == 2, "a lane owns one or two output columns");
-    constexpr bool kReadFirst = TPW == 1;
+    static_assert(TPW == 2, "a lane owns two neighbouring output columns");
 #ifndef PL_SINK_STORES
 #define PL_SINK_STORES 0
 #endif
@@ -177,41 +176,27 @@ __global__ __launch_bounds__(64 * sweep_waves(H), 2) void k_sweep_mfma(SweepPara
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int col = lane & 15, kg = lane >> 4;    // MFMA result: column col, node kg of a tile
     const int wc0 = wave * WC;
-    // Output column of this lane in the wave's column tile t.  Where a wave owns two tiles they
-    // interleave (tile 0 the even, tile 1 the odd columns of the wave's 32), so that a lane's two
-    // columns are neighbours: one 8-byte access per lane wherever a row is read or written.
-    auto mcol = [&](int t) __attribute__((always_inline)) { return wc0 + (TPW == 2 ? 2 * col + t : col); };
+    // Output column of this lane in the wave's column tile t.  A wave's two tiles interleave (tile 0 the even, tile 1
+    // the odd columns of the wave's 32), so that a lane's two columns are neighbours: one 8-byte access per lane
+    // wherever a row is read or written.
+    auto mcol = [&](int t) __attribute__((always_inline)) { return wc0 + 2 * col + t; };
     // this lane's columns of a row of floats that starts at element `at`
     auto load_cols = [&](const float *base, uint32_t at, float (&v)[TPW]) __attribute__((always_inline)) {
-        if constexpr (TPW == 2) {
-            const float2 x = *reinterpret_cast<const float2 *>(base + static_cast<uint32_t>(at + mcol(0)));
-            v[0] = x.x;
-            v[1] = x.y;
-        } else {
-            v[0] = base[static_cast<uint32_t>(at + mcol(0))];
-        }
+        const float2 x = *reinterpret_cast<const float2 *>(base + static_cast<uint32_t>(at + mcol(0)));
+        v[0] = x.x;
+        v[1] = x.y;
     };
     // the same for rows of gate bytes
     auto load_gates = [&](const uint8_t *base, uint32_t at, int (&v)[TPW]) __attribute__((always_inline)) {
-        if constexpr (TPW == 2) {
-            const int x = *reinterpret_cast<const uint16_t *>(base + static_cast<uint32_t>(at + mcol(0)));
-            v[0] = x & 0xFF;
-            v[1] = x >> 8;
-        } else {
-            v[0] = base[static_cast<uint32_t>(at + mcol(0))];
-        }
+        const int x = *reinterpret_cast<const uint16_t *>(base + static_cast<uint32_t>(at + mcol(0)));
+        v[0] = x & 0xFF;
+        v[1] = x >> 8;
     };
     auto store_gates = [&](uint8_t *base, uint32_t at, const int (&v)[TPW]) __attribute__((always_inline)) {
-        if constexpr (TPW == 2)
-            *reinterpret_cast<uint16_t *>(base + static_cast<uint32_t>(at + mcol(0))) = static_cast<uint16_t>(v[0] | (v[1] << 8));
-        else
-            base[static_cast<uint32_t>(at + mcol(0))] = static_cast<uint8_t>(v[0]);
+        *reinterpret_cast<uint16_t *>(base + static_cast<uint32_t>(at + mcol(0))) = static_cast<uint16_t>(v[0] | (v[1] << 8));
     };
     auto store_cols = [&](float *base, uint32_t at, const float (&v)[TPW]) __attribute__((always_inline)) {
-        if constexpr (TPW == 2)
-            *reinterpret_cast<float2 *>(base + static_cast<uint32_t>(at + mcol(0))) = float2{v[0], v[1]};
-        else
-            base[static_cast<uint32_t>(at + mcol(0))] = v[0];
+        *reinterpret_cast<float2 *>(base + static_cast<uint32_t>(at + mcol(0))) = float2{v[0], v[1]};
     };
 
     const GraphView &gv = P.gv;
@@ -321,17 +306,10 @@ __global__ __launch_bounds__(64 * sweep_waves(H), 2) void k_sweep_mfma(SweepPara
             rr[t] = y[t] - trunc_bf16(y[t]);
             ll[t] = rr[t] - trunc_bf16(rr[t]);
         }
-        if constexpr (TPW == 2) {
-            uint32_t *dst = reinterpret_cast<uint32_t *>(act_at(buf, 4 * r, 0)) + 16 * wave + col;
-            dst[0] = pack_hi16(y[0], y[1]);
-            dst[LDA / 2] = pack_hi16(rr[0], rr[1]);
-            dst[LDA] = pack_hi16(ll[0], ll[1]);
-        } else {
-            unsigned short *dst = reinterpret_cast<unsigned short *>(act_at(buf, 4 * r, wc0 + col));
-            dst[0] = static_cast<unsigned short>(__float_as_uint(y[0]) >> 16);
-            dst[LDA] = static_cast<unsigned short>(__float_as_uint(rr[0]) >> 16);
-            dst[2 * LDA] = static_cast<unsigned short>(__float_as_uint(ll[0]) >> 16);
-        }
+        uint32_t *dst = reinterpret_cast<uint32_t *>(act_at(buf, 4 * r, 0)) + 16 * wave + col;
+        dst[0] = pack_hi16(y[0], y[1]);
+        dst[LDA / 2] = pack_hi16(rr[0], rr[1]);
+        dst[LDA] = pack_hi16(ll[0], ll[1]);
     };
 
     // ---- gather of a chunk: a_v = sum of neighbour messages, for rows kg and kg + 4 and this
@@ -410,62 +388,28 @@ __global__ __launch_bounds__(64 * sweep_waves(H), 2) void k_sweep_mfma(SweepPara
                 // An entry is a table slot or a node id; the other source of the pair is the
                 // table's zero row or the spare (all-zero, never written) row of msg, so both are
                 // always read and added, in list order.
-                if constexpr (TPW == 1) {
-                    // The list is walked in passes of PB entries, three passes per step.  The
-                    // sixteen lanes of the row's group first load the step's entries (one load
-                    // each per pass, all in flight together) and hand them round with lane
-                    // shuffles; then a pass issues all its loads before the first use.
-                    constexpr int PB = 16;
-                    for (int p0 = d0; p0 < d1; p0 += 3 * PB) {
-                        int idv[3];
+                // (there are no registers to have more of a list under way: four entries at a time)
+                for (int p = d0; p < d1; p += 4) {
+                    int u[4];
 #pragma unroll
-                        for (int q = 0; q < 3; ++q) {
-                            const int at = p0 + q * PB + (col % PB);
-                            idv[q] = (at < d1) ? plan.ovf[at] : -1 - kZeroSlot;
-                        }
+                    for (int k = 0; k < 4; ++k) u[k] = p + k < d1 ? plan.ovf[p + k] : -1 - kZeroSlot;
+                    float xl[4][TPW], xg[4][TPW];
 #pragma unroll
-                        for (int q = 0; q < 3; ++q) {
-                            if (p0 + q * PB >= d1) break;
-                            float xl[PB], xg[PB];
+                    for (int k = 0; k < 4; ++k) {
+                        const float *row = msgtab + (u[k] < 0 ? -1 - u[k] : kZeroSlot) * LDM;
+                        const int v = u[k] >= 0 ? n0 + u[k] : spare_row;
 #pragma unroll
-                            for (int k = 0; k < PB; ++k) {
-                                const int u = __shfl(idv[q], (lane & 48) + k);
-                                const float *row = msgtab + (u < 0 ? -1 - u : kZeroSlot) * LDM;
-                                const int v = u >= 0 ? n0 + u : spare_row;
-                                xl[k] = row[wc0 + col];
-                                xg[k] = msg[static_cast<uint32_t>(v * H + wc0 + col)];
-                            }
-#pragma unroll
-                            for (int k = 0; k < PB; ++k) {
-                                s[0] += BW ? xl[k] + xg[k] : fabsf(xl[k]) + fabsf(xg[k]);
-                                if (!BW) signs |= __float_as_uint(xl[k]) | __float_as_uint(xg[k]);
-                            }
+                        for (int t = 0; t < TPW; ++t) {
+                            xl[k][t] = row[mcol(t)];
+                            xg[k][t] = msg[static_cast<uint32_t>(v * H + mcol(t))];
                         }
                     }
-                } else {
-                    // two column tiles per wave leave no registers for that: four entries at a time
-                    for (int p = d0; p < d1; p += 4) {
-                        int u[4];
 #pragma unroll
-                        for (int k = 0; k < 4; ++k) u[k] = p + k < d1 ? plan.ovf[p + k] : -1 - kZeroSlot;
-                        float xl[4][TPW], xg[4][TPW];
+                    for (int k = 0; k < 4; ++k) {
 #pragma unroll
-                        for (int k = 0; k < 4; ++k) {
-                            const float *row = msgtab + (u[k] < 0 ? -1 - u[k] : kZeroSlot) * LDM;
-                            const int v = u[k] >= 0 ? n0 + u[k] : spare_row;
-#pragma unroll
-                            for (int t = 0; t < TPW; ++t) {
-                                xl[k][t] = row[mcol(t)];
-                                xg[k][t] = msg[static_cast<uint32_t>(v * H + mcol(t))];
-                            }
-                        }
-#pragma unroll
-                        for (int k = 0; k < 4; ++k) {
-#pragma unroll
-                            for (int t = 0; t < TPW; ++t)
-                                s[t] += BW ? xl[k][t] + xg[k][t] : fabsf(xl[k][t]) + fabsf(xg[k][t]);
-                            if (!BW) signs |= __float_as_uint(xl[k][0]) | __float_as_uint(xg[k][0]);
-                        }
+                        for (int t = 0; t < TPW; ++t)
+                            s[t] += BW ? xl[k][t] + xg[k][t] : fabsf(xl[k][t]) + fabsf(xg[k][t]);
+                        if (!BW) signs |= __float_as_uint(xl[k][0]) | __float_as_uint(xg[k][0]);
                     }
                 }
             }
@@ -592,8 +536,6 @@ __global__ __launch_bounds__(64 * sweep_waves(H), 2) void k_sweep_mfma(SweepPara
 #pragma unroll
         for (int n = 0; n < NL; ++n) {
             // ---- rows of A from LDS (activation parts), weights from registers
-            // One row tile: the A fragments are read first (a1), the loads and stores of the
-            // pipeline ("mid block") are issued while they travel, then the matrix instructions.
             bf16x8 a1[KS];
             float bias_n[TPW];
 #pragma unroll
@@ -743,9 +685,8 @@ __global__ __launch_bounds__(64 * sweep_waves(H), 2) void k_sweep_mfma(SweepPara
                 if constexpr (kLdsFirst) hbm_stores();
             };
 
-            // The loads and stores of the pipeline (the "mid block" below) are issued while the A
-            // fragments travel from LDS where a wave has the registers to hold the fragments
-            // meanwhile (one column tile per wave); otherwise behind the matrix instructions.
+            // The loads and stores of the pipeline: behind the matrix instructions (there are no registers to hold
+            // the A fragments meanwhile).
             auto mid_block = [&]() __attribute__((always_inline)) {
                 if (n == 0) {
                     // First layer: the far messages of chunk c + 2
@@ -821,24 +762,13 @@ __global__ __launch_bounds__(64 * sweep_waves(H), 2) void k_sweep_mfma(SweepPara
                 }
 
             };
-            if constexpr (kReadFirst) {
-                if (!two) read_one_tile();
-                __builtin_amdgcn_sched_barrier(0);
-                mid_block();
-                __builtin_amdgcn_sched_barrier(0);
-                if (two)
-                    mfma_two_tiles();
-                else
-                    mfma_one_tile();
+            if (two) {
+                mfma_two_tiles();
             } else {
-                if (two) {
-                    mfma_two_tiles();
-                } else {
-                    read_one_tile();
-                    mfma_one_tile();
-                }
-                mid_block();
+                read_one_tile();
+                mfma_one_tile();
             }
+            mid_block();
 
             epilogue(0, std::false_type{});
             if constexpr (kind == 0 && kSinkStores)
@@ -974,6 +904,10 @@ void launch_sweep_mfma(const GraphView &gv, const ModelView &mv, const Workspace
                        hipStream_t s)
 {
     if (gv.B == 0) return;
+    if (mv.H != 128) {     // (32 or 64 columns: kernels_tiles.hip)
+        launch_sweep_tiles(gv, mv, ws, fa, wfrag, bias, WS, first_sweep, more_sweeps, keep, keep_stride, gates, s);
+        return;
+    }
     // keep, gates: where a single sweep also stores a_v, the layer outputs and the ReLU gates for the
     // reverse pass (TR)
     const bool tr = keep && gates && first_sweep && !more_sweeps;
@@ -1000,8 +934,6 @@ void launch_sweep_mfma(const GraphView &gv, const ModelView &mv, const Workspace
         return;                                                                  \
     }
     PL_CASE(128, 1, 2) PL_CASE(128, 1, 1)
-    PL_CASE(64, 1, 2) PL_CASE(64, 1, 1) PL_CASE(64, 3, 2) PL_CASE(64, 3, 1)
-    PL_CASE(32, 1, 2) PL_CASE(32, 1, 1) PL_CASE(32, 3, 2) PL_CASE(32, 3, 1)
 #undef PL_CASE
 }
 
@@ -1014,6 +946,10 @@ void launch_sweep_mfma_bw(const GraphView &gv, const ModelView &mv, const uint4 
                           float *delta, size_t delta_stride, hipStream_t s)
 {
     if (gv.B == 0) return;
+    if (mv.H != 128) {
+        launch_sweep_tiles_bw(gv, mv, wfrag, bias, WS, cur_node, demb, dagg, mask4, delta, delta_stride, s);
+        return;
+    }
     SweepParams P{gv, wfrag, bias, demb, nullptr, dagg, nullptr, cur_node, nullptr, nullptr, mv.D,
                   mask4, delta, delta_stride};
     const dim3 grid(2 * gv.B);
@@ -1024,8 +960,6 @@ void launch_sweep_mfma_bw(const GraphView &gv, const ModelView &mv, const uint4 
         return;                                                                              \
     }
     PL_CASE(128, 1, 2) PL_CASE(128, 1, 1)
-    PL_CASE(64, 1, 2) PL_CASE(64, 1, 1) PL_CASE(64, 3, 2) PL_CASE(64, 3, 1)
-    PL_CASE(32, 1, 2) PL_CASE(32, 1, 1) PL_CASE(32, 3, 2) PL_CASE(32, 3, 1)
 #undef PL_CASE
 }
 

@@ -1,5 +1,5 @@
-"""The sweep kernels of narrow networks (a layer in a wave's lanes): every width and depth they take, chunks of one
-to eight rows, rows with one source more or less than a record or a pass of a list holds, near and far; and the sizes
+"""The sweep kernels of narrow networks (a layer in a wave's lanes, or on matrix cores where it is wider, deeper or in
+bf16): every width and depth they take, chunks of one to eight rows, rows with one source more or less than a record or a pass of a list holds, near and far; and the sizes
 of a batch at which another kernel takes over.  Embeddings, gradients and node sets against the oracles."""
 import numpy as np
 import pytest
@@ -42,7 +42,7 @@ def _batch(seed, D, H, L, k, wd, shapes):
     return w
 
 
-WIDTHS = [(8, 1), (8, 2), (16, 1), (16, 2), (32, 1), (32, 2), (64, 1)]
+WIDTHS = [(8, 1), (8, 2), (16, 1), (16, 2), (32, 1), (32, 2), (64, 1), (64, 2)]
 # sources of the two last nodes: lists of 2 .. 130 entries, around the 8 that are requested ahead and the H that a
 # row's lanes hold; chain levels of 1 .. 8 rows and more than one chunk
 SHAPES = [(2, 1), (1, 5), (1, 6), (7, 1), (8, 1), (6, 2), (9, 3), (15, 4), (16, 5), (30, 8), (33, 7), (63, 1), (64, 9), (130, 2)]
