@@ -21,13 +21,16 @@
 //     read is off the chain, and no branch or copy makes anything wait for it.
 //   * A record holds the ids of up to two children themselves (longer lists their place in cidx), so
 //     the handler starts with the read of the children's states.
-//   * A bus queues operations, not transfers: the transfers of an operation leave back to back, and
-//     their destinations are a list of two entries in the operation's record (longer lists in xl).
+//   * A bus queues operations, not transfers: the transfers of an operation leave back to back.  Which devices an output
+//     goes to follows from the placement: the lists are made by all threads while the graph is staged, not by the
+//     handler of the operation's end, and two entries of them travel with the operation in 16 bits.
+//   * An item that leaves its queue becomes the pending event of the same lane, whose registers hold its record: lane
+//     selects, no way through scalar registers.
 //   * A child that becomes runnable on an idle device starts from the registers that its record was
 //     read into.
-// About 100 instructions per event.  256 NASNet-like graphs (3124 nodes, 8 devices, about 7300 events
-// each): 2.67 ms; 4.56 ms with lane-masked queues, a transfer record per transfer and every read on the
-// chain; 5.11 ms when only the reads were taken off the chain (more instructions).
+// About 80 instructions per event.  256 NASNet-like graphs (3124 nodes, 8 devices, about 7300 events
+// each): 2.30 ms; 2.65 ms with the destinations found by the handler and items moved through scalar registers; 4.56 ms with
+// lane-masked queues, a transfer record per transfer and every read on the chain.
 //
 // Timestamps are float32 with one rounding per operation (no fused multiply-add), and events
 // are ordered by (timestamp, creation number): the order is the same as that of a scalar
@@ -53,10 +56,13 @@ constexpr uint32_t kDevBits = 5, kNoDev = (1u << kDevBits) - 1, kInput = 1u << k
 // child, with kFirst set where it is the first to its device.
 constexpr uint32_t kFirst = 0x8000u;
 
-// LDS: rec [n + 1] {cost, or transfers | first entry << 16 once the output waits for the bus; duration of
-// a transfer; children: id | id << 14, or kList | place in cidx | number << 14; link | second entry << 16},
-// node [n + 1] states, cidx [e] children (ascending per node), xl [e] transfer lists of more than two
-// entries, from the place of the operation's first child.  States take 16 bits where 32 do not fit.
+// LDS: rec [n + 1] {cost; duration of a transfer; children: id | id << 14, or kList | place in cidx | number << 14;
+// link | crossings << 16}, node [n + 1] states, cidx [e] children (ascending per node), xl [e] transfer lists of more
+// than two entries, from the place of the operation's first child.  Crossings (one transfer per destination): number
+// of destinations | first << 5 | second << 10; which they are follows from the placement alone, so they are found
+// while the graph is staged, all operations at once.  (With one transfer per child the handler finds them, and an output
+// that waits for the bus has transfers | first entry << 16 in place of its cost, its second entry in the crossings' place.)
+//  States take 16 bits where 32 do not fit.
 template <typename Word>
 constexpr size_t sim_lds(size_t n, size_t e)
 {
@@ -151,6 +157,23 @@ __global__ __launch_bounds__(kSimThreads) void k_simulate(GraphView gv, int D, i
 #pragma unroll 4
     for (int i = threadIdx.x; i < e; i += kSimThreads) cidx[i] = static_cast<uint16_t>(gv.nbr_idx[1][e0 + i] - n0);
     __syncthreads();
+    if constexpr (!PC) {
+        for (int v = threadIdx.x; v < n; v += kSimThreads) {
+            const uint32_t kids = rec[v].z, listed = kids & kList;
+            const uint32_t c0 = kids & kIdMask, cnt = listed ? (kids & ~kList) >> kIdBits : 2u;
+            uint32_t sent = 1u << (node[v] & kNoDev) | 1u << kNoDev, m = 0, cross = 0;    // (a child that is not there needs none)
+            for (uint32_t i = 0; i < cnt; ++i) {
+                const uint32_t c = listed ? cidx[c0 + i] : (i == 0 ? c0 : kids >> kIdBits), pd = node[c] & kNoDev;
+                if ((sent >> pd) & 1u) continue;
+                sent |= 1u << pd;
+                if (m < 2) cross |= pd << (5 + 5 * m);
+                if (listed) xl[c0 + m] = static_cast<uint16_t>(pd);
+                ++m;
+            }
+            link_of(static_cast<uint32_t>(v))[1] = static_cast<uint16_t>(cross | m);
+        }
+        __syncthreads();
+    }
     if (rec[n].x != 0) {
         if (threadIdx.x == 0) {
             out_runtime[b] = __builtin_nanf("");
@@ -165,8 +188,10 @@ __global__ __launch_bounds__(kSimThreads) void k_simulate(GraphView gv, int D, i
     constexpr uint32_t kIdle = 0xFFFFFFFFu;
     uint32_t ev_t = kIdle, ev_key = 0;                    // pending event: time (bits); operation | creation number << 14
     uint32_t cur_dur = 0, cur_kids = 0;                   // its operation's transfer duration and children
-    uint32_t x_cur = 0, x_more = 0;                       // bus: list entry in progress | the next one << 16; entries
-                                                          // left | place in xl of the entry after the next << 14
+    // Device: crossings of its operation.  Bus: destinations left, the one in progress with them | its device << 5 | the
+    // next one << 10 | number of the entry after that << 15.  (One transfer per child: list entry in progress | the
+    // next one << 16, and x_more: entries left | place in xl of the entry after the next << 14.)
+    uint32_t x_cur = 0, x_more = 0;
     uint32_t head = none, tail = none;                    // queue
     uint4 hr = rec[none];                                 // record of the queue's first item
     uint32_t seq = 0, n_events = 0, last = 0;
@@ -189,10 +214,11 @@ __global__ __launch_bounds__(kSimThreads) void k_simulate(GraphView gv, int D, i
         return t;
     };
     // operation v starts on device q
-    auto start_op = [&](uint32_t q, uint32_t v, uint32_t now, uint32_t cost, uint32_t dur, uint32_t kids) __attribute__((always_inline)) {
+    auto start_op = [&](uint32_t q, uint32_t v, uint32_t now, uint32_t cost, uint32_t dur, uint32_t kids, uint32_t w) __attribute__((always_inline)) {
         const float t = schedule(q, now, cost, v);
         put(cur_dur, q, dur);
         put(cur_kids, q, kids);
+        if constexpr (!PC) put(x_cur, q, w >> 16);
         if constexpr (TL) {
             op_start[n0 + static_cast<int>(v)] = __uint_as_float(now);
             op_end[n0 + static_cast<int>(v)] = t;
@@ -206,6 +232,28 @@ __global__ __launch_bounds__(kSimThreads) void k_simulate(GraphView gv, int D, i
         put(cur_kids, q, kids);
         put(x_cur, q, e1 | e2 << 16);
         put(x_more, q, (m - 1) | ((kids & kIdMask) + 2) << kIdBits);
+    };
+
+    // bus q starts the transfers of operation o, whose crossings are x
+    auto start_crossing = [&](uint32_t q, uint32_t now, uint32_t o, uint32_t dur, uint32_t kids, uint32_t x) __attribute__((always_inline)) {
+        schedule(q, now, dur, o);
+        put(cur_dur, q, dur);
+        put(cur_kids, q, kids);
+        put(x_cur, q, x | 2u << 15);
+    };
+    // The first item of queue q (whose record lane q holds) becomes lane q's pending event and leaves the queue: all of
+    // it in the lane itself.  `after`: the lane's duration; x: its new x_cur.
+    auto start_first = [&](uint32_t q, uint32_t now, uint32_t after, uint32_t x) __attribute__((always_inline)) {
+        const bool it = lane == q;
+        const float t = __fadd_rn(__uint_as_float(now), __uint_as_float(after));
+        ev_t = it ? __float_as_uint(t) : ev_t;
+        ev_key = it ? head | seq << kIdBits : ev_key;
+        ++seq;
+        cur_dur = it ? hr.y : cur_dur;
+        cur_kids = it ? hr.z : cur_kids;
+        x_cur = it ? x : x_cur;
+        head = it ? hr.w & 0xFFFFu : head;
+        return t;
     };
 
     for (int base = 0; base < n; base += 64) {            // operations without parents, ascending id
@@ -222,7 +270,7 @@ __global__ __launch_bounds__(kSimThreads) void k_simulate(GraphView gv, int D, i
         const uint32_t v = get(head, d);
         if (v == none) continue;
         const uint4 r = rec[v];
-        start_op(d, v, 0, first_lane(r.x), first_lane(r.y), first_lane(r.z));
+        start_op(d, v, 0, first_lane(r.x), first_lane(r.y), first_lane(r.z), first_lane(r.w));
         put(head, d, first_lane(r.w) & 0xFFFFu);
     }
     hr = rec[head];
@@ -255,13 +303,16 @@ __global__ __launch_bounds__(kSimThreads) void k_simulate(GraphView gv, int D, i
             const uint32_t v = get(head, dev);
             wait = v ^ none;
             if (v == none) return;
-            put(head, dev, get(hr.w, dev) & 0xFFFFu);
-            start_op(dev, v, now, get(hr.x, dev), get(hr.y, dev), get(hr.z, dev));
+            const float t = start_first(dev, now, hr.x, hr.w >> 16);
+            if constexpr (TL) {
+                op_start[n0 + static_cast<int>(v)] = __uint_as_float(now);
+                op_end[n0 + static_cast<int>(v)] = __uint_as_float(get(__float_as_uint(t), dev));
+            }
         };
         auto runnable = [&](uint32_t dev, uint32_t v, const uint4 &r, uint32_t l) __attribute__((always_inline)) {
             if (__builtin_expect(wait == 0, 1)) {
                 wait = 1;
-                start_op(dev, v, now, get(r.x, l), get(r.y, l), get(r.z, l));
+                start_op(dev, v, now, get(r.x, l), get(r.y, l), get(r.z, l), PC ? 0u : get(r.w, l));
             } else {
                 push(dev, v);
             }
@@ -294,9 +345,24 @@ __global__ __launch_bounds__(kSimThreads) void k_simulate(GraphView gv, int D, i
 
         if (slot < nd) {
             last = now;
-            uint32_t m = 0, e1 = 0, e2 = 0;               // transfers of the output: number and first two entries
+            const uint32_t cross = PC ? 0u : get(x_cur, slot);   // (before the device goes on with its queue)
+            uint32_t m = 0, e1 = 0, e2 = 0;               // (one per child) transfers of the output: number and first two entries
             uint4 r;
-            if (__builtin_expect(!(kids & kList), 1)) {
+            if constexpr (!PC) {
+                if (__builtin_expect(!(kids & kList), 1)) {
+                    const uint32_t word = two_kids(slot, r);
+                    next_op(slot);
+                    const uint32_t w0 = get(word, 0), w1 = get(word, 1), want = kInput | slot;
+                    if (__builtin_expect(w0 == want, 0)) runnable(slot, kids & kIdMask, r, 0);
+                    if (__builtin_expect(w1 == want, 0)) runnable(slot, kids >> kIdBits, r, 1);
+                } else {
+                    next_op(slot);
+                    for (uint32_t base = 0; base < cnt; base += 64) {
+                        uint32_t c;
+                        (void)more_kids(slot, c0 + base, cnt - base, c, r);
+                    }
+                }
+            } else if (__builtin_expect(!(kids & kList), 1)) {
                 const uint32_t word = two_kids(slot, r);
                 next_op(slot);
                 const uint32_t w0 = get(word, 0), w1 = get(word, 1), want = kInput | slot;
@@ -305,11 +371,11 @@ __global__ __launch_bounds__(kSimThreads) void k_simulate(GraphView gv, int D, i
                 const uint32_t d0 = w0 & kNoDev, d1 = w1 & kNoDev;
                 const uint32_t same_dev = d0 == d1 ? 1u : 0u;
                 if (d0 != slot && d0 != kNoDev) {
-                    e1 = PC ? (kids & kIdMask) | kFirst : d0;
+                    e1 = (kids & kIdMask) | kFirst;
                     m = 1;
                 }
-                if (d1 != slot && d1 != kNoDev && (PC || m == 0 || !same_dev)) {
-                    e2 = PC ? kids >> kIdBits | (m == 0 || !same_dev ? kFirst : 0u) : d1;
+                if (d1 != slot && d1 != kNoDev) {
+                    e2 = kids >> kIdBits | (m == 0 || !same_dev ? kFirst : 0u);
                     e1 = m == 0 ? e2 : e1;
                     ++m;
                 }
@@ -327,16 +393,9 @@ __global__ __launch_bounds__(kSimThreads) void k_simulate(GraphView gv, int D, i
                         rest &= ~__ballot(pc == pd);
                         if ((sent >> pd) & 1u) continue;
                         sent |= 1u << pd;
-                        if constexpr (PC) {
-                            firsts |= 1ull << l;
-                        } else {
-                            e1 = m == 0 ? pd : e1;
-                            e2 = m == 1 ? pd : e2;
-                            xl[c0 + m] = static_cast<uint16_t>(pd);
-                            ++m;
-                        }
+                        firsts |= 1ull << l;
                     }
-                    if (PC && cross != 0ull) {
+                    if (cross != 0ull) {
                         const uint32_t x = c | (((firsts >> lane) & 1ull) ? kFirst : 0u);
                         if ((cross >> lane) & 1ull)
                             xl[c0 + m + static_cast<uint32_t>(__popcll(cross & ((1ull << lane) - 1ull)))] = static_cast<uint16_t>(x);
@@ -350,8 +409,17 @@ __global__ __launch_bounds__(kSimThreads) void k_simulate(GraphView gv, int D, i
                 }
             }
             // the output joins the bus's queue, or starts to cross at once
-            if (__builtin_expect(m != 0, 1)) {
-                const uint32_t bus = nd + slot;
+            const uint32_t bus = nd + slot;
+            if constexpr (!PC) {
+                if (__builtin_expect((cross & kNoDev) != 0, 1)) {
+                    if (get(ev_t, bus) == kIdle) {
+                        start_crossing(bus, now, o, dur, kids, cross);
+                    } else {
+                        *link_of(o) = static_cast<uint16_t>(none);
+                        push(bus, o);
+                    }
+                }
+            } else if (__builtin_expect(m != 0, 1)) {
                 if (get(ev_t, bus) == kIdle) {
                     start_transfers(bus, now, o, dur, kids, m, e1, e2);
                 } else {
@@ -377,7 +445,7 @@ __global__ __launch_bounds__(kSimThreads) void k_simulate(GraphView gv, int D, i
                 wait = ~get(ev_t, dev);                   // (idle: its queue is empty)
                 if ((word >> kDevBits) == 1u) runnable(dev, c, r, 0);
             } else {
-                const uint32_t dev = xc & 0xFFFFu;
+                const uint32_t dev = xc >> 5 & kNoDev;
                 if constexpr (TL) arrival[static_cast<size_t>(n0 + static_cast<int>(o)) * D + dev] = __uint_as_float(now);
                 wait = ~get(ev_t, dev);                   // (idle: its queue is empty)
                 if (__builtin_expect(!(kids & kList), 1)) {
@@ -393,19 +461,32 @@ __global__ __launch_bounds__(kSimThreads) void k_simulate(GraphView gv, int D, i
                 }
             }
             // the bus goes on with the operation's next transfer, or with its queue
-            const uint32_t more = get(x_more, slot), left = more & kIdMask;
-            if (__builtin_expect(left != 0, 0)) {
-                uint32_t x = xc >> 16;
-                if (left > 1) x |= first_lane(xl[more >> kIdBits]) << 16;
-                put(x_cur, slot, x);
-                put(x_more, slot, more + (1u << kIdBits) - 1u);
-                schedule(slot, now, dur, o);
+            if constexpr (!PC) {
+                const uint32_t left = (xc & kNoDev) - 1u;
+                if (__builtin_expect(left != 0, 0)) {
+                    uint32_t x = left | (xc >> 10 & kNoDev) << 5;
+                    const uint32_t at = xc >> 15;
+                    if (left > 1) x |= first_lane(xl[c0 + at]) << 10;
+                    put(x_cur, slot, x | (at + 1u) << 15);
+                    schedule(slot, now, dur, o);
+                } else if (get(head, slot) != none) {
+                    start_first(slot, now, hr.y, hr.w >> 16 | 2u << 15);
+                }
             } else {
-                const uint32_t q = get(head, slot);
-                if (q != none) {
-                    const uint32_t a = get(hr.x, slot), w = get(hr.w, slot);
-                    put(head, slot, w & 0xFFFFu);
-                    start_transfers(slot, now, q, get(hr.y, slot), get(hr.z, slot), a & 0xFFFFu, a >> 16, w >> 16);
+                const uint32_t more = get(x_more, slot), left = more & kIdMask;
+                if (__builtin_expect(left != 0, 0)) {
+                    uint32_t x = xc >> 16;
+                    if (left > 1) x |= first_lane(xl[more >> kIdBits]) << 16;
+                    put(x_cur, slot, x);
+                    put(x_more, slot, more + (1u << kIdBits) - 1u);
+                    schedule(slot, now, dur, o);
+                } else {
+                    const uint32_t q = get(head, slot);
+                    if (q != none) {
+                        const uint32_t a = get(hr.x, slot), w = get(hr.w, slot);
+                        put(head, slot, w & 0xFFFFu);
+                        start_transfers(slot, now, q, get(hr.y, slot), get(hr.z, slot), a & 0xFFFFu, a >> 16, w >> 16);
+                    }
                 }
             }
         }
