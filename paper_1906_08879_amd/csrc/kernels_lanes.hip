@@ -21,7 +21,7 @@
 // microsecond, less than a load from HBM.
 //
 // Forward sweep of 64 layered graphs of 200 nodes (H = 32, L = 2, 40 chunks): 66.9 us on matrix cores, 40 here;
-// one random graph of 32 nodes (H = 8): 35.6 us by the generic kernel, 7 here.
+// one random graph of 32 nodes (H = 8): 35.6 us by the generic kernel, 8 here.
 #include <type_traits>
 
 #include "internal.h"
@@ -549,7 +549,7 @@ __global__ __launch_bounds__(64 * lane_waves(H), 2) void k_sweep_lanes(LaneParam
 }  // namespace
 
 // Where these kernels are the faster ones.  H = 8, 16: everywhere (the generic kernel: random graphs of 32 nodes, 1 graph
-// 35.6 -> 7 us, a forward pass of 4096 graphs 497 -> 290 us).  H = 32 and 64 as long as all workgroups of a batch are
+// 35.6 -> 8 us, a forward pass of 4096 graphs 497 -> 290 us).  H = 32 and 64 as long as all workgroups of a batch are
 // on the chip at once, two of four waves or one of eight to each of 256 compute units (forward pass, against the
 // matrix-core sweep, whose workgroups are smaller: Inception-like graphs, H = 32, 256 graphs 294 -> 250 us, 320 graphs
 // 310 -> 386; NMT-like graphs, H = 64, one layer, 128 graphs 552 -> 458 us, 160 graphs 607 -> 832), and with fp32
