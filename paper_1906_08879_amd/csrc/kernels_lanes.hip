@@ -45,60 +45,69 @@ __device__ __forceinline__ void lds_barrier()
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
-// Sum of w[k] * (x of lane k of this lane's row of sixteen), k = 0 .. 15.  The compiler does not fold a DPP move into
+// Sums of w[k] * (x of lane k of this lane's row of sixteen), k = 0 .. 15.  The compiler does not fold a DPP move into
 // a multiply-add, so this is assembly.  A DPP read needs two wait states after the vector unit has written the
-// register (WAIT; the blocks of a layer keep their order, so its first block waits for all), and a plain vector
-// instruction must read the result (an addition, in dense).
-#define PL_MAC16 \
-    "v_mul_f32_dpp %0, %1, %2 row_newbcast:0 row_mask:0xf bank_mask:0xf\n" \
-    "v_fmac_f32_dpp %0, %1, %3 row_newbcast:1 row_mask:0xf bank_mask:0xf\n" \
-    "v_fmac_f32_dpp %0, %1, %4 row_newbcast:2 row_mask:0xf bank_mask:0xf\n" \
-    "v_fmac_f32_dpp %0, %1, %5 row_newbcast:3 row_mask:0xf bank_mask:0xf\n" \
-    "v_fmac_f32_dpp %0, %1, %6 row_newbcast:4 row_mask:0xf bank_mask:0xf\n" \
-    "v_fmac_f32_dpp %0, %1, %7 row_newbcast:5 row_mask:0xf bank_mask:0xf\n" \
-    "v_fmac_f32_dpp %0, %1, %8 row_newbcast:6 row_mask:0xf bank_mask:0xf\n" \
-    "v_fmac_f32_dpp %0, %1, %9 row_newbcast:7 row_mask:0xf bank_mask:0xf\n" \
-    "v_fmac_f32_dpp %0, %1, %10 row_newbcast:8 row_mask:0xf bank_mask:0xf\n" \
-    "v_fmac_f32_dpp %0, %1, %11 row_newbcast:9 row_mask:0xf bank_mask:0xf\n" \
-    "v_fmac_f32_dpp %0, %1, %12 row_newbcast:10 row_mask:0xf bank_mask:0xf\n" \
-    "v_fmac_f32_dpp %0, %1, %13 row_newbcast:11 row_mask:0xf bank_mask:0xf\n" \
-    "v_fmac_f32_dpp %0, %1, %14 row_newbcast:12 row_mask:0xf bank_mask:0xf\n" \
-    "v_fmac_f32_dpp %0, %1, %15 row_newbcast:13 row_mask:0xf bank_mask:0xf\n" \
-    "v_fmac_f32_dpp %0, %1, %16 row_newbcast:14 row_mask:0xf bank_mask:0xf\n" \
-    "v_fmac_f32_dpp %0, %1, %17 row_newbcast:15 row_mask:0xf bank_mask:0xf"
-template <bool WAIT>
+// register, and the compiler does not look for that inside assembly: all sums of a layer are one statement that begins
+// with the wait states, so that whatever writes an input comes before them.  A plain vector instruction must read
+// the results (an addition, in dense).
+#define PL_MAC16(A, X, W0, W1, W2, W3, W4, W5, W6, W7, W8, W9, WA, WB, WC, WD, WE, WF) \
+    "v_mul_f32_dpp %" #A ", %" #X ", %" #W0 " row_newbcast:0 row_mask:0xf bank_mask:0xf\n" \
+    "v_fmac_f32_dpp %" #A ", %" #X ", %" #W1 " row_newbcast:1 row_mask:0xf bank_mask:0xf\n" \
+    "v_fmac_f32_dpp %" #A ", %" #X ", %" #W2 " row_newbcast:2 row_mask:0xf bank_mask:0xf\n" \
+    "v_fmac_f32_dpp %" #A ", %" #X ", %" #W3 " row_newbcast:3 row_mask:0xf bank_mask:0xf\n" \
+    "v_fmac_f32_dpp %" #A ", %" #X ", %" #W4 " row_newbcast:4 row_mask:0xf bank_mask:0xf\n" \
+    "v_fmac_f32_dpp %" #A ", %" #X ", %" #W5 " row_newbcast:5 row_mask:0xf bank_mask:0xf\n" \
+    "v_fmac_f32_dpp %" #A ", %" #X ", %" #W6 " row_newbcast:6 row_mask:0xf bank_mask:0xf\n" \
+    "v_fmac_f32_dpp %" #A ", %" #X ", %" #W7 " row_newbcast:7 row_mask:0xf bank_mask:0xf\n" \
+    "v_fmac_f32_dpp %" #A ", %" #X ", %" #W8 " row_newbcast:8 row_mask:0xf bank_mask:0xf\n" \
+    "v_fmac_f32_dpp %" #A ", %" #X ", %" #W9 " row_newbcast:9 row_mask:0xf bank_mask:0xf\n" \
+    "v_fmac_f32_dpp %" #A ", %" #X ", %" #WA " row_newbcast:10 row_mask:0xf bank_mask:0xf\n" \
+    "v_fmac_f32_dpp %" #A ", %" #X ", %" #WB " row_newbcast:11 row_mask:0xf bank_mask:0xf\n" \
+    "v_fmac_f32_dpp %" #A ", %" #X ", %" #WC " row_newbcast:12 row_mask:0xf bank_mask:0xf\n" \
+    "v_fmac_f32_dpp %" #A ", %" #X ", %" #WD " row_newbcast:13 row_mask:0xf bank_mask:0xf\n" \
+    "v_fmac_f32_dpp %" #A ", %" #X ", %" #WE " row_newbcast:14 row_mask:0xf bank_mask:0xf\n" \
+    "v_fmac_f32_dpp %" #A ", %" #X ", %" #WF " row_newbcast:15 row_mask:0xf bank_mask:0xf\n"
+#define PL_W4(w) "v"((w)[0]), "v"((w)[1]), "v"((w)[2]), "v"((w)[3])
+#define PL_W16(w) PL_W4(w), PL_W4((w) + 4), PL_W4((w) + 8), PL_W4((w) + 12)
 __device__ __forceinline__ float mac16(float x, const float *w)
 {
-    float acc;
-    if constexpr (WAIT)
-        asm volatile("s_nop 1\n" PL_MAC16 : "=&v"(acc) : "v"(x), "v"(w[0]), "v"(w[1]), "v"(w[2]), "v"(w[3]), 
-                     "v"(w[4]), "v"(w[5]), "v"(w[6]), "v"(w[7]), "v"(w[8]), "v"(w[9]), "v"(w[10]), 
-                     "v"(w[11]), "v"(w[12]), "v"(w[13]), "v"(w[14]), "v"(w[15]));
-    else
-        asm volatile(PL_MAC16 : "=&v"(acc) : "v"(x), "v"(w[0]), "v"(w[1]), "v"(w[2]), "v"(w[3]), 
-                     "v"(w[4]), "v"(w[5]), "v"(w[6]), "v"(w[7]), "v"(w[8]), "v"(w[9]), "v"(w[10]), 
-                     "v"(w[11]), "v"(w[12]), "v"(w[13]), "v"(w[14]), "v"(w[15]));
-    return acc;
+    float s;
+    asm volatile("s_nop 1\n" PL_MAC16(0, 1, 2, 3, 4, 5, 6, 7, 8, 9, 10, 11, 12, 13, 14, 15, 16, 17)
+                 : "=&v"(s) : "v"(x), PL_W16(w));
+    return s;
+}
+__device__ __forceinline__ void mac32(float x0, float x1, const float *w, float &s0, float &s1)
+{
+    asm volatile("s_nop 1\n" PL_MAC16(0, 2, 4, 5, 6, 7, 8, 9, 10, 11, 12, 13, 14, 15, 16, 17, 18, 19)
+                 PL_MAC16(1, 3, 20, 21, 22, 23, 24, 25, 26, 27, 28, 29, 30, 31, 32, 33, 34, 35)
+                 : "=&v"(s0), "=&v"(s1) : "v"(x0), "v"(x1), PL_W16(w), PL_W16(w + 16));
+}
+__device__ __forceinline__ void mac64(float x0, float x1, float x2, float x3, const float *w, float &s0, float &s1, float &s2,
+                                      float &s3)
+{
+    asm volatile("s_nop 1\n" PL_MAC16(0, 4, 8, 9, 10, 11, 12, 13, 14, 15, 16, 17, 18, 19, 20, 21, 22, 23)
+                 PL_MAC16(1, 5, 24, 25, 26, 27, 28, 29, 30, 31, 32, 33, 34, 35, 36, 37, 38, 39)
+                 PL_MAC16(2, 6, 40, 41, 42, 43, 44, 45, 46, 47, 48, 49, 50, 51, 52, 53, 54, 55)
+                 PL_MAC16(3, 7, 56, 57, 58, 59, 60, 61, 62, 63, 64, 65, 66, 67, 68, 69, 70, 71)
+                 : "=&v"(s0), "=&v"(s1), "=&v"(s2), "=&v"(s3)
+                 : "v"(x0), "v"(x1), "v"(x2), "v"(x3), PL_W16(w), PL_W16(w + 16), PL_W16(w + 32), PL_W16(w + 48));
 }
 #undef PL_MAC16
 
-// Sum of w[k] * (x of lane k of this lane's group of four), k = 0 .. 3.
-#define PL_MAC4 \
-    "v_mul_f32_dpp %0, %1, %2 quad_perm:[0,0,0,0] row_mask:0xf bank_mask:0xf\n" \
-    "v_fmac_f32_dpp %0, %1, %3 quad_perm:[1,1,1,1] row_mask:0xf bank_mask:0xf\n" \
-    "v_fmac_f32_dpp %0, %1, %4 quad_perm:[2,2,2,2] row_mask:0xf bank_mask:0xf\n" \
-    "v_fmac_f32_dpp %0, %1, %5 quad_perm:[3,3,3,3] row_mask:0xf bank_mask:0xf"
-template <bool WAIT>
-__device__ __forceinline__ float mac4(float x, const float *w)
+// The same over the lanes of this lane's group of four: s0 of x0, s1 of x1.
+#define PL_MAC4(A, X, W0, W1, W2, W3) \
+    "v_mul_f32_dpp %" #A ", %" #X ", %" #W0 " quad_perm:[0,0,0,0] row_mask:0xf bank_mask:0xf\n" \
+    "v_fmac_f32_dpp %" #A ", %" #X ", %" #W1 " quad_perm:[1,1,1,1] row_mask:0xf bank_mask:0xf\n" \
+    "v_fmac_f32_dpp %" #A ", %" #X ", %" #W2 " quad_perm:[2,2,2,2] row_mask:0xf bank_mask:0xf\n" \
+    "v_fmac_f32_dpp %" #A ", %" #X ", %" #W3 " quad_perm:[3,3,3,3] row_mask:0xf bank_mask:0xf\n"
+__device__ __forceinline__ void mac8(float x0, float x1, const float *w, float &s0, float &s1)
 {
-    float acc;
-    if constexpr (WAIT)
-        asm volatile("s_nop 1\n" PL_MAC4 : "=&v"(acc) : "v"(x), "v"(w[0]), "v"(w[1]), "v"(w[2]), "v"(w[3]));
-    else
-        asm volatile(PL_MAC4 : "=&v"(acc) : "v"(x), "v"(w[0]), "v"(w[1]), "v"(w[2]), "v"(w[3]));
-    return acc;
+    asm volatile("s_nop 1\n" PL_MAC4(0, 2, 4, 5, 6, 7) PL_MAC4(1, 3, 8, 9, 10, 11)
+                 : "=&v"(s0), "=&v"(s1) : "v"(x0), "v"(x1), PL_W4(w), PL_W4(w + 4));
 }
 #undef PL_MAC4
+#undef PL_W16
+#undef PL_W4
 
 // rows of sixteen lanes (A, B, C, D) -> lo = (A, A, C, C), hi = (B, B, D, D)
 __device__ __forceinline__ void swap16(float x, float &lo, float &hi)
@@ -132,13 +141,15 @@ __device__ __forceinline__ float dense(float x, const float (&w)[H], float b)
 {
     if constexpr (H == 8) {
         const float y = __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x141, 0xF, 0xF, true));   // row_half_mirror
-        return (mac4<true>(x, &w[0]) + mac4<true>(y, &w[4])) + b;
+        float s0, s1;
+        mac8(x, y, w, s0, s1);
+        return (s0 + s1) + b;
     } else if constexpr (H == 16) {
-        return mac16<true>(x, &w[0]) + b;
+        return mac16(x, w) + b;
     } else if constexpr (H == 32) {
-        float lo, hi;
+        float lo, hi, s0, s1;
         swap16(x, lo, hi);
-        const float s0 = mac16<true>(lo, &w[0]), s1 = mac16<false>(hi, &w[16]);
+        mac32(lo, hi, w, s0, s1);
         return (s0 + s1) + b;
     } else {
         static_assert(H == 64, "a row has 8, 16, 32 or 64 lanes");
@@ -146,8 +157,8 @@ __device__ __forceinline__ float dense(float x, const float (&w)[H], float b)
         swap16(x, p, q);
         swap32(p, r0, r2);
         swap32(q, r1, r3);
-        const float s0 = mac16<true>(r0, &w[0]), s1 = mac16<false>(r1, &w[16]);
-        const float s2 = mac16<false>(r2, &w[32]), s3 = mac16<false>(r3, &w[48]);
+        float s0, s1, s2, s3;
+        mac64(r0, r1, r2, r3, w, s0, s1, s2, s3);
         return ((s0 + s1) + (s2 + s3)) + b;
     }
 }
