@@ -16,7 +16,8 @@
 //   * Two LDS barriers per chunk: one between the messages that a chunk leaves in the table and the sums of the
 //     next chunk, one that keeps a wave from overwriting a table row which another wave still sums.
 // The chunk plan (plan.cpp), the table of the last kRing chunks' messages, far messages, the reachability flag
-// in a message's sign bit and the rows that take the stores of unused chunk rows are those of kernels_mfma.hip.
+// in a message's sign bit and the rows that take the stores of unused chunk rows are those of kernels_mfma.hip; but
+// a wave owns rows here, not columns, so the far message that it reads is another wave's (message_barrier).
 // Everything a chunk needs from HBM is requested two chunks ahead, records four: a chunk takes about half a
 // microsecond, less than a load from HBM.
 //
@@ -43,6 +44,17 @@ __device__ __forceinline__ void lds_barrier()
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
     __builtin_amdgcn_s_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
+// Workgroup barrier behind which every wave can read what was stored before it, from LDS and from memory: a row's
+// far message is read by another wave than the one that stored it.  (A workgroup's waves share an L1 that keeps their
+// accesses in order, so this is the same code as lds_barrier.  Threadgroup-split mode, where they would not, is
+// closed to a kernel that allocates LDS.)
+__device__ __forceinline__ void message_barrier()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
 }
 
 // Sums of w[k] * (x of lane k of this lane's row of sixteen), k = 0 .. 15.  The compiler does not fold a DPP move into
@@ -536,7 +548,7 @@ __global__ __launch_bounds__(64 * lane_waves(H), 2) void k_sweep_lanes(LaneParam
             msgtab[(ring * CH + r) * H + col] = t;
             elem(msg, at4(v_msg)) = t;
         }
-        lds_barrier();                              // this chunk's messages are in the table
+        message_barrier();                          // this chunk's messages are in the table, and in msg
         a = gather(info1, rA, farA, idsA, pre, inN.gates, c + 1 < c_end, sign);
         rows0 = c + 1 < c_end ? rows_of(info1) : 0;
         p0 = static_cast<int>(first(rA[2]));

@@ -69,3 +69,33 @@ def test_either_side_of_the_batch_limit(H, L, B):
     ref = oracle.forward_workload(w, n_threads=8)
     assert_rows_close(run_library(w)["emb"], ref["emb"], H, f"H {H} L {L} B {B}")
     _compare(w, f"H {H} L {L} B {B}")
+
+
+def _ladder(width, distance, levels):
+    """`levels` levels of `width` nodes, a chunk each: a node's parents are one of the level before and, as its
+    single far source, one that many chunks back that another wave stored (the mirrored row)."""
+    src, dst = [], []
+    for level in range(1, levels):
+        for i in range(width):
+            v = level * width + i
+            src.append((level - 1) * width + i)
+            dst.append(v)
+            if level >= distance:
+                src.append((level - distance) * width + width - 1 - i)
+                dst.append(v)
+    return levels * width, np.array(src, np.int32), np.array(dst, np.int32)
+
+
+@pytest.mark.parametrize("H,L", WIDTHS)
+@pytest.mark.parametrize("k", [1, 2])
+def test_far_sources_of_other_waves(H, L, k):
+    """Far sources at the shortest distance at which the table does not hold them any more (five chunks), one nearer and
+    one further, for chunks of as many rows as two, four and eight waves take."""
+    graphs = [_ladder(width, distance, 15) for width in (2, 5, 8) for distance in (4, 5, 6)]
+    rng = np.random.default_rng(H + L)
+    w = custom_workload(rng, [g[0] for g in graphs], 3, H, L, k, 1, "fp32", w_scale=0.05)
+    w.n_edges = np.array([len(g[1]) for g in graphs], np.int32)
+    w.edge_src, w.edge_dst = np.concatenate([g[1] for g in graphs]), np.concatenate([g[2] for g in graphs])
+    ref = oracle.forward_workload(w, n_threads=8)
+    assert_rows_close(run_library(w)["emb"], ref["emb"], H, f"H {H} L {L} k {k}")
+    _compare(w, f"H {H} L {L} k {k}")
