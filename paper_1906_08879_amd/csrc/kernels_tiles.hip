@@ -80,8 +80,21 @@ struct SweepParams {
 
 constexpr int tile_waves(int H) { return H / 16; }   // wave w owns output columns [16 w, 16 w + 16)
 
+// Waves per SIMD that a variant leaves room for: a chain is all latency, so a batch that fits on the chip at once takes the time of
+// one chain and one that does not takes two.  Left alone, the compiler gives the variants with one bf16 part per weight, the
+// later sweeps and the reverse pass a few registers more than that many waves can have (130 to 180 instead of 128 or
+// 168), and batches just past the smaller limit paid for it (4-module Inception-like graphs, without / with the bound: gradient of
+// 320 graphs, H = 64, bf16, 723 -> 645 us; 513 graphs, H = 32, fp32, 706 -> 643 us; forward, two sweeps, 512 graphs, H = 64, bf16, one
+// layer, 328 -> 287 us).  On batches that fit either way it costs 2 % at most (256 -> 251 us
+// without it: forward, two sweeps, 768 graphs, H = 32, bf16).  No variant spills.
+constexpr int tile_residency(int H, int WS, int L, bool FF, bool BW)
+{
+    if (WS == 1) return L == 1 ? (FF ? 3 : 4) : (H == 32 && !FF && !BW ? 4 : 3);
+    return FF || (H == 64 && L == 2) ? 2 : 3;
+}
+
 template <int H, int WS, int L, bool FF, bool WX, bool BW, bool TR>
-__global__ __launch_bounds__(64 * tile_waves(H), 2) void k_sweep_tiles(SweepParams P)
+__global__ __launch_bounds__(64 * tile_waves(H), tile_residency(H, WS, L, FF, BW)) void k_sweep_tiles(SweepParams P)
 {
     static_assert(!BW || (!FF && !WX), "the reverse pass reads its input from emb and writes no xb");
     static_assert(!TR || (FF && !WX && !BW), "activations are kept for a single forward sweep");
@@ -239,7 +252,7 @@ __global__ __launch_bounds__(64 * tile_waves(H), 2) void k_sweep_tiles(SweepPara
         constexpr int K0 = decltype(k0c)::value, K1 = decltype(k1c)::value;
         float x[K1 - K0];
 #pragma unroll
-        for (int k = K0; k < K1; ++k) x[k - K0] = msgtab[((slots >> (6 * k)) & 63u) * LDM + mc];
+        for (int k = K0; k < K1; ++k) x[k - K0] = elem(msgtab, ((slots >> (6 * k)) & 63u) * (4u * LDM) + 4u * mc);
 #pragma unroll
         for (int k = K0; k < K1; ++k) add(s, signs, x[k - K0]);
     };

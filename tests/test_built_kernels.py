@@ -1,6 +1,6 @@
 """Properties of the built kernels that results do not show, read from the library's own gfx950 code: wait states between
 a vector write and a DPP read of it in the sweep of narrow networks, whose multiply-adds are assembly that the
-compiler does not look into."""
+compiler does not look into; and how many workgroups of the matrix-core sweeps a compute unit holds."""
 import os
 import re
 import shutil
@@ -105,3 +105,32 @@ def test_no_dpp_sum_leans_on_the_statement_before_it():
     assert len(sums) >= 4
     for t in sums:
         assert t.startswith('"s_nop 1\\n"'), t[:80]
+
+
+def _kernels(code_object, kernel):
+    """(template arguments, vector registers, bytes of scratch) of the code object's kernels of that name."""
+    for entry in _tool("llvm-readelf", "--notes", code_object).split("- .agpr_count:")[1:]:
+        name = re.search(r"\.name:\s+(\S+)", entry)[1]
+        args = re.search(kernel + r"I((?:L[ib]\d+E)+)E", name)
+        if args:
+            yield ([int(x) for x in re.findall(r"L[ib](\d+)E", args[1])], int(re.search(r"\.vgpr_count:\s+(\d+)", entry)[1]),
+                   int(re.search(r"\.private_segment_fixed_size:\s+(\d+)", entry)[1]))
+
+
+# (H, parts per weight, layers) -> waves per SIMD of a first sweep, a later sweep and the reverse pass
+WAVES = {(64, 3, 2): (2, 2, 2), (64, 1, 2): (3, 3, 3), (64, 3, 1): (2, 3, 3), (64, 1, 1): (3, 4, 4),
+         (32, 3, 2): (2, 3, 3), (32, 1, 2): (3, 4, 3), (32, 3, 1): (3, 3, 3), (32, 1, 1): (3, 4, 4)}
+
+
+@needs_llvm
+def test_sweeps_on_matrix_cores_keep_their_residency(code_objects):
+    """A SIMD's 512 registers, handed out in eights, hold as many waves of every variant as a batch is dispatched for,
+    and nothing is spilled."""
+    seen = set()
+    for obj in code_objects:
+        for (H, WS, L, first, _, reverse, _), registers, scratch in _kernels(obj, "k_sweep_tiles"):
+            want = WAVES[(H, WS, L)][0 if first else (2 if reverse else 1)]
+            waves = 512 // (-(-registers // 8) * 8)
+            assert waves >= want and scratch == 0, (H, WS, L, first, reverse, registers, scratch)
+            seen.add((H, WS, L))
+    assert seen == set(WAVES)
