@@ -99,3 +99,24 @@ def test_far_sources_of_other_waves(H, L, k):
     ref = oracle.forward_workload(w, n_threads=8)
     assert_rows_close(run_library(w)["emb"], ref["emb"], H, f"H {H} L {L} k {k}")
     _compare(w, f"H {H} L {L} k {k}")
+
+
+def _chain(levels):
+    """One node a level: as many chunks as levels, two nodes back as a second source."""
+    pairs = [(v - back, v) for v in range(levels) for back in (1, 2) if v >= back]
+    src, dst = zip(*pairs) if pairs else ((), ())
+    return levels, np.array(src, np.int32), np.array(dst, np.int32)
+
+
+@pytest.mark.parametrize("H,L,k,wd", [(64, 2, 1, "fp32"), (64, 1, 1, "bf16"), (32, 2, 2, "bf16"), (64, 1, 3, "bf16"), (32, 2, 1, "fp32")])
+def test_every_number_of_chunks(H, L, k, wd):
+    """Graphs of 1 to 13 chunks: the loop's turns of four and what is left over, in the matrix-core kernel (that leaves
+    in the middle of a turn, or does not where no registers are left for the test) and in the lanes."""
+    graphs = [_chain(n) for n in range(1, 14)]
+    rng = np.random.default_rng(H + L)
+    w = custom_workload(rng, [g[0] for g in graphs], 3, H, L, k, 1, wd)
+    w.n_edges = np.array([len(g[1]) for g in graphs], np.int32)
+    w.edge_src, w.edge_dst = np.concatenate([g[1] for g in graphs]), np.concatenate([g[2] for g in graphs])
+    ref = oracle.forward_workload(w, n_threads=8)
+    assert_rows_close(run_library(w)["emb"], ref["emb"], H, f"H {H} L {L} k {k} {wd}")
+    _compare(w, f"H {H} L {L} k {k} {wd}")
