@@ -326,14 +326,14 @@ __global__ __launch_bounds__(kThreads) void k_classes(GraphView gv,
 }
 
 // ------------------------------------------------------------------ step 3: pooling
-// Workgroup (chunk c, graph b) handles a contiguous slice of the graph's nodes; in a launch of three workgroups deep,
-// workgroup z of them only the nodes of set z.  Nodes are
+// Workgroup (chunk c, graph b) handles a contiguous slice of the graph's nodes; with SIDE there are three of them, and
+// workgroup z takes only the nodes of set z.  Nodes are
 // bucketed by set (in node order, so the summation order is fixed), pushed through that
 // set's l network in tiles, and summed per (set, device group) into LDS accumulators.
 // Partial sums go to partial[b][c][3G][H]; the head kernel adds the chunks in order.
 constexpr int kSub = 256;   // nodes classified at a time
 
-template <int RPT>
+template <int RPT, bool SIDE>
 __global__ __launch_bounds__(kThreads) void k_pool_generic(GraphView gv, ModelView mv,
                                                            const float *__restrict__ emb,
                                                            const uint8_t *__restrict__ reach,
@@ -349,7 +349,7 @@ __global__ __launch_bounds__(kThreads) void k_pool_generic(GraphView gv, ModelVi
     __shared__ int s_dev[kTile];
     const int H = mv.H, G = mv.G, D = mv.D, L = mv.L;
     const int b = blockIdx.y, c = blockIdx.x, tid = threadIdx.x;
-    const int set_begin = gridDim.z == 1 ? 0 : blockIdx.z, set_end = gridDim.z == 1 ? 3 : set_begin + 1;
+    const int set_begin = SIDE ? blockIdx.z : 0, set_end = SIDE ? set_begin + 1 : 3;
     if (c == 0 && set_begin == 0 && tid == 0) head_done[b] = 0;        // for this pass's head
     const int n0 = gv.node_off[b], n_b = gv.node_off[b + 1] - n0;
     int chunks = (n_b + kPoolChunk - 1) / kPoolChunk;
@@ -509,15 +509,24 @@ void launch_pool_generic(const GraphView &gv, const ModelView &mv, const Workspa
     // A tile of nodes is a chain of loads through l's layers: few graphs take their sets side by side, as long as there is
     // a compute unit for each workgroup; many fill the chip with one workgroup per slice (forward pass, random graphs
     // of 32 nodes, H = 8, one workgroup / side by side: 1 graph 30.6 / 28.3 us, 64 graphs 35.7 / 32.8, 128 graphs
-    // 36.3 / 37.9, 1024 graphs 89 / 105; layered graphs, H = 48: 16 graphs 366 / 357, 64 graphs 387 / 396).
+    // 36.3 / 37.9, 1024 graphs 89 / 105; layered graphs, H = 48: 16 graphs 366 / 357, 64 graphs 387 / 396).  Wide networks
+    // read more weights per tile, and share the L2 caches to do it: their line is lower (layered graphs, H = 256: 16 graphs 3884 /
+    // 3713, 24 graphs 3834 / 3956; random graphs, H = 128: 40 graphs 434 / 419, 56 graphs 440 / 453).
     const int64_t slices = gv.B + gv.n_tot / kPoolChunk;      // about
-    const unsigned sets = 3 * slices <= 256 ? 3 : 1;
-#define CALL(R)                                                                              \
-    allow_lds(k_pool_generic<R>, lds);                                                       \
-    hipLaunchKernelGGL(k_pool_generic<R>, dim3(ws.n_chunks, gv.B, sets), dim3(kThreads), lds, s, gv, mv, \
+    const bool side = 3 * slices <= (mv.H <= 64 ? 256 : 160);
+#define LAUNCH(R, SIDE, SETS)                                                                      \
+    allow_lds(k_pool_generic<R, SIDE>, lds);                                                       \
+    hipLaunchKernelGGL((k_pool_generic<R, SIDE>), dim3(ws.n_chunks, gv.B, SETS), dim3(kThreads), lds, s, gv, mv, \
                        ws.emb, ws.reach, fa.placement, fa.cur_node, ws.partial, ws.n_chunks, ws.head_done)
+#define CALL(R)                        \
+    if (side) {                        \
+        LAUNCH(R, true, 3);            \
+    } else {                           \
+        LAUNCH(R, false, 1);           \
+    }
     PL_DISPATCH_RPT(pick_rpt(mv.H), CALL)
 #undef CALL
+#undef LAUNCH
 }
 
 }  // namespace pl

@@ -8,7 +8,7 @@ from gpu_common import custom_workload, run_library
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("D,H,group,n", [(2, 8, 1, 32), (3, 17, 0, 1), (4, 48, 1, 300)])
+@pytest.mark.parametrize("D,H,group,n", [(2, 8, 1, 32), (3, 17, 0, 1), (4, 48, 1, 300), (3, 100, 1, 200), (2, 256, 1, 140)])
 def test_same_bits_beside_few_and_many_graphs(D, H, group, n):
     rng = np.random.default_rng(H + n)
     one = custom_workload(rng, [n], D, H, 2, 1, group)
