@@ -29,7 +29,7 @@
 //   * A child that becomes runnable on an idle device starts from the registers that its record was
 //     read into.
 // About 80 instructions per event.  256 NASNet-like graphs (3124 nodes, 8 devices, about 7300 events
-// each): 2.30 ms; 2.65 ms with the destinations found by the handler and items moved through scalar registers; 4.56 ms with
+// each): 2.31 ms; 2.65 ms with the destinations found by the handler and items moved through scalar registers; 4.56 ms with
 // lane-masked queues, a transfer record per transfer and every read on the chain.
 //
 // Timestamps are float32 with one rounding per operation (no fused multiply-add), and events
@@ -158,19 +158,47 @@ __global__ __launch_bounds__(kSimThreads) void k_simulate(GraphView gv, int D, i
     for (int i = threadIdx.x; i < e; i += kSimThreads) cidx[i] = static_cast<uint16_t>(gv.nbr_idx[1][e0 + i] - n0);
     __syncthreads();
     if constexpr (!PC) {
-        for (int v = threadIdx.x; v < n; v += kSimThreads) {
+        // A thread per operation, until every other device has been found.  A list of more than kWide children goes to the
+        // whole wave, 64 children at a time: the walk of one thread is two dependent reads per child (a node of 5000 children:
+        // 400 us of 2240, 8 now; of 130: 11 of 125).
+        constexpr uint32_t kWide = 64;
+        const uint32_t all = (1u << D) - 1u | 1u << kNoDev;    // (a child that is not there needs no transfer)
+        const uint32_t lane = threadIdx.x & 63u;
+        for (int v0 = static_cast<int>(threadIdx.x - lane); v0 < n; v0 += kSimThreads) {
+            const uint32_t v = min(static_cast<uint32_t>(v0) + lane, none);
             const uint32_t kids = rec[v].z, listed = kids & kList;
             const uint32_t c0 = kids & kIdMask, cnt = listed ? (kids & ~kList) >> kIdBits : 2u;
-            uint32_t sent = 1u << (node[v] & kNoDev) | 1u << kNoDev, m = 0, cross = 0;    // (a child that is not there needs none)
-            for (uint32_t i = 0; i < cnt; ++i) {
-                const uint32_t c = listed ? cidx[c0 + i] : (i == 0 ? c0 : kids >> kIdBits), pd = node[c] & kNoDev;
-                if ((sent >> pd) & 1u) continue;
-                sent |= 1u << pd;
-                if (m < 2) cross |= pd << (5 + 5 * m);
-                if (listed) xl[c0 + m] = static_cast<uint16_t>(pd);
-                ++m;
+            const uint32_t own = 1u << (node[v] & kNoDev) | 1u << kNoDev;
+            if (cnt <= kWide) {
+                uint32_t sent = own, m = 0, cross = 0;
+                for (uint32_t i = 0; i < cnt && sent != all; ++i) {
+                    const uint32_t c = listed ? cidx[c0 + i] : (i == 0 ? c0 : kids >> kIdBits), pd = node[c] & kNoDev;
+                    if ((sent >> pd) & 1u) continue;
+                    sent |= 1u << pd;
+                    if (m < 2) cross |= pd << (5 + 5 * m);
+                    if (listed) xl[c0 + m] = static_cast<uint16_t>(pd);
+                    ++m;
+                }
+                link_of(v)[1] = static_cast<uint16_t>(cross | m);
             }
-            link_of(static_cast<uint32_t>(v))[1] = static_cast<uint16_t>(cross | m);
+            for (unsigned long long wide = __ballot(cnt > kWide); wide != 0ull; wide &= wide - 1ull) {
+                const uint32_t l = static_cast<uint32_t>(__builtin_ctzll(wide)), w = static_cast<uint32_t>(v0) + l;
+                const uint32_t w0 = get(c0, l), w_cnt = get(cnt, l);
+                uint32_t sent = get(own, l), m = 0, cross = 0;
+                for (uint32_t base = 0; base < w_cnt && sent != all; base += 64) {
+                    const uint32_t i = base + lane, pd = i < w_cnt ? node[cidx[w0 + i]] & kNoDev : kNoDev;
+                    unsigned long long rest = __ballot(!((sent >> pd) & 1u));
+                    while (rest != 0ull) {                    // destinations in the order of their first child
+                        const uint32_t d = get(pd, static_cast<uint32_t>(__builtin_ctzll(rest)));
+                        rest &= ~__ballot(pd == d);
+                        sent |= 1u << d;
+                        if (m < 2) cross |= d << (5 + 5 * m);
+                        if (lane == 0) xl[w0 + m] = static_cast<uint16_t>(d);
+                        ++m;
+                    }
+                }
+                if (lane == 0) link_of(w)[1] = static_cast<uint16_t>(cross | m);
+            }
         }
         __syncthreads();
     }
@@ -276,6 +304,10 @@ __global__ __launch_bounds__(kSimThreads) void k_simulate(GraphView gv, int D, i
     hr = rec[head];
 
     const uint32_t max_events = static_cast<uint32_t>(n + e + 8);   // every operation and transfer ends once
+    // The loop begins on a boundary of 32 bytes: a single wave waits for its instructions, and where the loop's branches lie
+    // within the lines that it fetches moves the whole simulation by 5 % (256 NASNet-like graphs: 2.31 to 2.43 ms over the
+    // eight places that four-byte instructions can have).
+    asm volatile(".p2align 5");
     do {
         // ---- next event: smallest (timestamp, creation number).  Timestamps are >= 0, so their
         // bit patterns order like the values.

@@ -61,3 +61,30 @@ def test_graphs_at_the_size_limit(n, e, per_child):
     pairs = np.array(sorted(pairs))
     w = _workload([(n, pairs[:, 0], pairs[:, 1])], 8, rng, ties=False)
     _check(w, per_child)
+
+
+@pytest.mark.parametrize("per_child", [0, 1])
+@pytest.mark.parametrize("D", [1, 2, 16])
+def test_nodes_of_thousands_of_children(D, per_child):
+    """A node whose children are all on its own device, all on one other, spread, or on one other device except for the last
+    few, which are the only ones on theirs; lists of one wave more or less, several of them in a graph."""
+    rng = np.random.default_rng(D)
+
+    def hubs(counts):
+        src, dst, n = [], [], len(counts)
+        for hub, kids in enumerate(counts):
+            src += [hub] * kids
+            dst += list(range(n, n + kids))
+            n += kids
+        return n, np.array(src), np.array(dst)
+
+    graphs = [hubs(c) for c in ((5000,), (5000,), (5000,), (4999,), (64, 65, 63, 129, 0, 1, 2, 3, 64, 1500))]
+    w = _workload(graphs, D, rng, ties=D == 2)
+    off = np.concatenate([[0], np.cumsum(w.n_nodes)])
+    w.placement[off[0]:off[1]] = 0
+    w.placement[off[1]] = 0
+    w.placement[off[1] + 1:off[2]] = D - 1
+    w.placement[off[3]:off[4]] = D // 2
+    w.placement[off[3]] = 0
+    w.placement[off[4] - min(D, 7):off[4]] = np.arange(min(D, 7))
+    _check(w, per_child)
