@@ -31,7 +31,6 @@ namespace pl {
 
 namespace {
 
-typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4;
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int CH = kChunkRows, RING = kRing;

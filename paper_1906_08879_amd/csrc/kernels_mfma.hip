@@ -138,21 +138,7 @@ __global__ __launch_bounds__(64 * sweep_waves(H), 2) void k_sweep_mfma(SweepPara
     constexpr int kZeroSlot = kMsgSlots;
     static_assert(NTL % NW == 0, "column tiles must divide over the waves");
     static_assert(TPW == 2, "a lane owns two neighbouring output columns");
-#ifndef PL_SINK_STORES
-#define PL_SINK_STORES 0
-#endif
-    constexpr bool kSinkStores = PL_SINK_STORES;
-#ifndef PL_UNCOND_T1
-#define PL_UNCOND_T1 0
-#endif
-    // What a later chunk's second row tile needs is loaded whether or not that chunk has one
-    // (its records then name the all-zero rows): no branch splits the code of a layer.  The
-    // reverse pass, which loads four values per row and column tile, keeps the test.
-    constexpr bool kLoadTile1Always = PL_UNCOND_T1;
-#ifndef PL_SPLIT_KINDS
-#define PL_SPLIT_KINDS (!BW)
-#endif
-    constexpr bool kSplitKinds = PL_SPLIT_KINDS;
+    constexpr bool kSplitKinds = !BW;          // chunks of one and of two row tiles as code of their own
     // A forward sweep writes what the next layer waits for to LDS before it stores to HBM; the
     // variants that keep activations or feed another sweep have no registers to hold the values
     // meanwhile.
@@ -577,13 +563,9 @@ __global__ __launch_bounds__(64 * sweep_waves(H), 2) void k_sweep_mfma(SweepPara
             // wc0 + 16 t + col, the three partial products in rows 0..2 of its accumulators.
             // Row tile 0 is handled by code common to both kinds of chunk, so that its stores
             // are on every path (see sink_row).
-            // `dead`: the row tile is beyond the chunk's rows (a chunk of one tile): nothing is
-            // computed for it, but its global stores are issued all the same (to the sink rows),
-            // so that both kinds of chunk leave the same number of stores behind every load.
-            auto epilogue = [&](int ct, auto deadc) __attribute__((always_inline)) {
-                constexpr bool dead = decltype(deadc)::value;
+            auto epilogue = [&](int ct) __attribute__((always_inline)) {
                 const int r = ct * kTileNodes + kg;
-                const bool live = !dead && r < rows;
+                const bool live = r < rows;
                 const int v_emb = live ? vg0[ct] : gv.n_tot;
                 const int v_msg = live ? vg0[ct] : sink_row;
                 // row of this node in the kept / delta array `slot` (unused rows: the spare row)
@@ -593,27 +575,20 @@ __global__ __launch_bounds__(64 * sweep_waves(H), 2) void k_sweep_mfma(SweepPara
                 };
                 float yv[TPW], ypre[TPW];
 #pragma unroll
-                for (int t = 0; t < TPW; ++t) yv[t] = dead ? 0.0f : acc[ct][t][0] + acc[ct][t][1] + acc[ct][t][2];
+                for (int t = 0; t < TPW; ++t) yv[t] = acc[ct][t][0] + acc[ct][t][1] + acc[ct][t][2];
                 if constexpr (BW) {
                     // delta slot of this layer's gated output: f's layers L-2 .. 0, then g's
                     // layers L-1 .. 0; slot = index into the 2L delta arrays (f first)
                     if (n == 0) {
-                        float g[TPW];
-#pragma unroll
-                        for (int t = 0; t < TPW; ++t) g[t] = dead ? 0.0f : gs0[ct][t];
-                        store_cols(dlt, delta_at(L - 1), g);
+                        store_cols(dlt, delta_at(L - 1), gs0[ct]);
                     }
                     auto gate = [&](int bit) __attribute__((always_inline)) {
-                        if constexpr (!dead) {
 #pragma unroll
-                            for (int t = 0; t < TPW; ++t) yv[t] = (mC[ct][t] & bit) ? yv[t] : 0.0f;
-                        }
+                        for (int t = 0; t < TPW; ++t) yv[t] = (mC[ct][t] & bit) ? yv[t] : 0.0f;
                     };
                     if (n == L - 1) {                // end of f^T: ds_v = outside gradient + f path
-                        if constexpr (!dead) {
 #pragma unroll
-                            for (int t = 0; t < TPW; ++t) yv[t] += FF ? x0[ct][t] : xC[ct][t];
-                        }
+                        for (int t = 0; t < TPW; ++t) yv[t] += FF ? x0[ct][t] : xC[ct][t];
                         store_cols(P.emb, static_cast<uint32_t>(v_emb * 2 * H + (1 - dir) * H), yv);
                         gate(4);
                         store_cols(dlt, delta_at(L + L - 1), yv);
@@ -626,27 +601,25 @@ __global__ __launch_bounds__(64 * sweep_waves(H), 2) void k_sweep_mfma(SweepPara
                     }
                     if (n == NL - 1) {               // end of g^T: da_v
                         store_cols(msg, static_cast<uint32_t>(v_msg * H), yv);
-                        if constexpr (!dead) store_cols(msgtab, static_cast<uint32_t>((ring * CH + r) * LDM), yv);
+                        store_cols(msgtab, static_cast<uint32_t>((ring * CH + r) * LDM), yv);
                     }
-                    if constexpr (!dead) {
-                        if (n < NL - 1) put_rows((n + 1) & 1, r, yv);
-                    }
+                    if (n < NL - 1) put_rows((n + 1) & 1, r, yv);
                     return;
                 }
 #pragma unroll
                 for (int t = 0; t < TPW; ++t) {
                     float y = yv[t];
-                    if constexpr (!dead) y = fmaxf(y + bias_n[t], 0.0f);
-                    if constexpr (TR && !dead) {
+                    y = fmaxf(y + bias_n[t], 0.0f);
+                    if constexpr (TR) {
                         const int bit = n == NL - 1 ? 1 : (n == L - 1 ? 4 : (n == 0 ? 8 : 2));
                         gate_bits[ct][t] = (n == 0 ? 0 : gate_bits[ct][t]) | (y > 0.0f ? bit : 0);
                     }
                     ypre[t] = y;
                     if (n == L - 1) {                    // end of g: residual update of s_v
-                        if constexpr (!dead) y += FF ? x0[ct][t] : xC[ct][t];
+                        y += FF ? x0[ct][t] : xC[ct][t];
                     }
                     if (n == NL - 1) {                   // end of f: the message of v, flagged
-                        const uint32_t flag = (!dead && (bit0[ct] | (vg0[ct] == cur))) ? 0x80000000u : 0u;
+                        const uint32_t flag = (bit0[ct] | (vg0[ct] == cur)) ? 0x80000000u : 0u;
                         y = __uint_as_float(__float_as_uint(y) | flag);
                     }
                     yv[t] = y;
@@ -658,11 +631,8 @@ __global__ __launch_bounds__(64 * sweep_waves(H), 2) void k_sweep_mfma(SweepPara
                         // the output of g's last layer is only ever needed as a gate
                         if (n < NL - 1 && n != L - 1) store_cols(dlt, delta_at(1 + n), ypre);
                         if (n == NL - 1) {
-                            int gb[TPW];
-#pragma unroll
-                            for (int t = 0; t < TPW; ++t) gb[t] = dead ? 0 : gate_bits[ct][t];
-                            store_gates(gates_out, live ? static_cast<uint32_t>(vg0[ct] * H)
-                                                        : static_cast<uint32_t>((2 - dir) * gv.n_tot * H), gb);
+                                store_gates(gates_out, live ? static_cast<uint32_t>(vg0[ct] * H)
+                                                        : static_cast<uint32_t>((2 - dir) * gv.n_tot * H), gate_bits[ct]);
                         }
                     }
                     if (n == L - 1) {
@@ -675,13 +645,11 @@ __global__ __launch_bounds__(64 * sweep_waves(H), 2) void k_sweep_mfma(SweepPara
                 // What the next layer (or the next chunk's gather) waits for goes to LDS; where the
                 // registers allow, before the stores to HBM, which then follow while the LDS
                 // writes complete.
-                if constexpr (!dead) {
-                    if (n < NL - 1)
-                        put_rows((n + 1) & 1, r, yv);
-                    else
-                        store_cols(msgtab, static_cast<uint32_t>((ring * CH + r) * LDM), yv);
-                    if constexpr (kLdsFirst) __builtin_amdgcn_sched_barrier(0);
-                }
+                if (n < NL - 1)
+                    put_rows((n + 1) & 1, r, yv);
+                else
+                    store_cols(msgtab, static_cast<uint32_t>((ring * CH + r) * LDM), yv);
+                if constexpr (kLdsFirst) __builtin_amdgcn_sched_barrier(0);
                 if constexpr (kLdsFirst) hbm_stores();
             };
 
@@ -694,7 +662,7 @@ __global__ __launch_bounds__(64 * sweep_waves(H), 2) void k_sweep_mfma(SweepPara
                     // a far source reads the row of zeros.  The messages were stored by this wave
                     // at least kRing - 1 chunks ago; see the note at the top of the file.
                     const uint32_t info2 = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(rB[0][3])));
-                    const bool two2 = kLoadTile1Always || rows_of(info2) > kTileNodes;
+                    const bool two2 = rows_of(info2) > kTileNodes;
                     float dterm[NT][TPW];
                     if constexpr (FF) {
 #pragma unroll
@@ -727,7 +695,7 @@ __global__ __launch_bounds__(64 * sweep_waves(H), 2) void k_sweep_mfma(SweepPara
                 // per row and chunk, and a load queued behind a layer's stores returned too late for
                 // the next chunk (2.35 -> 2.22 ms; no change for the forward sweeps).
                 if (n == ((NL > 2 && !BW) ? 1 : 0)) {
-                    const bool two1 = kLoadTile1Always || rows1 > kTileNodes;
+                    const bool two1 = rows1 > kTileNodes;
 #pragma unroll
                     for (int ct = 0; ct < NT; ++ct) {
                         rC[ct] = load_rec(c + 3, ct);
@@ -770,11 +738,8 @@ __global__ __launch_bounds__(64 * sweep_waves(H), 2) void k_sweep_mfma(SweepPara
             }
             mid_block();
 
-            epilogue(0, std::false_type{});
-            if constexpr (kind == 0 && kSinkStores)
-                epilogue(1, std::true_type{});
-            else if (two)
-                epilogue(1, std::false_type{});
+            epilogue(0);
+            if (two) epilogue(1);
 
             // The table rows that chunk c + 1 sums were all written by this wave (its own
             // columns), so its gather follows without a barrier.
