@@ -135,10 +135,16 @@ int pl_weights_create(const pl_model_cfg *cfg, const float *host_blob, size_t n_
                       pl_weights **out);
 int pl_weights_destroy(pl_weights *w);                  /* NULL is accepted */
 
-/* Kernel selection for forward passes that use `w`: 0 (default) = the fastest kernels that
- * cover the configuration (matrix-core sweeps for H in {32, 64, 128} with bf16 weights,
- * H in {32, 64} with fp32 weights, n_layers <= 2); 1 = the generic fp32 kernels, which
- * cover every supported configuration.  Both compute the same function. */
+/* Kernel selection for passes that use `w`: 0 (default) = the fastest kernels that cover the
+ * configuration; 1 = the generic fp32 kernels, which cover every supported configuration.  Both
+ * compute the same function.  With n_layers <= 2 the message passing of path 0 runs
+ *   - as fp32 multiply-adds in a wave's lanes for H in {8, 16}, and with fp32 weights for H = 32 in
+ *     batches of at most 256 graphs and, with one layer, for H = 64 in batches of at most 128;
+ *   - on matrix cores for H in {32, 64} otherwise, and for H = 128 with bf16 weights;
+ * and in the generic kernels in every other case.  The kernels take their fp32 sums in different
+ * orders.  A graph's embeddings, pooled sums and logits are the same bits whatever else is in its
+ * batch, except on the two sides of those limits: there they agree to rounding (logits to about
+ * 2e-7 of their 2-norm). */
 int pl_weights_set_path(pl_weights *w, int32_t path);
 
 /* ---- the forward pass (Section 2.2 steps 1-3 + policy head, Appendix A.7).

@@ -340,7 +340,7 @@ int ensure_grad_workspace(pl_graph_batch *g, const ModelView &mv, hipStream_t s)
     PL_HIP(take(&gw.fact, 2 * L * NH));
     PL_HIP(take(&gw.gact, 2 * L * NH));
     PL_HIP(take(&gw.agg, 2 * NH));
-    // the matrix-core chain kernel reads row 2 n of dagg as an all-zero row and stores the rows
+    // the chain kernels other than the generic one read row 2 n of dagg as an all-zero row and store the rows
     // of unused chunk slots to row 2 n + 1, to row n of demb and to the spare floats of dfg
     PL_HIP(take(&gw.dagg, 2 * NH + 2 * H));
     launch_fill_zero(gw.dagg + 2 * NH, 2 * H, s);
@@ -510,7 +510,7 @@ int forward_impl(pl_graph_batch *g, const float *node_feats, const int32_t *plac
     StageTimer &timer = static_ws ? off : g->timer;
     ForwardArgs fa{node_feats, placement, cur_node, out_logits, out_probs, out_pooled, keep_hin, keep_hact};
     const GraphView &gv = g->view;
-    // the matrix-core sweep addresses its buffers with 32-bit offsets
+    // the sweeps other than the generic one address their buffers with 32-bit offsets
     const bool fits32 = (static_cast<double>(g->host.n_tot) + 2) * 2 * mv.H * sizeof(float) < 4.0e9;
     const bool fast = w->path == 0 && w->cfg.k_sweeps > 0 && fits32;
     const bool lanes = fast && sweep_lanes_preferred(mv.H, mv.L, gv.B, w->cfg.weight_dtype), mfma = fast && !lanes && w->d_wfrag;

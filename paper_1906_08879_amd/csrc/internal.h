@@ -104,8 +104,8 @@ struct Workspace {
     unsigned char *base = nullptr;  // the one allocation that holds every buffer but reach (null: not owned)
     float *emb = nullptr;       // [n_tot, 2H]  [td ; bu]
     float *msg = nullptr;       // [2, n_tot, H]
-    float *xb = nullptr;        // [2, n_tot, H]  sweep input in bucket order (matrix-core path)
-    float4 *featb = nullptr;    // [n_tot] raw-feature records in node order (matrix-core path)
+    float *xb = nullptr;        // [2, n_tot, H]  input of sweeps after the first, in bucket order (not on the generic path)
+    float4 *featb = nullptr;    // [n_tot] raw-feature records in node order (sweep of 128 columns)
     uint8_t *reach = nullptr;   // [2, n_tot]   0: descendant-of-v* bit, 1: ancestor-of-v* bit
     float *partial = nullptr;   // [B, n_chunks_max, 3G, H] pooling partial sums
     // for the reverse pass (null: not kept)
@@ -287,7 +287,7 @@ void launch_sweep_tiles_bw(const GraphView &gv, const ModelView &mv, const uint4
                           int WS, const int32_t *cur_node, float *demb, float *dagg, uint8_t *mask4,
                           float *delta, size_t delta_stride, hipStream_t s);
 
-// ---- matrix-core sweep (kernels_mfma.hip)
+// ---- matrix-core sweep (kernels_mfma.hip: 128 columns; hands 32 and 64 on)
 bool sweep_mfma_supported(int H, int L, int weight_dtype);
 void pack_sweep_weights(const ModelView &mv, const float *blob, int WS, std::vector<uint16_t> *frag,
                         std::vector<float> *bias, bool reverse = false);

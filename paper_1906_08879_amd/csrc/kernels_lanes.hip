@@ -12,17 +12,18 @@
 //     through DPP from lane k of its row of sixteen (row_newbcast), so a layer is H multiply-adds in fp32 and
 //     nothing else; the sixteen lanes of the other halves of a wider row come over by v_permlane16_swap /
 //     v_permlane32_swap.  97 ns a layer at H = 32, 196 at H = 64, 53 at H = 8 (a wave per SIMD, micro-benchmark).
-//     A chunk is issue-bound from there: about 170 of its 280 instructions are the layers' (H = 32, L = 2).
+//     That is 0.4 of a chunk's 1 us (H = 32, L = 2): about 170 of the 280 instructions of a wave with rows are the
+//     layers'.  Waves issue in 0.45 of their cycles and wait for memory or LDS in 0.09; the rest is barriers and
+//     instructions that need the result before them (SQ counters).
 //   * Two LDS barriers per chunk: one between the messages that a chunk leaves in the table and the sums of the
 //     next chunk, one that keeps a wave from overwriting a table row which another wave still sums.
 // The chunk plan (plan.cpp), the table of the last kRing chunks' messages, far messages, the reachability flag
 // in a message's sign bit and the rows that take the stores of unused chunk rows are those of kernels_mfma.hip; but
 // a wave owns rows here, not columns, so the far message that it reads is another wave's (message_barrier).
-// Everything a chunk needs from HBM is requested two chunks ahead, records four: a chunk takes about half a
-// microsecond, less than a load from HBM.
+// Everything a chunk needs from HBM is requested two chunks ahead, records four.
 //
 // Forward sweep of 64 layered graphs of 200 nodes (H = 32, L = 2, 40 chunks): 66.9 us on matrix cores, 40 here;
-// one random graph of 32 nodes (H = 8): 35.6 us by the generic kernel, 8 here.
+// one random graph of 32 nodes (H = 8): 35.6 us by the generic kernel, 9.5 here (kernel traces).
 #include <type_traits>
 
 #include "internal.h"
@@ -571,12 +572,13 @@ __global__ __launch_bounds__(64 * lane_waves(H), 2) void k_sweep_lanes(LaneParam
 }  // namespace
 
 // Where these kernels are the faster ones.  H = 8, 16: everywhere (the generic kernel: random graphs of 32 nodes, 1 graph
-// 35.6 -> 8 us, a forward pass of 4096 graphs 497 -> 290 us).  H = 32 and 64 as long as all workgroups of a batch are
+// 35.6 -> 9.5 us, a forward pass of 4096 graphs 497 -> 290 us).  H = 32 and 64 as long as all workgroups of a batch are
 // on the chip at once, two of four waves or one of eight to each of 256 compute units (forward pass, against the
 // matrix-core sweep, whose workgroups are smaller: Inception-like graphs, H = 32, 256 graphs 294 -> 250 us, 320 graphs
 // 310 -> 386; NMT-like graphs, H = 64, one layer, 128 graphs 552 -> 458 us, 160 graphs 607 -> 832), and with fp32
 // weights: bf16 weights take a third of the matrix instructions, and their sums round less often than these here (H = 64:
-// states 1.1e-7 from float64 against 1.3e-7; with fp32 weights 1.5e-7 against 1.3e-7).
+// states 1.1e-7 from float64 against 1.3e-7; with fp32 weights 1.5e-7 against 1.3e-7).  The two kernels take their sums in
+// different orders, so at H = 32 and 64 the last bits of a graph's results depend on the size of its batch.
 bool sweep_lanes_preferred(int H, int L, int B, int weight_dtype)
 {
     if (L < 1 || L > 2) return false;

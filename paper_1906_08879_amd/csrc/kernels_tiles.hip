@@ -4,9 +4,9 @@
 // split exactly into three bf16 parts as three rows of A, weights (split likewise where they are fp32) as B operands in
 // registers, a wave owns sixteen output columns from end to end, A rows cross waves through LDS, a barrier per layer; so
 // are the chunk plan, the table of the last kRing chunks' messages, the sign bit that carries reachability, the spare
-// rows, and the meaning of FF, WX, BW and TR.  A wave has one column tile here and registers to spare, and the time
-// of a chunk went elsewhere (64 columns, cycles per chunk: 900 in the sum of the next chunk's sources, 700 in issuing
-// its loads, 500 in matrix instructions).  Hence:
+// rows, and the meaning of FF, WX, BW and TR.  A wave has one column tile here and registers to spare, and in the kernel
+// that served all widths the sum of the next chunk's sources and the issue of its loads took longer than the matrix
+// instructions.  Hence:
 //   * No register that a load is still filling is ever copied: four sets of records and two of everything else keep
 //     their places in a loop over four chunks, and all is requested two chunks ahead of its use, records four.
 //   * A row with a list of sources (the attention of a translation model: 41 of them, 7400 cycles) forms the byte offsets of
@@ -16,6 +16,8 @@
 //   * The sum of a chunk with one row tile and one near source per row, the usual one, is code without a taken branch.
 // Forward pass, 64 NMT-like graphs 665 -> 567 us, 128 Inception-like ones 318 -> 290 us; 512 of those 741 -> 690 us.
 // What is left of a chunk is its four dependent layers (LDS, six matrix instructions, epilogue, barrier: 450 cycles each).
+// Waves issue in 0.40 of their cycles, 0.20 are waits for memory or LDS, the matrix cores are busy in 0.08 of the chip's
+// (SQ counters, 64 NMT-like graphs on a quarter of it).
 #include <type_traits>
 
 #include "internal.h"

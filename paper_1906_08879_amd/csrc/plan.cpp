@@ -1,4 +1,4 @@
-// Host-side gather plan for the matrix-core sweep kernel.
+// Host-side gather plan of the sweep kernels (kernels_lanes.hip, kernels_tiles.hip, kernels_mfma.hip).
 //
 // The sweep (Section 2.2 step 2) visits a graph level by level; a level is cut into chunks
 // of at most kChunkRows nodes.  The kernel keeps the messages of the last kRing chunks in an

@@ -1,5 +1,5 @@
-// Chunk plan of the matrix-core sweep kernel: constants and records shared by the host builder
-// (plan.cpp) and the kernel (kernels_mfma.hip).
+// Chunk plan of the sweep kernels: constants and records shared by the host builder (plan.cpp) and the
+// kernels (kernels_lanes.hip, kernels_tiles.hip, kernels_mfma.hip).
 #pragma once
 #include <hip/hip_runtime.h>
 
@@ -10,7 +10,7 @@ namespace pl {
 
 struct HostLayout;
 
-// ---- gather plan of the matrix-core sweep kernel (plan.cpp)
+// ---- gather plan (plan.cpp)
 constexpr int kChunkRows = 8;    // nodes per chunk: two MFMA row tiles of four nodes
 constexpr int kRing = 4;         // chunks whose messages stay in the LDS table
 constexpr int kMaxNear = 5;      // table slots held in a row record (6 bits each)

@@ -14,7 +14,7 @@ bool workspace_fits(const Workspace &ws, const ModelView &mv) { return ws.H == m
 // may be null: then only the size is computed) and returns the block's size in bytes.  Every
 // buffer starts on a 256-byte boundary.  With `with_reach` the reachability bytes are part of
 // the block, otherwise ws->reach is left alone.
-// Rows past the data (matrix-core sweep): emb row n, msg row 2n + 1, xb row 2n and reach byte
+// Rows past the data (the sweeps that walk chunks: all but the generic one): emb row n, msg row 2n + 1, xb row 2n and reach byte
 // 2n + 1 take the stores of a chunk's unused rows; msg row 2n and reach byte 2n are never
 // written, must read as zero, and are the target of dummy loads.
 size_t carve_workspace(unsigned char *base, size_t n, size_t B, const ModelView &mv, bool with_reach, Workspace *ws)

@@ -111,8 +111,7 @@ def test_small_batches_of_the_workloads(name, B):
 @pytest.mark.parametrize("H,wd", [(32, "fp32"), (64, "bf16"), (128, "bf16")])
 def test_dense_graphs_with_long_neighbour_lists(H, wd):
     """Nodes with dozens of parents and children: the reverse chain sums their gradients through
-    the overflow lists of the chunk plan (both list walks of the kernel: one and two column tiles
-    per wave)."""
+    the overflow lists of the chunk plan (the list walks of the three sweep kernels, one per case)."""
     rng = np.random.default_rng(40 + H)
     w = custom_workload(rng, [150, 90, 33], 4, H, 2, 1, 1, wd, p_edge=0.4, w_scale=0.05)
     _compare(w, f"dense graphs H={H} {wd}")
@@ -121,7 +120,7 @@ def test_dense_graphs_with_long_neighbour_lists(H, wd):
 @pytest.mark.parametrize("name", ["layered200", "nmt"])
 def test_generic_kernels_on_matrix_core_shapes(name):
     """pl_weights_set_path(1): the generic fp32 reverse-pass kernels on shapes that normally take
-    the matrix-core kernels meet the same bar, and the two paths agree closely."""
+    the faster kernels (layered200: chain in a wave's lanes) meet the same bar, and the two paths agree closely."""
     w = make_workload(name, B=2)
     actions, coeff, _ = _actions_and_coeff(w, 3)
     ref_grad, _ = og.gradient_workload(w, actions, coeff.astype(np.float64))
@@ -334,7 +333,8 @@ def test_empty_batch_is_accepted():
 def test_several_sweeps(D, H, L, k, wd):
     """k >= 2 repetitions of the message passing (Section 2.2 step 2): the sweeps are differentiated
     from the last to the first with the states and messages that the forward pass copied aside;
-    generic kernels, matrix-core chain, and matrix-core dense layers with the generic chain."""
+    generic kernels, chain in a wave's lanes, matrix-core chain, and matrix-core dense layers with
+    the generic chain."""
     rng = np.random.default_rng(7 * H + k)
     w = custom_workload(rng, [30, 1, 12, 45], D, H, L, k, 1, wd, w_scale=0.07)
     _compare(w, f"k={k} D={D} H={H} L={L} {wd}")

@@ -124,7 +124,7 @@ def test_node_sets_at_full_size_and_through_every_gather_path():
     """The same at the benchmark's launch shape (three graphs of the full NASNet batch checked,
     all of them pooled), with two sweeps (Section 2.2 step 2 repeated: the bits come from the
     first sweep), and on dense random DAGs whose rows go through the neighbour lists and the
-    staging of far sources in the matrix-core sweep kernel."""
+    far sources of the sweep kernels."""
     w = make_workload("nasnet")
     got = run_library(w, want_emb=False, want_class=True)
     for b in (0, w.B // 2, w.B - 1):
@@ -218,8 +218,9 @@ def test_pooling_on_the_widest_shape(D, L, group, sizes):
 
 @pytest.mark.parametrize("name", ["layered200", "nmt", "nasnet"])
 def test_generic_kernels_on_matrix_core_shapes(name):
-    """The generic fp32 kernels (pl_weights_set_path 1) on shapes the matrix-core kernels
-    normally take: same bar against the oracle, and both paths agree closely."""
+    """The generic fp32 kernels (pl_weights_set_path 1) on shapes the faster kernels normally
+    take (layered200: the sweep in a wave's lanes, pooling on matrix cores; the others: both on
+    matrix cores): same bar against the oracle for both paths."""
     w = make_workload(name, B=2)
     ref = oracle.forward_workload(w, n_threads=THREADS, want_emb=True)
     slow = run_library(w, path=1)
@@ -399,10 +400,12 @@ def test_forward_replays_from_a_hip_graph(name, B):
 
 @pytest.mark.parametrize("seed", range(12))
 def test_random_dags_through_the_matrix_core_kernels(seed):
-    """Random DAGs of many densities through every path of the matrix-core sweep and pooling
-    kernels: short and long row records, neighbour lists, more than eight and more than
+    """Random DAGs of many densities through every path of the sweep kernels and the matrix-core
+    pooling kernels: short and long row records, neighbour lists, more than eight and more than
     sixteen far sources per chunk, one and two row tiles, all three widths, both weight
-    formats, one to three sweeps."""
+    formats, one to three sweeps.  (One-layer fp32 networks of 32 and 64 columns, the fp32 seeds
+    here, run their sweeps in a wave's lanes; in batches large enough for the matrix-core sweep
+    they are in test_gpu_tiles.py.)"""
     rng = np.random.default_rng(1000 + seed)
     H = (32, 64, 128)[seed % 3]
     wd = "bf16" if (H == 128 or seed % 2) else "fp32"

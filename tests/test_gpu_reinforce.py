@@ -66,9 +66,9 @@ def test_one_policy_gradient_estimate_end_to_end(name, rollouts):
     term per decision (Appendix A.7 "Entropy")."""
     import torch
     import paper_1906_08879_amd as pl
-    if name == "ragged":     # graphs of different length on the matrix-core path (H = 32, fp32 weights)
+    if name == "ragged":     # graphs of different length, sweep in a wave's lanes, pooling on matrix cores (H = 32, fp32 weights)
         base_w = custom_workload(np.random.default_rng(8), [40, 25], 4, 32, w_scale=0.15)
-    else:                    # generic kernels (H = 8), three devices
+    else:                    # sweep in a wave's lanes, the rest generic (H = 8), three devices
         base_w = custom_workload(np.random.default_rng(9), [20, 14], 3, 8, w_scale=0.1)
     n_graphs = base_w.B
     w, group = _rollout_batch(base_w, rollouts)
