@@ -224,7 +224,11 @@ int pl_episode_step(pl_graph_batch *g, int32_t D, const float *logits, const flo
  * such steps).  Arguments as above, and
  *   uniforms     dev [n_steps, B]
  *   logits       dev [B, D], or [n_steps, B, D] when keep_logits != 0 (every step's logits)
- *   out_actions  dev [n_steps, B] or NULL;  out_logp  dev [n_steps, B] or NULL */
+ *   out_actions  dev [n_steps, B] or NULL;  out_logp  dev [n_steps, B] or NULL
+ * Small batches take several steps in one forward pass over all states that these steps can reach (at most 256
+ * graphs together), which leaves every result the same bits; the copies take up to 4 GiB of device memory, allocated
+ * on the first such call, kept by the batch and freed with it.  Where they cannot be had (no memory, or a stream that
+ * is being captured when they are not there yet) the steps go one by one. */
 int pl_episode_run(pl_graph_batch *g, const pl_weights *w, float *node_feats, int32_t *placement,
                    int32_t *cur_node, const int32_t *order, const float *uniforms, int32_t t0,
                    int32_t n_steps, float *logits, int32_t keep_logits, int32_t *out_actions,

@@ -86,6 +86,7 @@ struct pl_graph_batch {
     pl::GraphView view{};
     pl::Workspace ws;
     pl::GradWorkspace gw;
+    pl::EpisodeCopies ahead;
     // pl_simulate_reward: one block with peaks [B, sim_D], op_start, op_end [n_tot], arrival, arrival_last
     // [n_tot, sim_D], run times [B] and workgroup counters [B] (zero between calls)
     float *sim_start = nullptr, *sim_end = nullptr, *sim_arrival = nullptr, *sim_arrival_last = nullptr, *sim_rt = nullptr;
@@ -463,6 +464,9 @@ GraphExtent graph_extent(const HostLayout &h)
     return {static_cast<int>(n_max), static_cast<int>(e_max)};
 }
 
+// The sweeps other than the generic one address their buffers with 32-bit offsets.
+bool sweep_offsets_fit(double n_tot, int H) { return (n_tot + 2) * 2 * H * sizeof(float) < 4.0e9; }
+
 // StageMarks hook over a batch's timer: an event at the beginning and at the end of a stage.
 void stage_mark(void *ctx, int stage, bool begin, hipStream_t s)
 {
@@ -482,14 +486,14 @@ void stage_mark(void *ctx, int stage, bool begin, hipStream_t s)
 
 // static_ws: the intermediate buffers of a call that must not allocate (the batch is on the
 // device already, stage timing is off); otherwise the batch's own buffers are used, allocated on
-// the first call.
+// the first call.  copies: copies of the batch's graphs to take in its place, with their buffers.
 int forward_impl(pl_graph_batch *g, const float *node_feats, const int32_t *placement,
                  const int32_t *cur_node, const pl_weights *w, float *out_logits, float *out_probs,
                  float *out_node_emb, float *out_pooled, uint8_t *out_class, void *stream, bool validate,
                  float *keep = nullptr, size_t keep_stride = 0, float *keep_pool = nullptr,
                  bool *pool_kept = nullptr, float *snap_emb = nullptr, float *snap_msg = nullptr,
                  const Workspace *static_ws = nullptr, uint8_t *gates = nullptr, float *keep_hin = nullptr,
-                 float *keep_hact = nullptr)
+                 float *keep_hact = nullptr, const EpisodeCopies *copies = nullptr)
 {
     if (!g || !w) return fail(PL_ERR_NULL, "graph batch or weights handle is NULL");
     if (g->host.B == 0) return PL_OK;
@@ -501,18 +505,16 @@ int forward_impl(pl_graph_batch *g, const float *node_feats, const int32_t *plac
         (rc = validate_state(g, w->cfg.D, placement, cur_node, nullptr, false, s)))
         return rc;
     const ModelView &mv = w->view;
-    if (!static_ws) {
+    if (!static_ws && !copies) {
         if ((rc = ensure_on_device(g))) return rc;
         if ((rc = ensure_workspace(g, mv, s))) return rc;
     }
-    const Workspace &ws = static_ws ? *static_ws : g->ws;
+    const Workspace &ws = copies ? copies->ws : static_ws ? *static_ws : g->ws;
     StageTimer off;
     StageTimer &timer = static_ws ? off : g->timer;
     ForwardArgs fa{node_feats, placement, cur_node, out_logits, out_probs, out_pooled, keep_hin, keep_hact};
-    const GraphView &gv = g->view;
-    // the sweeps other than the generic one address their buffers with 32-bit offsets
-    const bool fits32 = (static_cast<double>(g->host.n_tot) + 2) * 2 * mv.H * sizeof(float) < 4.0e9;
-    const bool fast = w->path == 0 && w->cfg.k_sweeps > 0 && fits32;
+    const GraphView &gv = copies ? copies->view : g->view;
+    const bool fast = w->path == 0 && w->cfg.k_sweeps > 0 && sweep_offsets_fit(gv.n_tot, mv.H);
     const bool lanes = fast && sweep_lanes_preferred(mv.H, mv.L, gv.B, w->cfg.weight_dtype), mfma = fast && !lanes && w->d_wfrag;
     {
         // these sweeps compute x_v themselves from the raw features (first sweep)
@@ -568,6 +570,112 @@ int forward_impl(pl_graph_batch *g, const float *node_feats, const int32_t *plac
                               hipMemcpyDeviceToDevice, s));
     PL_HIP(hipGetLastError());
     return PL_OK;
+}
+
+// ---- steps of an episode taken ahead (kernels_episode.hip says why)
+constexpr int kAheadGraphs = 256;                                  // most graphs in all copies
+constexpr size_t kAheadBytes = static_cast<size_t>(4) << 30;       // most memory that they may take
+
+int64_t states_within(int D, int steps)   // states that fewer than `steps` steps can reach
+{
+    int64_t all = 0, at = 1;
+    for (int i = 0; i < steps; ++i, at *= D) all += at;
+    return all;
+}
+
+size_t carve_copies(unsigned char *base, size_t n, size_t B, int copies, const ModelView &mv, EpisodeCopies *c)
+{
+    size_t at = 0;
+    auto take = [&](size_t bytes) {
+        unsigned char *p = base ? base + at : nullptr;
+        at += (bytes + 255) / 256 * 256;
+        return p;
+    };
+    const size_t N = n * copies, G = B * copies;
+    c->view.node_off = reinterpret_cast<int32_t *>(take(sizeof(int32_t) * (G + 1)));
+    c->view.tmpl = reinterpret_cast<int32_t *>(take(sizeof(int32_t) * G));
+    c->view.node_graph = reinterpret_cast<int32_t *>(take(sizeof(int32_t) * N));
+    c->feats = reinterpret_cast<float *>(take(sizeof(float) * N * 3));
+    c->placement = reinterpret_cast<int32_t *>(take(sizeof(int32_t) * N));
+    c->cur_node = reinterpret_cast<int32_t *>(take(sizeof(int32_t) * G));
+    c->logits = reinterpret_cast<float *>(take(sizeof(float) * G * mv.D));
+    return at + carve_workspace(base ? base + at : nullptr, N, G, mv, true, &c->ws);
+}
+
+// How many steps of an episode one pass takes.  With S states in the copies of B graphs a pass takes about
+// 1 + S B / 512 times as long as a pass over the B graphs alone, as long as S B <= 256 (measured, us, 1 / 37 / 64 / 128 /
+// 256 graphs: Inception-like at H = 64 250 / 262 / 268 / 284 / 346, NASNet-like at H = 128 1455 / 1532 / 1543 / 1698 /
+// 2067, layered at H = 32 59 / 63 / 64 / 69 / 88, 32 nodes at H = 8 26 / 29 / 30 / 34 / 44); with more graphs than that
+// workgroups wait for each other (NASNet-like, 320 graphs: 3450, Inception-like 568).  The largest number of steps over
+// that time is taken: eight steps of one NASNet-like graph on eight devices go as 3 + 3 + 2.  Only for the sweeps that
+// walk a chunk plan, and only as far as the kernels stay the ones of the batch itself, so that a state's logits are the
+// same bits.
+int steps_ahead(const pl_graph_batch *g, const pl_weights *w, int n_steps)
+{
+    const ModelView &mv = w->view;
+    const int B = g->host.B;
+    const double n = static_cast<double>(g->host.n_tot);
+    if (w->path != 0 || w->cfg.k_sweeps == 0 || !sweep_offsets_fit(n, mv.H)) return 1;
+    const bool lanes = sweep_lanes_preferred(mv.H, mv.L, B, w->cfg.weight_dtype);
+    if (!lanes && !w->d_wfrag) return 1;
+    int best = 1;
+    double rate = 0.0;
+    for (int m = 1; m <= n_steps; ++m) {
+        const int64_t S = states_within(mv.D, m);
+        if (m > 1) {
+            if (S * B > kAheadGraphs || !sweep_offsets_fit(n * S, mv.H) ||
+                sweep_lanes_preferred(mv.H, mv.L, static_cast<int>(S * B), w->cfg.weight_dtype) != lanes)
+                break;
+            EpisodeCopies sized;
+            if (carve_copies(nullptr, static_cast<size_t>(n), B, static_cast<int>(S), mv, &sized) > kAheadBytes) break;
+        }
+        const double r = m / (1.0 + static_cast<double>(S * B) / 512.0);
+        if (r > rate) {
+            rate = r;
+            best = m;
+        }
+    }
+    // (as many passes as that takes, of equal length)
+    const int passes = (n_steps + best - 1) / best;
+    return (n_steps + passes - 1) / passes;
+}
+
+// Room for `copies` copies of the batch.  False where there is none (and then none is needed: steps go one by one):
+// no memory, or a stream that is being captured, which must not allocate.
+bool ensure_copies(pl_graph_batch *g, const ModelView &mv, int copies, hipStream_t s)
+{
+    EpisodeCopies &c = g->ahead;
+    if (c.base && c.copies == copies && c.D == mv.D && workspace_fits(c.ws, mv)) return true;
+    const size_t n = static_cast<size_t>(g->host.n_tot), B = static_cast<size_t>(g->host.B);
+    EpisodeCopies sized;
+    const size_t bytes = carve_copies(nullptr, n, B, copies, mv, &sized);
+    if (bytes > c.bytes) {
+        hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+        if (hipStreamIsCapturing(s, &capture) != hipSuccess || capture != hipStreamCaptureStatusNone) {
+            (void)hipGetLastError();
+            return false;
+        }
+        (void)hipFree(c.base);
+        c = EpisodeCopies();
+        unsigned char *base = nullptr;
+        if (hipMalloc(reinterpret_cast<void **>(&base), bytes) != hipSuccess) {
+            (void)hipGetLastError();
+            return false;
+        }
+        c.base = base;
+        c.bytes = bytes;
+    }
+    carve_copies(c.base, n, B, copies, mv, &c);
+    c.copies = copies;
+    c.D = mv.D;
+    launch_copies_index(g->view, copies, const_cast<int32_t *>(c.view.node_off), const_cast<int32_t *>(c.view.tmpl),
+                        const_cast<int32_t *>(c.view.node_graph), s);
+    c.view.B = static_cast<int32_t>(B) * copies;
+    c.view.n_tot = static_cast<int32_t>(n) * copies;
+    for (int dir = 0; dir < 2; ++dir) c.view.plan[dir] = g->view.plan[dir];
+    clear_spare_messages(c.ws, n * copies, s);
+    clear_reach(c.ws, n * copies, s);
+    return true;
 }
 
 // ---- intermediate buffers for callers that cannot allocate: one fixed block per device
@@ -665,6 +773,7 @@ int pl_graph_batch_destroy(pl_graph_batch *g)
     }
     free_workspace(g->ws);
     free_grad_workspace(g->gw);
+    (void)hipFree(g->ahead.base);
     (void)hipFree(g->sim_peaks);
     for (auto &v : g->timer.ev)
         for (hipEvent_t e : v) (void)hipEventDestroy(e);
@@ -971,15 +1080,32 @@ int pl_episode_run(pl_graph_batch *g, const pl_weights *w, float *node_feats, in
         if (rc) return rc;
     }
     const size_t B = static_cast<size_t>(g->host.B), D = static_cast<size_t>(w->cfg.D);
-    for (int32_t i = 0; i < n_steps; ++i) {
+    hipStream_t s = static_cast<hipStream_t>(stream);
+    int rc = ensure_on_device(g);
+    if (rc) return rc;
+    int ahead = steps_ahead(g, w, n_steps);
+    const int copies = static_cast<int>(states_within(w->cfg.D, ahead));
+    if (ahead > 1 && !ensure_copies(g, w->view, copies, s)) ahead = 1;
+    const int n_max = ahead > 1 ? graph_extent(g->host).n_max : 0;
+    for (int32_t i = 0; i < n_steps; i += ahead) {
         float *l = keep_logits ? logits + static_cast<size_t>(i) * B * D : logits;
-        int rc = forward_impl(g, node_feats, placement, cur_node, w, l, nullptr, nullptr, nullptr, nullptr, stream,
-                              false);
-        if (rc) return rc;
-        launch_episode_step(g->view, w->cfg.D, l, uniforms + static_cast<size_t>(i) * B, order, t0 + i,
-                            node_feats, placement, cur_node, out_actions ? out_actions + static_cast<size_t>(i) * B : nullptr,
-                            out_logp ? out_logp + static_cast<size_t>(i) * B : nullptr,
-                            static_cast<hipStream_t>(stream));
+        const float *u = uniforms + static_cast<size_t>(i) * B;
+        int32_t *actions = out_actions ? out_actions + static_cast<size_t>(i) * B : nullptr;
+        float *logp = out_logp ? out_logp + static_cast<size_t>(i) * B : nullptr;
+        if (ahead > 1) {
+            const EpisodeCopies &c = g->ahead;
+            launch_copies_state(g->view, w->cfg.D, copies, n_max, order, t0 + i, node_feats, placement, cur_node, c.feats,
+                                c.placement, c.cur_node, s);
+            rc = forward_impl(g, c.feats, c.placement, c.cur_node, w, c.logits, nullptr, nullptr, nullptr, nullptr, stream,
+                              false, nullptr, 0, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, &c);
+            if (rc) return rc;
+            launch_copies_steps(g->view, w->cfg.D, std::min(ahead, n_steps - i), c.logits, u, order, t0 + i, node_feats,
+                                placement, cur_node, l, keep_logits ? B * D : 0, actions, logp, s);
+        } else {
+            rc = forward_impl(g, node_feats, placement, cur_node, w, l, nullptr, nullptr, nullptr, nullptr, stream, false);
+            if (rc) return rc;
+            launch_episode_step(g->view, w->cfg.D, l, u, order, t0 + i, node_feats, placement, cur_node, actions, logp, s);
+        }
     }
     PL_HIP(hipGetLastError());
     return PL_OK;

@@ -120,6 +120,17 @@ struct Workspace {
     int32_t H = 0, G = 0;
 };
 
+// ---- copies of a batch, one for every state that the next steps of an episode can reach (kernels_episode.hip)
+struct EpisodeCopies {
+    unsigned char *base = nullptr;   // the one allocation that holds everything
+    size_t bytes = 0;
+    int32_t copies = 0, D = 0;       // what it is laid out for (with ws.H, ws.G)
+    float *feats = nullptr, *logits = nullptr;       // [copies, n_tot, 3], [copies, B, D]
+    int32_t *placement = nullptr, *cur_node = nullptr;
+    Workspace ws;
+    GraphView view{};
+};
+
 // (workspace.cpp)
 bool workspace_fits(const Workspace &ws, const ModelView &mv);
 size_t carve_workspace(unsigned char *base, size_t n, size_t B, const ModelView &mv, bool with_reach, Workspace *ws);
@@ -172,6 +183,16 @@ void launch_head_bw(const GraphView &gv, const ModelView &mv, const float *blob_
 void launch_episode_step(const GraphView &gv, int D, const float *logits, const float *uniforms,
                          const int32_t *order, int t, float *node_feats, int32_t *placement,
                          int32_t *cur_node, int32_t *out_action, float *out_logp, hipStream_t s);
+
+// steps taken ahead: copies of the batch, one for every state that its next steps can reach
+void launch_copies_index(const GraphView &gv, int copies, int32_t *node_off, int32_t *tmpl, int32_t *node_graph,
+                         hipStream_t s);
+void launch_copies_state(const GraphView &gv, int D, int copies, int n_max, const int32_t *order, int t, const float *feats,
+                         const int32_t *placement, const int32_t *cur_node, float *out_feats, int32_t *out_placement,
+                         int32_t *out_cur, hipStream_t s);
+void launch_copies_steps(const GraphView &gv, int D, int steps, const float *copy_logits, const float *uniforms,
+                         const int32_t *order, int t, float *node_feats, int32_t *placement, int32_t *cur_node,
+                         float *out_logits, size_t logits_stride, int32_t *out_action, float *out_logp, hipStream_t s);
 
 void launch_episode_apply(const GraphView &gv, int D, const int32_t *actions, const int32_t *order, int t,
                           float *node_feats, int32_t *placement, int32_t *cur_node, hipStream_t s);

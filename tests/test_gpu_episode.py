@@ -228,3 +228,74 @@ def test_ragged_batch_graphs_finish_at_different_steps():
     out = run_device_episode(w, n_steps, order, uniforms, placement0)
     for b in range(w.B):
         check_against_replay(w, b, n_steps, order, uniforms, placement0, out, complete=True)
+
+
+def ragged_workload(rng, sizes, D, H, L, wd, k=1, group=1):
+    from workloads import tiny_random_dag, weight_count
+    from workloads.synthetic import Workload
+    n_nodes, n_edges, srcs, dsts = [], [], [], []
+    for n in sizes:
+        s, d = tiny_random_dag(rng, n, 0.2)
+        n_nodes.append(n); n_edges.append(len(s)); srcs.append(s); dsts.append(d)
+    N = sum(sizes)
+    feats = np.stack([rng.lognormal(0, 1, N), rng.lognormal(2, 1, N), np.zeros(N)], axis=1)
+    return Workload(name="ragged", B=len(sizes), D=D, H=H, n_layers=L, k_sweeps=k, group_by_device=group, weight_dtype=wd,
+                    n_nodes=np.array(n_nodes, np.int32), n_edges=np.array(n_edges, np.int32),
+                    edge_src=np.concatenate(srcs).astype(np.int32), edge_dst=np.concatenate(dsts).astype(np.int32),
+                    node_feats=feats.astype(np.float32), placement=np.zeros(N, np.int32),
+                    cur_node=np.zeros(len(sizes), np.int32),
+                    weights=rng.normal(0, 0.02, weight_count(D, H, L, bool(group))).astype(np.float32))
+
+
+# (steps per pass: 7, 4, 2, 3 of 7, 2, 1; both sides of the batch sizes where another kernel would take more copies)
+@pytest.mark.parametrize("graphs,D,H,L,wd,k,group,n_steps", [
+    (1, 2, 8, 2, "fp32", 1, 1, 20), (3, 4, 16, 1, "fp32", 2, 0, 9), (51, 4, 32, 2, "fp32", 1, 1, 5),
+    (5, 3, 64, 1, "fp32", 1, 1, 7), (43, 2, 64, 1, "fp32", 1, 1, 4), (64, 2, 64, 2, "fp32", 2, 1, 5),
+    (1, 16, 64, 2, "bf16", 1, 0, 3), (2, 8, 128, 2, "bf16", 1, 1, 8), (4, 1, 32, 2, "bf16", 1, 1, 13),
+    (130, 2, 8, 2, "fp32", 1, 1, 3)])
+def test_steps_taken_together_equal_single_steps_bit_for_bit(graphs, D, H, L, wd, k, group, n_steps):
+    """pl_episode_run against a loop of pl_embed_forward and pl_episode_step: logits, actions, log-probabilities and
+    states are the same bits, also for graphs that finish on the way, that are over or in no valid state from the
+    start, and whose visiting order names a node twice; again on the same batch with fewer steps, then with more."""
+    import torch
+    import paper_1906_08879_amd as pl
+    dev = torch.device("cuda:0")
+    rng = np.random.default_rng(1000 * graphs + H)
+    sizes = [int(x) for x in rng.integers(2, 40, graphs)]
+    w = ragged_workload(rng, sizes, D, H, L, wd, k, group)
+    off = np.concatenate([[0], np.cumsum(sizes)])
+    order = np.concatenate([rng.permutation(n) for n in sizes]).astype(np.int32)
+    order[off[0] + 1] = order[off[0]]                                # the first graph visits a node twice
+    cur = order[off[:-1]].copy()
+    if graphs > 2:
+        cur[1], cur[2] = -1, sizes[2]
+    placement = rng.integers(0, D, w.n_tot).astype(np.int32)
+    uniforms = rng.random((2 * n_steps, graphs), dtype=np.float32)
+    to = lambda a: torch.from_numpy(np.ascontiguousarray(a)).to(dev)  # noqa: E731
+    wt = pl.Weights(w.weights, D, H, L, k, group, wd)
+    runs = {}
+    for together in (True, False):
+        g = pl.GraphBatch(w.n_nodes, w.n_edges, w.edge_src, w.edge_dst)
+        out = []
+        f, p, c, o, u = to(w.node_feats), to(placement), to(cur), to(order), to(uniforms)
+        t0 = 0
+        for steps, keep in ((n_steps, True), (max(1, n_steps // 2), False), (n_steps, True)):
+            t0 = 0 if t0 + steps > 2 * n_steps else t0
+            logits = torch.full((steps if keep else 1, graphs, D), 7.0, device=dev)
+            act = torch.full((steps, graphs), 99, dtype=torch.int32, device=dev)
+            logp = torch.full((steps, graphs), 9.0, device=dev)
+            if together:
+                pl.episode_run(g, wt, f, p, c, o, u[t0:t0 + steps], t0, steps, logits, keep, act, logp)
+            else:
+                for i in range(steps):
+                    l = logits[i if keep else 0]
+                    pl.embed_forward(g, f, p, c, wt, l)
+                    pl.episode_step(g, D, l, u[t0 + i], o, t0 + i, f, p, c, act[i], logp[i])
+            t0 += steps
+            torch.cuda.synchronize()
+            out += [x.cpu().numpy().view(np.int32) for x in (logits, act, logp, f, p, c)]
+        runs[together] = out
+        g.close()
+    wt.close()
+    for i, (a, b) in enumerate(zip(runs[True], runs[False])):
+        np.testing.assert_array_equal(a, b, err_msg=f"output {i}")
