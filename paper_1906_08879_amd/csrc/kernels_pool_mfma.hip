@@ -66,7 +66,8 @@ __global__ __launch_bounds__(kThreads) void k_pool_sort(GraphView gv, const uint
                                                         int single, int32_t *__restrict__ klist,
                                                         int32_t *__restrict__ koff, uint32_t *__restrict__ head_done)
 {
-    __shared__ uint16_t hist[kMaxKeys][kThreads];    // nodes of key k in thread t's block, then their first position
+    // nodes of key k in thread t's block, then their first position among the key's (a graph may have more than 65535)
+    __shared__ __attribute__((aligned(16))) int hist[kMaxKeys][kThreads];
     __shared__ int total[kMaxKeys + 1];
     const int b = blockIdx.x, tid = threadIdx.x;
     if (tid == 0) head_done[b] = 0;                  // for this pass's head
@@ -102,14 +103,21 @@ __global__ __launch_bounds__(kThreads) void k_pool_sort(GraphView gv, const uint
             if (keys[u] >= 0) hist[keys[u]][tid] += 1;
     }
     __syncthreads();
-    if (tid < K) {                                   // exclusive prefix over the threads, per key
-        int run = 0;
-        for (int t = 0; t < kThreads; ++t) {
-            const int c = hist[tid][t];
-            hist[tid][t] = static_cast<uint16_t>(run);
-            run += c;
+    const int lane = tid & 63;                       // exclusive prefix over the threads, a wave to a key, four threads to a lane
+    for (int k = tid >> 6; k < K; k += kThreads / 64) {
+        static_assert(kThreads == 4 * 64, "a lane takes four threads' counts");
+        int4 *at = reinterpret_cast<int4 *>(&hist[k][4 * lane]);
+        const int4 c = *at;
+        const int own = c.x + c.y + c.z + c.w;
+        int run = own;
+#pragma unroll
+        for (int step = 1; step < 64; step *= 2) {
+            const int before = __shfl_up(run, step);
+            run += lane >= step ? before : 0;
         }
-        total[tid] = run;
+        if (lane == 63) total[k] = run;
+        run -= own;
+        *at = int4{run, run + c.x, run + c.x + c.y, run + c.x + c.y + c.z};
     }
     __syncthreads();
     if (tid == 0) {                                  // exclusive prefix over the keys

@@ -7,7 +7,7 @@ import numpy as np
 import pytest
 
 import oracle
-from gpu_common import (assert_logits_close, assert_probs_close, assert_rows_close, logit_errors, normalised,
+from gpu_common import (assert_logits_close, assert_probs_close, assert_rows_close, custom_workload, logit_errors, normalised,
                         run_library)
 from workloads import CONFIG_NAMES, make_workload, make_states, tiny_random_dag, weight_count
 from workloads.synthetic import Workload
@@ -469,3 +469,17 @@ def test_rollouts_of_one_graph_share_a_layout_bit_for_bit():
         gb = run_gradient(w, actions, coeff, handles=(g_ord, wt))
         np.testing.assert_array_equal(ga["grad"], gb["grad"], err_msg=name + " gradient")
         g_rep.close(); g_ord.close(); wt.close()
+
+
+def test_more_than_65535_nodes_in_one_set():
+    """A graph whose nodes are nearly all unrelated to the current one: pooling's node lists against the generic kernels'."""
+    rng = np.random.default_rng(65536)
+    n = 70001
+    w = custom_workload(rng, [1], 2, 32, 1, 1, 0)
+    w.n_nodes, w.n_edges = np.array([n], np.int32), np.array([3], np.int32)
+    w.edge_src, w.edge_dst = np.array([5, 5, 9], np.int32), np.array([7, 9, 70000], np.int32)
+    w.node_feats = np.stack([rng.lognormal(0, 1, n), rng.lognormal(2, 1, n), rng.random(n) < 0.5], axis=1).astype(np.float32)
+    w.placement, w.cur_node = rng.integers(0, 2, n).astype(np.int32), np.array([9], np.int32)
+    got, ref = run_library(w, want_emb=False), run_library(w, want_emb=False, path=1)
+    # (sums of seventy thousand fp32 terms, in two orders)
+    np.testing.assert_allclose(got["pooled"], ref["pooled"], rtol=1e-4, atol=1e-4 * np.abs(ref["pooled"]).max())
