@@ -148,7 +148,15 @@ struct ForwardArgs {
     float *keep_hact = nullptr;
 };
 
-constexpr int kPoolChunk = 128;   // nodes per pooling workgroup
+constexpr int kPoolChunk = 128;   // nodes per slice of a graph's pooling
+// Slices of a graph of n nodes: one for every 128 nodes, in small graphs for every 64 (layered graphs of 200 nodes, with two
+// and with four: pooling of 64 at H = 32 13.8 / 10.8 us; forward pass of 256 at H = 48 582 / 499 us, at H = 128 189 / 170).
+__host__ __device__ inline int pool_slices(int n, int most)
+{
+    const int by_chunk = (n + kPoolChunk - 1) / kPoolChunk, by_half = (2 * n + kPoolChunk - 1) / kPoolChunk;
+    const int want = by_chunk > 4 ? by_chunk : (by_half < 4 ? by_half : 4);
+    return want < most ? want : most;
+}
 
 void launch_project(const GraphView &gv, const ModelView &mv, const Workspace &ws,
                     const ForwardArgs &fa, bool to_emb, bool to_xb, hipStream_t s);
@@ -212,7 +220,7 @@ int launch_simulate_reward(const GraphView &gv, int D, int n_max, int e_max, con
                            hipStream_t s);
 
 // ---- matrix-core pooling (kernels_pool_mfma.hip); writes ws.partial as [B, kPoolSlices, 3G, H]
-constexpr int kPoolSlices = 4;
+constexpr int kPoolSlices = 8;
 bool pool_mfma_supported(int H, int L, int weight_dtype);
 void pack_pool_weights(const ModelView &mv, const float *blob, int WS, std::vector<uint16_t> *frag,
                        std::vector<float> *bias);

@@ -352,8 +352,7 @@ __global__ __launch_bounds__(kThreads) void k_pool_generic(GraphView gv, ModelVi
     const int set_begin = SIDE ? blockIdx.z : 0, set_end = SIDE ? set_begin + 1 : 3;
     if (c == 0 && set_begin == 0 && tid == 0) head_done[b] = 0;        // for this pass's head
     const int n0 = gv.node_off[b], n_b = gv.node_off[b + 1] - n0;
-    int chunks = (n_b + kPoolChunk - 1) / kPoolChunk;
-    if (chunks > max_chunks) chunks = max_chunks;
+    const int chunks = pool_slices(n_b, max_chunks);
     if (c >= chunks) return;
     const int per = (n_b + chunks - 1) / chunks;
     const int lo = n0 + c * per, hi = min(n0 + n_b, lo + per);

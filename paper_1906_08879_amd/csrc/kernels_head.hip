@@ -276,7 +276,7 @@ __global__ __launch_bounds__(head_threads(HT, SHAPE)) void k_head(GraphView gv, 
     const int n0 = gv.node_off[b], n_b = gv.node_off[b + 1] - n0;
     const int cl = cur_node[b];
     const bool cur_ok = cl >= 0 && cl < n_b;
-    const int chunks = min((n_b + kPoolChunk - 1) / kPoolChunk, max_chunks);
+    const int chunks = pool_slices(n_b, max_chunks);
     const size_t BG = static_cast<size_t>(gv.B) * G;
     // place of element i of a set's rows in the arrays kept for the reverse pass
     auto kept = [&](int set, int l, int layers, int i) {

@@ -9,7 +9,7 @@
 //   k_pool_stream (H = 128, bf16 weights) one workgroup per graph, or per (set, graph) in small
 //                 batches; every wave walks tiles of its own with the weights in LDS, the rows
 //                 coming straight from HBM and the two layers chained in registers (see there);
-//   k_pool_tiles  (H <= 64) one workgroup per (set, slice of the set's tiles, graph).  A tile is
+//   k_pool_tiles  (H <= 64) one workgroup per (slice of a set's tiles, graph).  A tile is
 //                 up to sixteen nodes of ONE key, so the sum over a tile's rows needs no per-device
 //                 selection: a lane adds its four nodes' outputs to one running sum, which is
 //                 written out when the device changes.
@@ -37,7 +37,7 @@ typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4;
 constexpr int kThreads = 256;
 constexpr int kBatch = 16;          // nodes per tile: one MFMA row tile per bf16 part
 constexpr int kMaxKeys = 3 * kMaxD; // (set, device group) keys of a graph
-constexpr int kAhead = 2;            // k-steps between reading an A fragment from LDS and using it
+constexpr int kAhead = 1;            // k-steps between reading an A fragment from LDS and using it
 
 __device__ __forceinline__ void lds_barrier()
 {
@@ -164,8 +164,12 @@ struct PoolParams {
 
 // KEEP: the outputs of every layer of l_i are also written to HBM, by the lane that holds them,
 // for the reverse pass (a node belongs to one set and is handled by one workgroup).
+// Three workgroups to a compute unit (64 columns, fp32 weights, two layers: 168 registers; A fragments two k-steps ahead
+// of their use took 179 and left room for two).  64 NMT-like graphs, 128 and 185 Inception-like ones: 42, 36 and
+// 53 us with two, 33, 33 and 41 with three.  A tile takes about 0.95 us in a workgroup alone on its compute unit: 415
+// instructions of a wave, 54 of them on the matrix cores.
 template <int H, int WS, int L, bool KEEP = false>
-__global__ __launch_bounds__(kThreads, 2) void k_pool_tiles(PoolParams P)
+__global__ __launch_bounds__(kThreads, 3) void k_pool_tiles(PoolParams P)
 {
     constexpr int K1 = 2 * H;                    // input width of the first layer
     constexpr int KS1 = K1 / 32, KS2 = H / 32;
@@ -187,27 +191,42 @@ __global__ __launch_bounds__(kThreads, 2) void k_pool_tiles(PoolParams P)
     };
     __shared__ int tile_node[8][kBatch];     // node ids of the tiles t - 1 .. t + 4 (slot = tile & 7)
 
-    const int set = blockIdx.x, slice = blockIdx.y, b = blockIdx.z;
+    const int b = blockIdx.y;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int col = lane & 15, kg = lane >> 4;
     const GraphView &gv = P.gv;
     const int g0 = gv.node_off[b], g_n = gv.node_off[b + 1] - g0;
     const int G = P.G;
-    // a graph's sets are cut into slices (as many as the generic pooling kernel uses chunks)
-    int slices = (g_n + kPoolChunk - 1) / kPoolChunk;
-    if (slices > P.max_slices) slices = P.max_slices;
-    if (slice >= slices) return;
-    // tiles of this set: for every device group ceil(count / 16), in device order; this
-    // workgroup takes the tiles [t_lo, t_hi) of that list
-    const int32_t *kb = P.koff + static_cast<size_t>(b) * (kMaxKeys + 1) + set * G;
-    int n_tiles = 0;
-    for (int d = 0; d < G; ++d) n_tiles += (kb[d + 1] - kb[d] + kBatch - 1) / kBatch;
-    const int t_lo = static_cast<int>(static_cast<long long>(n_tiles) * slice / slices);
-    const int t_hi = static_cast<int>(static_cast<long long>(n_tiles) * (slice + 1) / slices);
-    float *dst = P.partial + (((static_cast<size_t>(b) * P.max_slices + slice) * 3 + set) * G) * H;
-    if (t_lo >= t_hi) {
-        for (int i = tid; i < G * H; i += kThreads) dst[i] = 0.0f;
-        return;
+    // A graph's tiles (for every set and device group ceil(count / 16), in device order) are shared out over `slices`
+    // workgroups or up to two more, whatever the sizes of the sets: a set gets one for every ceil(tiles / slices) of its
+    // own, one if it is empty.  Most of a graph is in one set; with as many workgroups to each, that set's had the
+    // most to do and the others' were in the way (64 NMT-like graphs 54 us, 128 Inception-like ones 40).
+    const int slices = pool_slices(g_n, P.max_slices);
+    if (slices == 0 || static_cast<int>(blockIdx.x) >= slices + 2) return;
+    // (first positions of the graph's keys, one to a lane: reading one costs no trip to memory)
+    const int k_lane = P.koff[static_cast<size_t>(b) * (kMaxKeys + 1) + min(lane, 3 * G)];
+    static_assert(kMaxKeys < 64, "a lane for every key's position");
+    auto first_of = [&](int k) { return __builtin_amdgcn_readlane(k_lane, k); };
+    auto tiles_of = [&](int k) { return static_cast<int>(static_cast<unsigned>(first_of(k + 1) - first_of(k) + kBatch - 1) / kBatch); };
+    int in_set[3], share = 0;
+    auto count_tiles = [&]() {
+        int all = 0;
+        for (int i = 0; i < 3; ++i) {
+            in_set[i] = 0;
+            for (int d = 0; d < G; ++d) in_set[i] += tiles_of(i * G + d);
+            all += in_set[i];
+        }
+        share = (all + slices - 1) / slices;
+    };
+    auto parts_of = [&](int i) { return in_set[i] ? (in_set[i] + share - 1) / share : 1; };   // (at most `slices`)
+    // workgroups 0 .. 2 take the first part of each set (their weights are on the way before the sets' sizes are known),
+    // the others the rest in order
+    int set = blockIdx.x, slice = 0;
+    if (set >= 3) {
+        count_tiles();
+        slice = set - 2;
+        for (set = 0; set < 3 && slice >= parts_of(set); ++set) slice -= parts_of(set) - 1;
+        if (set == 3) return;
     }
 
     // ---- weights of l_set into registers (B operand: lane holds column 16 nt + col)
@@ -243,29 +262,41 @@ __global__ __launch_bounds__(kThreads, 2) void k_pool_tiles(PoolParams P)
             }
         }
     }
+    if (blockIdx.x < 3) count_tiles();
+    // this workgroup takes the tiles [t_lo, t_hi) of the set's
+    const int parts = parts_of(set), kb = set * G, n_tiles = in_set[set];
+    const int t_lo = static_cast<int>(static_cast<long long>(n_tiles) * slice / parts);
+    const int t_hi = static_cast<int>(static_cast<long long>(n_tiles) * (slice + 1) / parts);
+    auto sums = [&](int i) { return P.partial + (((static_cast<size_t>(b) * P.max_slices + i) * 3 + set) * G) * H; };
+    float *dst = sums(slice);
+    if (slice == parts - 1)                      // the head reads `slices` sums of every set
+        for (int i = parts; i < slices; ++i)
+            for (int j = tid; j < G * H; j += kThreads) sums(i)[j] = 0.0f;
+    if (t_lo >= t_hi) {
+        for (int i = tid; i < G * H; i += kThreads) dst[i] = 0.0f;
+        return;
+    }
     const bool my_cols = wave * TPW < NTL;        // narrow networks leave the last waves without columns
 
-    // ---- tile walk: (device group d, first node position p, node count) of tile t
+    // ---- tile walk: (device group, first node position, node count) of tile t, which only grows
     int d_cur = 0, d_first = 0;                   // device group of the walk; tiles before it
-    auto seek = [&](int t) {                      // t only grows
-        while (d_cur < G && t >= d_first + (kb[d_cur + 1] - kb[d_cur] + kBatch - 1) / kBatch) {
-            d_first += (kb[d_cur + 1] - kb[d_cur] + kBatch - 1) / kBatch;
+    auto find = [&](int t, int &cnt, int &dev) {
+        while (d_cur + 1 < G && t >= d_first + tiles_of(kb + d_cur)) {
+            d_first += tiles_of(kb + d_cur);
             ++d_cur;
         }
+        const int p = first_of(kb + d_cur) + (t - d_first) * kBatch;
+        cnt = min(kBatch, first_of(kb + d_cur + 1) - p);
+        dev = d_cur;
+        return p;
     };
     // Rows travel two tiles ahead of the matrix instructions (a workgroup keeps 32 KB of loads
     // in flight); the node ids of a tile are staged in LDS earlier still, so a row load never
     // waits for an id load.  Ring of eight id slots (slot = tile & 7).
-    // The id of a tile's node tid (threads 0..15) is fetched before the row loads of the same
-    // iteration are issued and published after them: loads return in order, so the wait for the
-    // id then leaves the row loads in flight.
-    auto fetch_id = [&](int t, int &cnt, int &dev) {
-        seek(t);
-        const int p = kb[d_cur] + (t - d_first) * kBatch;
-        cnt = min(kBatch, kb[d_cur + 1] - p);
-        dev = d_cur;
-        return tid < kBatch ? P.klist[g0 + p + (tid < cnt ? tid : 0)] : 0;   // rows past the end repeat the first
-    };
+    // The id of a tile's node tid (threads 0..15) is requested at the beginning of a step, ahead of the step's row
+    // loads, and published at its end: loads return in order, so the wait for it leaves the row loads in flight, and it
+    // has had the length of the step to arrive.
+    auto request_id = [&](int p, int cnt) { return P.klist[g0 + p + (tid < cnt ? tid : 0)]; };   // rows past the end repeat the first
     auto publish_id = [&](int t, int id) {
         if (tid < kBatch) tile_node[t & 7][tid] = id;
     };
@@ -316,10 +347,23 @@ __global__ __launch_bounds__(kThreads, 2) void k_pool_tiles(PoolParams P)
     int cnt_r[5], dev_r[5];            // nodes and device group of the tiles t .. t + 4 (uniform)
 #pragma unroll
     for (int j = 0; j < 5; ++j) cnt_r[j] = dev_r[j] = 0;
+    {                                  // ids of the first four tiles: one load, a thread of the first wave to each
+        const int q = lane / kBatch, i = lane % kBatch;
+        int p_q = 0, cnt_q = 0;
 #pragma unroll
-    for (int j = 0; j < 4; ++j)
-        if (t_lo + j < t_hi) publish_id(t_lo + j, fetch_id(t_lo + j, cnt_r[j], dev_r[j]));
+        for (int j = 0; j < 4; ++j)
+            if (t_lo + j < t_hi) {
+                const int p = find(t_lo + j, cnt_r[j], dev_r[j]);
+                p_q = q == j ? p : p_q;
+                cnt_q = q == j ? cnt_r[j] : cnt_q;
+            }
+        static_assert(4 * kBatch == 64, "a wave requests four tiles");
+        if (wave == 0 && cnt_q > 0) tile_node[(t_lo + q) & 7][i] = P.klist[g0 + p_q + (i < cnt_q ? i : 0)];
+    }
     __syncthreads();
+    // Every path through a step issues the same loads (tiles past the last one stand for it) and the same stores, so that
+    // a wait for rows that are two tiles old waits for nothing younger.
+    auto row_tile = [&](int t) { return min(t, t_hi - 1); };
     load_rows(t_lo, xa);
     if (t_lo + 1 < t_hi) load_rows(t_lo + 1, xb);
 #pragma unroll
@@ -330,13 +374,11 @@ __global__ __launch_bounds__(kThreads, 2) void k_pool_tiles(PoolParams P)
     // interleaved between the k-steps of the first layer, into the other half of act1.
     auto step = [&](int t, f32x4 (&xs)[NLD]) {
         const int cnt = cnt_r[0], dev = dev_r[0], my_slot = t & 7, buf = (t - t_lo) & 1;
-        const bool more = t + 1 < t_hi;
-        int id4 = 0;
-        if (t + 4 < t_hi) id4 = fetch_id(t + 4, cnt_r[4], dev_r[4]);
+        const int p4 = find(row_tile(t + 4), cnt_r[4], dev_r[4]);
+        const int id4 = request_id(p4, cnt_r[4]);
         // every wave has finished tile t - 1 (its reads of act2 and of the other half of act1),
         // and the rows of tile t, split during tile t - 1, are visible
         lds_barrier();
-        if (t + 4 < t_hi) publish_id(t + 4, id4);
         if (dev != run_dev) {
             flush();
             run_dev = dev;
@@ -383,16 +425,14 @@ __global__ __launch_bounds__(kThreads, 2) void k_pool_tiles(PoolParams P)
                     __builtin_amdgcn_sched_barrier(0);
                 }
                 // NLD items of the split spread over the KS1 k-steps
-                if (more) {
 #pragma unroll
-                    for (int i = 0; i < NLD; ++i)
-                        if (i * KS1 / NLD == ks) split_item(buf ^ 1, xs, i);
-                }
+                for (int i = 0; i < NLD; ++i)
+                    if (i * KS1 / NLD == ks) split_item(buf ^ 1, xs, i);
                 __builtin_amdgcn_sched_barrier(0);
             }
         }
         // the registers of the split rows are free: the rows of tile t + 3 go in flight
-        if (t + 3 < t_hi) load_rows(t + 3, xs);
+        load_rows(row_tile(t + 3), xs);
         if constexpr (L > 1) {
             if (my_cols) {
 #pragma unroll
@@ -404,10 +444,8 @@ __global__ __launch_bounds__(kThreads, 2) void k_pool_tiles(PoolParams P)
                         y[tt] = fmaxf(acc[0][tt][i] + acc[1][tt][i] + acc[2][tt][i] + bias1[tt], 0.0f);
                         r[tt] = y[tt] - trunc_bf16(y[tt]);
                         l[tt] = r[tt] - trunc_bf16(r[tt]);
-                        if constexpr (KEEP) {
-                            if (node < cnt)
-                                P.keep[static_cast<size_t>(tile_node[my_slot][node]) * H + 16 * (wave * TPW + tt) + col] = y[tt];
-                        }
+                        if constexpr (KEEP)   // (rows past the tile's end: the first node's value once more)
+                            P.keep[static_cast<size_t>(tile_node[my_slot][node]) * H + 16 * (wave * TPW + tt) + col] = y[tt];
                     }
                     if constexpr (TPW == 2) {
                         // word 16 wave + col of a row: columns 32 wave + col and 32 wave + 16 + col
@@ -466,21 +504,24 @@ __global__ __launch_bounds__(kThreads, 2) void k_pool_tiles(PoolParams P)
                 const float y = fmaxf(acc[0][tt][i] + acc[1][tt][i] + acc[2][tt][i] + bl, 0.0f);
                 if constexpr (KEEP) {
                     const int nt = wave * TPW + tt;
-                    if (node < cnt && nt < NTL)
+                    if (nt < NTL)
                         P.keep[(static_cast<size_t>(L - 1) * gv.n_tot + tile_node[my_slot][node]) * H + 16 * nt + col] = y;
                 }
                 run[tt] += node < cnt ? y : 0.0f;
             }
         }
+        publish_id(t + 4, id4);   // (read after the next step's barrier)
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
             cnt_r[j] = cnt_r[j + 1];
             dev_r[j] = dev_r[j + 1];
         }
     };
-    for (int t = t_lo; t < t_hi; t += 2) {
+    for (int t = t_lo;;) {
         step(t, xb);
-        if (t + 1 < t_hi) step(t + 1, xa);
+        if (++t == t_hi) break;
+        step(t, xa);
+        if (++t == t_hi) break;
     }
     flush();
     // device groups without a tile in this slice
@@ -541,8 +582,7 @@ __global__ __launch_bounds__(kStreamThreads, 1) void k_pool_stream(PoolParams P)
     const GraphView &gv = P.gv;
     const int g0 = gv.node_off[b], g_n = gv.node_off[b + 1] - g0;
     const int G = P.G;
-    int slices = (g_n + kPoolChunk - 1) / kPoolChunk;
-    if (slices > P.max_slices) slices = P.max_slices;
+    const int slices = pool_slices(g_n, P.max_slices);
     // A workgroup takes the sets blockIdx.x, blockIdx.x + gridDim.x, ..: all three of its graph
     // (grid.x = 1: every workgroup then has the same share of a batch of equal graphs, whatever
     // the sizes of the sets) or one (grid.x = 3, for batches that would not fill the chip otherwise).
@@ -883,8 +923,7 @@ __global__ __launch_bounds__(kStreamThreads, 1) void k_pool_stream_bw(PoolBwPara
     const int g0 = gv.node_off[b], g_n = gv.node_off[b + 1] - g0;
     const int G = P.G;
     const size_t NH = static_cast<size_t>(gv.n_tot) * H;
-    int slices = (g_n + kPoolChunk - 1) / kPoolChunk;
-    if (slices > P.max_slices) slices = P.max_slices;
+    const int slices = pool_slices(g_n, P.max_slices);
     for (int set = blockIdx.x; set < 3; set += gridDim.x) {
     if (set != static_cast<int>(blockIdx.x)) __syncthreads();
     const int32_t *kb = P.koff + static_cast<size_t>(b) * (kMaxKeys + 1) + set * G;
@@ -1243,7 +1282,7 @@ int launch_pool_mfma(const GraphView &gv, const ModelView &mv, const Workspace &
         return kStreamWaves;
     }
     PoolParams P{gv, wfrag, bias, ws.emb, ws.klist, ws.koff, ws.partial, kPoolSlices, mv.G, keep};
-    const dim3 grid(3, kPoolSlices, gv.B), block(kThreads);
+    const dim3 grid(kPoolSlices + 2, gv.B), block(kThreads);
 #define PL_CASE(HH, WW, LL)                                                          \
     if (mv.H == HH && WS == WW && mv.L == LL) {                                      \
         if (keep)                                                                    \
