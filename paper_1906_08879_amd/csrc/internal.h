@@ -231,9 +231,8 @@ void pack_pool_stream_weights(const ModelView &mv, const float *blob, std::vecto
 // pooled node from the kept layer outputs; reads the sort (ws.klist, ws.koff) of the forward pass
 bool pool_stream_bw_supported(int H, int L, int weight_dtype);
 void pack_pool_stream_bw_weights(const ModelView &mv, const float *blob, std::vector<uint16_t> *frag);
-void launch_pool_stream_bw(const GraphView &gv, const ModelView &mv, const Workspace &ws, const int32_t *placement,
-                           const uint4 *frag, const float *lact, const float *dP, const uint8_t *cls, float *dl,
-                           float *demb, hipStream_t s);
+void launch_pool_stream_bw(const GraphView &gv, const ModelView &mv, const Workspace &ws, const uint4 *frag, const float *lact,
+                           const float *dP, float *dl, float *demb, hipStream_t s);
 // returns the number of slices per graph that ws.partial holds afterwards
 int launch_pool_mfma(const GraphView &gv, const ModelView &mv, const Workspace &ws,
                      const ForwardArgs &fa, const uint4 *wfrag, const uint4 *afrag, const float *bias, int WS,

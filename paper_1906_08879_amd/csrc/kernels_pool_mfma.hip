@@ -888,7 +888,7 @@ __global__ __launch_bounds__(kStreamThreads, 1) void k_pool_stream(PoolParams P)
 // columns of the B operand, deltas split exactly into three bf16 parts, the result of the first
 // product chained into the second in registers.  Both deltas are also written out for the weight
 // gradients.  Nodes that were pooled nowhere (device id out of range) are not visited:
-// k_zero_unpooled clears their rows.
+// the kernel that makes the sets' row lists clears their rows of d e.
 struct PoolBwParams {
     GraphView gv;
     const uint4 *wfrag;        // see pack_pool_stream_bw_weights
@@ -1108,21 +1108,6 @@ __global__ __launch_bounds__(kStreamThreads, 1) void k_pool_stream_bw(PoolBwPara
     }   // sets
 }
 
-// Rows of the deltas of l and of d e for nodes that belong to a set but were pooled nowhere (device
-// id out of range): zero.
-__global__ __launch_bounds__(kThreads) void k_zero_unpooled(int n_tot, int H, int L, int D, const uint8_t *__restrict__ cls,
-                                                            const int32_t *__restrict__ placement,
-                                                            float *__restrict__ dl, float *__restrict__ demb)
-{
-    const int v = blockIdx.x * kThreads + threadIdx.x;
-    if (v >= n_tot || cls[v] == 0) return;
-    const int dev = placement[v];
-    if (dev >= 0 && dev < D) return;
-    for (int l = 0; l < L; ++l)
-        for (int i = 0; i < H; ++i) dl[(static_cast<size_t>(l) * n_tot + v) * H + i] = 0.0f;
-    for (int i = 0; i < 2 * H; ++i) demb[static_cast<size_t>(v) * 2 * H + i] = 0.0f;
-}
-
 // Appends the MFMA B-operand fragments of one layer: index ((nt * KS + ks) * WS + ws) * 64 + lane,
 // lane l holds W[32 ks + 8 (l / 16) + i][16 nt + l % 16], i = 0..7, as bf16 part ws of the exact
 // three-way split of the weight (ws = 0 only when the weights are bf16 already).
@@ -1232,13 +1217,10 @@ bool pool_stream_bw_supported(int H, int L, int weight_dtype)
     return weight_dtype == PL_WEIGHTS_BF16 && H == 128 && L == 2;
 }
 
-void launch_pool_stream_bw(const GraphView &gv, const ModelView &mv, const Workspace &ws, const int32_t *placement,
-                           const uint4 *frag, const float *lact, const float *dP, const uint8_t *cls, float *dl,
-                           float *demb, hipStream_t s)
+void launch_pool_stream_bw(const GraphView &gv, const ModelView &mv, const Workspace &ws, const uint4 *frag, const float *lact,
+                           const float *dP, float *dl, float *demb, hipStream_t s)
 {
     if (gv.B == 0) return;
-    hipLaunchKernelGGL(k_zero_unpooled, dim3((gv.n_tot + kThreads - 1) / kThreads), dim3(kThreads), 0, s, gv.n_tot, mv.H,
-                       mv.L, mv.D, cls, placement, dl, demb);
     PoolBwParams P{gv, frag, lact, dP, ws.klist, ws.koff, dl, demb, kStreamWaves, mv.G};
     const dim3 grid(gv.B < kStreamGraphsPerChip ? 3 : 1, gv.B), block(kStreamThreads);
     hipLaunchKernelGGL((k_pool_stream_bw<128>), grid, block, 0, s, P);
