@@ -458,59 +458,135 @@ __global__ __launch_bounds__(kThreads) void k_bw_proj(GraphView gv, ModelView mv
     }
 }
 
-// The same with four columns per thread, for H a multiple of four (vector loads and stores; the
-// per-node values are read once per four columns).  The sum takes its terms in the order of
-// k_bw_proj, which is the forward pass's.
+// Gradient of the input projection, H a multiple of four, large batches: per slab of nodes, phi^T dx and the column sums of dx, with
+// dx_v = (de_td + de_bu) [x_v > 0] formed on the way; neither dx nor phi exists in memory.  One read of d e bounds it (819 MB
+// of 256 NASNet-like graphs).  A thread takes four columns of every so manieth node of the slab.  A row of phi is three
+// numbers and two ones, so a node is five multiply-adds a column; its device's row of the sum is picked by comparison,
+// with five to eight devices in LDS (a thread's own entries: a read and a write instead of sixteen instructions a column,
+// 351 -> 160 us).  The pre-activation takes its terms in the forward pass's order.  Sums: a thread's nodes in order, the
+// threads of a column in a fixed order, then the slabs (k_wgrad_reduce).
 typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4p;
+template <int DM>                              // most devices
 __global__ __launch_bounds__(kThreads) void k_bw_proj4(GraphView gv, ModelView mv,
                                                        const float *__restrict__ feats,
                                                        const int32_t *__restrict__ placement,
                                                        const int32_t *__restrict__ cur_node,
-                                                       const float *__restrict__ demb,
-                                                       float *__restrict__ dx,
-                                                       float *__restrict__ phi, int phi_ld)
+                                                       const float *__restrict__ demb, int rows_per_slab,
+                                                       float *__restrict__ partial)
 {
-    const int H = mv.H, D = mv.D, q = H / 4;
-    const size_t idx = static_cast<size_t>(blockIdx.x) * kThreads + threadIdx.x;
-    if (idx >= static_cast<size_t>(gv.n_tot) * q) return;
-    const int v = static_cast<int>(idx / q), h = 4 * static_cast<int>(idx - static_cast<size_t>(v) * q);
-    const int b = gv.node_graph[v];
+    constexpr bool kLds = DM == 8;             // (of sixteen they would not fit)
+    constexpr int DR = kLds ? 0 : DM;
+    __shared__ f32x4p red[2][kThreads];
+    __shared__ f32x4p w_dev[(DM + 1) * (kMaxH / 4)];      // one-hot device rows of W_in, then a row of zeros
+    __shared__ f32x4p s_dev[kLds ? DM * kThreads : 1];
+    const int H = mv.H, D = mv.D, q = H / 4, groups = kThreads / q;
+    const int tid = threadIdx.x, grp = tid / q, c = tid - grp * q, h = 4 * c;
+    const int r_beg = blockIdx.x * rows_per_slab, r_end = min(gv.n_tot, r_beg + rows_per_slab);
     const float *W = mv.blob + mv.proj.w;
+    const f32x4p zero{0.f, 0.f, 0.f, 0.f};
     auto row = [&](int r) { return *reinterpret_cast<const f32x4p *>(W + static_cast<size_t>(r) * H + h); };
-    const float f_time = feats[v * 3 + 0], f_size = feats[v * 3 + 1], f_vis = feats[v * 3 + 2];
-    const int dev = placement[v];
-    const bool on_dev = dev >= 0 && dev < D;
-    const bool is_cur = v - gv.node_off[b] == cur_node[b];
-    const f32x4p bias = *reinterpret_cast<const f32x4p *>(mv.blob + mv.proj.b + h);
-    const f32x4p w0 = row(0), w1 = row(1), wd = row(2 + (on_dev ? dev : 0)), wc = row(2 + D), wv = row(3 + D);
-    const float *de = demb + static_cast<size_t>(v) * 2 * H + h;
-    const f32x4p g0 = *reinterpret_cast<const f32x4p *>(de), g1 = *reinterpret_cast<const f32x4p *>(de + H);
-    f32x4p out;
+    for (int i = tid; i < (DM + 1) * q; i += kThreads)
+        w_dev[i] = i < D * q ? *reinterpret_cast<const f32x4p *>(W + 2 * static_cast<size_t>(H) + 4 * i) : zero;
+    if constexpr (kLds)
+        for (int d = 0; d < DM; ++d) s_dev[d * kThreads + tid] = zero;
+    __syncthreads();
+    f32x4p s_time = zero, s_size = zero, s_cur = zero, s_vis = zero, s_one = zero, s_reg[DR + 1];
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
-        float s = bias[k];
-        s = fmaf(f_time, w0[k], s);
-        s = fmaf(f_size, w1[k], s);
-        if (on_dev) s += wd[k];
-        if (is_cur) s += wc[k];
-        s = fmaf(f_vis, wv[k], s);
-        out[k] = s > 0.0f ? g0[k] + g1[k] : 0.0f;
-    }
-    *reinterpret_cast<f32x4p *>(dx + static_cast<size_t>(v) * H + h) = out;
+    for (int d = 0; d <= DR; ++d) s_reg[d] = zero;
+    if (grp < groups) {
+        const f32x4p bias = *reinterpret_cast<const f32x4p *>(mv.blob + mv.proj.b + h);
+        const f32x4p w0 = row(0), w1 = row(1), wc = row(2 + D), wv = row(3 + D);
+        struct Node {
+            float time, size, vis;
+            int dev;
+            f32x4p g0, g1;
+        };
+        auto load = [&](int v) __attribute__((always_inline)) {
+            Node x;
+            x.time = feats[v * 3 + 0];
+            x.size = feats[v * 3 + 1];
+            x.vis = feats[v * 3 + 2];
+            x.dev = placement[v];
+            const float *de = demb + static_cast<size_t>(v) * 2 * H + h;
+            x.g0 = *reinterpret_cast<const f32x4p *>(de);
+            x.g1 = *reinterpret_cast<const f32x4p *>(de + H);
+            return x;
+        };
+        int cur = -1, graph_end = -1;          // of the graph that the last node was in
+        auto take = [&](int v, const Node &x) __attribute__((always_inline)) {
+            if (v >= graph_end) {
+                const int b = gv.node_graph[v], n0 = gv.node_off[b], cl = cur_node[b];
+                graph_end = gv.node_off[b + 1];
+                cur = cl >= 0 && cl < graph_end - n0 ? n0 + cl : -1;
+            }
+            const bool on_dev = x.dev >= 0 && x.dev < D, is_cur = v == cur;
+            const f32x4p wd = w_dev[(on_dev ? x.dev : DM) * q + c];
+            f32x4p dx;
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
-        const int c = h + k;
-        if (c < phi_ld) {                   // phi_ld >= F: columns past F are zero
-            float p;
-            if (c == 0) p = f_time;
-            else if (c == 1) p = f_size;
-            else if (c < 2 + D) p = (dev == c - 2) ? 1.0f : 0.0f;
-            else if (c == 2 + D) p = is_cur ? 1.0f : 0.0f;
-            else if (c == 3 + D) p = f_vis;
-            else p = 0.0f;
-            phi[static_cast<size_t>(v) * phi_ld + c] = p;
+            for (int k = 0; k < 4; ++k) {
+                float s = bias[k];
+                s = fmaf(x.time, w0[k], s);
+                s = fmaf(x.size, w1[k], s);
+                s += wd[k];
+                s += is_cur ? wc[k] : 0.0f;
+                s = fmaf(x.vis, wv[k], s);
+                dx[k] = s > 0.0f ? x.g0[k] + x.g1[k] : 0.0f;
+            }
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                s_time[k] = fmaf(x.time, dx[k], s_time[k]);
+                s_size[k] = fmaf(x.size, dx[k], s_size[k]);
+                s_vis[k] = fmaf(x.vis, dx[k], s_vis[k]);
+                s_one[k] += dx[k];
+                s_cur[k] += is_cur ? dx[k] : 0.0f;
+#pragma unroll
+                for (int d = 0; d < DR; ++d) s_reg[d][k] += x.dev == d ? dx[k] : 0.0f;
+            }
+            if constexpr (kLds) {
+                const int at = (on_dev ? x.dev : 0) * kThreads + tid;
+                f32x4p t = s_dev[at];
+#pragma unroll
+                for (int k = 0; k < 4; ++k) t[k] += on_dev ? dx[k] : 0.0f;
+                s_dev[at] = t;
+            }
+        };
+        int v = r_beg + grp;
+        for (; v + 3 * groups < r_end; v += 4 * groups) {
+            Node x[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) x[u] = load(v + u * groups);
+#pragma unroll
+            for (int u = 0; u < 4; ++u) take(v + u * groups, x[u]);
         }
+        for (; v < r_end; v += groups) take(v, load(v));
     }
+    // the threads of a column: those of a wave by shuffles where a wave holds whole groups, the rest through LDS
+    const bool whole = 64 % q == 0;
+    const int terms = whole ? kThreads / 64 : groups, step = whole ? 64 : q;
+    float *dst = partial + static_cast<size_t>(blockIdx.x) * static_cast<size_t>(mv.F + 1) * H + h;
+    int turn = 0;
+    auto put = [&](int r, f32x4p t) __attribute__((always_inline)) {
+        if (whole)
+            for (int lanes = q; lanes < 64; lanes *= 2)
+#pragma unroll
+                for (int k = 0; k < 4; ++k) t[k] += __shfl_xor(t[k], lanes);
+        f32x4p *buf = red[turn ^= 1];          // (a barrier lies between two uses of one)
+        buf[tid] = t;
+        __syncthreads();
+        if (grp == 0) {
+            t = buf[tid];
+            for (int k = 1; k < terms; ++k) t += buf[tid + k * step];
+            *reinterpret_cast<f32x4p *>(dst + static_cast<size_t>(r) * H) = t;
+        }
+    };
+    put(0, s_time);
+    put(1, s_size);
+#pragma unroll
+    for (int d = 0; d < DM; ++d)
+        if (d < D) put(2 + d, kLds ? s_dev[d * kThreads + tid] : s_reg[kLds ? 0 : d]);
+    put(2 + D, s_cur);
+    put(3 + D, s_vis);
+    put(4 + D, s_one);
 }
 
 // phi rows when H < F (more raw features than embedding columns): one thread per (node, feature).
@@ -1482,6 +1558,19 @@ int wgrad_rows_per_slab(int64_t R)
     return static_cast<int>((per + kWgRB - 1) / kWgRB * kWgRB);
 }
 
+// Which of the two kernels takes the projection's gradient: k_bw_proj4 saves a write and a read of dx and phi and costs a
+// chain of its own (projection, contractions and slab sums of 64 layered graphs, 0.4 million elements of dx, with k_bw_proj
+// and with it: 34 / 37 us; of 48 NMT-like graphs, 4.5 million: 94 / 91; of 256 NASNet-like ones, 102 million: 2.65 / 2.35 ms).
+bool proj_fused(int64_t R, int H) { return H % 4 == 0 && R * H >= 3000000; }
+
+// Four nodes in flight to a thread, and about four workgroups to a compute unit.
+int proj_rows_per_slab(int64_t R, int H)
+{
+    const int64_t batch = 4 * (kThreads / (H / 4));
+    const int64_t per = (R + 1023) / 1024;
+    return static_cast<int>((per + batch - 1) / batch * batch);
+}
+
 }  // namespace
 
 // Room for the slab sums of the contractions that one launch takes: of all of a pass, or, on large
@@ -1501,6 +1590,7 @@ size_t wgrad_workspace_floats(int64_t n, int64_t B, const ModelView &mv)
     };
     const int H = mv.H, L = mv.L;
     need(n, std::max(32, mv.F), H, 1);
+    if (proj_fused(n, H)) largest = std::max(largest, static_cast<size_t>(1025) * (mv.F + 1) * H);   // (slabs of the projection's)
     need(n, H, H, 4 * L + 3 * (L - 1));
     need(n, 2 * H, H, 3);
     need(B * mv.G, H, H, 3 * L);
@@ -1538,7 +1628,7 @@ public:
         const int per = cores ? wgrad_rows_per_slab_cores(R) : wgrad_rows_per_slab(R);
         const int slabs = static_cast<int>((R + per - 1) / per);
         const size_t floats = (static_cast<size_t>(slabs) * (static_cast<size_t>(I) * J + J) + 63) / 64 * 64;
-        if (n_[0] + n_[1] + n_[2] == kWgradJobs || used_ + floats > capacity_) flush();
+        if (n_[0] + n_[1] + n_[2] + n_[3] == kWgradJobs || used_ + floats > capacity_) flush();
         // the bf16-split kernel addresses its operands with 32-bit element offsets
         const int kind = !cores ? 1 : static_cast<double>(R) * std::max(lda, ldd) < 4.0e9 ? 0 : 2;
         jobs_[kind][n_[kind]++] = {A, Dl, list, list_count, row_cls, partial_ + used_, grad_ + ly.w, lda, ldd, want,
@@ -1546,11 +1636,24 @@ public:
         used_ += floats;
     }
 
+    // Slab sums [slabs][n_in J + J] that another kernel takes: their place, and their sum with the next flush.
+    float *add_sums(int R, int per, const LayerRef &ly)
+    {
+        const int slabs = (R + per - 1) / per;
+        const size_t floats = (static_cast<size_t>(slabs) * (static_cast<size_t>(ly.n_in) * ly.n_out + ly.n_out) + 63) / 64 * 64;
+        if (n_[0] + n_[1] + n_[2] + n_[3] == kWgradJobs || used_ + floats > capacity_) flush();
+        float *at = partial_ + used_;
+        jobs_[3][n_[3]++] = {nullptr, nullptr, nullptr, nullptr, nullptr, at, grad_ + ly.w, 0, 0, 0, R, ly.n_in, ly.n_out, ly.n_in, per,
+                             slabs};
+        used_ += floats;
+        return at;
+    }
+
     void flush()
     {
         WgradBatch wb{};
         int n = 0, blocks[2] = {0, 0}, sum_blocks = 0;
-        for (int kind = 0; kind < 3; ++kind)
+        for (int kind = 0; kind < 4; ++kind)
             for (int k = 0; k < n_[kind]; ++k, ++n) {
                 const WgradJob &j = jobs_[kind][k];
                 wb.job[n] = j;
@@ -1578,16 +1681,16 @@ public:
         if (n_[1])
             hipLaunchKernelGGL(k_wgrad, dim3(blocks[1]), dim3(kThreads), 0, s_, wb, n_[0], n_[0] + n_[1]);
         hipLaunchKernelGGL(k_wgrad_reduce, dim3(sum_blocks), dim3(kThreads), 0, s_, wb, n);
-        n_[0] = n_[1] = n_[2] = 0;
+        n_[0] = n_[1] = n_[2] = n_[3] = 0;
         used_ = 0;
     }
 
 private:
     float *grad_, *partial_;
     size_t capacity_, used_ = 0;
-    int H_, generic_, n_[3] = {0, 0, 0};
+    int H_, generic_, n_[4] = {0, 0, 0, 0};
     hipStream_t s_;
-    WgradJob jobs_[3][kWgradJobs];   // by kernel: k_wgrad_split, k_wgrad, k_wgrad_mfma
+    WgradJob jobs_[4][kWgradJobs];   // by kernel: k_wgrad_split, k_wgrad, k_wgrad_mfma; slab sums taken elsewhere
 };
 
 struct DenseCall {
@@ -1813,25 +1916,28 @@ void launch_backward(const GraphView &gv, const ModelView &mv, const float *blob
     // 4. projection
     mark(PL_STAGE_BW_PROJ, true);
     {
-        const size_t total = NH;
-        if (H % 4 == 0)
-            hipLaunchKernelGGL(k_bw_proj4, dim3(static_cast<unsigned>((total / 4 + kThreads - 1) / kThreads)),
-                               dim3(kThreads), 0, s, gv, mv, fa.node_feats, fa.placement, fa.cur_node, gw.demb,
-                               gw.dx, gw.phi, dense ? 32 : mv.F);
-        else
-            hipLaunchKernelGGL(k_bw_proj, dim3(static_cast<unsigned>((total + kThreads - 1) / kThreads)),
-                               dim3(kThreads), 0, s, gv, mv, fa.node_feats, fa.placement, fa.cur_node, gw.demb,
-                               gw.dx, gw.phi, dense ? 32 : mv.F);
-        if (H < mv.F) {
-            const size_t tf = static_cast<size_t>(n) * mv.F;
-            hipLaunchKernelGGL(k_bw_phi, dim3(static_cast<unsigned>((tf + kThreads - 1) / kThreads)),
-                               dim3(kThreads), 0, s, gv, mv, fa.node_feats, fa.placement, fa.cur_node, gw.phi);
+        if (proj_fused(n, H)) {
+            const int per = proj_rows_per_slab(n, H);
+            float *sums = wq.add_sums(n, per, mv.proj);
+#define CALL(DM)                                                                                                       \
+    hipLaunchKernelGGL(k_bw_proj4<DM>, dim3((n + per - 1) / per), dim3(kThreads), 0, s, gv, mv, fa.node_feats, fa.placement, \
+                       fa.cur_node, gw.demb, per, sums)
+            if (mv.D <= 4) { CALL(4); } else if (mv.D <= 8) { CALL(8); } else { CALL(kMaxD); }
+#undef CALL
+        } else {
+            hipLaunchKernelGGL(k_bw_proj, dim3(static_cast<unsigned>((NH + kThreads - 1) / kThreads)), dim3(kThreads), 0, s,
+                               gv, mv, fa.node_feats, fa.placement, fa.cur_node, gw.demb, gw.dx, gw.phi, dense ? 32 : mv.F);   // (raw features padded to 32 columns)
+            if (H < mv.F) {
+                const size_t tf = static_cast<size_t>(n) * mv.F;
+                hipLaunchKernelGGL(k_bw_phi, dim3(static_cast<unsigned>((tf + kThreads - 1) / kThreads)),
+                                   dim3(kThreads), 0, s, gv, mv, fa.node_feats, fa.placement, fa.cur_node, gw.phi);
+            }
+            wq.add(gw.phi, dense ? 32 : mv.F, gw.dx, H, n, mv.proj, dense ? 32 : 0);
         }
     }
     mark(PL_STAGE_BW_PROJ, false);
     // 5. weight gradients
     mark(PL_STAGE_BW_WGRAD, true);
-    wq.add(gw.phi, dense ? 32 : mv.F, gw.dx, H, n, mv.proj, dense ? 32 : 0);   // (raw features padded to 32 columns)
     for (int l = 0; l < L; ++l)
         for (int set = 0; set < 3; ++set)
             wq.add(l == 0 ? ws.emb : gw.lact + static_cast<size_t>(l - 1) * NH, l == 0 ? 2 * H : H,

@@ -50,3 +50,30 @@ def test_tables_against_the_oracle(sizes, D, H, L, k, wd, every):
     coeff = np.where(np.arange(w.B) % every == 0, rng.normal(0, 1, w.B), 0.0).astype(np.float32)
     ref, _ = og.gradient_workload(w, actions, coeff.astype(np.float64), only=[int(b) for b in range(0, w.B, every)])
     _assert_blocks_close(run_gradient(w, actions, coeff)["grad"], ref, D, H, L)
+
+
+@pytest.mark.parametrize("D,H,graphs,n", [(3, 32, 9, 10417), (8, 48, 3, 21001), (16, 64, 2, 24001), (5, 256, 2, 6001)])
+def test_projection_gradient_of_a_large_batch(D, H, graphs, n):
+    """The projection's gradient formed in one pass over d e (batches of three million elements and more) against the sum of
+    its graphs' gradients, each a batch of its own that takes the other kernel; device ids out of range are in no row."""
+    rng = np.random.default_rng(D * H)
+    w = custom_workload(rng, [1], D, H, 1, 1, 1)
+    dst = np.arange(1, n, 2)                       # every second node has a parent, the first ones in a chain
+    src = np.where(dst > 9, dst - 9, 0)
+    N = graphs * n
+    feats = np.stack([rng.lognormal(0, 1, N), rng.lognormal(1, 1, N), rng.random(N) < 0.5], axis=1).astype(np.float32)
+    placement = rng.integers(-1, D + 1, N).astype(np.int32)
+    cur = rng.integers(0, n, graphs).astype(np.int32)
+    act, co = rng.integers(0, D, graphs).astype(np.int32), rng.normal(0, 1, graphs).astype(np.float32)
+
+    def gradient(lo, hi):
+        k = hi - lo
+        w.B, w.n_nodes, w.n_edges = k, np.full(k, n, np.int32), np.full(k, len(dst), np.int32)
+        w.edge_src, w.edge_dst = np.tile(src, k).astype(np.int32), np.tile(dst, k).astype(np.int32)
+        w.node_feats, w.placement, w.cur_node = feats[lo * n:hi * n], placement[lo * n:hi * n], cur[lo:hi]
+        return run_gradient(w, act[lo:hi], co[lo:hi])["grad"][:(D + 5) * H].reshape(D + 5, H).astype(np.float64)
+
+    got, ref = gradient(0, graphs), sum(gradient(b, b + 1) for b in range(graphs))
+    # (a row is an fp32 sum of up to N terms in two orders; its terms cancel, so the bound is against the largest row)
+    assert np.all(np.abs(got - ref) <= 1e-5 * np.abs(ref).max())
+    assert np.abs(ref).max(axis=1).min() > 0
