@@ -1214,11 +1214,11 @@ static int policy_gradient_impl(pl_graph_batch *g, const float *node_feats, cons
                       w->cfg.k_sweeps > 1 ? g->gw.snap_emb : nullptr, g->gw.snap_msg, nullptr, g->gw.mask4,
                       g->gw.hin, g->gw.hact);
     if (rc) return rc;
-    if (!accumulate) launch_fill_zero(grad, plan_weights(w->cfg, nullptr), s);
     ForwardArgs fa{node_feats, placement, cur_node, out_logits, nullptr, nullptr};
     const StageMarks marks{&g->timer, stage_mark};
     const BackwardArgs ba{actions, coeff, entropy_coeff, grad, out_logp, out_entropy, g->gw.snap_emb, g->gw.snap_msg,
-                          w->path == 0 ? reinterpret_cast<const uint4 *>(w->d_pool_bwfrag) : nullptr};
+                          w->path == 0 ? reinterpret_cast<const uint4 *>(w->d_pool_bwfrag) : nullptr, accumulate != 0,
+                          plan_weights(w->cfg, nullptr)};
     launch_backward(g->view, mv, w->d_blob_t, g->ws, g->gw, fa, ba, w->cfg.k_sweeps, g->ws.n_chunks, w->path,
                     lanes, chain_cores ? reinterpret_cast<const uint4 *>(w->d_wfrag_bw) : nullptr, w->d_sweep_bias,
                     w->sweep_ws, keep, pool_kept, &marks, s);

@@ -291,6 +291,8 @@ struct BackwardArgs {
     const float *snap_msg;
     // fragments of the reverse streaming pooling kernel, or null (then the dense-layer kernels do it)
     const uint4 *pool_bw_frag = nullptr;
+    bool accumulate = false;      // add to grad instead of replacing it
+    size_t n_grad = 0;            // its entries
 };
 
 void launch_backward(const GraphView &gv, const ModelView &mv, const float *blob_t, const Workspace &ws,

@@ -645,7 +645,7 @@ __global__ __launch_bounds__(kThreads, 3) void k_dense_split(const float *__rest
                                                              const float *__restrict__ bias, int relu,
                                                              const float *__restrict__ M, int ldm,
                                                              float *__restrict__ Y, int ldy, size_t list_stride,
-                                                             size_t w_stride, size_t b_stride)
+                                                             size_t w_stride, size_t b_stride, size_t wt_half, int y_half)
 {
     constexpr int Hc = 32 * NJ, GSW = Hc + 8;
     extern __shared__ __attribute__((aligned(16))) unsigned char lds_raw[];
@@ -655,7 +655,8 @@ __global__ __launch_bounds__(kThreads, 3) void k_dense_split(const float *__rest
     const uint4 *cell_w = reinterpret_cast<const uint4 *>(half_w);
     rows += blockIdx.z * list_stride;
     if (n_rows_dev) R = min(R, n_rows_dev[blockIdx.z]);
-    Wt += blockIdx.z * w_stride;
+    Wt += blockIdx.z * w_stride + blockIdx.y * wt_half;
+    Y += blockIdx.y * y_half;
     if (bias) bias += blockIdx.z * b_stride;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int li = lane & 31, lk = lane >> 5;
@@ -991,6 +992,7 @@ struct WgradJob {
     int32_t lda, ldd, want, R, I, J, n_in, rows_per_slab, slabs;
     // list lengths of the jobs before this one whose slab sums lie before its own in the same place (n_rows_dev's neighbours)
     int32_t n_prior;
+    int32_t store;                  // the sum is stored instead of added to what is there
 };
 constexpr int kWgradJobs = 32;      // (a table travels in the 4 KB of kernel arguments)
 struct WgradBatch {
@@ -1068,16 +1070,16 @@ __global__ __launch_bounds__(kThreads) void k_wgrad(WgradBatch wb, int lo, int h
         red[(grp * (kWgI + 1) + kWgI) * J + j] = accb;
     }
     __syncthreads();
-    if (active && grp == 0) {
-        float *dst = w.partial + static_cast<size_t>(sl) * (static_cast<size_t>(I) * J + J);
-        for (int ii = 0; ii <= kWgI; ++ii) {
-            float s = 0.0f;
-            for (int gq = 0; gq < groups; ++gq) s += red[(gq * (kWgI + 1) + ii) * J + j];
-            if (ii < kWgI) {
-                if (i0 + ii < I) dst[static_cast<size_t>(i0 + ii) * J + j] = s;
-            } else if (ib == 0) {
-                dst[static_cast<size_t>(I) * J + j] = s;
-            }
+    // (an entry to a thread: where J is small, few threads have a column, and they would add all groups of every row)
+    float *dst = w.partial + static_cast<size_t>(sl) * (static_cast<size_t>(I) * J + J);
+    for (int e = tid; e < (kWgI + 1) * J; e += kThreads) {
+        const int ii = e / J;
+        float s = 0.0f;
+        for (int gq = 0; gq < groups; ++gq) s += red[gq * (kWgI + 1) * J + e];
+        if (ii < kWgI) {
+            if (i0 + ii < I) dst[static_cast<size_t>(i0) * J + e] = s;
+        } else if (ib == 0) {
+            dst[static_cast<size_t>(I) * J + (e - kWgI * J)] = s;
         }
     }
 }
@@ -1516,7 +1518,7 @@ __global__ __launch_bounds__(kThreads) void k_wgrad_reduce(WgradBatch wb, int n_
     if (q == 0 && idx < count) {
         float t = part[0][c];
         for (int k = 1; k < 8; ++k) t += part[k][c];
-        w.out[idx] += t;
+        w.out[idx] = w.store ? t : w.out[idx] + t;
     }
 }
 
@@ -1651,7 +1653,7 @@ public:
             used_ += floats;
         }
         jobs_[kind][n_[kind]++] = {A, Dl, list, list_count, row_cls, place_, grad_ + ly.w, lda, ldd, want,
-                                   static_cast<int32_t>(R), I, J, ly.n_in, per, slabs, share};
+                                   static_cast<int32_t>(R), I, J, ly.n_in, per, slabs, share, store_};
     }
 
     // Slab sums [slabs][n_in J + J] that another kernel takes: their place, and their sum with the next flush.
@@ -1662,10 +1664,13 @@ public:
         if (n_[0] + n_[1] + n_[2] + n_[3] == kWgradJobs || used_ + floats > capacity_) flush();
         float *at = partial_ + used_;
         jobs_[3][n_[3]++] = {nullptr, nullptr, nullptr, nullptr, nullptr, at, grad_ + ly.w, 0, 0, 0, R, ly.n_in, ly.n_out, ly.n_in, per,
-                             slabs, 0};
+                             slabs, 0, store_};
         used_ += floats;
         return at;
     }
+
+    // Contractions added from now on are the first of their layers' in this pass, and their sums go in place of what is there.
+    void store_sums(bool yes) { store_ = yes; }
 
     void flush()
     {
@@ -1705,6 +1710,7 @@ public:
 
 private:
     float *grad_, *partial_, *place_ = nullptr;
+    int32_t store_ = 0;
     size_t capacity_, used_ = 0;
     int H_, generic_, n_[4] = {0, 0, 0, 0};
     hipStream_t s_;
@@ -1721,17 +1727,19 @@ struct DenseCall {
     // n_lists row lists in one launch: z-th list at rows + z list_stride with count n_rows_dev[z],
     // weights at Wt + z w_stride, bias + z b_stride
     int n_lists = 1; size_t list_stride = 0, w_stride = 0, b_stride = 0;
+    // n_halves blocks of output columns: block k has its weights at Wt + k wt_half and goes to Y + k y_half
+    int n_halves = 1; size_t wt_half = 0; int y_half = 0;
 };
 
 void launch_dense(const DenseCall &c, int H, hipStream_t s)
 {
     if (c.R <= 0) return;
-    const dim3 grid((c.R + kDenseRows - 1) / kDenseRows, 1, c.n_lists);
+    const dim3 grid((c.R + kDenseRows - 1) / kDenseRows, c.n_halves, c.n_lists);
 #define CALL(NJ)                                                                                                 \
     allow_lds_bw(k_dense_split<NJ>, dense_split_lds_bytes(NJ));                                                  \
     hipLaunchKernelGGL(k_dense_split<NJ>, grid, dim3(kThreads), dense_split_lds_bytes(NJ), s, c.X, c.ldx, c.rows, \
                        c.n_rows_dev, c.R, c.K, c.Wt, c.ldwt, c.bias, c.relu, c.M, c.ldm, c.Y, c.ldy, c.list_stride, \
-                       c.w_stride, c.b_stride)
+                       c.w_stride, c.b_stride, c.wt_half, c.y_half)
     if (H == 32) { CALL(1); } else if (H == 64) { CALL(2); } else { CALL(4); }
 #undef CALL
 }
@@ -1754,6 +1762,10 @@ void launch_backward(const GraphView &gv, const ModelView &mv, const float *blob
         if (marks && marks->mark) marks->mark(marks->ctx, stage, begin, s);
     };
     WgradQueue wq(grad, gw.partial, gw.partial_floats, H, generic, s);
+    // Unless the call adds to grad, the sums of a layer's first contraction are stored: every layer has one, but f and g
+    // without a sweep.
+    if (!ba.accumulate && k_sweeps == 0) launch_fill_zero(grad, ba.n_grad, s);
+    const bool fresh = !ba.accumulate && k_sweeps > 0;
     // 1. head
     mark(PL_STAGE_BW_HEAD, true);
     launch_head_bw(gv, mv, blob_t, fa.cur_node,
@@ -1811,15 +1823,15 @@ void launch_backward(const GraphView &gv, const ModelView &mv, const float *blob
                 c.w_stride = w_stride;
                 launch_dense(c, H, s);
             }
-            for (int half = 0; half < 2; ++half) {   // the first layer is [2H, H]: inputs half H .. half H + H - 1
-                DenseCall c{gw.dl, H, gw.lists, gw.counts, n, H,
-                            mv.blob + l0.layer[0].w + static_cast<size_t>(half) * H * H, H, nullptr, 0, nullptr, 0,
-                            gw.demb + half * H, 2 * H};
-                c.n_lists = 3;
-                c.list_stride = static_cast<size_t>(n);
-                c.w_stride = w_stride;
-                launch_dense(c, H, s);
-            }
+            // the first layer is [2H, H]: inputs half H .. half H + H - 1
+            DenseCall c{gw.dl, H, gw.lists, gw.counts, n, H, mv.blob + l0.layer[0].w, H, nullptr, 0, nullptr, 0, gw.demb, 2 * H};
+            c.n_lists = 3;
+            c.list_stride = static_cast<size_t>(n);
+            c.w_stride = w_stride;
+            c.n_halves = 2;
+            c.wt_half = static_cast<size_t>(H) * H;
+            c.y_half = H;
+            launch_dense(c, H, s);
         }
         }
     } else {
@@ -1918,6 +1930,7 @@ void launch_backward(const GraphView &gv, const ModelView &mv, const float *blob
     }
     {
         mark(PL_STAGE_BW_WGRAD, true);
+        wq.store_sums(fresh && j == k_sweeps - 1);
         for (int dir = 0; dir < 2; ++dir)
             for (int l = 0; l < L; ++l) {
                 const float *dfl = gw.dfg + dir * gw.dfg_stride + static_cast<size_t>(l) * NH;
@@ -1933,6 +1946,7 @@ void launch_backward(const GraphView &gv, const ModelView &mv, const float *blob
     }
     // 4. projection
     mark(PL_STAGE_BW_PROJ, true);
+    wq.store_sums(fresh);
     {
         if (proj_fused(n, H)) {
             const int per = proj_rows_per_slab(n, H);
