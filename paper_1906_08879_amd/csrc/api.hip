@@ -550,9 +550,13 @@ int forward_impl(pl_graph_batch *g, const float *node_feats, const int32_t *plac
     if (out_class) launch_classes(gv, cur_node, ws.reach, out_class, s);
     const bool pool_mfma = w->d_pool_frag && w->path == 0;
     int pool_slices = ws.n_chunks;
+    // (its graphs are the batch's, in a batch of copies too)
+    const int n_max = !pool_mfma && w->path == 0 ? graph_extent(g->host).n_max : 0;
+    const bool in_head = n_max > 0 && pool_in_head(mv.H, mv.L, gv.B, n_max);
     {
         StageScope scope(timer, PL_STAGE_POOL, s);
-        if (pool_mfma)
+        if (in_head) {
+        } else if (pool_mfma)
             pool_slices = launch_pool_mfma(gv, mv, ws, fa, reinterpret_cast<const uint4 *>(w->d_pool_frag),
                                            reinterpret_cast<const uint4 *>(w->d_pool_afrag), w->d_pool_bias,
                                            w->sweep_ws, keep_pool, s);
@@ -562,7 +566,7 @@ int forward_impl(pl_graph_batch *g, const float *node_feats, const int32_t *plac
     }
     {
         StageScope scope(timer, PL_STAGE_HEAD, s);
-        launch_head(gv, mv, ws, fa, pool_slices, s);
+        launch_head(gv, mv, ws, fa, pool_slices, in_head ? n_max : 0, s);
     }
     if (out_node_emb)
         PL_HIP(hipMemcpyAsync(out_node_emb, ws.emb,

@@ -170,8 +170,9 @@ void launch_pool_generic(const GraphView &gv, const ModelView &mv, const Workspa
                          const ForwardArgs &fa, hipStream_t s);
 
 // ---- policy head (kernels_head.hip)
+bool pool_in_head(int H, int L, int B, int n_max);
 void launch_head(const GraphView &gv, const ModelView &mv, const Workspace &ws, const ForwardArgs &fa, int max_chunks,
-                 hipStream_t s);
+                 int n_max, hipStream_t s);
 struct HeadBwArgs {
     const double *hid64;          // [B, H], logit [B, D]: left by the forward pass
     const float *logit;

@@ -235,11 +235,26 @@ struct HeadOut {
     uint32_t *done;       // (SPLIT) [B] workgroups of a graph that have written theirs; cleared by the pooling kernels
 };
 
+// Pooling of small graphs of narrow networks within the head's workgroup (pool_in_head): reachability and placement, and
+// where its LDS begins.  reach is null where a kernel of its own has left partial sums.
+struct PoolHere {
+    const uint8_t *reach;
+    const int32_t *placement;
+    int lds_at;
+};
+constexpr int kHerePoolNodes = 64, kHerePoolH = 16;
+// floats of the three l networks, of embedding rows, of two layers' outputs; keys
+constexpr int here_ld(int H) { return 2 * H + 1; }
+constexpr size_t here_lds(int H, int L, int n)
+{
+    return sizeof(float) * (static_cast<size_t>(3) * ((L + 1) * H * H + L * H) + static_cast<size_t>(n) * (here_ld(H) + 2 * (H + 1)) + n);
+}
+
 template <int HT, int RT, HeadShape SHAPE>
 __global__ __launch_bounds__(head_threads(HT, SHAPE)) void k_head(GraphView gv, ModelView mv, const float *__restrict__ emb,
                                                               const float *__restrict__ partial,
                                                               const int32_t *__restrict__ cur_node, int max_chunks,
-                                                              HeadOut o)
+                                                              HeadOut o, PoolHere here)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
     __shared__ double hid[kMaxH];
@@ -286,16 +301,67 @@ __global__ __launch_bounds__(head_threads(HT, SHAPE)) void k_head(GraphView gv, 
     // ---- P[set][group] = sum of the pooling partials in slice order
     const int first = set_first * G * H;
     const float *src = partial + static_cast<size_t>(b) * max_chunks * 3 * G * H + first;
-    for (int i = tid; i < n_sets * G * H; i += T) {
-        float s = 0.0f;
-#pragma unroll 8
-        for (int c = 0; c < chunks; ++c) s += src[static_cast<size_t>(c) * 3 * G * H + i];
+    auto pooled = [&](int i, float s) {
         x[i] = s;
         if (o.out_pooled) o.out_pooled[static_cast<size_t>(b) * 3 * G * H + first + i] = s;
         if (o.hin) {
             const int set = i / (G * H);
             o.hin[kept(set_first + set, 0, 1, i - set * G * H)] = s;
         }
+    };
+    bool here_pooled = false;
+    if constexpr (HT == 0 && SHAPE == kPerGraph) {
+        // Or, for a small graph: l of its nodes, a thread to an output, and their sums, in the order of the kernel that
+        // otherwise does it (bias first, then the inputs; nodes ascending).
+        here_pooled = here.reach != nullptr;
+        if (here_pooled) {
+            float *wl = reinterpret_cast<float *>(lds + here.lds_at);          // per set: matrices and biases as in the blob
+            const int per_set = (L + 1) * H * H + L * H, ld = here_ld(H), la = H + 1;
+            float *rows = wl + 3 * per_set, *act = rows + n_b * ld;
+            int *key = reinterpret_cast<int *>(act + 2 * n_b * la);
+            for (int i = tid; i < 3 * per_set; i += T) {
+                const int set = i / per_set;
+                wl[i] = mv.blob[mv.l[0].layer[0].w + set * (mv.l[1].layer[0].w - mv.l[0].layer[0].w) + i - set * per_set];
+            }
+            for (int i = tid; i < n_b * 2 * H; i += T) {
+                const int v = i / (2 * H);
+                rows[v * ld + i - v * 2 * H] = emb[static_cast<size_t>(n0) * 2 * H + i];
+            }
+            for (int v = tid; v < n_b; v += T) {
+                const int dev = here.placement[n0 + v];
+                const int set = mv.single_set ? 0 : (here.reach[static_cast<size_t>(gv.n_tot) + n0 + v] ? 0 : (here.reach[n0 + v] ? 1 : 2));
+                key[v] = v == cl ? -1 : set * G + (dev < 0 || dev >= D ? -3 * G : (G == 1 ? 0 : dev));   // (negative: in no sum)
+            }
+            __syncthreads();
+            const float *in = rows;
+            for (int l = 0, n_in = 2 * H, ldi = ld; l < L; ++l, n_in = H, ldi = la) {
+                float *out = act + l % 2 * n_b * la;
+                for (int i = tid; i < n_b * H; i += T) {
+                    const int v = i / H, j = i - v * H, k = key[v];
+                    if (k < 0) continue;
+                    const float *w = wl + k / G * per_set + (l == 0 ? 0 : 2 * H * H + H + (l - 1) * (H * H + H));
+                    float s = w[n_in * H + j];
+#pragma unroll 8
+                    for (int q = 0; q < n_in; ++q) s = fmaf(in[v * ldi + q], w[q * H + j], s);
+                    out[v * la + j] = fmaxf(s, 0.0f);
+                }
+                __syncthreads();
+                in = out;
+            }
+            for (int i = tid; i < 3 * G * H; i += T) {
+                const int k = i / H, j = i - k * H;
+                float s = 0.0f;
+#pragma unroll 8
+                for (int v = 0; v < n_b; ++v) s += key[v] == k ? in[v * la + j] : 0.0f;
+                pooled(i, s);
+            }
+        }
+    }
+    for (int i = tid; i < n_sets * G * H && !here_pooled; i += T) {
+        float s = 0.0f;
+#pragma unroll 8
+        for (int c = 0; c < chunks; ++c) s += src[static_cast<size_t>(c) * 3 * G * H + i];
+        pooled(i, s);
     }
     for (int i = tid; i < 2 * H && set_first == 0; i += T)
         z[i] = cur_ok ? emb[static_cast<size_t>(n0 + cl) * 2 * H + i] : 0.0f;
@@ -558,8 +624,18 @@ void allow_lds(K kernel, size_t bytes)
 
 }  // namespace
 
+// Narrow networks on batches that leave a compute unit to every graph, of graphs that one pass of a workgroup's threads
+// covers: the launch between costs more than the sums (forward pass with a pooling kernel and without: one graph of 32
+// nodes, H = 8, 26.3 / 22.0 us; 64 graphs of 64 nodes 46 / 30; 256 graphs of 64 nodes and 8 devices 67 / 33; 128 graphs of
+// 64 nodes, H = 16, 16 devices 58 / 40).  With more graphs than compute units the head has fewer threads.
+bool pool_in_head(int H, int L, int B, int n_max)
+{
+    return (H == 8 || H == 16) && L <= 2 && B <= kComputeUnits && n_max <= kHerePoolNodes;
+}
+
+// n_max: nodes of the largest graph, where the head pools (0: a kernel of its own has)
 void launch_head(const GraphView &gv, const ModelView &mv, const Workspace &ws, const ForwardArgs &fa, int max_chunks,
-                 hipStream_t s)
+                 int n_max, hipStream_t s)
 {
     if (gv.B == 0) return;
     const HeadOut o{ws.zbuf,      ws.hid,       ws.logit, fa.out_logits, fa.out_probs, fa.out_pooled,
@@ -568,10 +644,15 @@ void launch_head(const GraphView &gv, const ModelView &mv, const Workspace &ws, 
         constexpr int HT = decltype(ht)::value, RT = decltype(rt)::value;
         constexpr HeadShape SHAPE = decltype(shape)::value;
         const int threads = head_launch_threads(mv.H, gv.B, HT, SHAPE), sets = SHAPE == kPerSet ? 1 : 3;
-        const size_t lds = head_lds(mv.H, mv.G, RT, HT, SHAPE, threads, head_small(mv.H, mv.D, sets * mv.L + 1, HT));
+        size_t lds = head_lds(mv.H, mv.G, RT, HT, SHAPE, threads, head_small(mv.H, mv.D, sets * mv.L + 1, HT));
+        PoolHere here{nullptr, nullptr, 0};
+        if (n_max > 0) {
+            here = {ws.reach, fa.placement, static_cast<int>((lds + 15) / 16 * 16)};
+            lds = here.lds_at + here_lds(mv.H, mv.L, n_max);
+        }
         allow_lds(k_head<HT, RT, SHAPE>, lds);
         hipLaunchKernelGGL((k_head<HT, RT, SHAPE>), dim3(SHAPE == kPerSet ? 3 * gv.B : gv.B), dim3(threads), lds, s, gv, mv,
-                           ws.emb, ws.partial, fa.cur_node, max_chunks, o);
+                           ws.emb, ws.partial, fa.cur_node, max_chunks, o, here);
     });
 }
 

@@ -1,5 +1,6 @@
 """The generic pooling kernel's two launch shapes: a graph pooled beside few others (its sets side by side) and beside
-many (one workgroup per slice) gives the same bits, for graphs of one slice and of several."""
+many (one workgroup per slice) gives the same bits, for graphs of one slice and of several; narrow networks pool small
+graphs beside few others in the head's workgroup, in the same order."""
 import numpy as np
 import pytest
 
@@ -8,7 +9,7 @@ from gpu_common import custom_workload, run_library
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("D,H,group,n", [(2, 8, 1, 32), (3, 17, 0, 1), (4, 48, 1, 300), (3, 100, 1, 200), (2, 256, 1, 140)])
+@pytest.mark.parametrize("D,H,group,n", [(2, 8, 1, 32), (16, 16, 1, 64), (5, 8, 0, 64), (3, 16, 1, 65), (3, 17, 0, 1), (4, 48, 1, 300), (3, 100, 1, 200), (2, 256, 1, 140)])
 def test_same_bits_beside_few_and_many_graphs(D, H, group, n):
     rng = np.random.default_rng(H + n)
     one = custom_workload(rng, [n], D, H, 2, 1, group)
