@@ -9,7 +9,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libplaceto.so")
-SOURCES = ["api.hip", "kernels_generic.hip", "kernels_mfma.hip", "kernels_lanes.hip", "kernels_tiles.hip", "kernels_pool_mfma.hip", "kernels_head.hip", "kernels_episode.hip", "kernels_simulator.hip", "kernels_backward.hip", "layout.cpp", "plan.cpp", "workspace.cpp"]
+SOURCES = ["api.hip", "kernels_generic.hip", "kernels_mfma.hip", "kernels_lanes.hip", "kernels_tiles.hip", "kernels_wide.hip", "kernels_pool_mfma.hip", "kernels_head.hip", "kernels_episode.hip", "kernels_simulator.hip", "kernels_backward.hip", "layout.cpp", "plan.cpp", "workspace.cpp"]
 
 HIPCC_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
@@ -24,7 +24,7 @@ HIPCC_FLAGS = [
 # clang 22, whose code with and without it gives the same bits on the timed cases.)  Simulator: 3.38 -> 2.70 ms for 256 NASNet-like graphs; sweep:
 # forward pass 0.715 -> 0.690 ms (64 NMT-like graphs), 2.16 -> 2.12 ms (256 NASNet-like ones).
 _NO_STRUCTURE = ["-mllvm", "-structurizecfg-skip-uniform-regions"]
-SOURCE_FLAGS = {"kernels_simulator.hip": _NO_STRUCTURE, "kernels_mfma.hip": _NO_STRUCTURE, "kernels_tiles.hip": _NO_STRUCTURE, "kernels_lanes.hip": _NO_STRUCTURE}
+SOURCE_FLAGS = {"kernels_simulator.hip": _NO_STRUCTURE, "kernels_mfma.hip": _NO_STRUCTURE, "kernels_tiles.hip": _NO_STRUCTURE, "kernels_wide.hip": _NO_STRUCTURE, "kernels_lanes.hip": _NO_STRUCTURE}
 
 
 def hipcc() -> str:

@@ -318,7 +318,15 @@ void launch_sweep_tiles_bw(const GraphView &gv, const ModelView &mv, const uint4
                           int WS, const int32_t *cur_node, float *demb, float *dagg, uint8_t *mask4,
                           float *delta, size_t delta_stride, hipStream_t s);
 
-// ---- matrix-core sweep (kernels_mfma.hip: 128 columns; hands 32 and 64 on)
+// ---- matrix-core sweep of 128 columns, few graphs (kernels_wide.hip)
+void launch_sweep_wide(const GraphView &gv, const ModelView &mv, const Workspace &ws, const ForwardArgs &fa, const uint4 *wfrag,
+                       const float *bias, bool first_sweep, bool more_sweeps, float *keep, size_t keep_stride,
+                       uint8_t *gates, hipStream_t s);
+void launch_sweep_wide_bw(const GraphView &gv, const ModelView &mv, const uint4 *wfrag, const float *bias,
+                          const int32_t *cur_node, float *demb, float *dagg, uint8_t *mask4, float *delta,
+                          size_t delta_stride, hipStream_t s);
+
+// ---- matrix-core sweep (kernels_mfma.hip: 128 columns; hands 32 and 64, and few graphs, on)
 bool sweep_mfma_supported(int H, int L, int weight_dtype);
 void pack_sweep_weights(const ModelView &mv, const float *blob, int WS, std::vector<uint16_t> *frag,
                         std::vector<float> *bias, bool reverse = false);

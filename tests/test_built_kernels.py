@@ -134,3 +134,14 @@ def test_sweeps_on_matrix_cores_keep_their_residency(code_objects):
             assert waves >= want and scratch == 0, (H, WS, L, first, reverse, registers, scratch)
             seen.add((H, WS, L))
     assert seen == set(WAVES)
+
+
+@needs_llvm
+def test_wide_sweep_fits_a_compute_unit(code_objects):
+    """Eight waves of every variant of the sweep of 128 columns, two to a SIMD, without spills."""
+    seen = 0
+    for obj in code_objects:
+        for args, registers, scratch in _kernels(obj, "k_sweep_wide"):
+            assert registers <= 256 and scratch == 0, (args, registers, scratch)
+            seen += 1
+    assert seen == 12

@@ -8,6 +8,7 @@ import pytest
 
 import oracle
 from gpu_common import assert_rows_close, custom_workload, run_library
+from test_gpu_batch_size import _first
 from test_gpu_gradient import _compare
 from test_gpu_lanes import _chain, _fan
 
@@ -51,3 +52,21 @@ def test_random_dags(seed):
     w = custom_workload(rng, sizes, int(rng.integers(1, 9)), H, 1, 1 + (seed // 2) % 3, seed % 2, "fp32", p_edge=p_edge)
     ref = oracle.forward_workload(w, n_threads=8)
     assert_rows_close(run_library(w)["emb"], ref["emb"], H, f"seed {seed} H {H} p_edge {p_edge}")
+
+
+@pytest.mark.parametrize("L", [1, 2])
+@pytest.mark.parametrize("k", [1, 2, 3])
+def test_128_columns_beside_few_and_many_graphs(L, k):
+    """Up to 128 graphs 128 columns take this file's kernel with eight waves, in more the one of kernels_mfma.hip: the
+    same bits, lists of every length with near and far sources included; and every variant against the oracles."""
+    many = _batch(140, 3, 128, L, k, "bf16", 900 + L + 10 * k)
+    few, n = _first(many, len(LISTS))
+    edge, _ = _first(many, 128)
+    ref = oracle.forward_workload(few, n_threads=8)
+    got, whole, limit = run_library(few, want_class=True), run_library(many, want_class=True), run_library(edge, want_class=True)
+    assert_rows_close(got["emb"], ref["emb"], 128, f"L {L} k {k}")
+    for other in (whole, limit):
+        assert np.array_equal(got["emb"], other["emb"][:n])
+        assert np.array_equal(got["classes"], other["classes"][:n])
+        assert np.array_equal(got["logits"], other["logits"][:few.B])
+    _compare(few, f"H 128 L {L} k {k}")
