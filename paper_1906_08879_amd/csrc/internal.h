@@ -149,12 +149,14 @@ struct ForwardArgs {
 };
 
 constexpr int kPoolChunk = 128;   // nodes per slice of a graph's pooling
-// Slices of a graph of n nodes: one for every 128 nodes, in small graphs for every 64 (layered graphs of 200 nodes, with two
-// and with four: pooling of 64 at H = 32 13.8 / 10.8 us; forward pass of 256 at H = 48 582 / 499 us, at H = 128 189 / 170).
+// Slices of a graph of n nodes: one for every 128 nodes, in small graphs for every 64 up to six (pooling of 64 layered
+// graphs of 200 nodes, H = 32, with two and with four: 13.8 / 10.8 us; forward pass of 256 of them at H = 48 582 / 499 us, at
+// H = 128 189 / 170; of one of 300 nodes at H = 32 with four and with five 75.6 / 74.5 us; of 128 Inception-like graphs of 590
+// nodes with five and with six 275.5 / 277).
 __host__ __device__ inline int pool_slices(int n, int most)
 {
     const int by_chunk = (n + kPoolChunk - 1) / kPoolChunk, by_half = (2 * n + kPoolChunk - 1) / kPoolChunk;
-    const int want = by_chunk > 4 ? by_chunk : (by_half < 4 ? by_half : 4);
+    const int want = by_chunk > 6 ? by_chunk : (by_half < 6 ? by_half : 6);
     return want < most ? want : most;
 }
 

@@ -37,7 +37,6 @@ typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4;
 constexpr int kThreads = 256;
 constexpr int kBatch = 16;          // nodes per tile: one MFMA row tile per bf16 part
 constexpr int kMaxKeys = 3 * kMaxD; // (set, device group) keys of a graph
-constexpr int kAhead = 1;            // k-steps between reading an A fragment from LDS and using it
 
 __device__ __forceinline__ void lds_barrier()
 {
@@ -173,6 +172,7 @@ __global__ __launch_bounds__(kThreads, 3) void k_pool_tiles(PoolParams P)
 {
     constexpr int K1 = 2 * H;                    // input width of the first layer
     constexpr int KS1 = K1 / 32, KS2 = H / 32;
+    constexpr int kAhead = H == 64 && WS == 3 && L == 2 ? 1 : 2;   // k-steps between reading an A fragment from LDS and using it
     constexpr int NTL = H / 16;                  // output column tiles
     constexpr int TPW = (NTL + 3) / 4;           // column tiles per wave
     // bf16 row strides: K / 2 + 8 words.  Measured on this chip (SQ_LDS_BANK_CONFLICT): a
@@ -218,7 +218,9 @@ __global__ __launch_bounds__(kThreads, 3) void k_pool_tiles(PoolParams P)
         }
         share = (all + slices - 1) / slices;
     };
-    auto parts_of = [&](int i) { return in_set[i] ? (in_set[i] + share - 1) / share : 1; };   // (at most `slices`)
+    auto parts_of = [&](int i) {
+        return in_set[i] ? static_cast<int>(static_cast<unsigned>(in_set[i] + share - 1) / static_cast<unsigned>(share)) : 1;
+    };   // (at most `slices`)
     // workgroups 0 .. 2 take the first part of each set (their weights are on the way before the sets' sizes are known),
     // the others the rest in order
     int set = blockIdx.x, slice = 0;
@@ -265,8 +267,9 @@ __global__ __launch_bounds__(kThreads, 3) void k_pool_tiles(PoolParams P)
     if (blockIdx.x < 3) count_tiles();
     // this workgroup takes the tiles [t_lo, t_hi) of the set's
     const int parts = parts_of(set), kb = set * G, n_tiles = in_set[set];
-    const int t_lo = static_cast<int>(static_cast<long long>(n_tiles) * slice / parts);
-    const int t_hi = static_cast<int>(static_cast<long long>(n_tiles) * (slice + 1) / parts);
+    // (a graph of 2^24 nodes has 2^20 tiles and eight parts: 32 bits hold the products)
+    const int t_lo = static_cast<int>(static_cast<unsigned>(n_tiles) * static_cast<unsigned>(slice) / static_cast<unsigned>(parts));
+    const int t_hi = static_cast<int>(static_cast<unsigned>(n_tiles) * static_cast<unsigned>(slice + 1) / static_cast<unsigned>(parts));
     auto sums = [&](int i) { return P.partial + (((static_cast<size_t>(b) * P.max_slices + i) * 3 + set) * G) * H; };
     float *dst = sums(slice);
     if (slice == parts - 1)                      // the head reads `slices` sums of every set
