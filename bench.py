@@ -316,7 +316,8 @@ def main() -> int:
                             "graph, summed over the batch)"}
         # the reverse pass's largest stage: every layer's weight gradient is a contraction over rows,
         # 2 R I J flops each, that reads its two operands (R x I inputs, R x J deltas, fp32) once:
-        # projection (F inputs), 2 directions x (f, g) x L layers of H x H per sweep, l (2H x H, then
+        # projection (F inputs; formed in the projection's own stage from three million elements on), 2 directions x
+        # (f, g) x L layers of H x H per sweep, l (2H x H, then
         # H x H) over the nodes of the three sets (all nodes but the current ones).  With each operand
         # split into three bf16 parts and six products kept, the matrix cores have 6 x those flops to
         # do at the bf16 rate (less time than the operands take to arrive): the stage is priced
@@ -324,9 +325,9 @@ def main() -> int:
         wg_ms = gradient["stage_ms"].get("bw_wgrad")
         if wg_ms:
             n, H, L, F = float(w.n_tot), float(w.H), float(w.n_layers), float(w.D + 4)
-            n_set = n - w.B
-            flops = 2.0 * H * (n * F + n * 4.0 * L * H * w.k_sweeps + n_set * (2.0 * H + (L - 1.0) * H))
-            alg = 4.0 * (n * (F + H) + n * 4.0 * L * 2.0 * H * w.k_sweeps
+            n_set, n_proj = n - w.B, 0.0 if n * H >= 3e6 and w.H % 4 == 0 else n
+            flops = 2.0 * H * (n_proj * F + n * 4.0 * L * H * w.k_sweeps + n_set * (2.0 * H + (L - 1.0) * H))
+            alg = 4.0 * (n_proj * (F + H) + n * 4.0 * L * 2.0 * H * w.k_sweeps
                          + n_set * (3.0 * H + (L - 1.0) * 2.0 * H))
             gbs = alg / (wg_ms * 1e-3) / 1e9
             gradient["roofline"] = {"kernel": "weight-gradient contractions (bf16 matrix cores, operands split "
