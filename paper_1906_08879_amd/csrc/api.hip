@@ -551,7 +551,7 @@ int forward_impl(pl_graph_batch *g, const float *node_feats, const int32_t *plac
     const bool pool_mfma = w->d_pool_frag && w->path == 0;
     int pool_slices = ws.n_chunks;
     // (its graphs are the batch's, in a batch of copies too)
-    const int n_max = !pool_mfma && w->path == 0 ? graph_extent(g->host).n_max : 0;
+    const int n_max = !pool_mfma && w->path == 0 && pool_in_head(mv.H, mv.L, gv.B, 1) ? graph_extent(g->host).n_max : 0;
     const bool in_head = n_max > 0 && pool_in_head(mv.H, mv.L, gv.B, n_max);
     {
         StageScope scope(timer, PL_STAGE_POOL, s);
