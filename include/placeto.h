@@ -157,7 +157,9 @@ int pl_weights_set_path(pl_weights *w, int32_t path);
  * outside [0, D) contributes an all-zero one-hot and is pooled nowhere; a cur_node outside
  * its graph gives NaN logits for that graph; neither writes out of bounds.
  * The first call on a batch for a given (D, H) allocates the batch's intermediate buffers
- * (and is therefore not capturable into a HIP graph); later calls only launch kernels. */
+ * (and is therefore not capturable into a HIP graph); later calls only launch kernels.  The buffers are
+ * those of one network: a call with another H, or grouped by another number of devices, replaces them, and a pass
+ * that was captured before it must not be replayed any more. */
 int pl_embed_forward(pl_graph_batch *g, const float *node_feats, const int32_t *placement,
                      const int32_t *cur_node, const pl_weights *w, float *out_logits,
                      void *stream);
@@ -226,9 +228,10 @@ int pl_episode_step(pl_graph_batch *g, int32_t D, const float *logits, const flo
  *   logits       dev [B, D], or [n_steps, B, D] when keep_logits != 0 (every step's logits)
  *   out_actions  dev [n_steps, B] or NULL;  out_logp  dev [n_steps, B] or NULL
  * Small batches take several steps in one forward pass over all states that these steps can reach (at most 256
- * graphs together), which leaves every result the same bits; the copies take up to 4 GiB of device memory, allocated
- * on the first such call, kept by the batch and freed with it.  Where they cannot be had (no memory, or a stream that
- * is being captured when they are not there yet) the steps go one by one. */
+ * graphs together), which leaves every result the same bits.  The copies take device memory, at most 4 GiB a batch: it
+ * is allocated on the first such call, whatever its number of steps, and again only for a network whose copies do not
+ * fit in it; it is never moved, stays with the batch and is freed with it.  Where there is none (no memory, or a
+ * stream that is being captured when it is not there yet) the steps go one by one. */
 int pl_episode_run(pl_graph_batch *g, const pl_weights *w, float *node_feats, int32_t *placement,
                    int32_t *cur_node, const int32_t *order, const float *uniforms, int32_t t0,
                    int32_t n_steps, float *logits, int32_t keep_logits, int32_t *out_actions,

@@ -86,7 +86,7 @@ struct pl_graph_batch {
     pl::GraphView view{};
     pl::Workspace ws;
     pl::GradWorkspace gw;
-    pl::EpisodeCopies ahead;
+    pl::EpisodeRooms ahead;
     // pl_simulate_reward: one block with peaks [B, sim_D], op_start, op_end [n_tot], arrival, arrival_last
     // [n_tot, sim_D], run times [B] and workgroup counters [B] (zero between calls)
     float *sim_start = nullptr, *sim_end = nullptr, *sim_arrival = nullptr, *sim_arrival_last = nullptr, *sim_rt = nullptr;
@@ -577,33 +577,13 @@ int forward_impl(pl_graph_batch *g, const float *node_feats, const int32_t *plac
 }
 
 // ---- steps of an episode taken ahead (kernels_episode.hip says why)
-constexpr int kAheadGraphs = 256;                                  // most graphs in all copies
-constexpr size_t kAheadBytes = static_cast<size_t>(4) << 30;       // most memory that they may take
+constexpr int kAheadGraphs = 256;   // most graphs in all copies
 
 int64_t states_within(int D, int steps)   // states that fewer than `steps` steps can reach
 {
     int64_t all = 0, at = 1;
     for (int i = 0; i < steps; ++i, at *= D) all += at;
     return all;
-}
-
-size_t carve_copies(unsigned char *base, size_t n, size_t B, int copies, const ModelView &mv, EpisodeCopies *c)
-{
-    size_t at = 0;
-    auto take = [&](size_t bytes) {
-        unsigned char *p = base ? base + at : nullptr;
-        at += (bytes + 255) / 256 * 256;
-        return p;
-    };
-    const size_t N = n * copies, G = B * copies;
-    c->view.node_off = reinterpret_cast<int32_t *>(take(sizeof(int32_t) * (G + 1)));
-    c->view.tmpl = reinterpret_cast<int32_t *>(take(sizeof(int32_t) * G));
-    c->view.node_graph = reinterpret_cast<int32_t *>(take(sizeof(int32_t) * N));
-    c->feats = reinterpret_cast<float *>(take(sizeof(float) * N * 3));
-    c->placement = reinterpret_cast<int32_t *>(take(sizeof(int32_t) * N));
-    c->cur_node = reinterpret_cast<int32_t *>(take(sizeof(int32_t) * G));
-    c->logits = reinterpret_cast<float *>(take(sizeof(float) * G * mv.D));
-    return at + carve_workspace(base ? base + at : nullptr, N, G, mv, true, &c->ws);
 }
 
 // How many steps of an episode one pass takes.  With S states in the copies of B graphs a pass takes about
@@ -630,8 +610,7 @@ int steps_ahead(const pl_graph_batch *g, const pl_weights *w, int n_steps)
             if (S * B > kAheadGraphs || !sweep_offsets_fit(n * S, mv.H) ||
                 sweep_lanes_preferred(mv.H, mv.L, static_cast<int>(S * B), w->cfg.weight_dtype) != lanes)
                 break;
-            EpisodeCopies sized;
-            if (carve_copies(nullptr, static_cast<size_t>(n), B, static_cast<int>(S), mv, &sized) > kAheadBytes) break;
+            if (new_room_bytes(EpisodeRooms(), g->host.n_tot, B, static_cast<int>(S), mv) == 0) break;
         }
         const double r = m / (1.0 + static_cast<double>(S * B) / 512.0);
         if (r > rate) {
@@ -639,47 +618,39 @@ int steps_ahead(const pl_graph_batch *g, const pl_weights *w, int n_steps)
             best = m;
         }
     }
-    // (as many passes as that takes, of equal length)
-    const int passes = (n_steps + best - 1) / best;
-    return (n_steps + passes - 1) / passes;
+    return best;
 }
 
-// Room for `copies` copies of the batch.  False where there is none (and then none is needed: steps go one by one):
-// no memory, or a stream that is being captured, which must not allocate.
-bool ensure_copies(pl_graph_batch *g, const ModelView &mv, int copies, hipStream_t s)
+// Room for `copies` copies of the batch, or null where there is none (no memory, no room within the limit, or a stream that
+// is being captured: it must not allocate, and nothing that the host remembers of a room may depend on kernels that a
+// capture only records).  A new room is for as many copies as any number of steps takes.
+int ensure_copies(pl_graph_batch *g, const pl_weights *w, int copies, hipStream_t s, const CopiesRoom **room)
 {
-    EpisodeCopies &c = g->ahead;
-    if (c.base && c.copies == copies && c.D == mv.D && workspace_fits(c.ws, mv)) return true;
+    const ModelView &mv = w->view;
     const size_t n = static_cast<size_t>(g->host.n_tot), B = static_cast<size_t>(g->host.B);
-    EpisodeCopies sized;
-    const size_t bytes = carve_copies(nullptr, n, B, copies, mv, &sized);
-    if (bytes > c.bytes) {
-        hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
-        if (hipStreamIsCapturing(s, &capture) != hipSuccess || capture != hipStreamCaptureStatusNone) {
-            (void)hipGetLastError();
-            return false;
-        }
-        (void)hipFree(c.base);
-        c = EpisodeCopies();
-        unsigned char *base = nullptr;
-        if (hipMalloc(reinterpret_cast<void **>(&base), bytes) != hipSuccess) {
-            (void)hipGetLastError();
-            return false;
-        }
-        c.base = base;
-        c.bytes = bytes;
+    *room = copies > 1 ? find_room(g->ahead, n, B, copies, mv) : nullptr;
+    if (*room || copies == 1) return PL_OK;
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &capture) != hipSuccess || capture != hipStreamCaptureStatusNone) {
+        (void)hipGetLastError();
+        return PL_OK;
     }
-    carve_copies(c.base, n, B, copies, mv, &c);
-    c.copies = copies;
-    c.D = mv.D;
-    launch_copies_index(g->view, copies, const_cast<int32_t *>(c.view.node_off), const_cast<int32_t *>(c.view.tmpl),
-                        const_cast<int32_t *>(c.view.node_graph), s);
-    c.view.B = static_cast<int32_t>(B) * copies;
-    c.view.n_tot = static_cast<int32_t>(n) * copies;
-    for (int dir = 0; dir < 2; ++dir) c.view.plan[dir] = g->view.plan[dir];
-    clear_spare_messages(c.ws, n * copies, s);
-    clear_reach(c.ws, n * copies, s);
-    return true;
+    const int most = static_cast<int>(states_within(mv.D, steps_ahead(g, w, kAheadGraphs)));
+    const size_t bytes = new_room_bytes(g->ahead, n, B, most, mv);
+    if (bytes == 0) return PL_OK;
+    unsigned char *base = nullptr;
+    if (hipMalloc(reinterpret_cast<void **>(&base), bytes) != hipSuccess) {
+        (void)hipGetLastError();
+        base = nullptr;
+    }
+    *room = add_room(&g->ahead, base, bytes, most);
+    if (*room) {
+        EpisodeCopies c;
+        carve_copies(base, n, B, most, most, mv, &c);
+        launch_copies_index(g->view, most, const_cast<int32_t *>(c.view.node_off), const_cast<int32_t *>(c.view.tmpl),
+                            const_cast<int32_t *>(c.view.node_graph), s);
+    }
+    return PL_OK;
 }
 
 // ---- intermediate buffers for callers that cannot allocate: one fixed block per device
@@ -777,7 +748,7 @@ int pl_graph_batch_destroy(pl_graph_batch *g)
     }
     free_workspace(g->ws);
     free_grad_workspace(g->gw);
-    (void)hipFree(g->ahead.base);
+    for (int i = 0; i < g->ahead.n; ++i) (void)hipFree(g->ahead.room[i].base);
     (void)hipFree(g->sim_peaks);
     for (auto &v : g->timer.ev)
         for (hipEvent_t e : v) (void)hipEventDestroy(e);
@@ -1088,18 +1059,27 @@ int pl_episode_run(pl_graph_batch *g, const pl_weights *w, float *node_feats, in
     int rc = ensure_on_device(g);
     if (rc) return rc;
     int ahead = steps_ahead(g, w, n_steps);
+    {
+        const int passes = (n_steps + ahead - 1) / ahead;   // as many as that takes, of equal length
+        ahead = (n_steps + passes - 1) / passes;
+    }
     const int copies = static_cast<int>(states_within(w->cfg.D, ahead));
-    if (ahead > 1 && !ensure_copies(g, w->view, copies, s)) ahead = 1;
-    const int n_max = ahead > 1 ? graph_extent(g->host).n_max : 0;
+    const CopiesRoom *room = nullptr;
+    if ((rc = ensure_copies(g, w, copies, s, &room))) return rc;
+    if (!room) ahead = 1;
+    EpisodeCopies c;
+    if (room) {
+        carve_copies(room->base, static_cast<size_t>(g->host.n_tot), B, room->most, copies, w->view, &c);
+        for (int dir = 0; dir < 2; ++dir) c.view.plan[dir] = g->view.plan[dir];
+    }
+    const int n_max = room ? graph_extent(g->host).n_max : 0;
     for (int32_t i = 0; i < n_steps; i += ahead) {
         float *l = keep_logits ? logits + static_cast<size_t>(i) * B * D : logits;
         const float *u = uniforms + static_cast<size_t>(i) * B;
         int32_t *actions = out_actions ? out_actions + static_cast<size_t>(i) * B : nullptr;
         float *logp = out_logp ? out_logp + static_cast<size_t>(i) * B : nullptr;
-        if (ahead > 1) {
-            const EpisodeCopies &c = g->ahead;
-            launch_copies_state(g->view, w->cfg.D, copies, n_max, order, t0 + i, node_feats, placement, cur_node, c.feats,
-                                c.placement, c.cur_node, s);
+        if (room) {
+            launch_copies_state(g->view, w->cfg.D, copies, n_max, order, t0 + i, node_feats, placement, cur_node, c, s);
             rc = forward_impl(g, c.feats, c.placement, c.cur_node, w, c.logits, nullptr, nullptr, nullptr, nullptr, stream,
                               false, nullptr, 0, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, &c);
             if (rc) return rc;

@@ -4,6 +4,7 @@
 
 #include <cstdint>
 #include <cstring>
+#include <limits>
 #include <string>
 #include <vector>
 
@@ -121,10 +122,26 @@ struct Workspace {
 };
 
 // ---- copies of a batch, one for every state that the next steps of an episode can reach (kernels_episode.hip)
+// Room for them, kept by the batch: tables of the copies' graphs for `most` copies, of which fewer copies read the
+// beginning, and behind them what a pass writes.  The tables depend on the batch alone and are written once, when the
+// room is made; everything behind them is laid out, and cleared where it has to read as zero, by every pass for itself.
+// So passes of any networks and numbers of copies, replayed captured ones among them, can follow each other in any order,
+// as long as a room stays where it is: it is never moved and lives as long as the batch.
+struct CopiesRoom {
+    unsigned char *base;
+    size_t bytes;
+    int32_t most;
+};
+constexpr int kCopiesRooms = 8;
+struct EpisodeRooms {
+    CopiesRoom room[kCopiesRooms] = {};
+    int32_t n = 0;
+    size_t bytes = 0;                                     // of all rooms
+    size_t refused = std::numeric_limits<size_t>::max();  // smallest size that there was no memory for
+};
+
+// What one pass finds in a room.
 struct EpisodeCopies {
-    unsigned char *base = nullptr;   // the one allocation that holds everything
-    size_t bytes = 0;
-    int32_t copies = 0, D = 0;       // what it is laid out for (with ws.H, ws.G)
     float *feats = nullptr, *logits = nullptr;       // [copies, n_tot, 3], [copies, B, D]
     int32_t *placement = nullptr, *cur_node = nullptr;
     Workspace ws;
@@ -134,6 +151,10 @@ struct EpisodeCopies {
 // (workspace.cpp)
 bool workspace_fits(const Workspace &ws, const ModelView &mv);
 size_t carve_workspace(unsigned char *base, size_t n, size_t B, const ModelView &mv, bool with_reach, Workspace *ws);
+size_t carve_copies(unsigned char *base, size_t n, size_t B, int most, int copies, const ModelView &mv, EpisodeCopies *c);
+const CopiesRoom *find_room(const EpisodeRooms &rooms, size_t n, size_t B, int copies, const ModelView &mv);
+size_t new_room_bytes(const EpisodeRooms &rooms, size_t n, size_t B, int most, const ModelView &mv);
+const CopiesRoom *add_room(EpisodeRooms *rooms, unsigned char *base, size_t bytes, int most);
 
 // ---- kernel launchers (kernels_generic.hip)
 struct ForwardArgs {
@@ -199,8 +220,7 @@ void launch_episode_step(const GraphView &gv, int D, const float *logits, const 
 void launch_copies_index(const GraphView &gv, int copies, int32_t *node_off, int32_t *tmpl, int32_t *node_graph,
                          hipStream_t s);
 void launch_copies_state(const GraphView &gv, int D, int copies, int n_max, const int32_t *order, int t, const float *feats,
-                         const int32_t *placement, const int32_t *cur_node, float *out_feats, int32_t *out_placement,
-                         int32_t *out_cur, hipStream_t s);
+                         const int32_t *placement, const int32_t *cur_node, const EpisodeCopies &c, hipStream_t s);
 void launch_copies_steps(const GraphView &gv, int D, int steps, const float *copy_logits, const float *uniforms,
                          const int32_t *order, int t, float *node_feats, int32_t *placement, int32_t *cur_node,
                          float *out_logits, size_t logits_stride, int32_t *out_action, float *out_logp, hipStream_t s);

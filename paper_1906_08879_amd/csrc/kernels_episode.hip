@@ -86,16 +86,22 @@ __global__ __launch_bounds__(256) void k_copies_index(GraphView gv, int copies, 
     }
 }
 
-// States of the copies: a workgroup takes 256 nodes of one graph of one copy.
+// States of the copies: a workgroup takes 256 nodes of one graph of one copy.  The first one also clears what the pass
+// reads as zero without writing it (workspace.cpp), whose place depends on the number of copies.
 __global__ __launch_bounds__(256) void k_copies_state(GraphView gv, int D, const int32_t *__restrict__ order, int t,
                                                       const float *__restrict__ feats,
                                                       const int32_t *__restrict__ placement,
                                                       const int32_t *__restrict__ cur_node,
                                                       float *__restrict__ out_feats,
                                                       int32_t *__restrict__ out_placement,
-                                                      int32_t *__restrict__ out_cur)
+                                                      int32_t *__restrict__ out_cur, float *__restrict__ zero_msg,
+                                                      int n_zero_msg, uint32_t *__restrict__ zero_reach)
 {
     const int b = blockIdx.y, j = blockIdx.z;
+    if (blockIdx.x == 0 && b == 0 && j == 0) {
+        for (int i = threadIdx.x; i < n_zero_msg; i += 256) zero_msg[i] = 0.0f;
+        if (threadIdx.x < 5) zero_reach[threadIdx.x] = 0u;
+    }
     const int n0 = gv.node_off[b], n_b = gv.node_off[b + 1] - n0;
     const int v = blockIdx.x * 256 + threadIdx.x;
     int depth = 0, index = j;
@@ -267,11 +273,12 @@ void launch_copies_index(const GraphView &gv, int copies, int32_t *node_off, int
 }
 
 void launch_copies_state(const GraphView &gv, int D, int copies, int n_max, const int32_t *order, int t, const float *feats,
-                         const int32_t *placement, const int32_t *cur_node, float *out_feats, int32_t *out_placement,
-                         int32_t *out_cur, hipStream_t s)
+                         const int32_t *placement, const int32_t *cur_node, const EpisodeCopies &c, hipStream_t s)
 {
+    const size_t spare = 2 * static_cast<size_t>(c.view.n_tot);
     hipLaunchKernelGGL(k_copies_state, dim3((n_max + 255) / 256, gv.B, copies), dim3(256), 0, s, gv, D, order, t, feats,
-                       placement, cur_node, out_feats, out_placement, out_cur);
+                       placement, cur_node, c.feats, c.placement, c.cur_node, c.ws.msg + spare * c.ws.H, 2 * c.ws.H,
+                       reinterpret_cast<uint32_t *>(c.ws.reach + spare / 4 * 4));
 }
 
 void launch_copies_steps(const GraphView &gv, int D, int steps, const float *copy_logits, const float *uniforms,

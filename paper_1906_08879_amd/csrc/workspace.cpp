@@ -53,4 +53,60 @@ size_t carve_workspace(unsigned char *base, size_t n, size_t B, const ModelView 
     return at;
 }
 
+// ---- room for the copies of a batch's graphs (internal.h)
+constexpr size_t kCopiesBytes = static_cast<size_t>(4) << 30;   // most memory that a batch's rooms take together
+
+// Lays a pass of `copies` copies out in a room with tables for `most`, as carve_workspace does.
+size_t carve_copies(unsigned char *base, size_t n, size_t B, int most, int copies, const ModelView &mv, EpisodeCopies *c)
+{
+    size_t at = 0;
+    auto take = [&](size_t bytes) {
+        unsigned char *p = base ? base + at : nullptr;
+        at += (bytes + 255) / 256 * 256;
+        return p;
+    };
+    const size_t M = static_cast<size_t>(most), N = n * copies, G = B * copies;
+    c->view.node_off = reinterpret_cast<int32_t *>(take(sizeof(int32_t) * (B * M + 1)));
+    c->view.tmpl = reinterpret_cast<int32_t *>(take(sizeof(int32_t) * B * M));
+    c->view.node_graph = reinterpret_cast<int32_t *>(take(sizeof(int32_t) * n * M));
+    c->feats = reinterpret_cast<float *>(take(sizeof(float) * N * 3));
+    c->placement = reinterpret_cast<int32_t *>(take(sizeof(int32_t) * N));
+    c->cur_node = reinterpret_cast<int32_t *>(take(sizeof(int32_t) * G));
+    c->logits = reinterpret_cast<float *>(take(sizeof(float) * G * mv.D));
+    c->view.B = static_cast<int32_t>(G);
+    c->view.n_tot = static_cast<int32_t>(N);
+    return at + carve_workspace(base ? base + at : nullptr, N, G, mv, true, &c->ws);
+}
+
+// A room that a pass fits in, or null.
+const CopiesRoom *find_room(const EpisodeRooms &rooms, size_t n, size_t B, int copies, const ModelView &mv)
+{
+    EpisodeCopies sized;
+    for (int i = 0; i < rooms.n; ++i) {
+        const CopiesRoom &r = rooms.room[i];
+        if (copies <= r.most && carve_copies(nullptr, n, B, r.most, copies, mv, &sized) <= r.bytes) return &r;
+    }
+    return nullptr;
+}
+
+// Size of another room, for a network's largest pass; 0 where the batch may not have it, or asked for as much in vain.
+size_t new_room_bytes(const EpisodeRooms &rooms, size_t n, size_t B, int most, const ModelView &mv)
+{
+    EpisodeCopies sized;
+    const size_t bytes = carve_copies(nullptr, n, B, most, most, mv, &sized);
+    return rooms.n < kCopiesRooms && rooms.bytes + bytes <= kCopiesBytes && bytes < rooms.refused ? bytes : 0;
+}
+
+// base: the memory, or null if there was none.
+const CopiesRoom *add_room(EpisodeRooms *rooms, unsigned char *base, size_t bytes, int most)
+{
+    if (!base) {
+        rooms->refused = bytes;
+        return nullptr;
+    }
+    rooms->room[rooms->n] = {base, bytes, most};
+    rooms->bytes += bytes;
+    return &rooms->room[rooms->n++];
+}
+
 }  // namespace pl

@@ -299,3 +299,91 @@ def test_steps_taken_together_equal_single_steps_bit_for_bit(graphs, D, H, L, wd
     wt.close()
     for i, (a, b) in enumerate(zip(runs[True], runs[False])):
         np.testing.assert_array_equal(a, b, err_msg=f"output {i}")
+
+
+# (calls of one batch in turn: "e" runs at once, "c" is captured, "r" replays the last capture; then the number of steps, and a
+# second network of another width and number of devices as "w"; a call that was captured step by step, before there were copies,
+# uses the buffers of the batch's last network, as pl_embed_forward does, and is not replayed after the other one)
+@pytest.mark.parametrize("graphs,D,H,wd,D2,H2", [(1, 8, 128, "bf16", 8, 64), (3, 4, 16, "fp32", 8, 128), (1, 3, 64, "fp32", 16, 64)])
+@pytest.mark.parametrize("calls", [
+    "e8 c4 e4 r e8 r e4 r", "e8 c8 e4 r e8 r", "e4 c4 e8 r w8 r e3 r", "w8 e1 c8 r e8 r c3 r e4 r", "e1 c8 r e8 r c8 r e4 r", "e8 w8 c3 e8 r w8 r"])
+def test_captured_episodes_beside_others_on_the_same_batch(graphs, D, H, wd, D2, H2, calls):
+    """Every call and every replay of a captured one equals single steps, bit for bit, whatever ran on the batch before it
+    and between capture and replay."""
+    import torch
+    import paper_1906_08879_amd as pl
+    dev = torch.device("cuda:0")
+    rng = np.random.default_rng(H + D + graphs)
+    sizes = [int(x) for x in rng.integers(9, 40, graphs)]
+    to = lambda a: torch.from_numpy(np.ascontiguousarray(a)).to(dev)  # noqa: E731
+    w = ragged_workload(rng, sizes, D, H, 2, wd)
+    off = np.concatenate([[0], np.cumsum(sizes)])
+    order = np.concatenate([rng.permutation(n) for n in sizes]).astype(np.int32)
+    o, cur0, u = to(order), to(order[off[:-1]]), to(rng.random((8, graphs), dtype=np.float32))
+    f0 = to(w.node_feats)
+    g, single = (pl.GraphBatch(w.n_nodes, w.n_edges, w.edge_src, w.edge_dst) for _ in range(2))
+    side = torch.cuda.Stream()
+
+    class Net:
+        def __init__(self, D, H, wd, weights):
+            self.D, self.wt = D, pl.Weights(weights, D, H, 2, 1, 1, wd)
+            self.p0 = to(rng.integers(0, D, w.n_tot).astype(np.int32))
+
+        def call(self, steps, how):
+            """Reset, then the episode's first steps; returns what they write and, if captured, the graph."""
+            f, p, c = torch.empty_like(f0), torch.empty_like(self.p0), torch.empty_like(cur0)
+            out = (torch.full((steps, graphs, self.D), 7.0, device=dev), torch.full((steps, graphs), 9, dtype=torch.int32, device=dev),
+                   torch.full((steps, graphs), 9.0, device=dev), f, p, c)
+            batch = single if how == "single" else g
+
+            def run(stream):
+                f.copy_(f0); p.copy_(self.p0); c.copy_(cur0)
+                if how == "single":
+                    for i in range(steps):
+                        pl.embed_forward(batch, f, p, c, self.wt, out[0][i])
+                        pl.episode_step(batch, self.D, out[0][i], u[i], o, i, f, p, c, out[1][i], out[2][i])
+                else:
+                    pl.episode_run(batch, self.wt, f, p, c, o, u[:steps], 0, steps, out[0], True, out[1], out[2], stream=stream)
+
+            torch.cuda.synchronize()
+            if how != "capture":
+                run(torch.cuda.current_stream())
+                torch.cuda.synchronize()
+                return out, None
+            graph = torch.cuda.CUDAGraph()
+            with torch.cuda.stream(side):
+                graph.capture_begin()
+                run(side)
+                graph.capture_end()
+            return out, graph
+
+    main = Net(D, H, wd, w.weights)
+    other = ragged_workload(rng, sizes, D2, H2, 2, "bf16")
+    wide = Net(D2, H2, "bf16", other.weights)
+    want = {}
+
+    def same(net, steps, out, what):
+        if (net, steps) not in want:
+            want[net, steps] = [x.cpu().numpy().view(np.int32) for x in net.call(steps, "single")[0]]
+        for i, (a, b) in enumerate(zip(out, want[net, steps])):
+            np.testing.assert_array_equal(a.cpu().numpy().view(np.int32), b, err_msg=f"{what}: output {i}")
+
+    captured = None
+    for at, call in enumerate(calls.split()):
+        what = f"{calls}, call {at} ({call})"
+        if call == "r":
+            for x in captured[1]:
+                x.fill_(5)
+            captured[2].replay()
+            torch.cuda.synchronize()
+            same(main, captured[0], captured[1], what)
+            continue
+        steps = int(call[1:])
+        net = wide if call[0] == "w" else main
+        out, graph = net.call(steps, "capture" if call[0] == "c" else "eager")
+        if graph is None:
+            same(net, steps, out, what)
+        else:
+            captured = steps, out, graph
+    del captured, graph
+    g.close(); single.close(); main.wt.close(); wide.wt.close()
