@@ -621,20 +621,23 @@ int steps_ahead(const pl_graph_batch *g, const pl_weights *w, int n_steps)
     return best;
 }
 
-// Room for `copies` copies of the batch, or null where there is none (no memory, no room within the limit, or a stream that
-// is being captured: it must not allocate, and nothing that the host remembers of a room may depend on kernels that a
-// capture only records).  A new room is for as many copies as any number of steps takes.
+// Room for `copies` copies of the batch, and the batch's own buffers for where there is none (no memory, no room within
+// the limit, or a stream that is being captured: it must not allocate, and nothing that the host remembers of a room may
+// depend on kernels that a capture only records).  A new room is for as many copies as any number of steps takes.
 int ensure_copies(pl_graph_batch *g, const pl_weights *w, int copies, hipStream_t s, const CopiesRoom **room)
 {
     const ModelView &mv = w->view;
     const size_t n = static_cast<size_t>(g->host.n_tot), B = static_cast<size_t>(g->host.B);
     *room = copies > 1 ? find_room(g->ahead, n, B, copies, mv) : nullptr;
-    if (*room || copies == 1) return PL_OK;
+    const bool own = g->ws.emb && workspace_fits(g->ws, mv);
+    if (own && (*room || copies == 1)) return PL_OK;
     hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
     if (hipStreamIsCapturing(s, &capture) != hipSuccess || capture != hipStreamCaptureStatusNone) {
         (void)hipGetLastError();
         return PL_OK;
     }
+    const int rc = ensure_workspace(g, mv, s);
+    if (rc || *room || copies == 1) return rc;
     const int most = static_cast<int>(states_within(mv.D, steps_ahead(g, w, kAheadGraphs)));
     const size_t bytes = new_room_bytes(g->ahead, n, B, most, mv);
     if (bytes == 0) return PL_OK;

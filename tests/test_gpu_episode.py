@@ -387,3 +387,35 @@ def test_captured_episodes_beside_others_on_the_same_batch(graphs, D, H, wd, D2,
             captured = steps, out, graph
     del captured, graph
     g.close(); single.close(); main.wt.close(); wide.wt.close()
+
+
+def test_only_episodes_before_a_captured_forward_pass():
+    """A batch that only pl_episode_run has used, in passes of several steps, has the buffers of single passes too: a forward
+    pass captured then replays with the eager one's bits."""
+    import torch
+    import paper_1906_08879_amd as pl
+    dev = torch.device("cuda:0")
+    rng = np.random.default_rng(3)
+    w = ragged_workload(rng, [17, 23], 4, 64, 2, "bf16")
+    to = lambda a: torch.from_numpy(np.ascontiguousarray(a)).to(dev)  # noqa: E731
+    f, p, c = to(w.node_feats), to(w.placement), to(w.cur_node)
+    o = to(np.concatenate([np.arange(17), np.arange(23)]).astype(np.int32))
+    u = to(rng.random((6, 2), dtype=np.float32))
+    wt = pl.Weights(w.weights, 4, 64, 2, 1, 1, "bf16")
+    g = pl.GraphBatch(w.n_nodes, w.n_edges, w.edge_src, w.edge_dst)
+    logits, eager = (torch.empty((2, 4), device=dev) for _ in range(2))
+    pl.episode_run(g, wt, f, p, c, o, u, 0, 6, logits)
+    torch.cuda.synchronize()
+    side, graph = torch.cuda.Stream(), torch.cuda.CUDAGraph()
+    with torch.cuda.stream(side):
+        graph.capture_begin()
+        pl.embed_forward(g, f, p, c, wt, logits, stream=side)
+        graph.capture_end()
+    pl.embed_forward(g, f, p, c, wt, eager)
+    for _ in range(3):
+        logits.fill_(1.0)
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(logits, eager)
+    del graph
+    g.close(); wt.close()
