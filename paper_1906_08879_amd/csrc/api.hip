@@ -356,7 +356,8 @@ int ensure_grad_workspace(pl_graph_batch *g, const ModelView &mv, hipStream_t s)
     PL_HIP(take(&gw.phi, n * 32));   // F <= 20 columns, padded to 32 on the matrix-core path
     PL_HIP(hipMalloc(reinterpret_cast<void **>(&gw.cls), n + 16));
     PL_HIP(hipMalloc(reinterpret_cast<void **>(&gw.counts), 64));
-    PL_HIP(hipMalloc(reinterpret_cast<void **>(&gw.blk_cnt), sizeof(int32_t) * (3 * ((n + 255) / 256) + 4)));
+    // (three for every 256 nodes; or for every graph and every thousand of them, k_bw_set_begins)
+    PL_HIP(hipMalloc(reinterpret_cast<void **>(&gw.blk_cnt), sizeof(int32_t) * (3 * std::max((n + 255) / 256, B + B / 1024 + 1) + 4)));
     PL_HIP(hipMalloc(reinterpret_cast<void **>(&gw.lists), sizeof(int32_t) * (3 * n + 4)));
     PL_HIP(take(&gw.dP, 3 * BG * H));
     PL_HIP(take(&gw.hin, 3 * BG * H));

@@ -904,13 +904,48 @@ __global__ __launch_bounds__(kThreads) void k_bw_cls_fill(GraphView gv, const ui
 // One launch for the three above and one that cleared the rows: 64 layered graphs 20 -> 5.6 us, 48 NMT-like ones 28 -> 6.8,
 // 256 NASNet-like ones 57 -> 12.6.
 constexpr int kSetThreads = 1024;   // most: graphs of more than 512 nodes; 256 for smaller ones
+// Up to this many graphs every workgroup adds the sets' sizes in all graphs before its own.  In larger batches, where that
+// grows with the square of their number, a launch of its own (k_bw_set_begins) does it for a thousand graphs at a time.
+// Gradient of 1536 / 2048 / 4096 / 16384 graphs of 8 nodes, H = 32: alone 225 / 270 / 487 / 2173 us, with that launch
+// 227 / 267 / 448 / 1469 (three kernels without the sort's offsets: 250 / 286 / 462 / 1444).
+constexpr int kSetsAlone = 1536;
+constexpr int kSetGraphs = kSetThreads;   // graphs to a workgroup of k_bw_set_begins
+
+// begins[c][b]: nodes of set c in those graphs before b that the same workgroup takes; sums[w][c]: of all that workgroup w takes.
+__global__ __launch_bounds__(kSetThreads) void k_bw_set_begins(int B, int G, int koff_ld, const int32_t *__restrict__ koff,
+                                                               int32_t *__restrict__ begins, int32_t *__restrict__ sums)
+{
+    __shared__ int before[kSetThreads / 64][3];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int b = blockIdx.x * kSetGraphs + tid;
+    int size[3], run[3];
+    for (int c = 0; c < 3; ++c) {
+        const int32_t *k = koff + static_cast<size_t>(min(b, B - 1)) * koff_ld + c * G;
+        size[c] = b < B ? k[G] - k[0] : 0;
+    }
+    for (int c = 0; c < 3; ++c) {
+        run[c] = size[c];
+        for (int step = 1; step < 64; step *= 2) {
+            const int below = __shfl_up(run[c], step);
+            run[c] += lane >= step ? below : 0;
+        }
+        if (lane == 63) before[wave][c] = run[c];
+    }
+    __syncthreads();
+    for (int c = 0; c < 3; ++c) {
+        for (int w = 0; w < wave; ++w) run[c] += before[w][c];
+        if (b < B) begins[static_cast<size_t>(c) * B + b] = run[c] - size[c];
+        if (tid == kSetThreads - 1) sums[3 * blockIdx.x + c] = run[c];
+    }
+}
+
 __global__ __launch_bounds__(kSetThreads) void k_bw_sets(GraphView gv, int H, int Z, int G, int D, int single, int koff_ld,
                                                       const uint8_t *__restrict__ reach,
                                                       const int32_t *__restrict__ placement,
                                                       const int32_t *__restrict__ cur_node,
                                                       const int32_t *__restrict__ klist,
                                                       const int32_t *__restrict__ koff,
-                                                      const float *__restrict__ dz,
+                                                      const float *__restrict__ dz, const int32_t *__restrict__ begins,
                                                       uint8_t *__restrict__ cls, int32_t *__restrict__ counts,
                                                       int32_t *__restrict__ lists, float *__restrict__ demb)
 {
@@ -921,8 +956,14 @@ __global__ __launch_bounds__(kSetThreads) void k_bw_sets(GraphView gv, int H, in
     const int cur = (cl >= 0 && cl < n_b) ? n0 + cl : -1;
     auto first = [&](int g, int set) { return koff[static_cast<size_t>(g) * koff_ld + set * G]; };
     int sum[3] = {0, 0, 0};
-    for (int g = tid; g < b; g += threads)
-        for (int c = 0; c < 3; ++c) sum[c] += first(g, c + 1) - first(g, c);
+    if (begins) {
+        const int32_t *sums = begins + 3 * static_cast<size_t>(gv.B);
+        for (int w = tid; w < b / kSetGraphs; w += threads)
+            for (int c = 0; c < 3; ++c) sum[c] += sums[3 * w + c];
+    } else {
+        for (int g = tid; g < b; g += threads)
+            for (int c = 0; c < 3; ++c) sum[c] += first(g, c + 1) - first(g, c);
+    }
     for (int c = 0; c < 3; ++c) {
         for (int step = 32; step > 0; step /= 2) sum[c] += __shfl_xor(sum[c], step);
         if (lane == 0) before[wave][c] = sum[c];
@@ -938,7 +979,7 @@ __global__ __launch_bounds__(kSetThreads) void k_bw_sets(GraphView gv, int H, in
         for (int i = tid; i < 2 * H; i += threads) demb[static_cast<size_t>(cur) * 2 * H + i] = dz[static_cast<size_t>(b) * Z + i];
     __syncthreads();
     for (int c = 0; c < 3; ++c) {
-        int base = 0;
+        int base = begins ? begins[static_cast<size_t>(c) * gv.B + b] : 0;
         for (int w = 0; w < threads / 64; ++w) base += before[w][c];
         const int lo = first(b, c), n = first(b, c + 1) - lo;
         if (b == gv.B - 1 && tid == 0) counts[c] = base + n;
@@ -1781,9 +1822,15 @@ void launch_backward(const GraphView &gv, const ModelView &mv, const float *blob
     // 2. pooling
     if (dense) {
         if (pool_kept) {
-            hipLaunchKernelGGL(k_bw_sets, dim3(B), dim3(n > 512 * static_cast<int64_t>(B) ? kSetThreads : kThreads), 0, s, gv, H, mv.Z, G, mv.D, mv.single_set, 3 * kMaxD + 1,
-                               ws.reach, fa.placement, fa.cur_node, ws.klist, ws.koff, gw.dz, gw.cls, gw.counts, gw.lists,
-                               gw.demb);
+            constexpr int koff_ld = 3 * kMaxD + 1;
+            int32_t *begins = B > kSetsAlone ? gw.blk_cnt : nullptr;
+            if (begins)
+                hipLaunchKernelGGL(k_bw_set_begins, dim3((B + kSetGraphs - 1) / kSetGraphs), dim3(kSetThreads), 0, s, B, G, koff_ld,
+                                   ws.koff, begins, begins + 3 * static_cast<size_t>(B));
+            const int threads = n > 512 * static_cast<int64_t>(B) ? kSetThreads : begins && n <= 64 * static_cast<int64_t>(B) ? 64 : kThreads;
+            hipLaunchKernelGGL(k_bw_sets, dim3(B), dim3(threads), 0, s, gv, H,
+                               mv.Z, G, mv.D, mv.single_set, koff_ld, ws.reach, fa.placement, fa.cur_node, ws.klist, ws.koff,
+                               gw.dz, begins, gw.cls, gw.counts, gw.lists, gw.demb);
         } else {
             const int n_blocks = (n + kThreads - 1) / kThreads;
             hipLaunchKernelGGL(k_bw_cls_count, dim3(n_blocks), dim3(kThreads), 0, s, gv, H, mv.Z, mv.single_set, ws.reach,

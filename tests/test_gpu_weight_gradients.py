@@ -52,6 +52,19 @@ def test_tables_against_the_oracle(sizes, D, H, L, k, wd, every):
     _assert_blocks_close(run_gradient(w, actions, coeff)["grad"], ref, D, H, L)
 
 
+@pytest.mark.parametrize("graphs,n,D,H,L,wd", [
+    (1536, 3, 3, 32, 2, "fp32"), (1537, 3, 16, 32, 1, "fp32"), (2048, 2, 1, 64, 2, "bf16"), (2049, 2, 4, 128, 2, "bf16"),
+    (1601, 70, 2, 32, 2, "fp32"), (4100, 1, 4, 32, 2, "fp32")])
+def test_row_lists_of_many_graphs(graphs, n, D, H, L, wd):
+    """The node sets' row lists where a graph's part of them is found in one launch and in two, at the sizes where the
+    second one gets another workgroup: against the generic kernels, which have none."""
+    rng = np.random.default_rng(graphs + H)
+    w = custom_workload(rng, [int(x) for x in rng.integers(1, 2 * n, graphs)], D, H, L, 1, 1, wd, p_edge=0.1)
+    actions, coeff = rng.integers(0, D, w.B).astype(np.int32), rng.normal(0, 1, w.B).astype(np.float32)
+    got, ref = run_gradient(w, actions, coeff)["grad"], run_gradient(w, actions, coeff, path=1)["grad"].astype(np.float64)
+    _assert_blocks_close(got, ref, D, H, L)
+
+
 @pytest.mark.parametrize("D,H,graphs,n", [(3, 32, 9, 10417), (8, 48, 3, 21001), (16, 64, 2, 24001), (5, 256, 2, 6001)])
 def test_projection_gradient_of_a_large_batch(D, H, graphs, n):
     """The projection's gradient formed in one pass over d e (batches of three million elements and more) against the sum of
