@@ -808,8 +808,7 @@ __global__ __launch_bounds__(256) void k_feature_records(GraphView gv, const flo
 // exact three-way split (ws = 0 only when the weights are bf16 already).  k is the position of
 // an input column in the kernel's activation rows, 32 ks + 8 (l / 16) + i.  Where a wave owns two
 // column tiles (H = 128) they interleave: tile mt holds the columns 32 (mt / 2) + 2 c + mt % 2,
-// c = 0..15, so that a lane's two columns are neighbours (see mcol in the kernel); k_sweep_wide, whose waves own one, reads the
-// same fragments (its lanes' columns alternate between two tiles).
+// c = 0..15, so that a lane's two columns are neighbours (see mcol in the kernel).
 // With `reverse`, the fragments of the reverse pass: index dir is the direction whose chunks are
 // walked, the weights are those of the other direction, transposed, f's layers from the last to
 // the first and then g's (biases are not used there).
@@ -817,8 +816,9 @@ void pack_sweep_weights(const ModelView &mv, const float *blob, int WS, std::vec
                         std::vector<float> *bias, bool reverse)
 {
     const int H = mv.H, L = mv.L, MT = H / 16, KS = H / 32, NL = 2 * L;
-    const bool paired = MT / sweep_waves(H) == 2;
-    frag->assign(static_cast<size_t>(2) * NL * MT * KS * WS * 64 * 8, 0);
+    const bool both = MT / sweep_waves(H) == 2;      // the layout of two column tiles to a wave, then that of one
+    const size_t layout = static_cast<size_t>(2) * NL * MT * KS * WS * 64 * 8;
+    frag->assign((both ? 2 : 1) * layout, 0);
     bias->assign(static_cast<size_t>(2) * NL * H, 0.0f);
     auto to_bf16 = [](float x) {
         uint32_t u;
@@ -841,8 +841,9 @@ void pack_sweep_weights(const ModelView &mv, const float *blob, int WS, std::vec
             for (int mt = 0; mt < MT; ++mt)
                 for (int ks = 0; ks < KS; ++ks)
                     for (int lane = 0; lane < 64; ++lane)
-                        for (int i = 0; i < 8; ++i) {
-                            const int k = 32 * ks + 8 * (lane / 16) + i;
+                        for (int i = 0; i < (both ? 16 : 8); ++i) {
+                            const bool paired = both && i < 8;
+                            const int k = 32 * ks + 8 * (lane / 16) + i % 8;
                             const int m = paired ? 32 * (mt / 2) + 2 * (lane % 16) + mt % 2 : 16 * mt + lane % 16;
                             float rest = reverse ? blob[lr.w + static_cast<size_t>(m) * H + k]
                                                  : blob[lr.w + static_cast<size_t>(k) * H + m];
@@ -850,7 +851,8 @@ void pack_sweep_weights(const ModelView &mv, const float *blob, int WS, std::vec
                                 const uint16_t part = to_bf16(rest);
                                 rest -= from_bf16(part);
                                 const size_t at =
-                                    (((((static_cast<size_t>(dir) * NL + n) * MT + mt) * KS + ks) * WS + ws) * 64 + lane) * 8 + i;
+                                    (((((static_cast<size_t>(dir) * NL + n) * MT + mt) * KS + ks) * WS + ws) * 64 + lane) * 8 + i % 8 +
+                                    (both && !paired ? layout : 0);
                                 (*frag)[at] = part;
                             }
                         }
@@ -872,6 +874,10 @@ namespace {
 // eight; of 64 NMT-like ones, whose lists it sums sixteen entries at a time, 821 / 696 us; gradient of 128 NASNet-like graphs
 // 5.79 / 5.30 ms).  Past that the four-wave kernel has two workgroups on a compute unit where this one has one.
 constexpr int kWideGraphs = 128;
+const uint4 *one_tile_layout(const ModelView &mv, const uint4 *wfrag, int WS)
+{
+    return wfrag + static_cast<size_t>(2) * 2 * mv.L * (mv.H / 16) * (mv.H / 32) * WS * 64;
+}
 
 }  // namespace
 
@@ -886,7 +892,7 @@ void launch_sweep_mfma(const GraphView &gv, const ModelView &mv, const Workspace
         return;
     }
     if (gv.B <= kWideGraphs) {
-        launch_sweep_wide(gv, mv, ws, fa, wfrag, bias, first_sweep, more_sweeps, keep, keep_stride, gates, s);
+        launch_sweep_wide(gv, mv, ws, fa, one_tile_layout(mv, wfrag, WS), bias, first_sweep, more_sweeps, keep, keep_stride, gates, s);
         return;
     }
     // keep, gates: where a single sweep also stores a_v, the layer outputs and the ReLU gates for the
@@ -932,7 +938,7 @@ void launch_sweep_mfma_bw(const GraphView &gv, const ModelView &mv, const uint4 
         return;
     }
     if (gv.B <= kWideGraphs) {
-        launch_sweep_wide_bw(gv, mv, wfrag, bias, cur_node, demb, dagg, mask4, delta, delta_stride, s);
+        launch_sweep_wide_bw(gv, mv, one_tile_layout(mv, wfrag, WS), bias, cur_node, demb, dagg, mask4, delta, delta_stride, s);
         return;
     }
     SweepParams P{gv, wfrag, bias, demb, nullptr, dagg, nullptr, cur_node, nullptr, nullptr, mv.D,

@@ -60,9 +60,7 @@
         for (int ks = 0; ks < KS; ++ks)
 #pragma unroll
             for (int ws = 0; ws < WS; ++ws) {
-                // (at 128 columns a tile of fragments holds every other one of 32: pack_sweep_weights)
-                const size_t tile = H == 128 ? 2 * (mc / 32) + mc % 2 : wave, at_lane = H == 128 ? 16 * kg + mc % 32 / 2 : lane;
-                const size_t at = ((((static_cast<size_t>(dir) * NL + n) * NTL + tile) * KS + ks) * WS + ws) * 64 + at_lane;
+                const size_t at = ((((static_cast<size_t>(dir) * NL + n) * NTL + wave) * KS + ks) * WS + ws) * 64 + lane;
                 const uint4 raw = P.wfrag[at];
                 W[n][ks][ws] = *reinterpret_cast<const bf16x8 *>(&raw);
             }
