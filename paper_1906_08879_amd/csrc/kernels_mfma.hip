@@ -841,22 +841,32 @@ void pack_sweep_weights(const ModelView &mv, const float *blob, int WS, std::vec
             for (int mt = 0; mt < MT; ++mt)
                 for (int ks = 0; ks < KS; ++ks)
                     for (int lane = 0; lane < 64; ++lane)
-                        for (int i = 0; i < (both ? 16 : 8); ++i) {
-                            const bool paired = both && i < 8;
-                            const int k = 32 * ks + 8 * (lane / 16) + i % 8;
-                            const int m = paired ? 32 * (mt / 2) + 2 * (lane % 16) + mt % 2 : 16 * mt + lane % 16;
+                        for (int i = 0; i < 8; ++i) {
+                            const int k = 32 * ks + 8 * (lane / 16) + i;
+                            const int m = both ? 32 * (mt / 2) + 2 * (lane % 16) + mt % 2 : 16 * mt + lane % 16;
                             float rest = reverse ? blob[lr.w + static_cast<size_t>(m) * H + k]
                                                  : blob[lr.w + static_cast<size_t>(k) * H + m];
                             for (int ws = 0; ws < WS; ++ws) {
                                 const uint16_t part = to_bf16(rest);
                                 rest -= from_bf16(part);
                                 const size_t at =
-                                    (((((static_cast<size_t>(dir) * NL + n) * MT + mt) * KS + ks) * WS + ws) * 64 + lane) * 8 + i % 8 +
-                                    (both && !paired ? layout : 0);
+                                    (((((static_cast<size_t>(dir) * NL + n) * MT + mt) * KS + ks) * WS + ws) * 64 + lane) * 8 + i;
                                 (*frag)[at] = part;
                             }
                         }
         }
+    if (!both) return;
+    // The second layout has the first one's entries (eight values of a column) in another order.
+    const uint16_t *from = frag->data();
+    uint16_t *to = frag->data() + layout;
+    const int per_tile = KS * WS * 64;
+    for (int tile = 0; tile < 2 * NL * MT; ++tile)
+        for (int step = 0; step < KS * WS; ++step)
+            for (int lane = 0; lane < 64; ++lane, to += 8) {
+                const int m = 16 * (tile % MT) + lane % 16;
+                const int source = (tile / MT * MT + 2 * (m / 32) + m % 2) * per_tile + step * 64 + lane / 16 * 16 + m % 32 / 2;
+                std::memcpy(to, from + static_cast<size_t>(source) * 8, 16);
+            }
 }
 
 bool sweep_mfma_supported(int H, int L, int weight_dtype)
