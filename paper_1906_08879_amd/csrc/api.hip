@@ -551,16 +551,17 @@ int forward_impl(pl_graph_batch *g, const float *node_feats, const int32_t *plac
     if (out_class) launch_classes(gv, cur_node, ws.reach, out_class, s);
     const bool pool_mfma = w->d_pool_frag && w->path == 0;
     int pool_slices = ws.n_chunks;
-    // (its graphs are the batch's, in a batch of copies too)
-    const int n_max = !pool_mfma && w->path == 0 && pool_in_head(mv.H, mv.L, gv.B, 1) ? graph_extent(g->host).n_max : 0;
-    const bool in_head = n_max > 0 && pool_in_head(mv.H, mv.L, gv.B, n_max);
+    // the largest graph, looked up where a kernel's choice depends on it (of the batch's graphs, in a batch of copies too)
+    const bool may_pool_in_head = !pool_mfma && w->path == 0 && pool_in_head(mv.H, mv.L, gv.B, 1);
+    const int n_max = may_pool_in_head || (pool_mfma && pool_sort_asks(mv.G)) ? graph_extent(g->host).n_max : 0;
+    const bool in_head = may_pool_in_head && pool_in_head(mv.H, mv.L, gv.B, n_max);
     {
         StageScope scope(timer, PL_STAGE_POOL, s);
         if (in_head) {
         } else if (pool_mfma)
             pool_slices = launch_pool_mfma(gv, mv, ws, fa, reinterpret_cast<const uint4 *>(w->d_pool_frag),
                                            reinterpret_cast<const uint4 *>(w->d_pool_afrag), w->d_pool_bias,
-                                           w->sweep_ws, keep_pool, s);
+                                           w->sweep_ws, keep_pool, n_max, s);
         else
             launch_pool_generic(gv, mv, ws, fa, s);
         if (pool_kept) *pool_kept = pool_mfma && keep_pool;

@@ -256,10 +256,12 @@ bool pool_stream_bw_supported(int H, int L, int weight_dtype);
 void pack_pool_stream_bw_weights(const ModelView &mv, const float *blob, std::vector<uint16_t> *frag);
 void launch_pool_stream_bw(const GraphView &gv, const ModelView &mv, const Workspace &ws, const uint4 *frag, const float *lact,
                            const float *dP, float *dl, float *demb, hipStream_t s);
-// returns the number of slices per graph that ws.partial holds afterwards
+// n_max: nodes of the largest graph, needed where pool_sort_asks(); returns the number of slices per graph that ws.partial
+// holds afterwards
+inline bool pool_sort_asks(int G) { return 3 * G > 24; }
 int launch_pool_mfma(const GraphView &gv, const ModelView &mv, const Workspace &ws,
                      const ForwardArgs &fa, const uint4 *wfrag, const uint4 *afrag, const float *bias, int WS,
-                     float *keep, hipStream_t s);
+                     float *keep, int n_max, hipStream_t s);
 
 // ---- policy gradient (kernels_backward.hip): buffers owned by a batch for one (D, H, L)
 struct GradWorkspace {

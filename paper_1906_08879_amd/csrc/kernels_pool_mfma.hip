@@ -59,14 +59,19 @@ __device__ __forceinline__ float trunc_bf16(float x)
 // (global) grouped by key, koff[b][k] the position (within the graph) of key k's first node,
 // koff[b][3G] the number of pooled nodes.  The current node and nodes with a device id outside
 // [0, D) belong to no key.  Thread t counts, then places, the nodes of its own contiguous block.
+template <typename Count>
 __global__ __launch_bounds__(kThreads) void k_pool_sort(GraphView gv, const uint8_t *__restrict__ reach,
                                                         const int32_t *__restrict__ placement,
                                                         const int32_t *__restrict__ cur_node, int D, int G,
                                                         int single, int32_t *__restrict__ klist,
                                                         int32_t *__restrict__ koff, uint32_t *__restrict__ head_done)
 {
-    // nodes of key k in thread t's block, then their first position among the key's (a graph may have more than 65535)
-    __shared__ __attribute__((aligned(16))) int hist[kMaxKeys][kThreads];
+    // nodes of key k in thread t's block, then their first position among the key's
+    extern __shared__ __attribute__((aligned(16))) unsigned char lds_sort[];
+    Count (*hist)[kThreads] = reinterpret_cast<Count (*)[kThreads]>(lds_sort);
+    struct alignas(4 * sizeof(Count)) Four {
+        Count x, y, z, w;
+    };
     __shared__ int total[kMaxKeys + 1];
     const int b = blockIdx.x, tid = threadIdx.x;
     if (tid == 0) head_done[b] = 0;                  // for this pass's head
@@ -105,8 +110,8 @@ __global__ __launch_bounds__(kThreads) void k_pool_sort(GraphView gv, const uint
     const int lane = tid & 63;                       // exclusive prefix over the threads, a wave to a key, four threads to a lane
     for (int k = tid >> 6; k < K; k += kThreads / 64) {
         static_assert(kThreads == 4 * 64, "a lane takes four threads' counts");
-        int4 *at = reinterpret_cast<int4 *>(&hist[k][4 * lane]);
-        const int4 c = *at;
+        Four *at = reinterpret_cast<Four *>(&hist[k][4 * lane]);
+        const Four c = *at;
         const int own = c.x + c.y + c.z + c.w;
         int run = own;
 #pragma unroll
@@ -116,7 +121,8 @@ __global__ __launch_bounds__(kThreads) void k_pool_sort(GraphView gv, const uint
         }
         if (lane == 63) total[k] = run;
         run -= own;
-        *at = int4{run, run + c.x, run + c.x + c.y, run + c.x + c.y + c.z};
+        auto narrow = [](int x) { return static_cast<Count>(x); };
+        *at = Four{narrow(run), narrow(run + c.x), narrow(run + c.x + c.y), narrow(run + c.x + c.y + c.z)};
     }
     __syncthreads();
     if (tid == 0) {                                  // exclusive prefix over the keys
@@ -1253,11 +1259,21 @@ bool pool_mfma_supported(int H, int L, int weight_dtype)
 
 int launch_pool_mfma(const GraphView &gv, const ModelView &mv, const Workspace &ws,
                      const ForwardArgs &fa, const uint4 *wfrag, const uint4 *afrag, const float *bias, int WS,
-                     float *keep, hipStream_t s)
+                     float *keep, int n_max, hipStream_t s)
 {
     if (gv.B == 0) return kPoolSlices;
-    hipLaunchKernelGGL(k_pool_sort, dim3(gv.B), dim3(kThreads), 0, s, gv, ws.reach, fa.placement, fa.cur_node, mv.D,
-                       mv.G, mv.single_set, ws.klist, ws.koff, ws.head_done);
+    // LDS for the network's keys only, a KB each, and of more than 24 in 16 bits where no position needs more: with 48 KB a
+    // compute unit holds three workgroups, and batches of many small graphs wait for them (graphs of 8 nodes, 16384 with 12
+    // keys: 86 us with room for 48, now 56; 1024 with 48 keys: 15.6 in 32 bits, 10.6 in 16).
+    const int keys = 3 * mv.G;
+    auto sort = [&](auto kernel, size_t count) {
+        hipLaunchKernelGGL(kernel, dim3(gv.B), dim3(kThreads), count * kThreads * keys, s, gv, ws.reach, fa.placement, fa.cur_node,
+                           mv.D, mv.G, mv.single_set, ws.klist, ws.koff, ws.head_done);
+    };
+    if (pool_sort_asks(mv.G) && n_max <= 65535)
+        sort(k_pool_sort<uint16_t>, sizeof(uint16_t));
+    else
+        sort(k_pool_sort<int>, sizeof(int));
     // the shapes that the streaming kernel covers take it (eight slices per set, one per wave)
     if (afrag && WS == 1 && pool_stream_supported(mv.H, mv.L, PL_WEIGHTS_BF16)) {
         PoolParams Q{gv, afrag, bias, ws.emb, ws.klist, ws.koff, ws.partial, kStreamWaves, mv.G, keep};

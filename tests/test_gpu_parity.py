@@ -483,3 +483,19 @@ def test_more_than_65535_nodes_in_one_set():
     got, ref = run_library(w, want_emb=False), run_library(w, want_emb=False, path=1)
     # (sums of seventy thousand fp32 terms, in two orders)
     np.testing.assert_allclose(got["pooled"], ref["pooled"], rtol=1e-4, atol=1e-4 * np.abs(ref["pooled"]).max())
+
+
+@pytest.mark.parametrize("n", [65535, 65536])
+def test_one_of_many_keys_with_sixteen_bits_of_nodes(n):
+    """Sixteen devices, all nodes but one on one of them: the node lists on both sides of the size where their positions no
+    longer fit in 16 bits, against the generic kernels."""
+    rng = np.random.default_rng(n)
+    w = custom_workload(rng, [1], 16, 32, 1, 1, 1)
+    w.n_nodes, w.n_edges = np.array([n], np.int32), np.array([2], np.int32)
+    w.edge_src, w.edge_dst = np.array([5, 5], np.int32), np.array([7, n - 1], np.int32)
+    w.node_feats = np.stack([rng.lognormal(0, 1, n), rng.lognormal(2, 1, n), rng.random(n) < 0.5], axis=1).astype(np.float32)
+    w.placement, w.cur_node = np.full(n, 11, np.int32), np.array([9], np.int32)
+    w.placement[n // 2] = 15
+    got, ref = run_library(w, want_emb=False), run_library(w, want_emb=False, path=1)
+    # (sums of sixty-five thousand fp32 terms, in two orders)
+    np.testing.assert_allclose(got["pooled"], ref["pooled"], rtol=1e-4, atol=1e-4 * np.abs(ref["pooled"]).max())
