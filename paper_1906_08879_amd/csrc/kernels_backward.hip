@@ -458,14 +458,69 @@ __global__ __launch_bounds__(kThreads) void k_bw_proj(GraphView gv, ModelView mv
     }
 }
 
+typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4p;
+
+// The same with four columns per thread, for H a multiple of four (vector loads and stores; the
+// per-node values are read once per four columns; 300 layered graphs, H = 64, 16 devices: 22 us with k_bw_proj, 14).  The
+// sum takes its terms in the order of k_bw_proj, which is the forward pass's.
+__global__ __launch_bounds__(kThreads) void k_bw_proj_rows(GraphView gv, ModelView mv,
+                                                           const float *__restrict__ feats,
+                                                           const int32_t *__restrict__ placement,
+                                                           const int32_t *__restrict__ cur_node,
+                                                           const float *__restrict__ demb,
+                                                           float *__restrict__ dx,
+                                                           float *__restrict__ phi, int phi_ld)
+{
+    const int H = mv.H, D = mv.D, q = H / 4;
+    const size_t idx = static_cast<size_t>(blockIdx.x) * kThreads + threadIdx.x;
+    if (idx >= static_cast<size_t>(gv.n_tot) * q) return;
+    const int v = static_cast<int>(idx / q), h = 4 * static_cast<int>(idx - static_cast<size_t>(v) * q);
+    const int b = gv.node_graph[v];
+    const float *W = mv.blob + mv.proj.w;
+    auto row = [&](int r) { return *reinterpret_cast<const f32x4p *>(W + static_cast<size_t>(r) * H + h); };
+    const float f_time = feats[v * 3 + 0], f_size = feats[v * 3 + 1], f_vis = feats[v * 3 + 2];
+    const int dev = placement[v];
+    const bool on_dev = dev >= 0 && dev < D;
+    const bool is_cur = v - gv.node_off[b] == cur_node[b];
+    const f32x4p bias = *reinterpret_cast<const f32x4p *>(mv.blob + mv.proj.b + h);
+    const f32x4p w0 = row(0), w1 = row(1), wd = row(2 + (on_dev ? dev : 0)), wc = row(2 + D), wv = row(3 + D);
+    const float *de = demb + static_cast<size_t>(v) * 2 * H + h;
+    const f32x4p g0 = *reinterpret_cast<const f32x4p *>(de), g1 = *reinterpret_cast<const f32x4p *>(de + H);
+    f32x4p out;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        float s = bias[k];
+        s = fmaf(f_time, w0[k], s);
+        s = fmaf(f_size, w1[k], s);
+        if (on_dev) s += wd[k];
+        if (is_cur) s += wc[k];
+        s = fmaf(f_vis, wv[k], s);
+        out[k] = s > 0.0f ? g0[k] + g1[k] : 0.0f;
+    }
+    *reinterpret_cast<f32x4p *>(dx + static_cast<size_t>(v) * H + h) = out;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        const int c = h + k;
+        if (c < phi_ld) {                   // phi_ld >= F: columns past F are zero
+            float p;
+            if (c == 0) p = f_time;
+            else if (c == 1) p = f_size;
+            else if (c < 2 + D) p = (dev == c - 2) ? 1.0f : 0.0f;
+            else if (c == 2 + D) p = is_cur ? 1.0f : 0.0f;
+            else if (c == 3 + D) p = f_vis;
+            else p = 0.0f;
+            phi[static_cast<size_t>(v) * phi_ld + c] = p;
+        }
+    }
+}
+
 // Gradient of the input projection, H a multiple of four, large batches: per slab of nodes, phi^T dx and the column sums of dx, with
 // dx_v = (de_td + de_bu) [x_v > 0] formed on the way; neither dx nor phi exists in memory.  One read of d e bounds it (819 MB
 // of 256 NASNet-like graphs).  A thread takes four columns of every so manieth node of the slab.  A row of phi is three
 // numbers and two ones, so a node is five multiply-adds a column; its device's row of the sum is picked by comparison,
 // with five to eight devices in LDS (a thread's own entries: a read and a write instead of sixteen instructions a column,
 // 351 -> 160 us).  The pre-activation takes its terms in the forward pass's order.  Sums: a thread's nodes in order, the
-// threads of a column in a fixed order, then the slabs (k_wgrad_reduce).
-typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4p;
+// threads of a column in a fixed order, then the slabs (k_wgrad_reduce).  proj_fused says from which size on.
 template <int DM>                              // most devices
 __global__ __launch_bounds__(kThreads) void k_bw_proj4(GraphView gv, ModelView mv,
                                                        const float *__restrict__ feats,
@@ -1611,10 +1666,17 @@ int wgrad_rows_per_slab(int64_t R)
     return static_cast<int>((per + kWgRB - 1) / kWgRB * kWgRB);
 }
 
-// Which of the two kernels takes the projection's gradient: k_bw_proj4 saves a write and a read of dx and phi and costs a
-// chain of its own (projection, contractions and slab sums of 64 layered graphs, 0.4 million elements of dx, with k_bw_proj
-// and with it: 34 / 37 us; of 48 NMT-like graphs, 4.5 million: 94 / 91; of 256 NASNet-like ones, 102 million: 2.65 / 2.35 ms).
-bool proj_fused(int64_t R, int H) { return H % 4 == 0 && R * H >= 3000000; }
+// Whether the projection's gradient is formed in one pass over d e: k_bw_proj4 saves a write and a read of dx and phi, and costs
+// a thousand slab sums and, with every device, an entry of the sum per node.  Gradient of layered graphs, with
+// k_bw_proj_rows / with it (us), by millions of elements of dx:
+//   H = 32, 4 devices   1.5 261 / 264, 2.5 387 / 379, 4.5 590 / 578     16 devices   4.5 682 / 692, 9.6 1204 / 1194
+//   H = 64, 4 devices   3.8 474 / 485, 5.1 647 / 644, 11 1131 / 1114    16 devices   7.7 946 / 957, 26 2575 / 2540
+//   H = 128, 4 devices  3.3 573 / 578, 5.1 736 / 732, 11 1280 / 1271    16 devices   7.7 1420 / 1434, 26 3049 / 3025
+// (256 NASNet-like graphs, 102 million, 8 devices: 2.65 / 2.35 ms for projection, contractions and slab sums.)
+bool proj_fused(int64_t R, int H, int D)
+{
+    return H % 4 == 0 && R * H >= (D > 8 ? 12000000 : H <= 32 ? 2000000 : 4300000);
+}
 
 // Four nodes in flight to a thread, and about four workgroups to a compute unit.
 int proj_rows_per_slab(int64_t R, int H)
@@ -1643,7 +1705,7 @@ size_t wgrad_workspace_floats(int64_t n, int64_t B, const ModelView &mv)
     };
     const int H = mv.H, L = mv.L;
     need(n, std::max(32, mv.F), H, 1);
-    if (proj_fused(n, H)) largest = std::max(largest, static_cast<size_t>(1025) * (mv.F + 1) * H);   // (slabs of the projection's)
+    if (proj_fused(n, H, mv.D)) largest = std::max(largest, static_cast<size_t>(1025) * (mv.F + 1) * H);   // (slabs of the projection's)
     need(n, H, H, 4 * L + 3 * (L - 1));
     need(n, 2 * H, H, 3);
     need(B * mv.G, H, H, 3 * L);
@@ -1995,7 +2057,7 @@ void launch_backward(const GraphView &gv, const ModelView &mv, const float *blob
     mark(PL_STAGE_BW_PROJ, true);
     wq.store_sums(fresh);
     {
-        if (proj_fused(n, H)) {
+        if (proj_fused(n, H, mv.D)) {
             const int per = proj_rows_per_slab(n, H);
             float *sums = wq.add_sums(n, per, mv.proj);
 #define CALL(DM)                                                                                                       \
@@ -2004,7 +2066,9 @@ void launch_backward(const GraphView &gv, const ModelView &mv, const float *blob
             if (mv.D <= 4) { CALL(4); } else if (mv.D <= 8) { CALL(8); } else { CALL(kMaxD); }
 #undef CALL
         } else {
-            hipLaunchKernelGGL(k_bw_proj, dim3(static_cast<unsigned>((NH + kThreads - 1) / kThreads)), dim3(kThreads), 0, s,
+            const auto rows = H % 4 == 0 ? k_bw_proj_rows : k_bw_proj;
+            const size_t threads = H % 4 == 0 ? NH / 4 : NH;
+            hipLaunchKernelGGL(rows, dim3(static_cast<unsigned>((threads + kThreads - 1) / kThreads)), dim3(kThreads), 0, s,
                                gv, mv, fa.node_feats, fa.placement, fa.cur_node, gw.demb, gw.dx, gw.phi, dense ? 32 : mv.F);   // (raw features padded to 32 columns)
             if (H < mv.F) {
                 const size_t tf = static_cast<size_t>(n) * mv.F;

@@ -65,9 +65,10 @@ def test_row_lists_of_many_graphs(graphs, n, D, H, L, wd):
     _assert_blocks_close(got, ref, D, H, L)
 
 
-@pytest.mark.parametrize("D,H,graphs,n", [(3, 32, 9, 10417), (8, 48, 3, 21001), (16, 64, 2, 24001), (5, 256, 2, 6001)])
+@pytest.mark.parametrize("D,H,graphs,n", [(3, 32, 9, 10417), (8, 48, 3, 21001), (16, 64, 2, 24001), (5, 256, 2, 6001),
+                                              (8, 48, 5, 21001), (16, 64, 8, 24001), (5, 256, 3, 6001)])
 def test_projection_gradient_of_a_large_batch(D, H, graphs, n):
-    """The projection's gradient formed in one pass over d e (batches of three million elements and more) against the sum of
+    """The projection's gradient formed in one pass over d e (batches of two to twelve million elements and more) and not, against the sum of
     its graphs' gradients, each a batch of its own that takes the other kernel; device ids out of range are in no row."""
     rng = np.random.default_rng(D * H)
     w = custom_workload(rng, [1], D, H, 1, 1, 1)
