@@ -231,7 +231,9 @@ int pl_episode_step(pl_graph_batch *g, int32_t D, const float *logits, const flo
  * graphs together), which leaves every result the same bits.  The copies take device memory, at most 4 GiB a batch: it
  * is allocated on the first such call, whatever its number of steps, and again only for a network whose copies do not
  * fit in it; it is never moved, stays with the batch and is freed with it.  Where there is none (no memory, or a
- * stream that is being captured when it is not there yet) the steps go one by one. */
+ * stream that is being captured when it is not there yet) the steps go one by one.  The copies' work costs what other
+ * streams could have used: a program that fills the GPU from several streams can decline it by calls of one step
+ * each, which take no copies and no memory for them. */
 int pl_episode_run(pl_graph_batch *g, const pl_weights *w, float *node_feats, int32_t *placement,
                    int32_t *cur_node, const int32_t *order, const float *uniforms, int32_t t0,
                    int32_t n_steps, float *logits, int32_t keep_logits, int32_t *out_actions,
@@ -373,7 +375,8 @@ int pl_simulate_reward_ex(pl_graph_batch *g, int32_t D, const float *node_feats,
  * pass: head, pooling, per-node layers at the final states, the dependent chain, projection,
  * weight gradients).  pl_profile_read synchronises those
  * events and returns, per stage, the summed milliseconds and the number of launches since
- * the last reset.  Stage ids: see pl_stage. */
+ * the last reset (a pass of pl_episode_run that takes several steps counts once; pooling within the head's kernel is
+ * timed there).  Stage ids: see pl_stage. */
 typedef enum {
     PL_STAGE_PROJECT = 0, PL_STAGE_SWEEP = 1, PL_STAGE_POOL = 2, PL_STAGE_HEAD = 3,
     PL_STAGE_BW_HEAD = 4, PL_STAGE_BW_POOL = 5, PL_STAGE_BW_ACTS = 6, PL_STAGE_BW_CHAIN = 7,

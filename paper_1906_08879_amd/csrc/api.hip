@@ -588,14 +588,16 @@ int64_t states_within(int D, int steps)   // states that fewer than `steps` step
     return all;
 }
 
-// How many steps of an episode one pass takes.  With S states in the copies of B graphs a pass takes about
-// 1 + S B / 512 times as long as a pass over the B graphs alone, as long as S B <= 256 (measured, us, 1 / 37 / 64 / 128 /
-// 256 graphs: Inception-like at H = 64 250 / 262 / 268 / 284 / 346, NASNet-like at H = 128 1455 / 1532 / 1543 / 1698 /
-// 2067, layered at H = 32 59 / 63 / 64 / 69 / 88, 32 nodes at H = 8 26 / 29 / 30 / 34 / 44); with more graphs than that
-// workgroups wait for each other (NASNet-like, 320 graphs: 3450, Inception-like 568).  The largest number of steps over
-// that time is taken: eight steps of one NASNet-like graph on eight devices go as 3 + 3 + 2.  Only for the sweeps that
-// walk a chunk plan, and only as far as the kernels stay the ones of the batch itself, so that a state's logits are the
-// same bits.
+// How many steps of an episode one pass takes at most.  With S states in the copies of B graphs a pass takes at most about
+// 1 + S B / 512 times as long as a pass over the B graphs alone, as long as S B <= 256 (forward pass, us, 1 / 37 / 64 / 128 /
+// 256 graphs: Inception-like at H = 64 249 / 257 / 263 / 277 / 335, at H = 128 311 / 338 / 338 / 368 / 465; NASNet-like at
+// H = 128 1320 / 1392 / 1402 / 1460 / 1875, with 129 1800; NMT-like at H = 64 500 / 513 / 518 / 538 / 660; layered at H = 32
+// 59 / 61 / 63 / 66 / 84; 32 nodes at H = 8 22 / 24 / 24 / 24 / 25); with more graphs than that workgroups wait for each
+// other (NASNet-like, 320 graphs: 3270, Inception-like at H = 64 542).  The largest number of steps over that time is taken: eight
+// steps of one NASNet-like graph on eight devices go as 3 + 3 + 2.  Only for the sweeps that walk a chunk plan, and only while the
+// choice between the sweep in a wave's lanes and that on matrix cores stays the batch's own: those two differ in the last
+// bits.  Other kernels do change with the number of graphs (the sweep of 128 columns, the shapes of pooling and head), and
+// give the same bits in all of their forms.
 int steps_ahead(const pl_graph_batch *g, const pl_weights *w, int n_steps)
 {
     const ModelView &mv = w->view;

@@ -242,7 +242,7 @@ struct PoolHere {
     const int32_t *placement;
     int lds_at;
 };
-constexpr int kHerePoolNodes = 64, kHerePoolH = 16;
+constexpr int kHerePoolNodes = kPoolChunk / 2;   // graphs of one slice (pool_slices)
 // floats of the three l networks, of embedding rows, of two layers' outputs; keys
 constexpr int here_ld(int H) { return 2 * H + 1; }
 constexpr size_t here_lds(int H, int L, int n)
@@ -636,10 +636,12 @@ void allow_lds(K kernel, size_t bytes)
 
 }  // namespace
 
-// Narrow networks on batches that leave a compute unit to every graph, of graphs that one pass of a workgroup's threads
-// covers: the launch between costs more than the sums (forward pass with a pooling kernel and without: one graph of 32
-// nodes, H = 8, 26.3 / 22.0 us; 64 graphs of 64 nodes 46 / 30; 256 graphs of 64 nodes and 8 devices 67 / 33; 128 graphs of
-// 64 nodes, H = 16, 16 devices 58 / 40).  With more graphs than compute units the head has fewer threads.
+// Narrow networks on batches that leave a compute unit to every graph: the launch between costs more than the sums (forward
+// pass with a pooling kernel and without: one graph of 32 nodes, H = 8, 26.3 / 22.0 us; 64 graphs of 64 nodes 46 / 30; 256
+// graphs of 64 nodes and 8 devices 67 / 33; 128 graphs of 64 nodes, H = 16, 16 devices 58 / 40).  With more graphs than
+// compute units the head has fewer threads.  Graphs of one slice: here a sum takes a graph's nodes in one go, and with more
+// slices it would have other bits than in a larger batch, which another kernel pools (it would be faster still: one graph of
+// 72 / 128 nodes, H = 8, 30.3 / 42.0 us as it is, 27.4 / 36.6 here; from 160 nodes on, H = 16, slower).
 bool pool_in_head(int H, int L, int B, int n_max)
 {
     return (H == 8 || H == 16) && L <= 2 && B <= kComputeUnits && n_max <= kHerePoolNodes;
